@@ -67,9 +67,9 @@ WsLayout ws_layout(int T, int nseq, int tile0, int tile1, int hq, int hkv, int h
 }
 
 // rows per work item of the forward and of the backward kernels
-int tile_fwd(hyd_dtype dt) { return dt == HYD_BF16 ? kFwdBM : kF32Tile; }
-int tile_dq(hyd_dtype dt) { return dt == HYD_BF16 ? kDqBM : kF32Tile; }
-int tile_kv(hyd_dtype dt) { return dt == HYD_BF16 ? kKvBN : kF32Tile; }
+int tile_fwd(hyd_dtype dt) { return dt == HYD_BF16 ? kFwdBM : kF32BM; }
+int tile_dq(hyd_dtype dt) { return dt == HYD_BF16 ? kDqBM : kF32BM; }
+int tile_kv(hyd_dtype dt) { return dt == HYD_BF16 ? kKvBN : kF32KvBN; }
 
 
 bool head_dim_ok(hyd_dtype dt, int d) { (void)dt; return d == 64 || d == 128; }
@@ -159,6 +159,7 @@ struct DeviceInfo {
     bool ready = false, ok = false;
     int cus = 0;
     int occ_fwd = 1, occ_dq = 1, occ_kv = 1;
+    int occ_f32[2][3] = {};           // [head_dim == 128][fwd, dQ, dK/dV]
     void* scratch = nullptr;          // this device's copy of the array above
 };
 DeviceInfo g_dev[64];
@@ -172,6 +173,13 @@ bool prep_kernel(K kernel, int threads, int lds, int* occ) {
     if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, kernel, threads, lds) != hipSuccess) return false;
     if (occ) *occ = n < 1 ? 1 : n;
     return true;
+}
+
+template <int D>
+bool prep_f32(int* occ) {
+    return prep_kernel(hyd_fwd_fp32_kernel<D>, 64 * kF32Waves, f32_lds<D>(), occ) &&
+           prep_kernel(hyd_bwd_dq_fp32_kernel<D>, 64 * kF32Waves, f32_lds<D>(), occ + 1) &&
+           prep_kernel(hyd_bwd_dkdv_fp32_kernel<D>, 64 * kF32KvWaves, f32_lds<D>(), occ + 2);
 }
 
 hyd_status device_info(DeviceInfo** out) {
@@ -198,8 +206,7 @@ hyd_status device_info(DeviceInfo** out) {
                 !prep_kernel(hyd_bwd_dkdv_bf16_kernel<false, 64>, kKvThreads, kKvLds, nullptr) ||
                 !prep_kernel(hyd_bwd_dq_bf16_kernel<true, 64>, kDqThreads, kDqLds, nullptr) ||
                 !prep_kernel(hyd_bwd_dkdv_bf16_kernel<true, 64>, kKvThreads, kKvLds, nullptr) ||
-                !prep_kernel(hyd_bwd_dkdv_fp32_kernel<64>, kF32Tile, f32_dkdv_lds<64>(), nullptr) ||
-                !prep_kernel(hyd_bwd_dkdv_fp32_kernel<128>, kF32Tile, f32_dkdv_lds<128>(), nullptr))
+                !prep_f32<64>(d.occ_f32[0]) || !prep_f32<128>(d.occ_f32[1]))
                 return HYD_ERR_LAUNCH;
             void* sp = nullptr;
             if (hipGetSymbolAddress(&sp, HIP_SYMBOL(scratch)) != hipSuccess || !sp) return HYD_ERR_LAUNCH;
@@ -350,10 +357,10 @@ hyd_status fwd_impl(const void* q, const void* k, const void* v, const int32_t* 
         p.v = static_cast<const float*>(v); p.o_out = static_cast<float*>(o); p.lse_out = lse;
         p.T = total_tokens; p.hq = hq; p.hkv = hkv; p.scale = softmax_scale;
         p.hdr = sv.hdr; p.cursors = sv.hdr + kHdrCursor; p.items = sv.items; p.hm = hm; p.tr = t_trace;
-        const int grid = persistent_grid(*dev, 8, work);
+        const dim3 grid(persistent_grid(*dev, dev->occ_f32[head_dim == 128][0], work));
         KernelTimer kt("fwd_fp32", st);
-        if (head_dim == 64) hipLaunchKernelGGL(hyd_fwd_fp32_kernel<64>, dim3(grid), dim3(kF32Tile), 0, st, p);
-        else hipLaunchKernelGGL(hyd_fwd_fp32_kernel<128>, dim3(grid), dim3(kF32Tile), 0, st, p);
+        if (head_dim == 64) hipLaunchKernelGGL(hyd_fwd_fp32_kernel<64>, grid, dim3(64 * kF32Waves), f32_lds<64>(), st, p);
+        else hipLaunchKernelGGL(hyd_fwd_fp32_kernel<128>, grid, dim3(64 * kF32Waves), f32_lds<128>(), st, p);
     }
     return hipGetLastError() == hipSuccess ? HYD_OK : HYD_ERR_LAUNCH;
 }
@@ -394,7 +401,6 @@ hyd_status bwd_impl(const void* q, const void* k, const void* v, const void* o, 
         hipLaunchKernelGGL(hyd_schedule_prelude, dim3(w.n_sched), dim3(kPreludeThreads), 0, st, cu_seqlens, num_seqs, total_tokens,
                            tile_kv(dt), sv_kv, tile_dq(dt), sv_q, rope_tab, head_dim / 2, rope_base != 0.f ? log2((double)rope_base) : 0.0);
     }
-    const long long n_rows = (long long)total_tokens * hq;
     const long long work_q = (long long)sv_q.max_items * hq, work_kv = (long long)sv_kv.max_items * hkv;
     if (dt == HYD_BF16) {
         BwdScratch sc;
@@ -458,26 +464,20 @@ hyd_status bwd_impl(const void* q, const void* k, const void* v, const void* o, 
         p.dq = static_cast<float*>(dq); p.dk = static_cast<float*>(dk); p.dv = static_cast<float*>(dv);
         p.T = total_tokens; p.hq = hq; p.hkv = hkv; p.scale = softmax_scale;
         p.tr = t_trace;
-        const unsigned rd_grid = (unsigned)((n_rows + 255) / 256);
-        const int grid_q = persistent_grid(*dev, 8, work_q), grid_kv = persistent_grid(*dev, 2, work_kv);
-        if (head_dim == 64) {
-            { KernelTimer kt("bwd_rowdot_fp32", st);
-              hipLaunchKernelGGL(hyd_bwd_rowdot_fp32_kernel<64>, dim3(rd_grid), dim3(256), 0, st, p.o, p.d_o, Dvec, total_tokens, hq); }
-            p.hdr = sv_kv.hdr; p.items = sv_kv.items; p.cursors = sv_kv.hdr + kHdrCursor + kQueues; p.hm = head_map_kv(hkv);
-            { KernelTimer kt("bwd_dkdv_fp32", st);
-              hipLaunchKernelGGL(hyd_bwd_dkdv_fp32_kernel<64>, dim3(grid_kv), dim3(kF32Tile), f32_dkdv_lds<64>(), st, p); }
+        const int* occ = dev->occ_f32[head_dim == 128];
+        const dim3 grid_q(persistent_grid(*dev, occ[1], work_q)), grid_kv(persistent_grid(*dev, occ[2], work_kv));
+        // dQ first: it also writes the row sums D that dK/dV reads
+        {
             p.hdr = sv_q.hdr; p.items = sv_q.items; p.cursors = sv_q.hdr + kHdrCursor + 2 * kQueues; p.hm = head_map_q(hq, hkv);
-            { KernelTimer kt("bwd_dq_fp32", st);
-              hipLaunchKernelGGL(hyd_bwd_dq_fp32_kernel<64>, dim3(grid_q), dim3(kF32Tile), 0, st, p); }
-        } else {
-            { KernelTimer kt("bwd_rowdot_fp32", st);
-              hipLaunchKernelGGL(hyd_bwd_rowdot_fp32_kernel<128>, dim3(rd_grid), dim3(256), 0, st, p.o, p.d_o, Dvec, total_tokens, hq); }
+            KernelTimer kt("bwd_dq_fp32", st);
+            if (head_dim == 64) hipLaunchKernelGGL(hyd_bwd_dq_fp32_kernel<64>, grid_q, dim3(64 * kF32Waves), f32_lds<64>(), st, p);
+            else hipLaunchKernelGGL(hyd_bwd_dq_fp32_kernel<128>, grid_q, dim3(64 * kF32Waves), f32_lds<128>(), st, p);
+        }
+        {
             p.hdr = sv_kv.hdr; p.items = sv_kv.items; p.cursors = sv_kv.hdr + kHdrCursor + kQueues; p.hm = head_map_kv(hkv);
-            { KernelTimer kt("bwd_dkdv_fp32", st);
-              hipLaunchKernelGGL(hyd_bwd_dkdv_fp32_kernel<128>, dim3(grid_kv), dim3(kF32Tile), f32_dkdv_lds<128>(), st, p); }
-            p.hdr = sv_q.hdr; p.items = sv_q.items; p.cursors = sv_q.hdr + kHdrCursor + 2 * kQueues; p.hm = head_map_q(hq, hkv);
-            { KernelTimer kt("bwd_dq_fp32", st);
-              hipLaunchKernelGGL(hyd_bwd_dq_fp32_kernel<128>, dim3(grid_q), dim3(kF32Tile), 0, st, p); }
+            KernelTimer kt("bwd_dkdv_fp32", st);
+            if (head_dim == 64) hipLaunchKernelGGL(hyd_bwd_dkdv_fp32_kernel<64>, grid_kv, dim3(64 * kF32KvWaves), f32_lds<64>(), st, p);
+            else hipLaunchKernelGGL(hyd_bwd_dkdv_fp32_kernel<128>, grid_kv, dim3(64 * kF32KvWaves), f32_lds<128>(), st, p);
         }
     }
     return hipGetLastError() == hipSuccess ? HYD_OK : HYD_ERR_LAUNCH;

@@ -282,6 +282,7 @@ __global__ void __launch_bounds__(kDqThreads, 1) hyd_bwd_dq_bf16_kernel(BwdParam
     bool have = wf.first(p.hm, p.hdr, p.cursors, p.items, slot, wi);
     while (have) {
         ++n_done;
+        wf.claim(p.hm, p.cursors);
         __syncthreads();                                  // everybody has read the work slot: its bytes may be overwritten
         const int lev = wi.lev, head = wi.head, row0 = wi.row0, L = wi.len;
         const int q0 = (lev - 1) * kDqBM;
@@ -534,6 +535,7 @@ __global__ void __launch_bounds__(kKvThreads, 1) hyd_bwd_dkdv_bf16_kernel(BwdPar
     bool have = wf.first(p.hm, p.hdr, p.cursors, p.items, slot, wi);
     while (have) {
         ++n_done;
+        wf.claim(p.hm, p.cursors);
         const int lev = wi.lev, g = wi.head, row0 = wi.row0, L = wi.len;
         const int n_tiles = (L + kKvBN - 1) / kKvBN;
         const int j0 = (n_tiles - lev) * kKvBN;               // first key of the item

@@ -211,6 +211,7 @@ __global__ void __launch_bounds__(kFwdThreads, 1) hyd_fwd_bf16_kernel(FwdParams 
     bool have = wf.first(p.hm, p.hdr, p.cursors, p.items, slot, wi);
     while (have) {
         ++n_done;
+        wf.claim(p.hm, p.cursors);
         const int lev = wi.lev, head = wi.head, row0 = wi.row0, L = wi.len;
         const int q0 = (lev - 1) * kFwdBM;
         int Lq = L, kb = 0, kcap = L;                     // query rows [.., Lq), keys [kb, kcap)

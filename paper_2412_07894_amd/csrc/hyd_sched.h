@@ -179,14 +179,15 @@ __device__ __forceinline__ void decode_work(const HeadMap& hm, int n_items, int 
 // (item, head), fetches the item's 16-byte record and leaves the result in LDS for the workgroup.
 //
 // The chain "cursor atomic -> item record" is two dependent trips to memory, as long as a whole
-// short item, so the atomic is taken off the critical path: the one for item k+1 is issued when
-// item k begins (in next(), right after the barrier that ends item k-1) and its result is only
-// looked at when item k ends, an item's duration later.  What remains at the end of an item is
-// one trip for the record.  A workgroup thus holds one claimed item ahead of the one it works on
-// (holding two, with the record fetched early as well, costs more balance at the end of a launch
-// than it saves).  Only when a queue runs dry (eight times in a workgroup's life) is a claim
-// repeated on the next queue synchronously.  Every workgroup ends when all queues are empty
-// (the cursors only grow).
+// short item, so the atomic is taken off the critical path: a kernel calls claim() while it works on
+// an item and the result is only looked at in next().  What remains at the end of an item is one
+// trip for the record.  The fp32 kernels claim inside their tile loop, one step before an item's
+// last: a claimed item waits for its claimer, and with one to three items per workgroup, as in
+// small batches, workgroups that claim when an item begins hold the next-longest items next to
+// the longest ones (fp32 forward, 4096 tokens, 8 heads: 369 us against 499 us).  The bf16 kernels,
+// whose tile steps are ten times shorter, claim when an item begins: a branch in their tile loop
+// cost 8-14 %.  Only when a queue runs dry (eight times in a workgroup's life) is a claim repeated
+// on the next queue synchronously.  Every workgroup ends when all queues are empty (the cursors only grow).
 struct WorkItem { int seq, lev, head, row0, len; };
 constexpr int kSlotInts = 16;          // two buffers of 8 ints
 typedef __attribute__((ext_vector_type(4))) int i32x4;
@@ -198,12 +199,14 @@ struct WorkFetcher {
     int tried;        // queues found empty so far
     int n_items;
     int claim_q;      // queue of the claim in flight
-    int claim_w;      // its result (the atomic's return value; no use of it until one item later)
+    int claim_w;      // its result (the atomic's return value; no use of it until the item has ended)
+    bool claimed;     // a claim is in flight
     int nxt_item;     // next item: index (-1: none), head, and its record in flight
     int nxt_head;
     i32x4 nxt_rec;
 
     __device__ __forceinline__ void issue_claim(const HeadMap& hm, int* cursors) {
+        claimed = true;
         claim_q = queue;
         const bool open = tried < kQueues && queue_size(hm, n_items, queue) > 0;
         claim_w = open ? atomicAdd(&cursors[queue], 1) : 0x7fffffff;
@@ -213,6 +216,7 @@ struct WorkFetcher {
         int q = claim_q, w = claim_w;
         nxt_item = -1;
         nxt_head = 0;
+        claimed = false;
         while (tried < kQueues) {
             if (w < queue_size(hm, n_items, q)) {
                 decode_work(hm, n_items, q, w, nxt_item, nxt_head);
@@ -251,17 +255,20 @@ struct WorkFetcher {
             publish(slot);
         }
         __syncthreads();
-        if (threadIdx.x == 0) issue_claim(hm, cursors);  // for the item after the first
         return read(slot, w);
+    }
+    // Claims the item after the current one; all threads may call it, at most once per item.
+    __device__ __forceinline__ void claim(const HeadMap& hm, int* cursors) {
+        if (threadIdx.x == 0) issue_claim(hm, cursors);
     }
     __device__ __forceinline__ bool next(const HeadMap& hm, int* cursors, const int* __restrict__ items,
                                          int* slot, WorkItem& w) {
         if (threadIdx.x == 0) {
-            resolve(hm, cursors, items);                 // the claim issued when this item began
+            if (!claimed) issue_claim(hm, cursors);      // an item without steps
+            resolve(hm, cursors, items);
             publish(slot + 8 * (cur ^ 1));
         }
         __syncthreads();        // the next item is visible; everybody is done with the LDS tiles
-        if (threadIdx.x == 0) issue_claim(hm, cursors);  // for the item after the next
         cur ^= 1;
         return read(slot + 8 * cur, w);
     }
