@@ -211,7 +211,6 @@ __global__ void __launch_bounds__(kFwdThreads, 1) hyd_fwd_bf16_kernel(FwdParams 
     bool have = wf.first(p.hm, p.hdr, p.cursors, p.items, slot, wi);
     while (have) {
         ++n_done;
-        wf.claim(p.hm, p.cursors);
         const int lev = wi.lev, head = wi.head, row0 = wi.row0, L = wi.len;
         const int q0 = (lev - 1) * kFwdBM;
         int Lq = L, kb = 0, kcap = L;                     // query rows [.., Lq), keys [kb, kcap)
@@ -310,6 +309,7 @@ __global__ void __launch_bounds__(kFwdThreads, 1) hyd_fwd_bf16_kernel(FwdParams 
             if (t + 1 < n_kt) step(std::integral_constant<int, 1>{}, t + 1);
             if (t + 2 < n_kt) step(std::integral_constant<int, 2>{}, t + 2);
         }
+        wf.claim(p.hm, p.cursors);
         // epilogue: normalise, write O (bf16) and LSE (natural log)
         float l_lo, l_hi;
         both_halves(l_run, l_lo, l_hi);

@@ -181,12 +181,14 @@ __device__ __forceinline__ void decode_work(const HeadMap& hm, int n_items, int 
 // The chain "cursor atomic -> item record" is two dependent trips to memory, as long as a whole
 // short item, so the atomic is taken off the critical path: a kernel calls claim() while it works on
 // an item and the result is only looked at in next().  What remains at the end of an item is one
-// trip for the record.  The fp32 kernels claim inside their tile loop, one step before an item's
-// last: a claimed item waits for its claimer, and with one to three items per workgroup, as in
-// small batches, workgroups that claim when an item begins hold the next-longest items next to
-// the longest ones (fp32 forward, 4096 tokens, 8 heads: 369 us against 499 us).  The bf16 kernels,
-// whose tile steps are ten times shorter, claim when an item begins: a branch in their tile loop
-// cost 8-14 %.  Only when a queue runs dry (eight times in a workgroup's life) is a claim repeated
+// trip for the record.  A claimed item waits for its claimer, so the claim is made late: with one to
+// three items per workgroup, as in small batches, workgroups that claim when an item begins hold
+// the next-longest items next to the longest ones.  The fp32 kernels claim inside their tile loop,
+// one step before an item's last (fp32 forward, 4096 tokens, 8 heads: 369 us against 499 us).  The
+// bf16 kernels, whose tile steps are ten times shorter, claim behind the loop, so that the atomic
+// runs under the epilogue (a branch in their loop cost 8-14 %): against a claim at the item's
+// start a context-parallel ring takes 6 % less, a 16384-token step 2 %, a 2304-token step with two KV
+// heads 14 %.  Only when a queue runs dry (eight times in a workgroup's life) is a claim repeated
 // on the next queue synchronously.  Every workgroup ends when all queues are empty (the cursors only grow).
 struct WorkItem { int seq, lev, head, row0, len; };
 constexpr int kSlotInts = 16;          // two buffers of 8 ints
