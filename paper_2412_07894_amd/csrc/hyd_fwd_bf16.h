@@ -15,9 +15,18 @@
 // O^T[d][q] = V^T P^T directly as the B operand (contraction index = key = accumulator row),
 // while V^T fragments come out of the row-major V tile with the transposing LDS read.
 //
-// Reference maximum.  P = exp2(s - m_ref) is exact for ANY per-row reference m_ref as long as it
-// neither overflows nor loses the row, so m_ref is only moved (and O, l rescaled) when a tile's
-// row maximum exceeds it by more than 8 in the log2 domain; P then stays below 2^8.
+// Reference.  P = exp2(s - m_ref) is exact for ANY per-row reference m_ref as long as nothing
+// overflows: bf16 and fp32 keep the relative precision of a probability whatever its size.  So the
+// row maximum is taken over the FIRST tile only, and later tiles are not searched for a larger
+// score (16 three-way maxima and an exchange per tile and wave, 6 % of the kernel): what a larger
+// score does to the row sum l is looked at afterwards.  When l has passed 2^kRefSlack, O and l are
+// scaled back by a power of two and m_ref moves up by its exponent, exactly.  A score more than about
+// 100 (log2 units) above everything before it overflows on the spot; the check finds O or l
+// non-finite then, and the workgroup repeats the item with m_ref set to the true row maximum, from a
+// pass over the scores.  Measured (forward, MI355X): 131072 tokens, 40 heads, d = 128,
+// 12.65 -> 12.37 ms; 32768 tokens, 32 heads, d = 64, 1.089 -> 1.033 ms.  Starting the exponentials of key
+// block 0 under the score product of block 1, which no longer has to wait for a maximum, is 1.5-4 %
+// slower than this order.
 //
 // Causality.  A wave's 32 rows and the 32-key blocks are aligned, so a block is fully visible,
 // fully hidden, or THE diagonal block of the wave (key index in block > row index in block is
@@ -40,11 +49,12 @@ constexpr int kFwdStageBytes = 2 * kFwdTileBytes;                 // K tile, the
 // stage, which no K/V tile needs before the first step.
 constexpr int kFwdQxOff = kFwdStages * kFwdStageBytes;
 constexpr int kFwdQxBytes = 2 * kFwdTileBytes;
-constexpr int kFwdLds = kFwdQxOff + kFwdQxBytes + 64;                 // ring + Q staging + work slot
+constexpr int kFwdSlotOff = kFwdQxOff + kFwdQxBytes;                  // work slot (64 bytes), then the overflow flag
+constexpr int kFwdLds = kFwdSlotOff + 128;
 __device__ __forceinline__ constexpr int fwd_q_stage_off(int j) {
     return j < 2 ? kFwdQxOff + j * kFwdTileBytes : (kFwdStages - 1) * kFwdStageBytes + (j - 2) * kFwdTileBytes;
 }
-constexpr float kRefSlack = 8.f;                                  // log2 units, see "Reference maximum"
+constexpr float kRefSlack = 16777216.f;                           // 2^24, see "Reference"
 
 struct FwdParams {
     const uint16_t* q; const uint16_t* k; const uint16_t* v;
@@ -68,7 +78,7 @@ typedef __attribute__((address_space(3))) void lds_void;
 template <int D>
 __device__ __forceinline__ void fwd_tile(int Kt, int Vt, const FragAddr& fa, const bf16x8 (&qf)[D / 16],
                                          f32x16 (&acc_o)[D / 32], float& m_ref, float& l_run, float scale_log2,
-                                         int koff, bool diag) {
+                                         int koff, bool diag, bool find_max, bool& overflow) {
     constexpr int NK = D / 16, NDB = D / 32;
     // The instruction order below is pinned with scheduling fences: left alone, the compiler sinks
     // every LDS read next to its use and serialises read -> wait -> MFMA.
@@ -110,28 +120,17 @@ __device__ __forceinline__ void fwd_tile(int Kt, int Vt, const FragAddr& fa, con
             for (int r = 0; r < 16; ++r)
                 if (32 * kb + 8 * (r >> 2) + (r & 3) + k0 > 0) s[kb][r] = -INFINITY;
     }
-    // row maximum of the raw scores (a negative softmax scale has been folded into the sign of
-    // the Q fragments, so the largest raw score is the largest scaled score)
-    float mx = s[0][0];
+    if (find_max) {
+        // row maximum of the raw scores (a negative softmax scale has been folded into the sign of
+        // the Q fragments, so the largest raw score is the largest scaled score)
+        float mx = s[0][0];
 #pragma unroll
-    for (int kb = 0; kb < 2; ++kb)
+        for (int kb = 0; kb < 2; ++kb)
 #pragma unroll
-        for (int r = 0; r < 16; ++r) mx = fmaxf(mx, s[kb][r]);
-    {
+            for (int r = 0; r < 16; ++r) mx = fmaxf(mx, s[kb][r]);
         float lo, hi;
         both_halves(mx, lo, hi);
-        mx = fmaxf(lo, hi);
-    }
-    const float cand = mx * scale_log2;
-    if (__builtin_expect(__any(cand > m_ref + kRefSlack), 0)) {   // a row left the slack window
-        const float m_new = fmaxf(m_ref, cand);
-        const float alpha = __builtin_amdgcn_exp2f(m_ref - m_new);
-        l_run *= alpha;
-#pragma unroll
-        for (int db = 0; db < NDB; ++db)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) acc_o[db][r] *= alpha;
-        m_ref = m_new;
+        m_ref = fmaxf(m_ref, fmaxf(lo, hi) * scale_log2);
     }
     // P V: the exponentials of key step b+1 (8 scores) issue under the NDB MFMAs of step b (two
     // scores per MFMA for D = 128, four for D = 64); V fragments are read kVAhead MFMAs ahead.
@@ -165,6 +164,25 @@ __device__ __forceinline__ void fwd_tile(int Kt, int Vt, const FragAddr& fa, con
         if (db == NDB - 1) pcur = pnxt;
     }
     l_run += lsum;
+    if (__builtin_expect(__any(l_run > kRefSlack), 0)) {
+        float lo, hi;
+        both_halves(l_run, lo, hi);                    // O is shared by the halves of a row, so its scale is too
+        const uint32_t e = __float_as_uint(fmaxf(lo, hi)) >> 23;       // l > 0: biased exponent
+        uint32_t big = e << 23;                        // non-finite values have all exponent bits set
+#pragma unroll
+        for (int db = 0; db < NDB; ++db)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) big = max(big, __float_as_uint(acc_o[db][r]) & 0x7fffffffu);
+        if (big >= 0x7f800000u) overflow = true;
+        const int k = e > 127u && big < 0x7f800000u ? (int)e - 127 : 0;
+        const float alpha = __uint_as_float((uint32_t)(127 - k) << 23);
+        l_run *= alpha;
+        m_ref += (float)k;
+#pragma unroll
+        for (int db = 0; db < NDB; ++db)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) acc_o[db][r] *= alpha;
+    }
 }
 
 // R: range variant.  Each sequence has a query range [q_begin, q_end) and a key range
@@ -178,7 +196,8 @@ __global__ void __launch_bounds__(kFwdThreads, 1) hyd_fwd_bf16_kernel(FwdParams 
     constexpr int kRowB = D * 2;                                      // bytes of a row in global memory
     extern __shared__ __attribute__((aligned(16))) char smem[];
     static_assert(kFwdBM == 256 && kFwdStages == 3, "the Q staging assumes a 256-row tile and a free third stage");
-    int* slot = reinterpret_cast<int*>(smem + kFwdQxOff + kFwdQxBytes);
+    int* slot = reinterpret_cast<int*>(smem + kFwdSlotOff);
+    volatile int* redo = slot + 16;                                            // a wave of the workgroup has overflowed
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int l32 = lane & 31, half = lane >> 5;
@@ -265,12 +284,7 @@ __global__ void __launch_bounds__(kFwdThreads, 1) hyd_fwd_bf16_kernel(FwdParams 
             dma_rows<kFwdWaves>(make_rsrc(p.q + (int64_t)(row0 + q0) * q_stride + (int64_t)head * D, q_bytes), smem,
                                 [](int j) { return fwd_q_stage_off(j); }, kFwdBM / 64, q_stride_b, wave, dma_voff_q);
         }
-        f32x16 acc_o[D / 32];
-#pragma unroll
-        for (int db = 0; db < D / 32; ++db)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) acc_o[db][r] = 0.f;
-        float m_ref = -INFINITY, l_run = 0.f;
+        if (tid == 0) *redo = 0;
         __syncthreads();                                  // the first tiles and the Q rows have landed
         bf16x8 qf[D / 16];
         {
@@ -288,26 +302,47 @@ __global__ void __launch_bounds__(kFwdThreads, 1) hyd_fwd_bf16_kernel(FwdParams 
         }
         __builtin_amdgcn_s_barrier();                     // the staged Q may be overwritten (tile t_lo+2 goes there)
 
-        // one tile on ring stage ST (compile-time, so that fragment reads are base+immediate)
-        auto step = [&](auto stage_tag, int t) {
-            constexpr int ST = decltype(stage_tag)::value;
-            constexpr int Kt = ST * kFwdStageBytes, Vt = Kt + kFwdTileBytes;      // LDS offsets of the tiles
-            // the loads run two tiles ahead: tile t+1 was requested one step ago and precedes this
-            // step's loads in the (in-order) vmcnt queue
-            constexpr int ST2 = (ST + 2) % kFwdStages;
-            constexpr int kDmaPerTile = 2 * (16 / kFwdWaves);
-            const bool more2 = t + 2 < n_kt;
-            if (more2) dma_tile(t + 2, ST2);
-            if (active && t <= td)
-                fwd_tile<D>(Kt, Vt, fa, qf, acc_o, m_ref, l_run, scale_log2, t * kFwdBN + koff0, t == td);
-            if (more2) __builtin_amdgcn_s_waitcnt(0x0070 | (kDmaPerTile & 15));     // vmcnt(kDmaPerTile), lgkmcnt(0)
-            else __builtin_amdgcn_s_waitcnt(0x0070);                                // vmcnt(0), lgkmcnt(0)
-            __builtin_amdgcn_s_barrier();
-        };
-        for (int t = t_lo; t < n_kt; t += 3) {
-            step(std::integral_constant<int, 0>{}, t);
-            if (t + 1 < n_kt) step(std::integral_constant<int, 1>{}, t + 1);
-            if (t + 2 < n_kt) step(std::integral_constant<int, 2>{}, t + 2);
+        f32x16 acc_o[D / 32];
+        float m_ref = -INFINITY, l_run;
+        bool overflow = false;
+        int pass = 0;            // 0: reference from the first tile; after an overflow 1: row maxima of all tiles, 2: with those
+        while (true) {
+            if (pass == 1) m_ref = -INFINITY;
+            l_run = 0.f;
+#pragma unroll
+            for (int db = 0; db < D / 32; ++db)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) acc_o[db][r] = 0.f;
+            // one tile on ring stage ST (compile-time, so that fragment reads are base+immediate)
+            auto step = [&](auto stage_tag, int t) {
+                constexpr int ST = decltype(stage_tag)::value;
+                constexpr int Kt = ST * kFwdStageBytes, Vt = Kt + kFwdTileBytes;      // LDS offsets of the tiles
+                // the loads run two tiles ahead: tile t+1 was requested one step ago and precedes this
+                // step's loads in the (in-order) vmcnt queue
+                constexpr int ST2 = (ST + 2) % kFwdStages;
+                constexpr int kDmaPerTile = 2 * (16 / kFwdWaves);
+                const bool more2 = t + 2 < n_kt;
+                if (more2) dma_tile(t + 2, ST2);
+                if (active && t <= td)
+                    fwd_tile<D>(Kt, Vt, fa, qf, acc_o, m_ref, l_run, scale_log2, t * kFwdBN + koff0, t == td,
+                                pass == 1 || (pass == 0 && t == t_lo), overflow);
+                if (!more2 && __any(overflow)) *redo = 1;                               // seen by all behind the last barrier
+                if (more2) __builtin_amdgcn_s_waitcnt(0x0070 | (kDmaPerTile & 15));     // vmcnt(kDmaPerTile), lgkmcnt(0)
+                else __builtin_amdgcn_s_waitcnt(0x0070);                                // vmcnt(0), lgkmcnt(0)
+                __builtin_amdgcn_s_barrier();
+            };
+            for (int t = t_lo; t < n_kt; t += 3) {
+                step(std::integral_constant<int, 0>{}, t);
+                if (t + 1 < n_kt) step(std::integral_constant<int, 1>{}, t + 1);
+                if (t + 2 < n_kt) step(std::integral_constant<int, 2>{}, t + 2);
+            }
+            if (__builtin_expect(pass == 0 ? *redo == 0 : pass == 2, 1)) break;
+            ++pass;
+            __syncthreads();
+            if (tid == 0) *redo = 0;
+            dma_tile(t_lo, 0);
+            if (t_lo + 1 < n_kt) dma_tile(t_lo + 1, 1);
+            __syncthreads();
         }
         wf.claim(p.hm, p.cursors);
         // epilogue: normalise, write O (bf16) and LSE (natural log)
