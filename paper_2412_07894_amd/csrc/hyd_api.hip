@@ -26,12 +26,11 @@ inline size_t align_up(size_t x) { return (x + kAlign - 1) / kAlign * kAlign; }
 // different tiles), then the backward's row statistics ([Hq][T] floats; the fp32 path uses the
 // first one only) and, for bf16, the fp16 copies of Q, dO and K that its tile loops stream.
 constexpr int kBwdStatVecs = 4;
-constexpr int kHdrAbsmax = 40;            // header word of the dK/dV schedule that holds max |dO| (see BwdScratch)
 struct SchedLayout { size_t hdr, lev, order, items; int n_lev, max_items; };
 struct WsLayout {
     SchedLayout sched[2];
     int n_sched;
-    size_t stat[kBwdStatVecs], q16, do16, k16, rope_tab, total;
+    size_t stat[kBwdStatVecs], q16, do16, k16, absmax, rope_tab, total;
 };
 constexpr int kRopeTabEntries = 64;       // head_dim / 2 at most
 
@@ -61,6 +60,7 @@ WsLayout ws_layout(int T, int nseq, int tile0, int tile1, int hq, int hkv, int h
     w.q16 = at;  if (copies) at += align_up(2 * (size_t)T * (size_t)hq * (size_t)head_dim);
     w.do16 = at; if (copies) at += align_up(2 * (size_t)T * (size_t)hq * (size_t)head_dim);
     w.k16 = at;  if (copies) at += align_up(2 * (size_t)T * (size_t)hkv * (size_t)head_dim);
+    w.absmax = at; if (copies) at += align_up(sizeof(uint32_t) * kPrepMaxWg);
     w.rope_tab = at; at += align_up(sizeof(double) * kRopeTabEntries);       // rotary frequency table (the *_rope calls)
     w.total = at;
     return w;
@@ -329,7 +329,7 @@ hyd_status fwd_impl(const void* q, const void* k, const void* v, const int32_t* 
     double* rope_tab = rope_base != 0.f ? reinterpret_cast<double*>(static_cast<char*>(workspace) + w.rope_tab) : nullptr;
     {
         KernelTimer kt("schedule_prelude", st);
-        hipLaunchKernelGGL(hyd_schedule_prelude, dim3(1), dim3(kPreludeThreads), 0, st, cu_seqlens, num_seqs, total_tokens, tile, sv, tile, sv,
+        hipLaunchKernelGGL(hyd_schedule_prelude, dim3(1), dim3(kPreludeThreads), schedule_lds(sv.n_lev), st, cu_seqlens, num_seqs, total_tokens, tile, sv, tile, sv,
                            rope_tab, head_dim / 2, rope_base != 0.f ? log2((double)rope_base) : 0.0);
     }
     const HeadMap hm = head_map_q(hq, hkv);
@@ -394,13 +394,6 @@ hyd_status bwd_impl(const void* q, const void* k, const void* v, const void* o, 
     const SchedView sv_q = make_view(ws, w.sched[1], tile_dq(dt), max_seqlen);
     float* Dvec = reinterpret_cast<float*>(ws + w.stat[0]);
     double* rope_tab = rope_base != 0.f ? reinterpret_cast<double*>(ws + w.rope_tab) : nullptr;
-    // one launch builds the item list of the dK/dV kernel and, if the dQ kernel uses another tile
-    // size, the dQ kernel's too (one workgroup each)
-    {
-        KernelTimer kt("schedule_prelude", st);
-        hipLaunchKernelGGL(hyd_schedule_prelude, dim3(w.n_sched), dim3(kPreludeThreads), 0, st, cu_seqlens, num_seqs, total_tokens,
-                           tile_kv(dt), sv_kv, tile_dq(dt), sv_q, rope_tab, head_dim / 2, rope_base != 0.f ? log2((double)rope_base) : 0.0);
-    }
     const long long work_q = (long long)sv_q.max_items * hq, work_kv = (long long)sv_kv.max_items * hkv;
     if (dt == HYD_BF16) {
         BwdScratch sc;
@@ -408,20 +401,29 @@ hyd_status bwd_impl(const void* q, const void* k, const void* v, const void* o, 
         sc.kqmul = reinterpret_cast<float*>(ws + w.stat[1]);
         sc.lse2 = reinterpret_cast<float*>(ws + w.stat[2]);
         sc.Dkv = reinterpret_cast<float*>(ws + w.stat[3]);
-        sc.absmax = reinterpret_cast<uint32_t*>(sv_kv.hdr + kHdrAbsmax);      // the prelude has cleared the header
         sc.q16 = reinterpret_cast<uint16_t*>(ws + w.q16);
         sc.do16 = reinterpret_cast<uint16_t*>(ws + w.do16);
         sc.k16 = reinterpret_cast<uint16_t*>(ws + w.k16);
+        // item lists of both tile kernels and the row statistics in one launch
         {
-            KernelTimer kt("bwd_rowstats_bf16", st);
-            const int stat_tok = rowstats_tokens(hq);
-            const dim3 rgrid((unsigned)((total_tokens + stat_tok - 1) / stat_tok));
-            if (head_dim == 64)
-                hipLaunchKernelGGL(hyd_bwd_rowstats_bf16_kernel<64>, rgrid, dim3(256), rowstats_lds(hq), st, static_cast<const uint16_t*>(o),
-                                   static_cast<const uint16_t*>(d_o), lse, static_cast<const uint16_t*>(k), sc, total_tokens, hq, hkv, stat_tok);
-            else
-                hipLaunchKernelGGL(hyd_bwd_rowstats_bf16_kernel<kHeadDim>, rgrid, dim3(256), rowstats_lds(hq), st, static_cast<const uint16_t*>(o),
-                                   static_cast<const uint16_t*>(d_o), lse, static_cast<const uint16_t*>(k), sc, total_tokens, hq, hkv, stat_tok);
+            PrepParams pp;
+            pp.o = static_cast<const uint16_t*>(o); pp.d_o = static_cast<const uint16_t*>(d_o); pp.lse = lse; pp.k = static_cast<const uint16_t*>(k);
+            pp.T = total_tokens; pp.hq = hq; pp.hkv = hkv; pp.tok = prep_tokens(total_tokens, hq);
+            sc.absmax = reinterpret_cast<uint32_t*>(ws + w.absmax);
+            sc.n_absmax = prep_workgroups(total_tokens, pp.tok);
+            pp.sc = sc;
+            pp.cu = cu_seqlens; pp.nseq = num_seqs;
+            pp.ranges = ranged ? ranges : nullptr;
+            pp.n_sched = 2; pp.tile[0] = tile_kv(dt); pp.tile[1] = tile_dq(dt); pp.sv[0] = sv_kv; pp.sv[1] = sv_q;
+            pp.rope_tab = rope_tab; pp.log2_base = rope_tab ? log2((double)rope_base) : 0.0;
+            const dim3 grid((unsigned)(pp.n_sched + sc.n_absmax)), block(kPrepThreads);
+            const size_t lds = prep_lds(hq, pp.tok, sv_kv.n_lev, sv_q.n_lev);
+            KernelTimer kt("bwd_prep_bf16", st);
+            if (head_dim == 64) {
+                if (ranged) hipLaunchKernelGGL((hyd_bwd_prep_bf16_kernel<true, 64>), grid, block, lds, st, pp);
+                else hipLaunchKernelGGL((hyd_bwd_prep_bf16_kernel<false, 64>), grid, block, lds, st, pp);
+            } else if (ranged) hipLaunchKernelGGL(hyd_bwd_prep_bf16_kernel<true>, grid, block, lds, st, pp);
+            else hipLaunchKernelGGL(hyd_bwd_prep_bf16_kernel<false>, grid, block, lds, st, pp);
         }
         BwdParams p;
         p.q = static_cast<const uint16_t*>(q); p.v = static_cast<const uint16_t*>(v); p.d_o = static_cast<const uint16_t*>(d_o);
@@ -464,6 +466,12 @@ hyd_status bwd_impl(const void* q, const void* k, const void* v, const void* o, 
         p.dq = static_cast<float*>(dq); p.dk = static_cast<float*>(dk); p.dv = static_cast<float*>(dv);
         p.T = total_tokens; p.hq = hq; p.hkv = hkv; p.scale = softmax_scale;
         p.tr = t_trace;
+        {   // one launch builds both item lists, one workgroup each
+            KernelTimer kt("schedule_prelude", st);
+            const size_t lds_kv = schedule_lds(sv_kv.n_lev), lds_q = schedule_lds(sv_q.n_lev);
+            hipLaunchKernelGGL(hyd_schedule_prelude, dim3(w.n_sched), dim3(kPreludeThreads), lds_kv > lds_q ? lds_kv : lds_q, st, cu_seqlens,
+                               num_seqs, total_tokens, tile_kv(dt), sv_kv, tile_dq(dt), sv_q, nullptr, 0, 0.0);
+        }
         const int* occ = dev->occ_f32[head_dim == 128];
         const dim3 grid_q(persistent_grid(*dev, occ[1], work_q)), grid_kv(persistent_grid(*dev, occ[2], work_kv));
         // dQ first: it also writes the row sums D that dK/dV reads

@@ -45,90 +45,192 @@ struct BwdScratch {
     float* kqmul;       // [Hq][T]  2^-kq, kq = shift_of(row max |dO|)               (dQ kernel: row scale and its inverse)
     float* lse2;        // [Hq][T]  -LSE * log2(e)                                   (both kernels)
     float* Dkv;         // [Hq][T]  -D * 2^kg, kg = shift_of(max |dO| of the tensor) (dK/dV kernel; written by dQ)
-    uint32_t* absmax;   // max over dO of the 15-bit magnitude pattern; zeroed by the schedule prelude
+    uint32_t* absmax;   // [n_absmax, zeros up to a multiple of 4] maxima over parts of dO of the 15-bit magnitude pattern, one per workgroup of the statistics pass
+    int n_absmax;
     uint16_t* q16;      // [T][Hq][d]  fp16 copy of Q          (written by the dQ kernel, read by dK/dV)
     uint16_t* do16;     // [T][Hq][d]  fp16 copy of dO * 2^kg  (written by the dQ kernel, read by dK/dV)
     uint16_t* k16;      // [T][Hkv][d] fp16 copy of K          (written by the statistics pass)
 };
 
-// ---------------------------------------------------------------------------------------------
-// One pass over O, dO and K before the tile kernels (16 lanes per row, kStatTok = 32 tokens per workgroup):
-// the row statistics above except Dkv, the tensor's largest |dO|, and the fp16 copy of K.  A
-// workgroup walks the rows of its tokens in memory order and collects their statistics in LDS, so
-// that the [Hq][T] vectors are written in runs of kStatTok consecutive floats.  The statistics are
-// stored NEGATED: the form in which the two backward kernels consume them
-// (P = exp2(s * scale * log2(e) + (-LSE2)), dS = P * (dP + (-D))), so that dK/dV can use -D as the
-// initial value of its dP accumulator.  (The fp16 copies of Q and dO and Dkv are written by the dQ
-// kernel, which has those rows in LDS anyway.)
-// ---------------------------------------------------------------------------------------------
-// tokens per workgroup: 32, fewer with very many heads so that the statistics stay within 32 KB of LDS
-inline int rowstats_tokens(int hq) { const int t = 4096 / (hq > 0 ? hq : 1); return t > 32 ? 32 : (t < 1 ? 1 : t); }
-inline size_t rowstats_lds(int hq) { return sizeof(float) * 2 * (size_t)hq * rowstats_tokens(hq); }
-
-template <int HD = kHeadDim>
-__global__ void __launch_bounds__(256) hyd_bwd_rowstats_bf16_kernel(const uint16_t* __restrict__ o,
-                                                                   const uint16_t* __restrict__ d_o,
-                                                                   const float* __restrict__ lse,
-                                                                   const uint16_t* __restrict__ k,
-                                                                   BwdScratch sc, int T, int hq, int hkv, int kStatTok) {
-    extern __shared__ float st[];                  // [2][hq][kStatTok]: -D, kq
-    const int t0 = blockIdx.x * kStatTok;
-    const int nt = min(kStatTok, T - t0);
-    const int grp = threadIdx.x >> 4, c = threadIdx.x & 15;
-    const bool lane_on = HD == kHeadDim || c < HD / 8;
-    uint32_t gmax = 0;
-    for (int r = grp; r < nt * hq; r += 16) {      // row r of the block = (token t0 + r / hq, head r % hq)
-        const int64_t at = ((int64_t)t0 * hq + r) * HD + c * 8;
-        float acc = 0.f;
-        uint32_t amax = 0;
-        if (lane_on) {
-            const u32x4 a = *reinterpret_cast<const u32x4*>(o + at);
-            const u32x4 b = *reinterpret_cast<const u32x4*>(d_o + at);
+// kg = shift_of(largest |dO|): every wave takes the maximum of the partial maxima by itself.  The
+// loads all go out at once (kPrepMaxWg / 256 per lane), before the work fetcher's first trip to memory.
+constexpr int kPrepMaxWg = 2048;
+struct PartialMaxima {
+    u32x4 m[kPrepMaxWg / 256];
+    __device__ __forceinline__ void load(const BwdScratch& sc, int lane) {
 #pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                acc += bf16_lo(a[e]) * bf16_lo(b[e]) + bf16_hi(a[e]) * bf16_hi(b[e]);
-                amax = max(amax, max(b[e] & 0x7fffu, (b[e] >> 16) & 0x7fffu));
+        for (int i = 0; i < kPrepMaxWg / 256; ++i) {
+            m[i] = u32x4{0u, 0u, 0u, 0u};
+            if (4 * (lane + 64 * i) < sc.n_absmax) m[i] = *reinterpret_cast<const u32x4*>(sc.absmax + 4 * (lane + 64 * i));
+        }
+    }
+    __device__ __forceinline__ int shift() const {
+        uint32_t x = 0;
+#pragma unroll
+        for (int i = 0; i < kPrepMaxWg / 256; ++i) x = max(max(x, max(m[i][0], m[i][1])), max(m[i][2], m[i][3]));
+#pragma unroll
+        for (int d = 1; d < 64; d <<= 1) x = max(x, (uint32_t)__shfl_xor((int)x, d, 64));
+        return shift_of(x);
+    }
+};
+// ---------------------------------------------------------------------------------------------
+// Preparation of the backward, one launch: the first n_sched workgroups build the item lists of the
+// two tile kernels, the others make one pass over O, dO and K: the row statistics above except
+// Dkv, the maxima of |dO|, and the fp16 copy of K.  (The fp16 copies of Q and dO and Dkv are written by
+// the dQ kernel, which has those rows in LDS anyway.)  A lane per 16 bytes of a row; a workgroup walks the
+// rows of its tokens in memory order, four rows in flight per group of lanes, and collects their
+// statistics in LDS, so that the [Hq][T] vectors are written in runs of consecutive floats.  The
+// statistics are stored NEGATED: the form in which the two backward kernels consume them
+// (P = exp2(s * scale * log2(e) + (-LSE2)), dS = P * (dP + (-D))), so that dK/dV can use -D as the
+// initial value of its dP accumulator.
+//
+// Bound by HBM on large batches (5 TB/s, the rate of a copy) and by latency on small ones, hence
+// the split by tokens: a workgroup takes 32 of them at most, fewer as soon as that leaves less than
+// kPrepTarget workgroups.  The range variant skips the rows of dO outside a visit's query range and
+// the rows of K outside its key range, which nothing reads.
+// Measured (MI355X, this pass with the item lists; before: 32 tokens per workgroup, one row in
+// flight, sixteen lanes for a 128-byte row too, and a launch of its own for the lists, 7 us):
+// 2048 tokens, 8 heads: 11 us, before 28; 2129 tokens, 32 heads, d = 64: 13 us, before 76; 16384 tokens,
+// 32 heads: 96 us, before 133; one visit of a context-parallel ring (16384 tokens): 33 us, before 95;
+// 262144 tokens, 32/8 heads: 1.11 ms (5.0 TB/s), before 1.10.
+// ---------------------------------------------------------------------------------------------
+constexpr int kPrepThreads = 256, kPrepTarget = 1024;
+inline int prep_tokens(int T, int hq) {
+    int t = 4096 / (hq > 0 ? hq : 1);                      // statistics of a workgroup within 32 KB of LDS
+    t = t > 32 ? 32 : t;
+    if (t > T / kPrepTarget) t = T / kPrepTarget;
+    return t < 1 ? 1 : t;
+}
+inline int prep_workgroups(int T, int tok) {
+    const int n = (T + tok - 1) / tok;
+    return n < kPrepMaxWg ? n : kPrepMaxWg;
+}
+inline size_t prep_lds(int hq, int tok, int nl0, int nl1) {
+    const size_t st = sizeof(float) * 2 * (size_t)hq * tok + sizeof(int) * 32;
+    const size_t a = schedule_lds(nl0), b = schedule_lds(nl1), l = a > b ? a : b;
+    return st > l ? st : l;
+}
+struct PrepParams {
+    const uint16_t* o; const uint16_t* d_o; const float* lse; const uint16_t* k;
+    BwdScratch sc;
+    int T, hq, hkv, tok;
+    const int32_t* cu; int nseq;
+    const int32_t* ranges;                                 // range variant only
+    int n_sched; int tile[2]; SchedView sv[2];
+    double* rope_tab; double log2_base;
+};
+
+template <bool R, int HD = kHeadDim>
+__global__ void __launch_bounds__(kPrepThreads) hyd_bwd_prep_bf16_kernel(PrepParams p) {
+    extern __shared__ float st[];                  // [2][hq][tok]: -D, kq; then [tok] row flags (range variant)
+    const int tid = threadIdx.x;
+    if ((int)blockIdx.x < p.n_sched) {
+        const int w = blockIdx.x;
+        if (w == 0 && p.rope_tab) rope_table_fill(p.rope_tab, HD / 2, p.log2_base, tid, kPrepThreads);
+        build_schedule(p.cu, p.nseq, p.T, p.tile[w], p.sv[w], reinterpret_cast<int*>(st), kPrepThreads);
+        return;
+    }
+    const int wg = blockIdx.x - p.n_sched, n_wg = gridDim.x - p.n_sched;
+    const int T = p.T, hq = p.hq, hkv = p.hkv, tok = p.tok;
+    int* flags = reinterpret_cast<int*>(st + 2 * hq * tok);
+    constexpr int kLanes = HD / 8, kGrps = kPrepThreads / kLanes;       // lanes per row, rows at a time
+    const int grp = tid / kLanes, c = tid % kLanes;
+    uint32_t gmax = 0;
+    for (int t0 = wg * tok; t0 < T; t0 += n_wg * tok) {
+        const int nt = min(tok, T - t0);
+        if (R) {
+            if (tid < nt) {                        // the last sequence that starts at or before the row
+                const int t = t0 + tid;
+                int lo = 0, hi = p.nseq;
+                while (lo < hi) {
+                    const int mid = (lo + hi + 1) >> 1;
+                    if (p.cu[mid] <= t) lo = mid; else hi = mid - 1;
+                }
+                lo = min(lo, p.nseq - 1);
+                const i32x4 rg = *reinterpret_cast<const i32x4*>(p.ranges + 4 * lo);
+                const int pos = t - p.cu[lo];
+                flags[tid] = (pos >= rg[0] && pos < rg[1] ? 1 : 0) | (pos >= rg[2] && pos < rg[3] ? 2 : 0);
+            }
+            __syncthreads();
+        }
+        constexpr int kU = 4;                      // rows in flight
+        const int n_rows = nt * hq;
+        for (int r0 = grp; r0 < n_rows; r0 += kGrps * kU) {       // row r of the block = (token t0 + r / hq, head r % hq)
+            u32x4 a[kU], b[kU];
+            bool on[kU];
+#pragma unroll
+            for (int u = 0; u < kU; ++u) {
+                const int r = r0 + kGrps * u;
+                on[u] = r < n_rows && (!R || (flags[r / hq] & 1));
+                a[u] = u32x4{0u, 0u, 0u, 0u};
+                b[u] = u32x4{0u, 0u, 0u, 0u};
+                if (on[u]) {
+                    const int64_t at = ((int64_t)t0 * hq + r) * HD + c * 8;
+                    a[u] = *reinterpret_cast<const u32x4*>(p.o + at);
+                    b[u] = *reinterpret_cast<const u32x4*>(p.d_o + at);
+                }
+            }
+#pragma unroll
+            for (int u = 0; u < kU; ++u) {
+                float acc = 0.f;
+                uint32_t amax = 0;
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    acc += bf16_lo(a[u][e]) * bf16_lo(b[u][e]) + bf16_hi(a[u][e]) * bf16_hi(b[u][e]);
+                    amax = max(amax, max(b[u][e] & 0x7fffu, (b[u][e] >> 16) & 0x7fffu));
+                }
+#pragma unroll
+                for (int m = 1; m < kLanes; m <<= 1) {
+                    acc += __shfl_xor(acc, m, 64);
+                    amax = max(amax, (uint32_t)__shfl_xor((int)amax, m, 64));
+                }
+                const int r = r0 + kGrps * u;
+                if (c == 0 && on[u]) {
+                    const int tl = r / hq, h = r - tl * hq;
+                    st[h * tok + tl] = -acc;
+                    st[(hq + h) * tok + tl] = (float)shift_of(amax);
+                }
+                gmax = max(gmax, amax);
             }
         }
+        for (int r0 = grp; r0 < nt * hkv; r0 += kGrps * kU) {     // the K rows of the same tokens
+            u32x4 x[kU];
+            bool on[kU];
 #pragma unroll
-        for (int m = 1; m < 16; m <<= 1) {
-            acc += __shfl_xor(acc, m, 64);
-            amax = max(amax, (uint32_t)__shfl_xor((int)amax, m, 64));
-        }
-        if (c == 0) {
-            const int tl = r / hq, h = r - tl * hq;
-            st[h * kStatTok + tl] = -acc;
-            st[(hq + h) * kStatTok + tl] = (float)shift_of(amax);
-        }
-        gmax = max(gmax, amax);
-    }
-    for (int r = grp; r < nt * hkv; r += 16) {     // the K rows of the same tokens
-        if (lane_on) {
-            const int64_t at = ((int64_t)t0 * hkv + r) * HD + c * 8;
-            const u32x4 x = *reinterpret_cast<const u32x4*>(k + at);
-            u32x4 x16;
+            for (int u = 0; u < kU; ++u) {
+                const int r = r0 + kGrps * u;
+                on[u] = r < nt * hkv && (!R || (flags[r / hkv] & 2));
+                if (on[u]) x[u] = *reinterpret_cast<const u32x4*>(p.k + ((int64_t)t0 * hkv + r) * HD + c * 8);
+            }
 #pragma unroll
-            for (int e = 0; e < 4; ++e) x16[e] = bf16x2_to_f16x2(x[e]);
-            *reinterpret_cast<u32x4*>(sc.k16 + at) = x16;
+            for (int u = 0; u < kU; ++u) {
+                if (on[u]) {
+                    u32x4 x16;
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) x16[e] = bf16x2_to_f16x2(x[u][e]);
+                    *reinterpret_cast<u32x4*>(p.sc.k16 + ((int64_t)t0 * hkv + r0 + kGrps * u) * HD + c * 8) = x16;
+                }
+            }
         }
-    }
-    __syncthreads();
-    for (int idx = threadIdx.x; idx < hq * kStatTok; idx += 256) {
-        const int h = idx / kStatTok, tl = idx % kStatTok;
-        if (tl < nt) {
-            const int64_t at = (int64_t)h * T + t0 + tl;
-            const float l2 = -lse[at] * kLog2e, kq = st[(hq + h) * kStatTok + tl];
-            sc.Dq[at] = st[idx];
-            sc.kqmul[at] = pow2i(-(int)kq);
-            sc.lse2[at] = l2;
+        __syncthreads();
+        for (int idx = tid; idx < hq * tok; idx += kPrepThreads) {
+            const int h = idx / tok, tl = idx % tok;
+            if (tl < nt && (!R || (flags[tl] & 1))) {
+                const int64_t at = (int64_t)h * T + t0 + tl;
+                p.sc.Dq[at] = st[idx];
+                p.sc.kqmul[at] = pow2i(-(int)st[hq * tok + idx]);
+                p.sc.lse2[at] = -p.lse[at] * kLog2e;
+            }
         }
+        __syncthreads();                           // st and flags are free again
     }
-    // the tensor's maximum: one atomic per wave at most, and none once the stored value has caught
-    // up (the plain read only filters; the atomic decides)
 #pragma unroll
     for (int m = 1; m < 64; m <<= 1) gmax = max(gmax, (uint32_t)__shfl_xor((int)gmax, m, 64));
-    if ((threadIdx.x & 63) == 0 && gmax > __hip_atomic_load(sc.absmax, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
-        atomicMax(sc.absmax, gmax);
+    uint32_t* wmax = reinterpret_cast<uint32_t*>(st);
+    if ((tid & 63) == 0) wmax[tid >> 6] = gmax;
+    __syncthreads();
+    if (tid == 0) p.sc.absmax[wg] = max(max(wmax[0], wmax[1]), max(wmax[2], wmax[3]));
+    if (wg == n_wg - 1 && tid > 0 && tid < 4 && (wg + tid) / 4 == wg / 4) p.sc.absmax[wg + tid] = 0;
 }
 
 struct BwdParams {
@@ -274,12 +376,14 @@ __global__ void __launch_bounds__(kDqThreads, 1) hyd_bwd_dq_bf16_kernel(BwdParam
     // only the score product reads; a zero scale becomes an epsilon so that -inf * scale = -inf
     const float scale_log2 = fmaxf(fabsf(p.scale_log2), 1e-30f);
     const uint32_t sign_flip = p.scale_log2 < 0.f ? 0x80008000u : 0u;
-    const float up = pow2i(shift_of(*p.sc.absmax));                   // 2^kg
+    PartialMaxima pm;
+    pm.load(p.sc, lane);
     const bool wave_first_half = half == 0;                           // both halves of a wave hold the same rows
 
     WorkFetcher wf;
     WorkItem wi;
     bool have = wf.first(p.hm, p.hdr, p.cursors, p.items, slot, wi);
+    const float up = pow2i(pm.shift());                               // 2^kg
     while (have) {
         ++n_done;
         __syncthreads();                                  // everybody has read the work slot: its bytes may be overwritten
@@ -528,11 +632,13 @@ __global__ void __launch_bounds__(kKvThreads, 1) hyd_bwd_dkdv_bf16_kernel(BwdPar
     const float scale_log2 = fmaxf(fabsf(p.scale_log2), 1e-30f);
     const uint32_t sign_flip = p.scale_log2 < 0.f ? 0x80008000u : 0u;
     char* const pbuf = smem + kKvPOff + pair * 2 * kKvPBytes + lane * 8;      // + buf * kKvPBytes + q * 512
-    const float unscale = pow2i(-shift_of(*p.sc.absmax));                     // 2^-kg
+    PartialMaxima pm;
+    pm.load(p.sc, lane);
 
     WorkFetcher wf;
     WorkItem wi;
     bool have = wf.first(p.hm, p.hdr, p.cursors, p.items, slot, wi);
+    const float unscale = pow2i(-pm.shift());                         // 2^-kg
     while (have) {
         ++n_done;
         const int lev = wi.lev, g = wi.head, row0 = wi.row0, L = wi.len;

@@ -24,7 +24,7 @@ constexpr int kQueues = 8;
 constexpr int kHdrInts = 64;
 // header (ints): [0] n_items, [1] kSched* flags about cu_seqlens as the prelude saw it,
 // [8 + 8*k + x] cursor of queue x of kernel k (k = 0 fwd, 1 dK/dV, 2 dQ); the rest is zeroed by
-// the prelude and free for the kernels of the call ([40] of the dK/dV schedule: max |dO|)
+// the prelude
 constexpr int kHdrCursor = 8;
 constexpr int kHdrFlags = 1;
 constexpr int kSchedTooLong = 1;          // a sequence is longer than max_seqlen: its tiles beyond that bound got no item
@@ -67,33 +67,27 @@ __device__ __forceinline__ void wave_inclusive_scan(int* v, int n, int lane) {
 
 constexpr int kPreludeThreads = 1024;
 constexpr int kPreludeLdsLev = 4096;      // levels whose arrays fit the kernel's LDS
+// bytes of LDS that build_schedule needs for nl levels
+__host__ __device__ constexpr size_t schedule_lds(int nl) { return nl <= kPreludeLdsLev ? sizeof(int) * 3 * (size_t)(nl + 2) : 0; }
 
-// Builds the item list for tile size `tile` and clears the cursors; one workgroup per list
-// (blockIdx.x = 0: tile0 -> sv0, blockIdx.x = 1: tile1 -> sv1), so the two lists of the backward
-// come from one launch.  n_lev* bounds the tiles per sequence (from the caller's max_seqlen).
-// Order among items of equal cost: by sequence rank (arrival order among equals), which is
-// unspecified (it never changes a result: every output element has exactly one producer).
-// With rope_tab != NULL the first workgroup also fills the rotary frequency table of the call
-// (half_d entries, see hyd_rope_regs.h).
-__global__ void __launch_bounds__(kPreludeThreads) hyd_schedule_prelude(const int32_t* __restrict__ cu, int nseq, int T,
-                                                                       int tile0, SchedView sv0, int tile1, SchedView sv1,
-                                                                       double* rope_tab, int half_d, double log2_base) {
-    if (rope_tab && blockIdx.x == 0) rope_table_fill(rope_tab, half_d, log2_base, threadIdx.x, kPreludeThreads);
-    __shared__ int lds_lev[3 * (kPreludeLdsLev + 2)];
-    const bool second = blockIdx.x != 0;
-    const int tile = second ? tile1 : tile0;
-    const SchedView sv = second ? sv1 : sv0;
+// Builds the item list for tile size `tile` and clears the cursors; called by all `nthreads`
+// threads of one workgroup, lds_lev as sized by schedule_lds.  n_lev bounds the tiles per sequence
+// (from the caller's max_seqlen).  Order among items of equal cost: by sequence rank (arrival order
+// among equals), which is unspecified (it never changes a result: every output element has
+// exactly one producer).
+__device__ __forceinline__ void build_schedule(const int32_t* __restrict__ cu, int nseq, int T, int tile, const SchedView& sv,
+                                               int* lds_lev, int nthreads) {
     const int tid = threadIdx.x;
     const int nl = sv.n_lev;
     int* lev = nl <= kPreludeLdsLev ? lds_lev : sv.lev;
     int* hist = lev;                       // [n]: sequences with exactly n tiles; later the arrival counters
     int* cnt = lev + (nl + 2);             // [r]: sequences with >= nl - r tiles (levels in reversed order)
     int* offs = lev + 2 * (nl + 2);        // [r]: list position after level nl - r
-    for (int i = tid; i < nl + 2; i += kPreludeThreads) hist[i] = 0;
-    for (int i = tid; i < kHdrInts; i += kPreludeThreads) sv.hdr[i] = 0;
+    for (int i = tid; i < nl + 2; i += nthreads) hist[i] = 0;
+    for (int i = tid; i < kHdrInts; i += nthreads) sv.hdr[i] = 0;
     __syncthreads();
     int flags = (tid == 0 && (cu[0] != 0 || cu[nseq] != T)) ? kSchedBadSeqlens : 0;
-    for (int s = tid; s < nseq; s += kPreludeThreads) {
+    for (int s = tid; s < nseq; s += nthreads) {
         const int L = cu[s + 1] - cu[s];
         if (L < 0) flags |= kSchedBadSeqlens;
         if (L > 0 && (L + tile - 1) / tile > nl) flags |= kSchedTooLong;
@@ -112,10 +106,10 @@ __global__ void __launch_bounds__(kPreludeThreads) hyd_schedule_prelude(const in
     __syncthreads();
     const int n_items = nl > 0 ? min(offs[nl - 1], sv.max_items) : 0;
     if (tid == 0) sv.hdr[0] = n_items;
-    for (int i = tid; i < nl + 2; i += kPreludeThreads) hist[i] = 0;
+    for (int i = tid; i < nl + 2; i += nthreads) hist[i] = 0;
     __syncthreads();
     // rank of a sequence with n tiles = (#sequences with more tiles) + arrival order among equals
-    for (int s = tid; s < nseq; s += kPreludeThreads) {
+    for (int s = tid; s < nseq; s += nthreads) {
         const int L = cu[s + 1] - cu[s];
         const int n = min((L + tile - 1) / tile, nl);
         if (n == 0) continue;
@@ -125,7 +119,7 @@ __global__ void __launch_bounds__(kPreludeThreads) hyd_schedule_prelude(const in
     __syncthreads();
     // Level c (reversed index r = nl - c) holds the sequences of rank < cnt[r] at the list
     // positions [offs[r] - cnt[r], offs[r]): one thread per position finds its level by bisection.
-    for (int pos = tid; pos < n_items; pos += kPreludeThreads) {
+    for (int pos = tid; pos < n_items; pos += nthreads) {
         int lo = 0, hi = nl - 1;               // first r with offs[r] > pos
         while (lo < hi) {
             const int mid = (lo + hi) >> 1;
@@ -136,6 +130,17 @@ __global__ void __launch_bounds__(kPreludeThreads) hyd_schedule_prelude(const in
         int* rec = sv.items + 4 * pos;
         rec[0] = s; rec[1] = nl - lo; rec[2] = a; rec[3] = cu[s + 1] - a;
     }
+}
+
+// One list per workgroup: blockIdx.x = 0: tile0 -> sv0, blockIdx.x = 1: tile1 -> sv1.  With rope_tab != NULL the
+// first workgroup also fills the rotary frequency table of the call (half_d entries, see hyd_rope_regs.h).
+__global__ void __launch_bounds__(kPreludeThreads) hyd_schedule_prelude(const int32_t* __restrict__ cu, int nseq, int T,
+                                                                       int tile0, SchedView sv0, int tile1, SchedView sv1,
+                                                                       double* rope_tab, int half_d, double log2_base) {
+    extern __shared__ int lds_lev[];
+    if (rope_tab && blockIdx.x == 0) rope_table_fill(rope_tab, half_d, log2_base, threadIdx.x, kPreludeThreads);
+    const bool second = blockIdx.x != 0;
+    build_schedule(cu, nseq, T, second ? tile1 : tile0, second ? sv1 : sv0, lds_lev, kPreludeThreads);
 }
 
 // Number of work indices of queue x.
