@@ -76,16 +76,18 @@ bool head_dim_ok(hyd_dtype dt, int d) { (void)dt; return d == 64 || d == 128; }
 
 // Spread of (item, head) pairs over the 8 queues: whole KV groups per queue when the KV heads
 // divide over the queues, else single heads, else items striped with all heads in every queue.
-HeadMap head_map_q(int hq, int hkv) {
+HeadMap head_map_q(int hq, int hkv, int grid) {
     HeadMap hm;
+    hm.grid = grid;
     hm.heads = hq;
     if (hkv % kQueues == 0) { hm.striped = 0; hm.hpq = hq / kQueues; hm.group = hq / hkv; }
     else if (hq % kQueues == 0) { hm.striped = 0; hm.hpq = hq / kQueues; hm.group = 1; }
     else { hm.striped = 1; hm.hpq = hq; hm.group = 1; }
     return hm;
 }
-HeadMap head_map_kv(int hkv) {
+HeadMap head_map_kv(int hkv, int grid) {
     HeadMap hm;
+    hm.grid = grid;
     hm.heads = hkv;
     if (hkv % kQueues == 0) { hm.striped = 0; hm.hpq = hkv / kQueues; hm.group = 1; }
     else { hm.striped = 1; hm.hpq = hkv; hm.group = 1; }
@@ -332,7 +334,6 @@ hyd_status fwd_impl(const void* q, const void* k, const void* v, const int32_t* 
         hipLaunchKernelGGL(hyd_schedule_prelude, dim3(1), dim3(kPreludeThreads), schedule_lds(sv.n_lev), st, cu_seqlens, num_seqs, total_tokens, tile, sv, tile, sv,
                            rope_tab, head_dim / 2, rope_base != 0.f ? log2((double)rope_base) : 0.0);
     }
-    const HeadMap hm = head_map_q(hq, hkv);
     const long long work = (long long)sv.max_items * hq;
     if (dt == HYD_BF16) {
         FwdParams p;
@@ -340,10 +341,11 @@ hyd_status fwd_impl(const void* q, const void* k, const void* v, const int32_t* 
         p.v = static_cast<const uint16_t*>(v); p.o = static_cast<uint16_t*>(o); p.lse = lse;
         p.T = total_tokens; p.hq = hq; p.hkv = hkv;
         p.scale_log2 = softmax_scale * kLog2e;
-        p.hdr = sv.hdr; p.cursors = sv.hdr + kHdrCursor; p.items = sv.items; p.hm = hm; p.tr = t_trace;
+        p.hdr = sv.hdr; p.cursors = sv.hdr + kHdrCursor; p.items = sv.items; p.tr = t_trace;
         p.ranges = ranged ? ranges : nullptr;
         p.rope_tab = rope_tab;
         const dim3 grid(persistent_grid(*dev, dev->occ_fwd, work));
+        p.hm = head_map_q(hq, hkv, grid.x);
         KernelTimer kt(ranged ? "fwd_range_bf16" : "fwd_bf16", st);
         if (head_dim == 64) {
             if (ranged) hipLaunchKernelGGL((hyd_fwd_bf16_kernel<true, 64>), grid, dim3(kFwdThreads), kFwdLds, st, p);
@@ -356,8 +358,9 @@ hyd_status fwd_impl(const void* q, const void* k, const void* v, const int32_t* 
         p.q = static_cast<const float*>(q); p.k = static_cast<const float*>(k);
         p.v = static_cast<const float*>(v); p.o_out = static_cast<float*>(o); p.lse_out = lse;
         p.T = total_tokens; p.hq = hq; p.hkv = hkv; p.scale = softmax_scale;
-        p.hdr = sv.hdr; p.cursors = sv.hdr + kHdrCursor; p.items = sv.items; p.hm = hm; p.tr = t_trace;
+        p.hdr = sv.hdr; p.cursors = sv.hdr + kHdrCursor; p.items = sv.items; p.tr = t_trace;
         const dim3 grid(persistent_grid(*dev, dev->occ_f32[head_dim == 128][0], work));
+        p.hm = head_map_q(hq, hkv, grid.x);
         KernelTimer kt("fwd_fp32", st);
         if (head_dim == 64) hipLaunchKernelGGL(hyd_fwd_fp32_kernel<64>, grid, dim3(64 * kF32Waves), f32_lds<64>(), st, p);
         else hipLaunchKernelGGL(hyd_fwd_fp32_kernel<128>, grid, dim3(64 * kF32Waves), f32_lds<128>(), st, p);
@@ -437,8 +440,9 @@ hyd_status bwd_impl(const void* q, const void* k, const void* v, const void* o, 
         // dQ first: it also writes the fp16 copies of Q and dO that dK/dV streams
         {
             p.hdr = sv_q.hdr; p.items = sv_q.items;
-            p.cursors = sv_q.hdr + kHdrCursor + 2 * kQueues; p.hm = head_map_q(hq, hkv);
+            p.cursors = sv_q.hdr + kHdrCursor + 2 * kQueues;
             const dim3 grid(persistent_grid(*dev, dev->occ_dq, work_q));
+            p.hm = head_map_q(hq, hkv, grid.x);
             KernelTimer kt(ranged ? "bwd_dq_range_bf16" : "bwd_dq_bf16", st);
             if (head_dim == 64) {
                 if (ranged) hipLaunchKernelGGL((hyd_bwd_dq_bf16_kernel<true, 64>), grid, dim3(kDqThreads), kDqLds, st, p);
@@ -448,8 +452,9 @@ hyd_status bwd_impl(const void* q, const void* k, const void* v, const void* o, 
         }
         {
             p.hdr = sv_kv.hdr; p.items = sv_kv.items;
-            p.cursors = sv_kv.hdr + kHdrCursor + kQueues; p.hm = head_map_kv(hkv);
+            p.cursors = sv_kv.hdr + kHdrCursor + kQueues;
             const dim3 grid(persistent_grid(*dev, dev->occ_kv, work_kv));
+            p.hm = head_map_kv(hkv, grid.x);
             KernelTimer kt(ranged ? "bwd_dkdv_range_bf16" : "bwd_dkdv_bf16", st);
             if (head_dim == 64) {
                 if (ranged) hipLaunchKernelGGL((hyd_bwd_dkdv_bf16_kernel<true, 64>), grid, dim3(kKvThreads), kKvLds, st, p);
@@ -476,13 +481,13 @@ hyd_status bwd_impl(const void* q, const void* k, const void* v, const void* o, 
         const dim3 grid_q(persistent_grid(*dev, occ[1], work_q)), grid_kv(persistent_grid(*dev, occ[2], work_kv));
         // dQ first: it also writes the row sums D that dK/dV reads
         {
-            p.hdr = sv_q.hdr; p.items = sv_q.items; p.cursors = sv_q.hdr + kHdrCursor + 2 * kQueues; p.hm = head_map_q(hq, hkv);
+            p.hdr = sv_q.hdr; p.items = sv_q.items; p.cursors = sv_q.hdr + kHdrCursor + 2 * kQueues; p.hm = head_map_q(hq, hkv, grid_q.x);
             KernelTimer kt("bwd_dq_fp32", st);
             if (head_dim == 64) hipLaunchKernelGGL(hyd_bwd_dq_fp32_kernel<64>, grid_q, dim3(64 * kF32Waves), f32_lds<64>(), st, p);
             else hipLaunchKernelGGL(hyd_bwd_dq_fp32_kernel<128>, grid_q, dim3(64 * kF32Waves), f32_lds<128>(), st, p);
         }
         {
-            p.hdr = sv_kv.hdr; p.items = sv_kv.items; p.cursors = sv_kv.hdr + kHdrCursor + kQueues; p.hm = head_map_kv(hkv);
+            p.hdr = sv_kv.hdr; p.items = sv_kv.items; p.cursors = sv_kv.hdr + kHdrCursor + kQueues; p.hm = head_map_kv(hkv, grid_kv.x);
             KernelTimer kt("bwd_dkdv_fp32", st);
             if (head_dim == 64) hipLaunchKernelGGL(hyd_bwd_dkdv_fp32_kernel<64>, grid_kv, dim3(64 * kF32KvWaves), f32_lds<64>(), st, p);
             else hipLaunchKernelGGL(hyd_bwd_dkdv_fp32_kernel<128>, grid_kv, dim3(64 * kF32KvWaves), f32_lds<128>(), st, p);

@@ -307,6 +307,9 @@ __device__ __forceinline__ void dq_block(int Kt, int Vt, const FragAddr& fa, int
             if (i < NK) s = mfma32h(f[i % kAhead], qf[i], s);
             else dp = mfma32(f[i % kAhead], dof[i - NK], dp);
             if (i + kAhead < 2 * NK) f[i % kAhead] = frag_row(i + kAhead < NK ? Kt : Vt, fa, kb, (i + kAhead) % NK);
+            // the fence keeps the MFMA in front of the vector work that is to run under it: left to the
+            // scheduler, some exponentials came first (131072 tokens, 64/8 heads: 25.39 ms, fenced 24.97)
+            __builtin_amdgcn_sched_barrier(0);
             if (i >= NK) {                        // the exponentials of the finished score block run under the dP product
 #pragma unroll
                 for (int e = 0; e < 16 / NK; ++e) {

@@ -44,6 +44,7 @@ struct HeadMap {              // how (item, head) pairs are spread over the queu
     int heads;                // heads per item (Hq for fwd/dQ, Hkv for dK/dV)
     int hpq;                  // partitioned: heads per queue
     int group;                // partitioned: consecutive work indices share group-size heads
+    int grid;                 // workgroups of the launch
 };
 
 // In-place inclusive scan of v[0..n) by ONE wave (all 64 lanes call it; n arbitrary): every lane
@@ -179,9 +180,11 @@ __device__ __forceinline__ void decode_work(const HeadMap& hm, int n_items, int 
     }
 }
 
-// Persistent-workgroup work fetch.  Thread 0 takes work indices from the queue of its XCD through
-// an atomic cursor, moving on to the next queue when one is exhausted, resolves an index to
-// (item, head), fetches the item's 16-byte record and leaves the result in LDS for the workgroup.
+// Persistent-workgroup work fetch.  The first item of a workgroup is fixed: workgroup b starts with
+// work index b / 8 of queue b % 8 (workgroups are dispatched to the XCDs in turn, so that is the queue
+// of its XCD; nothing depends on it).  Later ones are claimed by thread 0 through the queues' atomic
+// cursors, which count from the last fixed index on; an index is resolved to (item, head), the
+// item's 16-byte record fetched and the result left in LDS for the workgroup.
 //
 // The chain "cursor atomic -> item record" is two dependent trips to memory, as long as a whole
 // short item, so the atomic is taken off the critical path: a kernel calls claim() while it works on
@@ -193,8 +196,14 @@ __device__ __forceinline__ void decode_work(const HeadMap& hm, int n_items, int 
 // bf16 kernels, whose tile steps are ten times shorter, claim behind the loop, so that the atomic
 // runs under the epilogue (a branch in their loop cost 8-14 %): against a claim at the item's
 // start a context-parallel ring takes 6 % less, a 16384-token step 2 %, a 2304-token step with two KV
-// heads 14 %.  Only when a queue runs dry (eight times in a workgroup's life) is a claim repeated
-// on the next queue synchronously.  Every workgroup ends when all queues are empty (the cursors only grow).
+// heads 14 %.
+//
+// When its queue is dry a workgroup reads all eight cursors at once and goes on to the next queue that
+// still has work, if there is one; if the fixed indices cover all work there is no claim at all.
+// Claiming from the eight queues in turn until the last one was dry took 3-12 us at the end of every
+// launch: forward of 256 tokens, 32 heads 24.1 us, now 12.3; 2048 tokens, 8 heads 35.6 -> 31.5, dQ 45.3 ->
+// 42, dK/dV 40.8 -> 36.5.
+// Every workgroup ends when all queues are empty (the cursors only grow).
 struct WorkItem { int seq, lev, head, row0, len; };
 constexpr int kSlotInts = 16;          // two buffers of 8 ints
 typedef __attribute__((ext_vector_type(4))) int i32x4;
@@ -203,41 +212,45 @@ struct WorkFetcher {
     int cur;          // slot buffer holding the current item (all threads)
     // the rest is thread 0's
     int queue;        // queue the next claim goes to
-    int tried;        // queues found empty so far
     int n_items;
-    int claim_q;      // queue of the claim in flight
-    int claim_w;      // its result (the atomic's return value; no use of it until the item has ended)
+    int claim_w;      // what the atomic of the claim in flight returns (any use of it waits for it: left alone until next())
     bool claimed;     // a claim is in flight
     int nxt_item;     // next item: index (-1: none), head, and its record in flight
     int nxt_head;
     i32x4 nxt_rec;
 
+    // first index of queue x that is claimed through its cursor
+    __device__ __forceinline__ static int fixed(const HeadMap& hm, int x) { return (hm.grid - x + kQueues - 1) / kQueues; }
+
     __device__ __forceinline__ void issue_claim(const HeadMap& hm, int* cursors) {
         claimed = true;
-        claim_q = queue;
-        const bool open = tried < kQueues && queue_size(hm, n_items, queue) > 0;
-        claim_w = open ? atomicAdd(&cursors[queue], 1) : 0x7fffffff;
+        claim_w = queue_size(hm, n_items, queue) > fixed(hm, queue) ? atomicAdd(&cursors[queue], 1) : 0x3fffffff;
     }
-    // Turns the claim in flight into (item, head) of the next item and requests its record.
-    __device__ __forceinline__ void resolve(const HeadMap& hm, int* cursors, const int* __restrict__ items) {
-        int q = claim_q, w = claim_w;
+    // Turns work index w of `queue` into (item, head) of the next item and requests its record.
+    __device__ __forceinline__ void resolve(const HeadMap& hm, int* cursors, const int* __restrict__ items, int w) {
         nxt_item = -1;
         nxt_head = 0;
         claimed = false;
-        while (tried < kQueues) {
-            if (w < queue_size(hm, n_items, q)) {
-                decode_work(hm, n_items, q, w, nxt_item, nxt_head);
-                break;
-            }
-            if (q == queue) {                       // that queue is exhausted: on to the next one
-                queue = (queue + 1) & (kQueues - 1);
-                ++tried;
-                if (tried >= kQueues) break;
-            }
-            q = queue;
-            w = queue_size(hm, n_items, q) > 0 ? atomicAdd(&cursors[q], 1) : 0x7fffffff;
+        while (w >= queue_size(hm, n_items, queue)) {        // that queue is exhausted
+            bool any = false;
+#pragma unroll
+            for (int x = 0; x < kQueues; ++x) any |= queue_size(hm, n_items, x) > fixed(hm, x);
+            if (!any) return;                                // all work was handed out with the launch
+            int taken[kQueues];
+#pragma unroll
+            for (int x = 0; x < kQueues; ++x)
+                taken[x] = fixed(hm, x) + __hip_atomic_load(&cursors[x], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            uint32_t open = 0;
+#pragma unroll
+            for (int x = 0; x < kQueues; ++x) open |= (taken[x] < queue_size(hm, n_items, x) ? 1u : 0u) << x;
+            if (!open) return;
+            // the next open queue after the present one
+            const uint32_t turned = ((open | (open << kQueues)) >> (queue + 1)) & ((1u << kQueues) - 1);
+            queue = (queue + __ffs(turned)) & (kQueues - 1);
+            w = fixed(hm, queue) + atomicAdd(&cursors[queue], 1);
         }
-        if (nxt_item >= 0) nxt_rec = *reinterpret_cast<const i32x4*>(items + 4 * nxt_item);
+        decode_work(hm, n_items, queue, w, nxt_item, nxt_head);
+        nxt_rec = *reinterpret_cast<const i32x4*>(items + 4 * nxt_item);
     }
     __device__ __forceinline__ void publish(int* buf) const {
         buf[0] = nxt_item;
@@ -254,11 +267,9 @@ struct WorkFetcher {
                                           const int* __restrict__ items, int* slot, WorkItem& w) {
         cur = 0;
         if (threadIdx.x == 0) {
-            queue = (__smid() >> 6) & (kQueues - 1);     // XCC id of this workgroup
-            tried = 0;
+            queue = blockIdx.x & (kQueues - 1);
             n_items = hdr[0];
-            issue_claim(hm, cursors);
-            resolve(hm, cursors, items);
+            resolve(hm, cursors, items, blockIdx.x / kQueues);
             publish(slot);
         }
         __syncthreads();
@@ -272,7 +283,7 @@ struct WorkFetcher {
                                          int* slot, WorkItem& w) {
         if (threadIdx.x == 0) {
             if (!claimed) issue_claim(hm, cursors);      // an item without steps
-            resolve(hm, cursors, items);
+            resolve(hm, cursors, items, fixed(hm, queue) + claim_w);
             publish(slot + 8 * (cur ^ 1));
         }
         __syncthreads();        // the next item is visible; everybody is done with the LDS tiles
