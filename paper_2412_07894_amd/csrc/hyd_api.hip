@@ -22,8 +22,7 @@ using namespace hyd;
 constexpr size_t kAlign = 256;
 inline size_t align_up(size_t x) { return (x + kAlign - 1) / kAlign * kAlign; }
 
-// Workspace: one or two schedules (the backward has one per tile size when its two kernels use
-// different tiles), then the backward's row statistics ([Hq][T] floats; the fp32 path uses the
+// Workspace: one schedule, two for the backward (dK/dV, dQ), then the backward's row statistics ([Hq][T] floats; the fp32 path uses the
 // first one only) and, for bf16, the fp16 copies of Q, dO and K that its tile loops stream.
 constexpr int kBwdStatVecs = 4;
 struct SchedLayout { size_t hdr, lev, order, items; int n_lev, max_items; };
@@ -38,7 +37,7 @@ size_t sched_layout(SchedLayout& v, size_t at, int T, int nseq, int tile) {
     v.n_lev = (T + tile - 1) / tile;
     if (v.n_lev < 1) v.n_lev = 1;
     v.max_items = T / tile + nseq + 1;
-    v.hdr = at;   at += align_up(sizeof(int) * kHdrInts);
+    v.hdr = at;   at += align_up(sizeof(int) * kHdrTotal);
     v.lev = at;   at += align_up(sizeof(int) * 3 * (size_t)(v.n_lev + 2));
     v.order = at; at += align_up(sizeof(int) * (size_t)(nseq > 0 ? nseq : 1));
     v.items = at; at += align_up(sizeof(int) * 4 * (size_t)v.max_items);
@@ -48,8 +47,8 @@ size_t sched_layout(SchedLayout& v, size_t at, int T, int nseq, int tile) {
 WsLayout ws_layout(int T, int nseq, int tile0, int tile1, int hq, int hkv, int head_dim, hyd_dtype dt, bool bwd) {
     WsLayout w;
     size_t at = sched_layout(w.sched[0], 0, T, nseq, tile0);
-    w.n_sched = tile1 != tile0 ? 2 : 1;
-    if (w.n_sched == 2) at = sched_layout(w.sched[1], at, T, nseq, tile1);
+    w.n_sched = bwd ? 2 : 1;
+    if (bwd) at = sched_layout(w.sched[1], at, T, nseq, tile1);
     else w.sched[1] = w.sched[0];
     const int n_stat = !bwd ? 0 : (dt == HYD_BF16 ? kBwdStatVecs : 1);
     for (int i = 0; i < kBwdStatVecs; ++i) {
@@ -440,7 +439,7 @@ hyd_status bwd_impl(const void* q, const void* k, const void* v, const void* o, 
         // dQ first: it also writes the fp16 copies of Q and dO that dK/dV streams
         {
             p.hdr = sv_q.hdr; p.items = sv_q.items;
-            p.cursors = sv_q.hdr + kHdrCursor + 2 * kQueues;
+            p.cursors = sv_q.hdr + kHdrCursor;
             const dim3 grid(persistent_grid(*dev, dev->occ_dq, work_q));
             p.hm = head_map_q(hq, hkv, grid.x);
             KernelTimer kt(ranged ? "bwd_dq_range_bf16" : "bwd_dq_bf16", st);
@@ -452,7 +451,7 @@ hyd_status bwd_impl(const void* q, const void* k, const void* v, const void* o, 
         }
         {
             p.hdr = sv_kv.hdr; p.items = sv_kv.items;
-            p.cursors = sv_kv.hdr + kHdrCursor + kQueues;
+            p.cursors = sv_kv.hdr + kHdrCursor;
             const dim3 grid(persistent_grid(*dev, dev->occ_kv, work_kv));
             p.hm = head_map_kv(hkv, grid.x);
             KernelTimer kt(ranged ? "bwd_dkdv_range_bf16" : "bwd_dkdv_bf16", st);
@@ -481,13 +480,13 @@ hyd_status bwd_impl(const void* q, const void* k, const void* v, const void* o, 
         const dim3 grid_q(persistent_grid(*dev, occ[1], work_q)), grid_kv(persistent_grid(*dev, occ[2], work_kv));
         // dQ first: it also writes the row sums D that dK/dV reads
         {
-            p.hdr = sv_q.hdr; p.items = sv_q.items; p.cursors = sv_q.hdr + kHdrCursor + 2 * kQueues; p.hm = head_map_q(hq, hkv, grid_q.x);
+            p.hdr = sv_q.hdr; p.items = sv_q.items; p.cursors = sv_q.hdr + kHdrCursor; p.hm = head_map_q(hq, hkv, grid_q.x);
             KernelTimer kt("bwd_dq_fp32", st);
             if (head_dim == 64) hipLaunchKernelGGL(hyd_bwd_dq_fp32_kernel<64>, grid_q, dim3(64 * kF32Waves), f32_lds<64>(), st, p);
             else hipLaunchKernelGGL(hyd_bwd_dq_fp32_kernel<128>, grid_q, dim3(64 * kF32Waves), f32_lds<128>(), st, p);
         }
         {
-            p.hdr = sv_kv.hdr; p.items = sv_kv.items; p.cursors = sv_kv.hdr + kHdrCursor + kQueues; p.hm = head_map_kv(hkv, grid_kv.x);
+            p.hdr = sv_kv.hdr; p.items = sv_kv.items; p.cursors = sv_kv.hdr + kHdrCursor; p.hm = head_map_kv(hkv, grid_kv.x);
             KernelTimer kt("bwd_dkdv_fp32", st);
             if (head_dim == 64) hipLaunchKernelGGL(hyd_bwd_dkdv_fp32_kernel<64>, grid_kv, dim3(64 * kF32KvWaves), f32_lds<64>(), st, p);
             else hipLaunchKernelGGL(hyd_bwd_dkdv_fp32_kernel<128>, grid_kv, dim3(64 * kF32KvWaves), f32_lds<128>(), st, p);

@@ -21,17 +21,18 @@ namespace hyd {
 
 constexpr int kQueues = 8;
 
-constexpr int kHdrInts = 64;
-// header (ints): [0] n_items, [1] kSched* flags about cu_seqlens as the prelude saw it,
-// [8 + 8*k + x] cursor of queue x of kernel k (k = 0 fwd, 1 dK/dV, 2 dQ); the rest is zeroed by
-// the prelude
-constexpr int kHdrCursor = 8;
+// header (ints): [0] n_items, [1] kSched* flags about cu_seqlens as the prelude saw it, the rest
+// zeros; then the cursors of the eight queues, 256 bytes apart: the workgroups of all XCDs claim
+// through them with device-scope atomics, which a shared line serialises (one line for all eight:
+// forward of 26177 tokens in sequences of 64-1024, 32 heads, d = 64: 227 us, apart 216)
+constexpr int kHdrInts = 64, kCursorStride = 64;
+constexpr int kHdrCursor = kHdrInts, kHdrTotal = kHdrInts + kQueues * kCursorStride;
 constexpr int kHdrFlags = 1;
 constexpr int kSchedTooLong = 1;          // a sequence is longer than max_seqlen: its tiles beyond that bound got no item
 constexpr int kSchedBadSeqlens = 2;       // cu_seqlens does not start at 0, does not end at T, or decreases
 
 struct SchedView {            // device pointers into the workspace (all int32)
-    int* hdr;                 // kHdrInts
+    int* hdr;                 // kHdrTotal
     int* lev;                 // 3 * (n_lev + 2): level arrays, used instead of LDS when n_lev is large
     int* order;               // n_seq: sequence index by rank (more tiles first, then arrival)
     int* items;               // 4 * max_items : records (s, c, first packed row, length), decreasing c
@@ -85,7 +86,7 @@ __device__ __forceinline__ void build_schedule(const int32_t* __restrict__ cu, i
     int* cnt = lev + (nl + 2);             // [r]: sequences with >= nl - r tiles (levels in reversed order)
     int* offs = lev + 2 * (nl + 2);        // [r]: list position after level nl - r
     for (int i = tid; i < nl + 2; i += nthreads) hist[i] = 0;
-    for (int i = tid; i < kHdrInts; i += nthreads) sv.hdr[i] = 0;
+    for (int i = tid; i < kHdrTotal; i += nthreads) sv.hdr[i] = 0;
     __syncthreads();
     int flags = (tid == 0 && (cu[0] != 0 || cu[nseq] != T)) ? kSchedBadSeqlens : 0;
     for (int s = tid; s < nseq; s += nthreads) {
@@ -224,7 +225,7 @@ struct WorkFetcher {
 
     __device__ __forceinline__ void issue_claim(const HeadMap& hm, int* cursors) {
         claimed = true;
-        claim_w = queue_size(hm, n_items, queue) > fixed(hm, queue) ? atomicAdd(&cursors[queue], 1) : 0x3fffffff;
+        claim_w = queue_size(hm, n_items, queue) > fixed(hm, queue) ? atomicAdd(&cursors[queue * kCursorStride], 1) : 0x3fffffff;
     }
     // Turns work index w of `queue` into (item, head) of the next item and requests its record.
     __device__ __forceinline__ void resolve(const HeadMap& hm, int* cursors, const int* __restrict__ items, int w) {
@@ -239,7 +240,7 @@ struct WorkFetcher {
             int taken[kQueues];
 #pragma unroll
             for (int x = 0; x < kQueues; ++x)
-                taken[x] = fixed(hm, x) + __hip_atomic_load(&cursors[x], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                taken[x] = fixed(hm, x) + __hip_atomic_load(&cursors[x * kCursorStride], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             uint32_t open = 0;
 #pragma unroll
             for (int x = 0; x < kQueues; ++x) open |= (taken[x] < queue_size(hm, n_items, x) ? 1u : 0u) << x;
@@ -247,7 +248,7 @@ struct WorkFetcher {
             // the next open queue after the present one
             const uint32_t turned = ((open | (open << kQueues)) >> (queue + 1)) & ((1u << kQueues) - 1);
             queue = (queue + __ffs(turned)) & (kQueues - 1);
-            w = fixed(hm, queue) + atomicAdd(&cursors[queue], 1);
+            w = fixed(hm, queue) + atomicAdd(&cursors[queue * kCursorStride], 1);
         }
         decode_work(hm, n_items, queue, w, nxt_item, nxt_head);
         nxt_rec = *reinterpret_cast<const i32x4*>(items + 4 * nxt_item);
