@@ -198,8 +198,9 @@ hyd_status hyd_varlen_attn_schedule_layout(int total_tokens, int num_seqs, int h
  * allocation): same computation and results as hyd_varlen_attn_fwd, with the schedule kept in a
  * fixed array inside the library (hyd_varlen_attn_fwd_noalloc_max_workspace() bytes per GPU,
  * held until the process ends).  It calls no hipMalloc / hipFree and no allocating routine.
- * Sizes whose forward workspace (hyd_varlen_attn_workspace_bytes(..., 0)) exceeds that array
- * are rejected with HYD_ERR_WORKSPACE before any HIP call; 2 MiB cover, for example, one million
+ * Sizes whose schedule does not fit that array are rejected with HYD_ERR_WORKSPACE before any HIP
+ * call (hyd_varlen_attn_workspace_bytes(..., 0) within it is always enough; larger ones may still do, as
+ * the call can go without the second copy of the item list); 2 MiB cover, for example, one million
  * tokens in 65536 sequences.  All calls on one GPU share the one array: two calls whose kernels
  * overlap in time (different streams, or different host threads) race on it, so serialise them.
  * Argument checks, errors and stream semantics otherwise as hyd_varlen_attn_fwd.

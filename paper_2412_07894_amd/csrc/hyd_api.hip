@@ -25,7 +25,7 @@ inline size_t align_up(size_t x) { return (x + kAlign - 1) / kAlign * kAlign; }
 // Workspace: one schedule, two for the backward (dK/dV, dQ), then the backward's row statistics ([Hq][T] floats; the fp32 path uses the
 // first one only) and, for bf16, the fp16 copies of Q, dO and K that its tile loops stream.
 constexpr int kBwdStatVecs = 4;
-struct SchedLayout { size_t hdr, lev, order, items; int n_lev, max_items; };
+struct SchedLayout { size_t hdr, lev, order, items, exec; int n_lev, max_items; };
 struct WsLayout {
     SchedLayout sched[2];
     int n_sched;
@@ -33,7 +33,8 @@ struct WsLayout {
 };
 constexpr int kRopeTabEntries = 64;       // head_dim / 2 at most
 
-size_t sched_layout(SchedLayout& v, size_t at, int T, int nseq, int tile) {
+// `compact`: the records are handed out in list order, without a second copy of them
+size_t sched_layout(SchedLayout& v, size_t at, int T, int nseq, int tile, bool compact) {
     v.n_lev = (T + tile - 1) / tile;
     if (v.n_lev < 1) v.n_lev = 1;
     v.max_items = T / tile + nseq + 1;
@@ -41,14 +42,16 @@ size_t sched_layout(SchedLayout& v, size_t at, int T, int nseq, int tile) {
     v.lev = at;   at += align_up(sizeof(int) * 3 * (size_t)(v.n_lev + 2));
     v.order = at; at += align_up(sizeof(int) * (size_t)(nseq > 0 ? nseq : 1));
     v.items = at; at += align_up(sizeof(int) * 4 * (size_t)v.max_items);
+    v.exec = v.items;
+    if (!compact) { v.exec = at; at += align_up(sizeof(int) * 4 * (size_t)v.max_items); }
     return at;
 }
 
-WsLayout ws_layout(int T, int nseq, int tile0, int tile1, int hq, int hkv, int head_dim, hyd_dtype dt, bool bwd) {
+WsLayout ws_layout(int T, int nseq, int tile0, int tile1, int hq, int hkv, int head_dim, hyd_dtype dt, bool bwd, bool compact = false) {
     WsLayout w;
-    size_t at = sched_layout(w.sched[0], 0, T, nseq, tile0);
+    size_t at = sched_layout(w.sched[0], 0, T, nseq, tile0, compact);
     w.n_sched = bwd ? 2 : 1;
-    if (bwd) at = sched_layout(w.sched[1], at, T, nseq, tile1);
+    if (bwd) at = sched_layout(w.sched[1], at, T, nseq, tile1, compact);
     else w.sched[1] = w.sched[0];
     const int n_stat = !bwd ? 0 : (dt == HYD_BF16 ? kBwdStatVecs : 1);
     for (int i = 0; i < kBwdStatVecs; ++i) {
@@ -70,6 +73,12 @@ int tile_fwd(hyd_dtype dt) { return dt == HYD_BF16 ? kFwdBM : kF32BM; }
 int tile_dq(hyd_dtype dt) { return dt == HYD_BF16 ? kDqBM : kF32BM; }
 int tile_kv(hyd_dtype dt) { return dt == HYD_BF16 ? kKvBN : kF32KvBN; }
 
+WsLayout fwd_layout(int T, int nseq, int hq, int hkv, int head_dim, hyd_dtype dt, bool compact) {
+    return ws_layout(T, nseq, tile_fwd(dt), tile_fwd(dt), hq, hkv, head_dim, dt, false, compact);
+}
+WsLayout bwd_layout(int T, int nseq, int hq, int hkv, int head_dim, hyd_dtype dt) {
+    return ws_layout(T, nseq, tile_kv(dt), tile_dq(dt), hq, hkv, head_dim, dt, true);
+}
 
 bool head_dim_ok(hyd_dtype dt, int d) { (void)dt; return d == 64 || d == 128; }
 
@@ -95,7 +104,7 @@ HeadMap head_map_kv(int hkv, int grid) {
 
 hyd_status validate_common(const int32_t* cu, int num_seqs, const int32_t* cu_host, int T,
                            int max_seqlen, int hq, int hkv, int head_dim, hyd_dtype dt,
-                           const void* ws, size_t ws_bytes, bool bwd) {
+                           const void* ws, size_t ws_bytes, bool bwd, bool compact = false) {
     if (dt != HYD_BF16 && dt != HYD_FP32) return HYD_ERR_DTYPE;
     if (T < 0 || num_seqs < 0 || max_seqlen < 0) return HYD_ERR_SHAPE;
     if (num_seqs == 0 && T != 0) return HYD_ERR_SHAPE;
@@ -118,7 +127,7 @@ hyd_status validate_common(const int32_t* cu, int num_seqs, const int32_t* cu_ho
         }
         if (longest > max_seqlen) return HYD_ERR_SHAPE;
     }
-    const size_t need = hyd_varlen_attn_workspace_bytes(T, num_seqs, hq, hkv, head_dim, dt, bwd ? 1 : 0);
+    const size_t need = (bwd ? bwd_layout(T, num_seqs, hq, hkv, head_dim, dt) : fwd_layout(T, num_seqs, hq, hkv, head_dim, dt, compact)).total;
     if (!ws || ((uintptr_t)ws % kAlign) != 0 || ws_bytes < need) return HYD_ERR_WORKSPACE;
     return HYD_OK;
 }
@@ -248,7 +257,10 @@ struct KernelTimer {       // brackets one launch with events when timing is on
 };
 
 // View of schedule `which`; its level count is bounded by the caller's max_seqlen.
-SchedView make_view(char* ws, const SchedLayout& v, int tile, int max_seqlen) {
+// `heads` work items per record are shared by `wgs` workgroups.  Sequences are grouped up to
+// 1024 bf16 (512 fp32) rows, 512 KB of K and V for a head, unless four or more query heads share
+// a KV head: their workgroups share its stream already, and the list's own order is balanced best.
+SchedView make_view(char* ws, const SchedLayout& v, int tile, int max_seqlen, hyd_dtype dt, int heads, int wgs, bool grouped_heads) {
     SchedView sv;
     sv.hdr = reinterpret_cast<int*>(ws + v.hdr);
     sv.lev = reinterpret_cast<int*>(ws + v.lev);
@@ -257,6 +269,9 @@ SchedView make_view(char* ws, const SchedLayout& v, int tile, int max_seqlen) {
     const int by_len = (max_seqlen + tile - 1) / tile;
     sv.n_lev = by_len < v.n_lev ? (by_len < 1 ? 1 : by_len) : v.n_lev;
     sv.max_items = v.max_items;
+    sv.exec = reinterpret_cast<int*>(ws + v.exec);
+    sv.group_max = v.exec == v.items || grouped_heads ? 0 : (dt == HYD_BF16 ? 1024 : 512) / tile;
+    sv.group_share = (float)heads / (16.f * (float)wgs);
     return sv;
 }
 
@@ -292,8 +307,8 @@ size_t hyd_varlen_attn_workspace_bytes(int total_tokens, int num_seqs, int hq, i
                                        hyd_dtype dt, int is_bwd) {
     if (total_tokens < 0 || num_seqs < 0 || hq <= 0 || hkv <= 0 || hq % hkv != 0) return 0;
     if ((dt != HYD_BF16 && dt != HYD_FP32) || !head_dim_ok(dt, head_dim)) return 0;
-    return (is_bwd ? ws_layout(total_tokens, num_seqs, tile_kv(dt), tile_dq(dt), hq, hkv, head_dim, dt, true)
-                   : ws_layout(total_tokens, num_seqs, tile_fwd(dt), tile_fwd(dt), hq, hkv, head_dim, dt, false)).total;
+    return (is_bwd ? bwd_layout(total_tokens, num_seqs, hq, hkv, head_dim, dt)
+                   : fwd_layout(total_tokens, num_seqs, hq, hkv, head_dim, dt, false)).total;
 }
 
 }  // extern "C"
@@ -307,10 +322,10 @@ hyd_status fwd_impl(const void* q, const void* k, const void* v, const int32_t* 
                     const int32_t* ranges_host, bool ranged, int total_tokens,
                     int max_seqlen, int hq, int hkv, int head_dim, float softmax_scale,
                     hyd_dtype dt, void* o, float* lse, void* workspace,
-                    size_t workspace_bytes, void* hip_stream, float rope_base = 0.f) {
+                    size_t workspace_bytes, void* hip_stream, float rope_base = 0.f, bool compact = false) {
     if (rope_base != 0.f && (dt != HYD_BF16 || !(rope_base > 1.f))) return dt != HYD_BF16 ? HYD_ERR_DTYPE : HYD_ERR_SHAPE;
     const hyd_status vs = validate_common(cu_seqlens, num_seqs, cu_seqlens_host, total_tokens, max_seqlen,
-                                          hq, hkv, head_dim, dt, workspace, workspace_bytes, false);
+                                          hq, hkv, head_dim, dt, workspace, workspace_bytes, false, compact);
     if (vs != HYD_OK) return vs;
     if (ranged) {
         const hyd_status rs = validate_ranges(ranges, ranges_host, cu_seqlens_host, num_seqs, max_seqlen, dt);
@@ -325,8 +340,9 @@ hyd_status fwd_impl(const void* q, const void* k, const void* v, const int32_t* 
     hipStream_t st = static_cast<hipStream_t>(hip_stream);
 
     const int tile = tile_fwd(dt);
-    const WsLayout w = ws_layout(total_tokens, num_seqs, tile, tile, hq, hkv, head_dim, dt, false);
-    const SchedView sv = make_view(static_cast<char*>(workspace), w.sched[0], tile, max_seqlen);
+    const WsLayout w = fwd_layout(total_tokens, num_seqs, hq, hkv, head_dim, dt, compact);
+    const int occ = dt == HYD_BF16 ? dev->occ_fwd : dev->occ_f32[head_dim == 128][0];
+    const SchedView sv = make_view(static_cast<char*>(workspace), w.sched[0], tile, max_seqlen, dt, hq, dev->cus * occ, hq >= 4 * hkv);
     double* rope_tab = rope_base != 0.f ? reinterpret_cast<double*>(static_cast<char*>(workspace) + w.rope_tab) : nullptr;
     {
         KernelTimer kt("schedule_prelude", st);
@@ -340,10 +356,10 @@ hyd_status fwd_impl(const void* q, const void* k, const void* v, const int32_t* 
         p.v = static_cast<const uint16_t*>(v); p.o = static_cast<uint16_t*>(o); p.lse = lse;
         p.T = total_tokens; p.hq = hq; p.hkv = hkv;
         p.scale_log2 = softmax_scale * kLog2e;
-        p.hdr = sv.hdr; p.cursors = sv.hdr + kHdrCursor; p.items = sv.items; p.tr = t_trace;
+        p.hdr = sv.hdr; p.cursors = sv.hdr + kHdrCursor; p.items = sv.exec; p.tr = t_trace;
         p.ranges = ranged ? ranges : nullptr;
         p.rope_tab = rope_tab;
-        const dim3 grid(persistent_grid(*dev, dev->occ_fwd, work));
+        const dim3 grid(persistent_grid(*dev, occ, work));
         p.hm = head_map_q(hq, hkv, grid.x);
         KernelTimer kt(ranged ? "fwd_range_bf16" : "fwd_bf16", st);
         if (head_dim == 64) {
@@ -357,8 +373,8 @@ hyd_status fwd_impl(const void* q, const void* k, const void* v, const int32_t* 
         p.q = static_cast<const float*>(q); p.k = static_cast<const float*>(k);
         p.v = static_cast<const float*>(v); p.o_out = static_cast<float*>(o); p.lse_out = lse;
         p.T = total_tokens; p.hq = hq; p.hkv = hkv; p.scale = softmax_scale;
-        p.hdr = sv.hdr; p.cursors = sv.hdr + kHdrCursor; p.items = sv.items; p.tr = t_trace;
-        const dim3 grid(persistent_grid(*dev, dev->occ_f32[head_dim == 128][0], work));
+        p.hdr = sv.hdr; p.cursors = sv.hdr + kHdrCursor; p.items = sv.exec; p.tr = t_trace;
+        const dim3 grid(persistent_grid(*dev, occ, work));
         p.hm = head_map_q(hq, hkv, grid.x);
         KernelTimer kt("fwd_fp32", st);
         if (head_dim == 64) hipLaunchKernelGGL(hyd_fwd_fp32_kernel<64>, grid, dim3(64 * kF32Waves), f32_lds<64>(), st, p);
@@ -390,10 +406,12 @@ hyd_status bwd_impl(const void* q, const void* k, const void* v, const void* o, 
     if (ds != HYD_OK) return ds;
     hipStream_t st = static_cast<hipStream_t>(hip_stream);
 
-    const WsLayout w = ws_layout(total_tokens, num_seqs, tile_kv(dt), tile_dq(dt), hq, hkv, head_dim, dt, true);
+    const WsLayout w = bwd_layout(total_tokens, num_seqs, hq, hkv, head_dim, dt);
     char* ws = static_cast<char*>(workspace);
-    const SchedView sv_kv = make_view(ws, w.sched[0], tile_kv(dt), max_seqlen);
-    const SchedView sv_q = make_view(ws, w.sched[1], tile_dq(dt), max_seqlen);
+    const int occ_q = dt == HYD_BF16 ? dev->occ_dq : dev->occ_f32[head_dim == 128][1];
+    const int occ_kv = dt == HYD_BF16 ? dev->occ_kv : dev->occ_f32[head_dim == 128][2];
+    const SchedView sv_kv = make_view(ws, w.sched[0], tile_kv(dt), max_seqlen, dt, hkv, dev->cus * occ_kv, hq >= 4 * hkv);
+    const SchedView sv_q = make_view(ws, w.sched[1], tile_dq(dt), max_seqlen, dt, hq, dev->cus * occ_q, hq >= 4 * hkv);
     float* Dvec = reinterpret_cast<float*>(ws + w.stat[0]);
     double* rope_tab = rope_base != 0.f ? reinterpret_cast<double*>(ws + w.rope_tab) : nullptr;
     const long long work_q = (long long)sv_q.max_items * hq, work_kv = (long long)sv_kv.max_items * hkv;
@@ -438,9 +456,9 @@ hyd_status bwd_impl(const void* q, const void* k, const void* v, const void* o, 
         p.rope_tab = rope_tab;
         // dQ first: it also writes the fp16 copies of Q and dO that dK/dV streams
         {
-            p.hdr = sv_q.hdr; p.items = sv_q.items;
+            p.hdr = sv_q.hdr; p.items = sv_q.exec;
             p.cursors = sv_q.hdr + kHdrCursor;
-            const dim3 grid(persistent_grid(*dev, dev->occ_dq, work_q));
+            const dim3 grid(persistent_grid(*dev, occ_q, work_q));
             p.hm = head_map_q(hq, hkv, grid.x);
             KernelTimer kt(ranged ? "bwd_dq_range_bf16" : "bwd_dq_bf16", st);
             if (head_dim == 64) {
@@ -450,9 +468,9 @@ hyd_status bwd_impl(const void* q, const void* k, const void* v, const void* o, 
             else hipLaunchKernelGGL(hyd_bwd_dq_bf16_kernel<false>, grid, dim3(kDqThreads), kDqLds, st, p);
         }
         {
-            p.hdr = sv_kv.hdr; p.items = sv_kv.items;
+            p.hdr = sv_kv.hdr; p.items = sv_kv.exec;
             p.cursors = sv_kv.hdr + kHdrCursor;
-            const dim3 grid(persistent_grid(*dev, dev->occ_kv, work_kv));
+            const dim3 grid(persistent_grid(*dev, occ_kv, work_kv));
             p.hm = head_map_kv(hkv, grid.x);
             KernelTimer kt(ranged ? "bwd_dkdv_range_bf16" : "bwd_dkdv_bf16", st);
             if (head_dim == 64) {
@@ -476,17 +494,16 @@ hyd_status bwd_impl(const void* q, const void* k, const void* v, const void* o, 
             hipLaunchKernelGGL(hyd_schedule_prelude, dim3(w.n_sched), dim3(kPreludeThreads), lds_kv > lds_q ? lds_kv : lds_q, st, cu_seqlens,
                                num_seqs, total_tokens, tile_kv(dt), sv_kv, tile_dq(dt), sv_q, nullptr, 0, 0.0);
         }
-        const int* occ = dev->occ_f32[head_dim == 128];
-        const dim3 grid_q(persistent_grid(*dev, occ[1], work_q)), grid_kv(persistent_grid(*dev, occ[2], work_kv));
+        const dim3 grid_q(persistent_grid(*dev, occ_q, work_q)), grid_kv(persistent_grid(*dev, occ_kv, work_kv));
         // dQ first: it also writes the row sums D that dK/dV reads
         {
-            p.hdr = sv_q.hdr; p.items = sv_q.items; p.cursors = sv_q.hdr + kHdrCursor; p.hm = head_map_q(hq, hkv, grid_q.x);
+            p.hdr = sv_q.hdr; p.items = sv_q.exec; p.cursors = sv_q.hdr + kHdrCursor; p.hm = head_map_q(hq, hkv, grid_q.x);
             KernelTimer kt("bwd_dq_fp32", st);
             if (head_dim == 64) hipLaunchKernelGGL(hyd_bwd_dq_fp32_kernel<64>, grid_q, dim3(64 * kF32Waves), f32_lds<64>(), st, p);
             else hipLaunchKernelGGL(hyd_bwd_dq_fp32_kernel<128>, grid_q, dim3(64 * kF32Waves), f32_lds<128>(), st, p);
         }
         {
-            p.hdr = sv_kv.hdr; p.items = sv_kv.items; p.cursors = sv_kv.hdr + kHdrCursor; p.hm = head_map_kv(hkv, grid_kv.x);
+            p.hdr = sv_kv.hdr; p.items = sv_kv.exec; p.cursors = sv_kv.hdr + kHdrCursor; p.hm = head_map_kv(hkv, grid_kv.x);
             KernelTimer kt("bwd_dkdv_fp32", st);
             if (head_dim == 64) hipLaunchKernelGGL(hyd_bwd_dkdv_fp32_kernel<64>, grid_kv, dim3(64 * kF32KvWaves), f32_lds<64>(), st, p);
             else hipLaunchKernelGGL(hyd_bwd_dkdv_fp32_kernel<128>, grid_kv, dim3(64 * kF32KvWaves), f32_lds<128>(), st, p);
@@ -543,11 +560,12 @@ hyd_status hyd_varlen_attn_fwd_noalloc(const void* q, const void* k, const void*
     if (hq <= 0 || hkv <= 0 || hq % hkv != 0) return HYD_ERR_HEADS;
     if (dt != HYD_BF16 && dt != HYD_FP32) return HYD_ERR_DTYPE;
     if (!head_dim_ok(dt, head_dim)) return HYD_ERR_HEADDIM;
-    if (hyd_varlen_attn_workspace_bytes(total_tokens, num_seqs, hq, hkv, head_dim, dt, 0) > kScratchBytes)
-        return HYD_ERR_WORKSPACE;
+    // (if need be without the second copy of the item records)
+    const bool compact = fwd_layout(total_tokens, num_seqs, hq, hkv, head_dim, dt, false).total > kScratchBytes;
+    if (compact && fwd_layout(total_tokens, num_seqs, hq, hkv, head_dim, dt, true).total > kScratchBytes) return HYD_ERR_WORKSPACE;
     // the rest of the argument checks, still before any HIP call (a stand-in for the workspace pointer)
     const hyd_status vs = validate_common(cu_seqlens, num_seqs, cu_seqlens_host, total_tokens, max_seqlen, hq, hkv, head_dim,
-                                          dt, reinterpret_cast<const void*>(kAlign), kScratchBytes, false);
+                                          dt, reinterpret_cast<const void*>(kAlign), kScratchBytes, false, compact);
     if (vs != HYD_OK) return vs;
     if (total_tokens == 0 || num_seqs == 0) return HYD_OK;
     if (!q || !k || !v || !o || !lse) return HYD_ERR_NULL;
@@ -555,7 +573,7 @@ hyd_status hyd_varlen_attn_fwd_noalloc(const void* q, const void* k, const void*
     const hyd_status ds = device_info(&dev);          // first call on a device: looks the array's address up
     if (ds != HYD_OK) return ds;
     return fwd_impl(q, k, v, cu_seqlens, num_seqs, cu_seqlens_host, nullptr, nullptr, false, total_tokens, max_seqlen,
-                    hq, hkv, head_dim, softmax_scale, dt, o, lse, dev->scratch, kScratchBytes, hip_stream);
+                    hq, hkv, head_dim, softmax_scale, dt, o, lse, dev->scratch, kScratchBytes, hip_stream, 0.f, compact);
 }
 
 hyd_status hyd_varlen_attn_bwd(const void* q, const void* k, const void* v, const void* o, const float* lse,
@@ -650,8 +668,8 @@ hyd_status hyd_varlen_attn_schedule_layout(int total_tokens, int num_seqs, int h
     if (hq <= 0 || hkv <= 0 || hq % hkv != 0) return HYD_ERR_HEADS;
     if (dt != HYD_BF16 && dt != HYD_FP32) return HYD_ERR_DTYPE;
     if (!head_dim_ok(dt, head_dim)) return HYD_ERR_HEADDIM;
-    const WsLayout w = is_bwd ? ws_layout(total_tokens, num_seqs, tile_kv(dt), tile_dq(dt), hq, hkv, head_dim, dt, true)
-                              : ws_layout(total_tokens, num_seqs, tile_fwd(dt), tile_fwd(dt), hq, hkv, head_dim, dt, false);
+    const WsLayout w = is_bwd ? bwd_layout(total_tokens, num_seqs, hq, hkv, head_dim, dt)
+                              : fwd_layout(total_tokens, num_seqs, hq, hkv, head_dim, dt, false);
     const SchedLayout& v = w.sched[which];
     *header_offset = v.hdr; *items_offset = v.items; *max_items = v.max_items;
     *tile = !is_bwd ? tile_fwd(dt) : (which == 0 ? tile_kv(dt) : tile_dq(dt));

@@ -20,6 +20,7 @@
 namespace hyd {
 
 constexpr int kQueues = 8;
+typedef __attribute__((ext_vector_type(4))) int i32x4;
 
 // header (ints): [0] n_items, [1] kSched* flags about cu_seqlens as the prelude saw it, the rest
 // zeros; then the cursors of the eight queues, 256 bytes apart: the workgroups of all XCDs claim
@@ -36,6 +37,9 @@ struct SchedView {            // device pointers into the workspace (all int32)
     int* lev;                 // 3 * (n_lev + 2): level arrays, used instead of LDS when n_lev is large
     int* order;               // n_seq: sequence index by rank (more tiles first, then arrival)
     int* items;               // 4 * max_items : records (s, c, first packed row, length), decreasing c
+    int* exec;                // the same records in the order in which they are handed out (see build_schedule); may be `items` itself
+    int group_max;            // levels 1 .. group_max at most are grouped by sequence (0 when exec == items)
+    float group_share;        // ... and at most (sum of all levels) * group_share
     int n_lev;                // upper bound on tiles per sequence
     int max_items;
 };
@@ -77,6 +81,19 @@ __host__ __device__ constexpr size_t schedule_lds(int nl) { return nl <= kPrelud
 // (from the caller's max_seqlen).  Order among items of equal cost: by sequence rank (arrival order
 // among equals), which is unspecified (it never changes a result: every output element has
 // exactly one producer).
+//
+// The order of execution differs from the list at its cheap end: the items of levels 1 .. C follow
+// sequence by sequence (longest sequence first, its highest level first).  In the list the tiles of
+// one short sequence lie as far apart as the levels do, and each reads the sequence's K and V (dK/dV:
+// Q and dO) from HBM again; next to each other they share them in the L2 of their XCD.  C is what
+// keeps a launch balanced: group_max levels (C tiles of a sequence and a head fit the L2 next to
+// those of the other workgroups) and a sixteenth of what a workgroup has to do in all, since the last
+// items handed out are no longer the cheapest ones.  Measured (forward / dQ / dK/dV in us, list order
+// -> this one, 32768 tokens, 32 heads): lengths 64-400 310 / 455 / 475 -> 284 / 412 / 447, 64-1024 366 /
+// 522 / 612 -> 353 / 496 / 573, 32 x 1024 435 / 593 / 803 -> 417 / 565 / 717.  With grouped heads (32/8), whose
+// workgroups share a stream across the group, it is within 1.5 % either way and left alone; so are
+// striped queues, which deal neighbouring items to different XCDs (dealing blocks of eight instead
+// gained nothing).
 __device__ __forceinline__ void build_schedule(const int32_t* __restrict__ cu, int nseq, int T, int tile, const SchedView& sv,
                                                int* lds_lev, int nthreads) {
     const int tid = threadIdx.x;
@@ -89,15 +106,19 @@ __device__ __forceinline__ void build_schedule(const int32_t* __restrict__ cu, i
     for (int i = tid; i < kHdrTotal; i += nthreads) sv.hdr[i] = 0;
     __syncthreads();
     int flags = (tid == 0 && (cu[0] != 0 || cu[nseq] != T)) ? kSchedBadSeqlens : 0;
+    float cost = 0.f;                      // sum of all levels
     for (int s = tid; s < nseq; s += nthreads) {
         const int L = cu[s + 1] - cu[s];
         if (L < 0) flags |= kSchedBadSeqlens;
         if (L > 0 && (L + tile - 1) / tile > nl) flags |= kSchedTooLong;
         const int n = min((L + tile - 1) / tile, nl);
         if (n > 0) atomicAdd(&hist[n], 1);
+        cost += 0.5f * (float)n * (float)(n + 1);
     }
+    if (cost > 0.f) atomicAdd(reinterpret_cast<float*>(hist), cost);        // hist[0] is not a level
     if (flags) atomicOr(&sv.hdr[kHdrFlags], flags);
     __syncthreads();
+    const int C = min(min(sv.group_max, nl), (int)fminf(*reinterpret_cast<const float*>(hist) * sv.group_share, 1e6f));
     if (tid < 64) {
         // cnt[r] = sum_{n >= nl - r} hist[n]; offs = inclusive scan of cnt
         for (int r = tid; r < nl; r += 64) cnt[r] = hist[nl - r];
@@ -127,10 +148,20 @@ __device__ __forceinline__ void build_schedule(const int32_t* __restrict__ cu, i
             const int mid = (lo + hi) >> 1;
             if (offs[mid] > pos) hi = mid; else lo = mid + 1;
         }
-        const int s = sv.order[pos - (offs[lo] - cnt[lo])];
-        const int a = cu[s];
-        int* rec = sv.items + 4 * pos;
-        rec[0] = s; rec[1] = nl - lo; rec[2] = a; rec[3] = cu[s + 1] - a;
+        const int rank = pos - (offs[lo] - cnt[lo]), c = nl - lo;
+        const int s = sv.order[rank];
+        const int a = cu[s], L = cu[s + 1] - a;
+        const i32x4 rec = {s, c, a, L};
+        *reinterpret_cast<i32x4*>(sv.items + 4 * pos) = rec;
+        if (sv.exec != sv.items) {
+            int e = pos;
+            if (c <= C) {
+                // items of higher levels, then the C lowest levels of the sequences of lower rank
+                e = (C < nl ? offs[nl - C - 1] : 0) + min((L + tile - 1) / tile, C) - c;
+                for (int x = 1; x <= C; ++x) e += min(rank, cnt[nl - x]);
+            }
+            *reinterpret_cast<i32x4*>(sv.exec + 4 * e) = rec;
+        }
     }
 }
 
@@ -207,8 +238,6 @@ __device__ __forceinline__ void decode_work(const HeadMap& hm, int n_items, int 
 // Every workgroup ends when all queues are empty (the cursors only grow).
 struct WorkItem { int seq, lev, head, row0, len; };
 constexpr int kSlotInts = 16;          // two buffers of 8 ints
-typedef __attribute__((ext_vector_type(4))) int i32x4;
-
 struct WorkFetcher {
     int cur;          // slot buffer holding the current item (all threads)
     // the rest is thread 0's
