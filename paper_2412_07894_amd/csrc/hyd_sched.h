@@ -118,7 +118,7 @@ __device__ __forceinline__ void build_schedule(const int32_t* __restrict__ cu, i
     if (cost > 0.f) atomicAdd(reinterpret_cast<float*>(hist), cost);        // hist[0] is not a level
     if (flags) atomicOr(&sv.hdr[kHdrFlags], flags);
     __syncthreads();
-    const int C = min(min(sv.group_max, nl), (int)fminf(*reinterpret_cast<const float*>(hist) * sv.group_share, 1e6f));
+    int C = min(min(sv.group_max, nl), (int)fminf(*reinterpret_cast<const float*>(hist) * sv.group_share, 1e6f));
     if (tid < 64) {
         // cnt[r] = sum_{n >= nl - r} hist[n]; offs = inclusive scan of cnt
         for (int r = tid; r < nl; r += 64) cnt[r] = hist[nl - r];
@@ -128,6 +128,8 @@ __device__ __forceinline__ void build_schedule(const int32_t* __restrict__ cu, i
     }
     __syncthreads();
     const int n_items = nl > 0 ? min(offs[nl - 1], sv.max_items) : 0;
+    // more items than any valid cu_seqlens has: positions of the grouped order would lie outside the records
+    if (nl > 0 && offs[nl - 1] > sv.max_items) C = 0;
     if (tid == 0) sv.hdr[0] = n_items;
     for (int i = tid; i < nl + 2; i += nthreads) hist[i] = 0;
     __syncthreads();
@@ -135,7 +137,7 @@ __device__ __forceinline__ void build_schedule(const int32_t* __restrict__ cu, i
     for (int s = tid; s < nseq; s += nthreads) {
         const int L = cu[s + 1] - cu[s];
         const int n = min((L + tile - 1) / tile, nl);
-        if (n == 0) continue;
+        if (n <= 0) continue;
         const int more = (n < nl) ? cnt[nl - (n + 1)] : 0;
         sv.order[more + atomicAdd(&hist[n], 1)] = s;
     }

@@ -40,3 +40,18 @@ def test_grouped_order_equals_small_batches(lo, hi, n, dtype):
         part = run(*(x[a:b].contiguous() for x in (q, k, v, do)), lens[s:s + step], d ** -0.5)
         for name, x, y in zip(("o", "lse", "dq", "dk", "dv"), whole, part):
             assert torch.equal(x[a:b], y), (name, s)
+
+
+def test_records_stay_in_the_workspace_when_seqlens_decrease():
+    """A decreasing cu_seqlens can ask for more items than the workspace has records for.  Nothing may be
+    written behind it, and the findings are read back."""
+    T, heads, d, n = 1000, 32, 64, 200
+    cu = torch.tensor([0] + [T if i % 2 == 0 else 0 for i in range(n)], dtype=torch.int32, device="cuda")
+    g = torch.Generator(device="cuda")
+    g.manual_seed(19)
+    q, k, v = (torch.randn((T, heads, d), device="cuda", generator=g).to(torch.bfloat16) for _ in range(3))
+    need = binding.workspace_bytes(T, n, heads, heads, d, binding.HYD_BF16, 0)
+    ws = torch.full((need + 65536,), 0x5a, dtype=torch.uint8, device="cuda")
+    binding.varlen_attn_fwd(q, k, v, cu, T, d ** -0.5, workspace=ws)
+    assert binding.schedule_status(ws, T, n, heads, heads, d, binding.HYD_BF16, 0) == 6
+    assert bool((ws[need:] == 0x5a).all())
