@@ -28,15 +28,22 @@ constexpr int kBwdStatVecs = 4;
 struct SchedLayout { size_t hdr, lev, order, items, exec; int n_lev, max_items; };
 struct WsLayout {
     SchedLayout sched[2];
+    SchedLayout split;      // query side by QuerySplit tiles, where an item takes several heads (lh > 0)
     int n_sched;
     size_t stat[kBwdStatVecs], q16, do16, k16, absmax, rope_tab, total;
 };
 constexpr int kRopeTabEntries = 64;       // head_dim / 2 at most
 
+// levels of a sequence of `len` rows, in whole multiples of 2^lh tiles: a list of split tiles covers
+// the same rows as the list of whole ones for every bound on the sequence length
+int levels(int len, int tile, int lh) {
+    const int whole = tile << lh, n = (len + whole - 1) / whole;
+    return (n < 1 ? 1 : n) << lh;
+}
+
 // `compact`: the records are handed out in list order, without a second copy of them
-size_t sched_layout(SchedLayout& v, size_t at, int T, int nseq, int tile, bool compact) {
-    v.n_lev = (T + tile - 1) / tile;
-    if (v.n_lev < 1) v.n_lev = 1;
+size_t sched_layout(SchedLayout& v, size_t at, int T, int nseq, int tile, int lh, bool compact) {
+    v.n_lev = levels(T, tile, lh);
     v.max_items = T / tile + nseq + 1;
     v.hdr = at;   at += align_up(sizeof(int) * kHdrTotal);
     v.lev = at;   at += align_up(sizeof(int) * 3 * (size_t)(v.n_lev + 2));
@@ -47,12 +54,15 @@ size_t sched_layout(SchedLayout& v, size_t at, int T, int nseq, int tile, bool c
     return at;
 }
 
-WsLayout ws_layout(int T, int nseq, int tile0, int tile1, int hq, int hkv, int head_dim, hyd_dtype dt, bool bwd, bool compact = false) {
+// lh: of the query side (the last list)
+WsLayout ws_layout(int T, int nseq, int tile0, int tile1, int lh, int hq, int hkv, int head_dim, hyd_dtype dt, bool bwd, bool compact = false) {
     WsLayout w;
-    size_t at = sched_layout(w.sched[0], 0, T, nseq, tile0, compact);
+    size_t at = sched_layout(w.sched[0], 0, T, nseq, tile0, 0, compact || (!bwd && lh > 0));
     w.n_sched = bwd ? 2 : 1;
-    if (bwd) at = sched_layout(w.sched[1], at, T, nseq, tile1, compact);
+    if (bwd) at = sched_layout(w.sched[1], at, T, nseq, tile1, 0, lh > 0);
     else w.sched[1] = w.sched[0];
+    if (lh > 0) at = sched_layout(w.split, at, T, nseq, (bwd ? tile1 : tile0) >> lh, lh, true);
+    else w.split = w.sched[1];
     const int n_stat = !bwd ? 0 : (dt == HYD_BF16 ? kBwdStatVecs : 1);
     for (int i = 0; i < kBwdStatVecs; ++i) {
         w.stat[i] = at;
@@ -68,22 +78,36 @@ WsLayout ws_layout(int T, int nseq, int tile0, int tile1, int hq, int hkv, int h
     return w;
 }
 
-// rows per work item of the forward and of the backward kernels
-int tile_fwd(hyd_dtype dt) { return dt == HYD_BF16 ? kFwdBM : kF32BM; }
-int tile_dq(hyd_dtype dt) { return dt == HYD_BF16 ? kDqBM : kF32BM; }
+// rows per work item of the forward and dQ kernels (over all of its heads) and of the dK/dV kernel
+static_assert(kFwdBM == 256 && kDqBM == 256, "QuerySplit");
+int tile_q(hyd_dtype dt) { return dt == HYD_BF16 ? 256 : kF32BM; }
 int tile_kv(hyd_dtype dt) { return dt == HYD_BF16 ? kKvBN : kF32KvBN; }
+// LH of QuerySplit: four heads per item where the query heads of a KV head come in fours and there
+// are items for two rounds of workgroups.  With fewer, a launch lasts as long as its longest items,
+// and those are shorter with 256-row tiles, whose waves drop out one by one on the diagonal (32/8 heads,
+// log-normal lengths, forward / dQ in us, whole -> split: 2048 tokens 37.1 / 51.1 -> 40.2 / 54.1; 4096
+// tokens 99.5 / 137.6 -> 99.0 / 136.2; 6144 143.8 / 202 -> 140.8 / 197.5; 32768 tokens of 64-1024 336.5 /
+// 478 -> 319 / 452; 64/8 heads, 16384 tokens 654 / 885 -> 612 / 852; 16/2 heads, 32768 tokens 449 / 594 ->
+// 421 / 569).  The range variants, whose rows are a part
+// of the tokens, keep whole tiles (a context-parallel ring of four, 16384 tokens: 2980 us, split 3018).
+// `compact`: whole tiles, which need the fewest records.
+constexpr long long kSplitPairs = 2 * 256 * 256;           // (token, head) pairs of two items for each of 256 CUs
+int split_lh(hyd_dtype dt, int T, int hq, int hkv, bool compact) {
+    return dt == HYD_BF16 && !compact && (hq / hkv) % 4 == 0 && (long long)T * hq >= kSplitPairs ? 2 : 0;
+}
 
 WsLayout fwd_layout(int T, int nseq, int hq, int hkv, int head_dim, hyd_dtype dt, bool compact) {
-    return ws_layout(T, nseq, tile_fwd(dt), tile_fwd(dt), hq, hkv, head_dim, dt, false, compact);
+    return ws_layout(T, nseq, tile_q(dt), tile_q(dt), split_lh(dt, T, hq, hkv, compact), hq, hkv, head_dim, dt, false, compact);
 }
 WsLayout bwd_layout(int T, int nseq, int hq, int hkv, int head_dim, hyd_dtype dt) {
-    return ws_layout(T, nseq, tile_kv(dt), tile_dq(dt), hq, hkv, head_dim, dt, true);
+    return ws_layout(T, nseq, tile_kv(dt), tile_q(dt), split_lh(dt, T, hq, hkv, false), hq, hkv, head_dim, dt, true);
 }
 
 bool head_dim_ok(hyd_dtype dt, int d) { (void)dt; return d == 64 || d == 128; }
 
 // Spread of (item, head) pairs over the 8 queues: whole KV groups per queue when the KV heads
 // divide over the queues, else single heads, else items striped with all heads in every queue.
+// `hq` counts the query heads in units of an item's heads.
 HeadMap head_map_q(int hq, int hkv, int grid) {
     HeadMap hm;
     hm.grid = grid;
@@ -192,6 +216,16 @@ bool prep_f32(int* occ) {
            prep_kernel(hyd_bwd_dkdv_fp32_kernel<D>, 64 * kF32KvWaves, f32_lds<D>(), occ + 2);
 }
 
+// [whole tiles, range variant, split tiles][head_dim == 64]
+typedef void (*FwdKernel)(FwdParams);
+typedef void (*BwdKernel)(BwdParams);
+constexpr FwdKernel kFwdKernels[3][2] = {{hyd_fwd_bf16_kernel<false, 128, 0>, hyd_fwd_bf16_kernel<false, 64, 0>},
+                                         {hyd_fwd_bf16_kernel<true, 128, 0>, hyd_fwd_bf16_kernel<true, 64, 0>},
+                                         {hyd_fwd_bf16_kernel<false, 128, 2>, hyd_fwd_bf16_kernel<false, 64, 2>}};
+constexpr BwdKernel kDqKernels[3][2] = {{hyd_bwd_dq_bf16_kernel<false, 128, 0>, hyd_bwd_dq_bf16_kernel<false, 64, 0>},
+                                        {hyd_bwd_dq_bf16_kernel<true, 128, 0>, hyd_bwd_dq_bf16_kernel<true, 64, 0>},
+                                        {hyd_bwd_dq_bf16_kernel<false, 128, 2>, hyd_bwd_dq_bf16_kernel<false, 64, 2>}};
+
 hyd_status device_info(DeviceInfo** out) {
     int dev = 0;
     if (hipGetDevice(&dev) != hipSuccess) return HYD_ERR_LAUNCH;
@@ -204,17 +238,13 @@ hyd_status device_info(DeviceInfo** out) {
         d.ok = strncmp(prop.gcnArchName, "gfx950", 6) == 0;
         d.cus = prop.multiProcessorCount;
         if (d.ok) {
-            if (!prep_kernel(hyd_fwd_bf16_kernel<false>, kFwdThreads, kFwdLds, &d.occ_fwd) ||
-                !prep_kernel(hyd_fwd_bf16_kernel<false, 64>, kFwdThreads, kFwdLds, nullptr) ||
-                !prep_kernel(hyd_fwd_bf16_kernel<true, 64>, kFwdThreads, kFwdLds, nullptr) ||
-                !prep_kernel(hyd_bwd_dq_bf16_kernel<false>, kDqThreads, kDqLds, &d.occ_dq) ||
-                !prep_kernel(hyd_bwd_dkdv_bf16_kernel<false>, kKvThreads, kKvLds, &d.occ_kv) ||
-                !prep_kernel(hyd_fwd_bf16_kernel<true>, kFwdThreads, kFwdLds, nullptr) ||
-                !prep_kernel(hyd_bwd_dq_bf16_kernel<true>, kDqThreads, kDqLds, nullptr) ||
+            for (int i = 0; i < 6; ++i)          // (the LDS of all variants allows one workgroup per CU)
+                if (!prep_kernel(kFwdKernels[i / 2][i % 2], kFwdThreads, kFwdLds, &d.occ_fwd) ||
+                    !prep_kernel(kDqKernels[i / 2][i % 2], kDqThreads, kDqLds, &d.occ_dq))
+                    return HYD_ERR_LAUNCH;
+            if (!prep_kernel(hyd_bwd_dkdv_bf16_kernel<false>, kKvThreads, kKvLds, &d.occ_kv) ||
                 !prep_kernel(hyd_bwd_dkdv_bf16_kernel<true>, kKvThreads, kKvLds, nullptr) ||
-                !prep_kernel(hyd_bwd_dq_bf16_kernel<false, 64>, kDqThreads, kDqLds, nullptr) ||
                 !prep_kernel(hyd_bwd_dkdv_bf16_kernel<false, 64>, kKvThreads, kKvLds, nullptr) ||
-                !prep_kernel(hyd_bwd_dq_bf16_kernel<true, 64>, kDqThreads, kDqLds, nullptr) ||
                 !prep_kernel(hyd_bwd_dkdv_bf16_kernel<true, 64>, kKvThreads, kKvLds, nullptr) ||
                 !prep_f32<64>(d.occ_f32[0]) || !prep_f32<128>(d.occ_f32[1]))
                 return HYD_ERR_LAUNCH;
@@ -256,18 +286,18 @@ struct KernelTimer {       // brackets one launch with events when timing is on
     }
 };
 
-// View of schedule `which`; its level count is bounded by the caller's max_seqlen.
+// View of a schedule of `tile` rows (a 2^lh-th of the kernel's tile); its level count is bounded by the caller's max_seqlen.
 // `heads` work items per record are shared by `wgs` workgroups.  Sequences are grouped up to
 // 1024 bf16 (512 fp32) rows, 512 KB of K and V for a head, unless four or more query heads share
 // a KV head: their workgroups share its stream already, and the list's own order is balanced best.
-SchedView make_view(char* ws, const SchedLayout& v, int tile, int max_seqlen, hyd_dtype dt, int heads, int wgs, bool grouped_heads) {
+SchedView make_view(char* ws, const SchedLayout& v, int tile, int lh, int max_seqlen, hyd_dtype dt, int heads, int wgs, bool grouped_heads) {
     SchedView sv;
     sv.hdr = reinterpret_cast<int*>(ws + v.hdr);
     sv.lev = reinterpret_cast<int*>(ws + v.lev);
     sv.order = reinterpret_cast<int*>(ws + v.order);
     sv.items = reinterpret_cast<int*>(ws + v.items);
-    const int by_len = (max_seqlen + tile - 1) / tile;
-    sv.n_lev = by_len < v.n_lev ? (by_len < 1 ? 1 : by_len) : v.n_lev;
+    const int by_len = levels(max_seqlen, tile, lh);
+    sv.n_lev = by_len < v.n_lev ? by_len : v.n_lev;
     sv.max_items = v.max_items;
     sv.exec = reinterpret_cast<int*>(ws + v.exec);
     sv.group_max = v.exec == v.items || grouped_heads ? 0 : (dt == HYD_BF16 ? 1024 : 512) / tile;
@@ -339,17 +369,23 @@ hyd_status fwd_impl(const void* q, const void* k, const void* v, const int32_t* 
     if (ds != HYD_OK) return ds;
     hipStream_t st = static_cast<hipStream_t>(hip_stream);
 
-    const int tile = tile_fwd(dt);
+    const int lh = ranged ? 0 : split_lh(dt, total_tokens, hq, hkv, compact);
+    const int tile = tile_q(dt), units = hq >> lh;
     const WsLayout w = fwd_layout(total_tokens, num_seqs, hq, hkv, head_dim, dt, compact);
     const int occ = dt == HYD_BF16 ? dev->occ_fwd : dev->occ_f32[head_dim == 128][0];
-    const SchedView sv = make_view(static_cast<char*>(workspace), w.sched[0], tile, max_seqlen, dt, hq, dev->cus * occ, hq >= 4 * hkv);
+    // where items take several heads, the list of whole tiles is built too, next to the one that is
+    // handed out (hyd_varlen_attn_schedule_layout shows it)
+    const bool grouped = hq >= 4 * hkv;
+    const SchedView sv_whole = make_view(static_cast<char*>(workspace), w.sched[0], tile, 0, max_seqlen, dt, units, dev->cus * occ, grouped);
+    const SchedView sv = lh ? make_view(static_cast<char*>(workspace), w.split, (256 >> lh), lh, max_seqlen, dt, units, dev->cus * occ, grouped) : sv_whole;
     double* rope_tab = rope_base != 0.f ? reinterpret_cast<double*>(static_cast<char*>(workspace) + w.rope_tab) : nullptr;
     {
         KernelTimer kt("schedule_prelude", st);
-        hipLaunchKernelGGL(hyd_schedule_prelude, dim3(1), dim3(kPreludeThreads), schedule_lds(sv.n_lev), st, cu_seqlens, num_seqs, total_tokens, tile, sv, tile, sv,
+        hipLaunchKernelGGL(hyd_schedule_prelude, dim3(lh ? 2 : 1), dim3(kPreludeThreads), schedule_lds_max(sv_whole.n_lev, sv.n_lev), st, cu_seqlens, num_seqs,
+                           total_tokens, tile, sv_whole, tile >> lh, sv,
                            rope_tab, head_dim / 2, rope_base != 0.f ? log2((double)rope_base) : 0.0);
     }
-    const long long work = (long long)sv.max_items * hq;
+    const long long work = (long long)sv.max_items * units;
     if (dt == HYD_BF16) {
         FwdParams p;
         p.q = static_cast<const uint16_t*>(q); p.k = static_cast<const uint16_t*>(k);
@@ -360,13 +396,9 @@ hyd_status fwd_impl(const void* q, const void* k, const void* v, const int32_t* 
         p.ranges = ranged ? ranges : nullptr;
         p.rope_tab = rope_tab;
         const dim3 grid(persistent_grid(*dev, occ, work));
-        p.hm = head_map_q(hq, hkv, grid.x);
+        p.hm = head_map_q(units, hkv, grid.x);
         KernelTimer kt(ranged ? "fwd_range_bf16" : "fwd_bf16", st);
-        if (head_dim == 64) {
-            if (ranged) hipLaunchKernelGGL((hyd_fwd_bf16_kernel<true, 64>), grid, dim3(kFwdThreads), kFwdLds, st, p);
-            else hipLaunchKernelGGL((hyd_fwd_bf16_kernel<false, 64>), grid, dim3(kFwdThreads), kFwdLds, st, p);
-        } else if (ranged) hipLaunchKernelGGL(hyd_fwd_bf16_kernel<true>, grid, dim3(kFwdThreads), kFwdLds, st, p);
-        else hipLaunchKernelGGL(hyd_fwd_bf16_kernel<false>, grid, dim3(kFwdThreads), kFwdLds, st, p);
+        hipLaunchKernelGGL(kFwdKernels[ranged ? 1 : lh][head_dim == 64], grid, dim3(kFwdThreads), kFwdLds, st, p);
     } else {
         F32Params p;
         memset(&p, 0, sizeof(p));
@@ -410,11 +442,15 @@ hyd_status bwd_impl(const void* q, const void* k, const void* v, const void* o, 
     char* ws = static_cast<char*>(workspace);
     const int occ_q = dt == HYD_BF16 ? dev->occ_dq : dev->occ_f32[head_dim == 128][1];
     const int occ_kv = dt == HYD_BF16 ? dev->occ_kv : dev->occ_f32[head_dim == 128][2];
-    const SchedView sv_kv = make_view(ws, w.sched[0], tile_kv(dt), max_seqlen, dt, hkv, dev->cus * occ_kv, hq >= 4 * hkv);
-    const SchedView sv_q = make_view(ws, w.sched[1], tile_dq(dt), max_seqlen, dt, hq, dev->cus * occ_q, hq >= 4 * hkv);
+    const int lh = ranged ? 0 : split_lh(dt, total_tokens, hq, hkv, false);
+    const int units = hq >> lh;
+    const bool grouped = hq >= 4 * hkv;
+    const SchedView sv_kv = make_view(ws, w.sched[0], tile_kv(dt), 0, max_seqlen, dt, hkv, dev->cus * occ_kv, grouped);
+    const SchedView sv_whole = make_view(ws, w.sched[1], tile_q(dt), 0, max_seqlen, dt, units, dev->cus * occ_q, grouped);
+    const SchedView sv_q = lh ? make_view(ws, w.split, (256 >> lh), lh, max_seqlen, dt, units, dev->cus * occ_q, grouped) : sv_whole;
     float* Dvec = reinterpret_cast<float*>(ws + w.stat[0]);
     double* rope_tab = rope_base != 0.f ? reinterpret_cast<double*>(ws + w.rope_tab) : nullptr;
-    const long long work_q = (long long)sv_q.max_items * hq, work_kv = (long long)sv_kv.max_items * hkv;
+    const long long work_q = (long long)sv_q.max_items * units, work_kv = (long long)sv_kv.max_items * hkv;
     if (dt == HYD_BF16) {
         BwdScratch sc;
         sc.Dq = Dvec;
@@ -434,10 +470,12 @@ hyd_status bwd_impl(const void* q, const void* k, const void* v, const void* o, 
             pp.sc = sc;
             pp.cu = cu_seqlens; pp.nseq = num_seqs;
             pp.ranges = ranged ? ranges : nullptr;
-            pp.n_sched = 2; pp.tile[0] = tile_kv(dt); pp.tile[1] = tile_dq(dt); pp.sv[0] = sv_kv; pp.sv[1] = sv_q;
+            pp.n_sched = lh ? 3 : 2;
+            pp.tile[0] = tile_kv(dt); pp.tile[1] = tile_q(dt); pp.tile[2] = tile_q(dt) >> lh;
+            pp.sv[0] = sv_kv; pp.sv[1] = sv_whole; pp.sv[2] = sv_q;
             pp.rope_tab = rope_tab; pp.log2_base = rope_tab ? log2((double)rope_base) : 0.0;
             const dim3 grid((unsigned)(pp.n_sched + sc.n_absmax)), block(kPrepThreads);
-            const size_t lds = prep_lds(hq, pp.tok, sv_kv.n_lev, sv_q.n_lev);
+            const size_t lds = prep_lds(hq, pp.tok, schedule_lds_max(sv_kv.n_lev, sv_q.n_lev));
             KernelTimer kt("bwd_prep_bf16", st);
             if (head_dim == 64) {
                 if (ranged) hipLaunchKernelGGL((hyd_bwd_prep_bf16_kernel<true, 64>), grid, block, lds, st, pp);
@@ -459,13 +497,9 @@ hyd_status bwd_impl(const void* q, const void* k, const void* v, const void* o, 
             p.hdr = sv_q.hdr; p.items = sv_q.exec;
             p.cursors = sv_q.hdr + kHdrCursor;
             const dim3 grid(persistent_grid(*dev, occ_q, work_q));
-            p.hm = head_map_q(hq, hkv, grid.x);
+            p.hm = head_map_q(units, hkv, grid.x);
             KernelTimer kt(ranged ? "bwd_dq_range_bf16" : "bwd_dq_bf16", st);
-            if (head_dim == 64) {
-                if (ranged) hipLaunchKernelGGL((hyd_bwd_dq_bf16_kernel<true, 64>), grid, dim3(kDqThreads), kDqLds, st, p);
-                else hipLaunchKernelGGL((hyd_bwd_dq_bf16_kernel<false, 64>), grid, dim3(kDqThreads), kDqLds, st, p);
-            } else if (ranged) hipLaunchKernelGGL(hyd_bwd_dq_bf16_kernel<true>, grid, dim3(kDqThreads), kDqLds, st, p);
-            else hipLaunchKernelGGL(hyd_bwd_dq_bf16_kernel<false>, grid, dim3(kDqThreads), kDqLds, st, p);
+            hipLaunchKernelGGL(kDqKernels[ranged ? 1 : lh][head_dim == 64], grid, dim3(kDqThreads), kDqLds, st, p);
         }
         {
             p.hdr = sv_kv.hdr; p.items = sv_kv.exec;
@@ -490,9 +524,8 @@ hyd_status bwd_impl(const void* q, const void* k, const void* v, const void* o, 
         p.tr = t_trace;
         {   // one launch builds both item lists, one workgroup each
             KernelTimer kt("schedule_prelude", st);
-            const size_t lds_kv = schedule_lds(sv_kv.n_lev), lds_q = schedule_lds(sv_q.n_lev);
-            hipLaunchKernelGGL(hyd_schedule_prelude, dim3(w.n_sched), dim3(kPreludeThreads), lds_kv > lds_q ? lds_kv : lds_q, st, cu_seqlens,
-                               num_seqs, total_tokens, tile_kv(dt), sv_kv, tile_dq(dt), sv_q, nullptr, 0, 0.0);
+            hipLaunchKernelGGL(hyd_schedule_prelude, dim3(w.n_sched), dim3(kPreludeThreads), schedule_lds_max(sv_kv.n_lev, sv_q.n_lev), st, cu_seqlens,
+                               num_seqs, total_tokens, tile_kv(dt), sv_kv, tile_q(dt), sv_q, nullptr, 0, 0.0);
         }
         const dim3 grid_q(persistent_grid(*dev, occ_q, work_q)), grid_kv(persistent_grid(*dev, occ_kv, work_kv));
         // dQ first: it also writes the row sums D that dK/dV reads
@@ -560,7 +593,7 @@ hyd_status hyd_varlen_attn_fwd_noalloc(const void* q, const void* k, const void*
     if (hq <= 0 || hkv <= 0 || hq % hkv != 0) return HYD_ERR_HEADS;
     if (dt != HYD_BF16 && dt != HYD_FP32) return HYD_ERR_DTYPE;
     if (!head_dim_ok(dt, head_dim)) return HYD_ERR_HEADDIM;
-    // (if need be without the second copy of the item records)
+    // (if need be with 256-row tiles and without the second copy of the item records)
     const bool compact = fwd_layout(total_tokens, num_seqs, hq, hkv, head_dim, dt, false).total > kScratchBytes;
     if (compact && fwd_layout(total_tokens, num_seqs, hq, hkv, head_dim, dt, true).total > kScratchBytes) return HYD_ERR_WORKSPACE;
     // the rest of the argument checks, still before any HIP call (a stand-in for the workspace pointer)
@@ -672,7 +705,7 @@ hyd_status hyd_varlen_attn_schedule_layout(int total_tokens, int num_seqs, int h
                               : fwd_layout(total_tokens, num_seqs, hq, hkv, head_dim, dt, false);
     const SchedLayout& v = w.sched[which];
     *header_offset = v.hdr; *items_offset = v.items; *max_items = v.max_items;
-    *tile = !is_bwd ? tile_fwd(dt) : (which == 0 ? tile_kv(dt) : tile_dq(dt));
+    *tile = is_bwd && which == 0 ? tile_kv(dt) : tile_q(dt);
     return HYD_OK;
 }
 

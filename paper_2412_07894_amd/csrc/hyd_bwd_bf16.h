@@ -75,7 +75,7 @@ struct PartialMaxima {
 };
 // ---------------------------------------------------------------------------------------------
 // Preparation of the backward, one launch: the first n_sched workgroups build the item lists of the
-// two tile kernels, the others make one pass over O, dO and K: the row statistics above except
+// tile kernels, the others make one pass over O, dO and K: the row statistics above except
 // Dkv, the maxima of |dO|, and the fp16 copy of K.  (The fp16 copies of Q and dO and Dkv are written by
 // the dQ kernel, which has those rows in LDS anyway.)  A lane per 16 bytes of a row; a workgroup walks the
 // rows of its tokens in memory order, four rows in flight per group of lanes, and collects their
@@ -105,10 +105,9 @@ inline int prep_workgroups(int T, int tok) {
     const int n = (T + tok - 1) / tok;
     return n < kPrepMaxWg ? n : kPrepMaxWg;
 }
-inline size_t prep_lds(int hq, int tok, int nl0, int nl1) {
+inline size_t prep_lds(int hq, int tok, size_t schedule) {
     const size_t st = sizeof(float) * 2 * (size_t)hq * tok + sizeof(int) * 32;
-    const size_t a = schedule_lds(nl0), b = schedule_lds(nl1), l = a > b ? a : b;
-    return st > l ? st : l;
+    return st > schedule ? st : schedule;
 }
 struct PrepParams {
     const uint16_t* o; const uint16_t* d_o; const float* lse; const uint16_t* k;
@@ -116,7 +115,7 @@ struct PrepParams {
     int T, hq, hkv, tok;
     const int32_t* cu; int nseq;
     const int32_t* ranges;                                 // range variant only
-    int n_sched; int tile[2]; SchedView sv[2];
+    int n_sched; int tile[3]; SchedView sv[3];
     double* rope_tab; double log2_base;
 };
 
@@ -248,7 +247,8 @@ struct BwdParams {
 };
 
 // ---------------------------------------------------------------------------------------------
-// dQ.  Work item = (sequence, query tile of 256 rows, query head); wave w of 8 owns rows 32w..32w+31.
+// dQ.  Work item = (sequence, query tile, query heads), 256 (row, head) pairs (see QuerySplit); each of 8
+// waves owns 32 rows of one head.
 // Same orientation, K/V ring and causal structure as the forward kernel: S^T[key][q] = K Q^T and
 // dP^T[key][q] = V dO^T put one query row in each lane, so LSE_i and D_i are per-lane scalars;
 // dS^T then is the B operand of dQ^T[d][q] = K^T dS^T, with K^T fragments from the transposing
@@ -350,8 +350,9 @@ __device__ __forceinline__ void dq_block(int Kt, int Vt, const FragAddr& fa, int
 
 // R: range variant (see the forward kernel): query tiles outside the query range are skipped,
 // the tile loop covers the key range only, dQ holds that key range's contribution.
-template <bool R, int D = kHeadDim>
+template <bool R, int D = kHeadDim, int LH = 0>
 __global__ void __launch_bounds__(kDqThreads, 1) hyd_bwd_dq_bf16_kernel(BwdParams p) {
+    using QS = QuerySplit<LH>;
     static_assert(D == 128 || D == 64, "head dimension");
     constexpr int kRowB = D * 2;                                      // bytes of a row in global memory
     static_assert(kDqBM == 256 && kDqStages == 3, "the Q / dO staging assumes a 256-row tile and a 3-stage ring");
@@ -390,8 +391,8 @@ __global__ void __launch_bounds__(kDqThreads, 1) hyd_bwd_dq_bf16_kernel(BwdParam
     while (have) {
         ++n_done;
         __syncthreads();                                  // everybody has read the work slot: its bytes may be overwritten
-        const int lev = wi.lev, head = wi.head, row0 = wi.row0, L = wi.len;
-        const int q0 = (lev - 1) * kDqBM;
+        const int lev = wi.lev, head0 = wi.head << LH, row0 = wi.row0, L = wi.len;
+        const int q0 = (lev - 1) * QS::kRows;
         int Lq = L, kb = 0, kcap = L;                     // query rows [.., Lq), keys [kb, kcap)
         if (R) {
             const i32x4 rg = *reinterpret_cast<const i32x4*>(p.ranges + 4 * wi.seq);
@@ -401,11 +402,12 @@ __global__ void __launch_bounds__(kDqThreads, 1) hyd_bwd_dq_bf16_kernel(BwdParam
                 continue;
             }
         }
-        const int kv_end = min(kcap, q0 + kDqBM);
+        const int kv_end = min(kcap, q0 + QS::kRows);
         const int n_kt = (kv_end + kDqBN - 1) / kDqBN;
         const int t_lo = R ? kb / kDqBN : 0;
-        const int g = head / G;
-        const int wrow0 = q0 + 32 * wave;
+        const int g = head0 / G;
+        const int head = head0 + QS::head_of(wave);
+        const int wrow0 = q0 + QS::row_of(wave);
         const int qrow = wrow0 + l32;
         const bool qvalid = qrow < Lq;
         const bool active = wrow0 < Lq;
@@ -435,13 +437,14 @@ __global__ void __launch_bounds__(kDqThreads, 1) hyd_bwd_dq_bf16_kernel(BwdParam
             }
         };
         dma_tile(t_lo, 0);
-        {   // rows q0 .. q0+255 of Q and dO of this head; rows past the query range read as zeros
-            const uint32_t q_bytes = (uint32_t)(min(Lq - q0, kDqBM) - 1) * q_stride_b + kRowB;
-            const int64_t off = (int64_t)(row0 + q0) * q_stride + (int64_t)head * D;
+        {   // the item's rows of Q and dO; rows past the query range read as zeros
+            const uint32_t q_bytes = (uint32_t)(min(Lq - q0, QS::kRows) - 1) * q_stride_b + (kRowB << LH);
+            const int64_t off = (int64_t)(row0 + q0) * q_stride + (int64_t)head0 * D;
+            auto tile_at = [&](int j) { return QS::tile_at(j, q_stride_b, kRowB); };
             dma_rows<kDqWaves>(make_rsrc(p.q + off, q_bytes), smem + kDqQxOff, [](int j) { return j * kDqTileBytes; },
-                               kDqBM / 64, q_stride_b, wave, dma_voff_q);
+                               kDqBM / 64, q_stride_b, tile_at, wave, dma_voff_q);
             dma_rows<kDqWaves>(make_rsrc(p.d_o + off, q_bytes), smem + kDqStageBytes, [](int j) { return j * kDqTileBytes; },
-                               kDqBM / 64, q_stride_b, wave, dma_voff_q);
+                               kDqBM / 64, q_stride_b, tile_at, wave, dma_voff_q);
         }
         float lse2 = 0.f, Dq = 0.f, unshift = 0.f;
         if (qvalid) {
@@ -705,10 +708,11 @@ __global__ void __launch_bounds__(kKvThreads, 1) hyd_bwd_dkdv_bf16_kernel(BwdPar
             static_assert(kKvBN == 128 && kKvPairs * 2 * kKvPBytes >= kKvBN * kRowBytes, "K/V staging");
             const uint32_t k_bytes = (uint32_t)(min(Lk - j0, kKvBN) - 1) * kv_stride_b + kRowB;
             const int64_t off = (int64_t)(row0 + j0) * kv_stride + (int64_t)g * D;
+            auto tile_at = [&](int j) { return (uint32_t)(64 * j) * kv_stride_b; };
             dma_rows<kKvWaves>(make_rsrc(p.sc.k16 + off, k_bytes), smem + 2 * kKvStageBytes, [](int j) { return j * kKvTileBytes; },
-                               kKvBN / 64, kv_stride_b, wave, dma_voff_kv);
+                               kKvBN / 64, kv_stride_b, tile_at, wave, dma_voff_kv);
             dma_rows<kKvWaves>(make_rsrc(p.v + off, k_bytes), smem + kKvPOff, [](int j) { return j * kKvTileBytes; },
-                               kKvBN / 64, kv_stride_b, wave, dma_voff_kv);
+                               kKvBN / 64, kv_stride_b, tile_at, wave, dma_voff_kv);
         }
         f32x16 acc[NDB];                                      // dV^T (role A) or dK^T (role B)
 #pragma unroll

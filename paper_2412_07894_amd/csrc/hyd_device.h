@@ -241,12 +241,12 @@ __device__ __forceinline__ uint32_t dma_lane_voff(int row, int lane, uint32_t ro
     return (D == kHeadDim || chunk < D / 8) ? (uint32_t)row * row_stride_b + (uint32_t)(chunk << 4) : kDmaOutOfRange;
 }
 
-// Direct-to-LDS load of a block of `n64` x 64 rows of 256 bytes (row r of the block at byte r *
-// row_stride_b of the resource) into LDS in the swizzled tile layout, 64-row tile j at lds + off(j).
-// All NW waves of the workgroup call it; each issues n64 * 16 / NW instructions.
-template <int NW, typename OffFn>
+// Direct-to-LDS load of a block of `n64` x 64 rows of 256 bytes (row r of 64-row tile j at byte
+// tile_at(j) + r * row_stride_b of the resource) into LDS in the swizzled tile layout, tile j at
+// lds + off(j).  All NW waves of the workgroup call it; each issues n64 * 16 / NW instructions.
+template <int NW, typename OffFn, typename AtFn>
 __device__ __forceinline__ void dma_rows(const __amdgpu_buffer_rsrc_t& rs, char* lds, OffFn off, int n64,
-                                         uint32_t row_stride_b, int wave, uint32_t voff) {
+                                         uint32_t row_stride_b, AtFn tile_at, int wave, uint32_t voff) {
     typedef __attribute__((address_space(3))) void lds_void_t;
 #pragma unroll
     for (int sub = 0; sub < 4; ++sub) {
@@ -254,7 +254,7 @@ __device__ __forceinline__ void dma_rows(const __amdgpu_buffer_rsrc_t& rs, char*
 #pragma unroll
             for (int j = 0; j < 16 / NW; ++j) {
                 char* d = lds + off(sub) + (4 * wave + j * NW * 4) * kRowBytes;
-                __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (lds_void_t*)d, 16, voff, (uint32_t)(sub * 64 + j * NW * 4) * row_stride_b, 0, 0);
+                __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (lds_void_t*)d, 16, voff, tile_at(sub) + (uint32_t)(j * NW * 4) * row_stride_b, 0, 0);
             }
         }
     }

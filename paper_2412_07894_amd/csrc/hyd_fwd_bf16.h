@@ -1,8 +1,8 @@
 // bf16 forward kernel: block-diagonal causal flash-style tile loop on MFMA with fp32 accumulation.
 //
-// Work item = (sequence, query tile of 256 rows, query head).  A workgroup has 8 waves; wave w
-// owns query rows 32w..32w+31 of the tile for the whole item, so the online softmax never crosses
-// waves.  K/V tiles of 64 keys travel global -> LDS by direct-to-LDS buffer loads (no staging
+// Work item = (sequence, query tile, query heads of one KV head), 256 (row, head) pairs in all (see
+// QuerySplit).  A workgroup has 8 waves; a wave owns 32 query rows of one head for the whole item, so
+// the online softmax never crosses waves.  K/V tiles of 64 keys travel global -> LDS by direct-to-LDS buffer loads (no staging
 // registers, no LDS store instructions) into a ring of three stages shared by the waves: while
 // tile t is consumed, tiles t+1 and t+2 are in flight.  One barrier per tile.  The Q rows of an
 // item come in the same way and are picked up from LDS as fragments; O leaves through LDS too, so
@@ -190,8 +190,9 @@ __device__ __forceinline__ void fwd_tile(int Kt, int Vt, const FragAddr& fa, con
 // outside the query range are skipped, the tile loop starts at the key range's first tile and
 // stops at its end, and a row that sees no key of the range gets O = 0 and LSE = -inf (the
 // neutral element of the log-sum-exp merge of partial results).
-template <bool R, int D = kHeadDim>
+template <bool R, int D = kHeadDim, int LH = 0>
 __global__ void __launch_bounds__(kFwdThreads, 1) hyd_fwd_bf16_kernel(FwdParams p) {
+    using QS = QuerySplit<LH>;
     static_assert(D == 128 || D == 64, "head dimension");
     constexpr int kRowB = D * 2;                                      // bytes of a row in global memory
     extern __shared__ __attribute__((aligned(16))) char smem[];
@@ -230,8 +231,8 @@ __global__ void __launch_bounds__(kFwdThreads, 1) hyd_fwd_bf16_kernel(FwdParams 
     bool have = wf.first(p.hm, p.hdr, p.cursors, p.items, slot, wi);
     while (have) {
         ++n_done;
-        const int lev = wi.lev, head = wi.head, row0 = wi.row0, L = wi.len;
-        const int q0 = (lev - 1) * kFwdBM;
+        const int lev = wi.lev, head0 = wi.head << LH, row0 = wi.row0, L = wi.len;
+        const int q0 = (lev - 1) * QS::kRows;
         int Lq = L, kb = 0, kcap = L;                     // query rows [.., Lq), keys [kb, kcap)
         if (R) {
             const i32x4 rg = *reinterpret_cast<const i32x4*>(p.ranges + 4 * wi.seq);
@@ -241,11 +242,12 @@ __global__ void __launch_bounds__(kFwdThreads, 1) hyd_fwd_bf16_kernel(FwdParams 
                 continue;
             }
         }
-        const int kv_end = min(kcap, q0 + kFwdBM);
+        const int kv_end = min(kcap, q0 + QS::kRows);
         const int n_kt = (kv_end + kFwdBN - 1) / kFwdBN;
         const int t_lo = R ? kb / kFwdBN : 0;             // first key tile
-        const int g = head / G;
-        const int wrow0 = q0 + 32 * wave;                 // first query row of this wave
+        const int g = head0 / G;
+        const int head = head0 + QS::head_of(wave);      // this wave's query head
+        const int wrow0 = q0 + QS::row_of(wave);         // and its first query row
         const int qrow = wrow0 + l32;
         const bool qvalid = qrow < Lq;
         const bool active = wrow0 < Lq;                   // else the wave only helps with the loads
@@ -279,10 +281,11 @@ __global__ void __launch_bounds__(kFwdThreads, 1) hyd_fwd_bf16_kernel(FwdParams 
         dma_tile(t_lo, 0);
         if (t_lo + 1 < n_kt) dma_tile(t_lo + 1, 1);
 
-        {   // Q rows q0 .. q0+255 of this head; rows past the query range read as zeros
-            const uint32_t q_bytes = (uint32_t)(min(Lq - q0, kFwdBM) - 1) * q_stride_b + kRowB;
-            dma_rows<kFwdWaves>(make_rsrc(p.q + (int64_t)(row0 + q0) * q_stride + (int64_t)head * D, q_bytes), smem,
-                                [](int j) { return fwd_q_stage_off(j); }, kFwdBM / 64, q_stride_b, wave, dma_voff_q);
+        {   // the item's Q rows; rows past the query range read as zeros (the last row ends with its last head)
+            const uint32_t q_bytes = (uint32_t)(min(Lq - q0, QS::kRows) - 1) * q_stride_b + (kRowB << LH);
+            dma_rows<kFwdWaves>(make_rsrc(p.q + (int64_t)(row0 + q0) * q_stride + (int64_t)head0 * D, q_bytes), smem,
+                                [](int j) { return fwd_q_stage_off(j); }, kFwdBM / 64, q_stride_b,
+                                [&](int j) { return QS::tile_at(j, q_stride_b, kRowB); }, wave, dma_voff_q);
         }
         if (tid == 0) *redo = 0;
         __syncthreads();                                  // the first tiles and the Q rows have landed

@@ -73,8 +73,12 @@ __device__ __forceinline__ void wave_inclusive_scan(int* v, int n, int lane) {
 
 constexpr int kPreludeThreads = 1024;
 constexpr int kPreludeLdsLev = 4096;      // levels whose arrays fit the kernel's LDS
-// bytes of LDS that build_schedule needs for nl levels
+// bytes of LDS that build_schedule needs for nl levels, and for the larger of two lists
 __host__ __device__ constexpr size_t schedule_lds(int nl) { return nl <= kPreludeLdsLev ? sizeof(int) * 3 * (size_t)(nl + 2) : 0; }
+inline size_t schedule_lds_max(int a, int b) {
+    const size_t x = schedule_lds(a), y = schedule_lds(b);
+    return x > y ? x : y;
+}
 
 // Builds the item list for tile size `tile` and clears the cursors; called by all `nthreads`
 // threads of one workgroup, lds_lev as sized by schedule_lds.  n_lev bounds the tiles per sequence
@@ -177,6 +181,22 @@ __global__ void __launch_bounds__(kPreludeThreads) hyd_schedule_prelude(const in
     const bool second = blockIdx.x != 0;
     build_schedule(cu, nseq, T, second ? tile1 : tile0, second ? sv1 : sv0, lds_lev, kPreludeThreads);
 }
+
+// Query side of an item of the bf16 forward and dQ kernels: 8 waves of 32 rows each, split as 2^LH
+// query heads of one KV head x 256 >> LH rows.  Waves that share 64 rows walk the same key tiles, so
+// with four heads (LH = 2) no wave of a workgroup idles behind the diagonal of another one, and a
+// sequence's last tile pads it to 64 rows instead of 256: a workgroup takes 136 steps of 64 keys
+// instead of 160 for four heads of a 1024-token sequence, 45 instead of 84 for 544 tokens.
+template <int LH>
+struct QuerySplit {
+    static constexpr int kRows = 256 >> LH;
+    __device__ __forceinline__ static int head_of(int wave) { return wave >> (3 - LH); }
+    __device__ __forceinline__ static int row_of(int wave) { return 32 * (wave & ((8 >> LH) - 1)); }
+    // byte offset of the item's 64-row tile j (tiles by head, then by row) from row 0 of its first head
+    __device__ __forceinline__ static uint32_t tile_at(int j, uint32_t row_stride_b, uint32_t row_b) {
+        return (uint32_t)(j >> (2 - LH)) * row_b + (uint32_t)(64 * (j & ((4 >> LH) - 1))) * row_stride_b;
+    }
+};
 
 // Number of work indices of queue x.
 __device__ __forceinline__ int queue_size(const HeadMap& hm, int n_items, int x) {

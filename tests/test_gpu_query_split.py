@@ -1,0 +1,68 @@
+"""Items of the forward and dQ kernels that take four query heads of 64 rows each (query heads in
+groups of four or eight) against items of one head and 256 rows: the same query heads with their KV
+heads repeated run as ungrouped ones.  Every row does the same arithmetic either way, so O, LSE and
+dQ agree bit for bit; dK and dV, which stream what the dQ kernel wrote, are the sum over the group,
+here rounded once per head to bf16 (2^-9 of each summand, in the 2-norm below 2^-8 of the sum)."""
+import pytest
+import torch
+
+from paper_2412_07894_amd import binding, workloads as wl
+
+pytestmark = pytest.mark.gpu
+
+EDGES = [1, 31, 32, 33, 63, 64, 65, 127, 129, 191, 193, 255, 256, 257, 320, 321, 700, 1025]
+
+
+@pytest.mark.parametrize("hq,hkv,d", [(4, 1, 128), (8, 1, 64), (16, 2, 128), (32, 8, 128), (32, 8, 64), (12, 3, 128)])
+@pytest.mark.parametrize("call", ["plain", "rope"])
+def test_split_heads_equal_repeated_kv_heads(hq, hkv, d, call):
+    lens = EDGES * (1 + 131072 // (hq * sum(EDGES)))          # enough (token, head) pairs for split items
+    T, ml, G = sum(lens), max(lens), hq // hkv
+    print(f"\n{call}: {hq}/{hkv} heads, d = {d}, T = {T}", flush=True)
+    cu = torch.from_numpy(wl.cu_seqlens(lens)).cuda()
+    g = torch.Generator(device="cuda")
+    g.manual_seed(23)
+    mk = lambda h: torch.randn((T, h, d), device="cuda", generator=g).to(torch.bfloat16)
+    q, k, v, do = mk(hq), mk(hkv), mk(hkv), mk(hq)
+
+    def run(kk, vv):
+        o, dq = torch.zeros_like(q), torch.zeros_like(q)
+        lse = torch.zeros((hq, T), dtype=torch.float32, device="cuda")
+        dk, dv = torch.zeros_like(kk), torch.zeros_like(vv)
+        s = d ** -0.5
+        if call == "rope":
+            binding.varlen_attn_fwd(q, kk, vv, cu, ml, s, out=o, lse=lse, rope_base=1e4)
+            binding.varlen_attn_bwd(q, kk, vv, o, lse, do, cu, ml, s, dq=dq, dk=dk, dv=dv, rope_base=1e4)
+        else:
+            binding.varlen_attn_fwd(q, kk, vv, cu, ml, s, out=o, lse=lse)
+            binding.varlen_attn_bwd(q, kk, vv, o, lse, do, cu, ml, s, dq=dq, dk=dk, dv=dv)
+        return o, lse, dq, dk, dv
+
+    split = run(k, v)
+    whole = run(*(x.repeat_interleave(G, dim=1).contiguous() for x in (k, v)))
+    for name, x, y in zip(("o", "lse", "dq"), split, whole):
+        assert torch.equal(x, y), name
+        assert torch.isfinite(x.float()).all() and bool((x != 0).any()), name
+    for name, x, y in zip(("dk", "dv"), split[3:], whole[3:]):
+        ref = y.view(T, hkv, G, d).double().sum(2)
+        rel = float((x.double() - ref).norm() / ref.norm())
+        assert rel < 2.0 ** -8, (name, rel)
+
+
+@pytest.mark.parametrize("max_seqlen", [100, 256, 300, 1000])
+def test_a_bound_below_the_longest_sequence_covers_whole_tiles(max_seqlen):
+    """A sequence longer than max_seqlen gets its first ceil(max_seqlen / 256) tiles of 256 rows, with
+    split heads as without."""
+    lens, hq, hkv, d = [1000, 40, 256] * 13, 8, 2, 128
+    T = sum(lens)
+    cu = torch.from_numpy(wl.cu_seqlens(lens)).cuda()
+    g = torch.Generator(device="cuda")
+    g.manual_seed(29)
+    mk = lambda h: torch.randn((T, h, d), device="cuda", generator=g).to(torch.bfloat16)
+    q, k, v = mk(hq), mk(hkv), mk(hkv)
+    full, _ = binding.varlen_attn_fwd(q, k, v, cu, max(lens), d ** -0.5)
+    o = torch.full_like(q, 7.0)
+    binding.varlen_attn_fwd(q, k, v, cu, max_seqlen, d ** -0.5, out=o)
+    covered = min(1000, -(-max_seqlen // 256) * 256)
+    assert torch.equal(o[:covered], full[:covered]) and torch.equal(o[1000:1296], full[1000:1296])
+    assert bool((o[covered:1000] == 7.0).all())
