@@ -30,7 +30,8 @@ struct WsLayout {
     SchedLayout sched[2];
     SchedLayout split;      // query side by QuerySplit tiles, where an item takes several heads (lh > 0)
     int n_sched;
-    size_t stat[kBwdStatVecs], q16, do16, k16, absmax, rope_tab, total;
+    int part_max;           // dK/dV items in parts: their number at most, and the parts' sums
+    size_t stat[kBwdStatVecs], q16, do16, k16, absmax, rope_tab, part, total;
 };
 constexpr int kRopeTabEntries = 64;       // head_dim / 2 at most
 
@@ -42,7 +43,7 @@ int levels(int len, int tile, int lh) {
 }
 
 // `compact`: the records are handed out in list order, without a second copy of them
-size_t sched_layout(SchedLayout& v, size_t at, int T, int nseq, int tile, int lh, bool compact) {
+size_t sched_layout(SchedLayout& v, size_t at, int T, int nseq, int tile, int lh, bool compact, int part_max = 1) {
     v.n_lev = levels(T, tile, lh);
     v.max_items = T / tile + nseq + 1;
     v.hdr = at;   at += align_up(sizeof(int) * kHdrTotal);
@@ -50,14 +51,25 @@ size_t sched_layout(SchedLayout& v, size_t at, int T, int nseq, int tile, int lh
     v.order = at; at += align_up(sizeof(int) * (size_t)(nseq > 0 ? nseq : 1));
     v.items = at; at += align_up(sizeof(int) * 4 * (size_t)v.max_items);
     v.exec = v.items;
-    if (!compact) { v.exec = at; at += align_up(sizeof(int) * 4 * (size_t)v.max_items); }
+    if (!compact) { v.exec = at; at += align_up(sizeof(int) * 4 * (size_t)v.max_items * (size_t)part_max); }
     return at;
+}
+
+// Parts that a dK/dV item may be taken in: as many as the sums of all rows fit kPartBytes for.  (Splitting
+// pays where few items keep few compute units busy, which needs a small batch or few KV heads.)
+constexpr size_t kPartBytes = 256u << 20;
+size_t part_bytes(int T, int hkv, int head_dim) { return 2 * sizeof(float) * (size_t)T * (size_t)hkv * (size_t)head_dim; }
+int part_limit(int T, int hkv, int head_dim) {
+    int n = hkv <= 65535 ? kPartsMax : 1;                  // KV heads are a grid dimension of the summing kernel
+    while (n > 1 && (size_t)n * part_bytes(T, hkv, head_dim) > kPartBytes) n >>= 1;
+    return n;
 }
 
 // lh: of the query side (the last list)
 WsLayout ws_layout(int T, int nseq, int tile0, int tile1, int lh, int hq, int hkv, int head_dim, hyd_dtype dt, bool bwd, bool compact = false) {
     WsLayout w;
-    size_t at = sched_layout(w.sched[0], 0, T, nseq, tile0, 0, compact || (!bwd && lh > 0));
+    w.part_max = bwd && dt == HYD_BF16 ? part_limit(T, hkv, head_dim) : 1;
+    size_t at = sched_layout(w.sched[0], 0, T, nseq, tile0, 0, compact || (!bwd && lh > 0), w.part_max);
     w.n_sched = bwd ? 2 : 1;
     if (bwd) at = sched_layout(w.sched[1], at, T, nseq, tile1, 0, lh > 0);
     else w.sched[1] = w.sched[0];
@@ -74,6 +86,7 @@ WsLayout ws_layout(int T, int nseq, int tile0, int tile1, int lh, int hq, int hk
     w.k16 = at;  if (copies) at += align_up(2 * (size_t)T * (size_t)hkv * (size_t)head_dim);
     w.absmax = at; if (copies) at += align_up(sizeof(uint32_t) * kPrepMaxWg);
     w.rope_tab = at; at += align_up(sizeof(double) * kRopeTabEntries);       // rotary frequency table (the *_rope calls)
+    w.part = at; if (w.part_max > 1) at += align_up((size_t)w.part_max * part_bytes(T, hkv, head_dim));
     w.total = at;
     return w;
 }
@@ -302,7 +315,34 @@ SchedView make_view(char* ws, const SchedLayout& v, int tile, int lh, int max_se
     sv.exec = reinterpret_cast<int*>(ws + v.exec);
     sv.group_max = v.exec == v.items || grouped_heads ? 0 : (dt == HYD_BF16 ? 1024 : 512) / tile;
     sv.group_share = (float)heads / (16.f * (float)wgs);
+    sv.part_max = 1; sv.part_q = 1; sv.steps_per_level = 0;
     return sv;
+}
+
+// Parts of the dK/dV items.  An item runs over the query tiles of its sequence for every head of the
+// group in turn, so with few KV heads or few tokens the longest items last longer than all the work does
+// spread over the workgroups.  The work is bounded from below by what the host knows (one sequence of
+// max_seqlen tokens, the others of equal length): where the longest item is well above a workgroup's
+// share of that, items are cut into parts of half a share, at least kPartSteps steps.  The fp32 sums
+// of a part cost about as much as five steps, and the pass that adds them 7-20 us, which is why an item
+// of less than two such parts, or less than 1.6 shares, stays whole (dK/dV in us, whole -> in parts with
+// the adding pass: 4096 tokens in one sequence, 10 heads, 1.55 shares: 121 -> 139; 16384 tokens, 64/8
+// heads, 1.05 shares: 1068 -> 1083).
+// Measured (log-normal lengths, dK/dV + adding pass in us, before -> now): 8/1 heads, 8192 tokens 650 ->
+// 123; 16/2 heads, 8192 tokens 666 -> 233, 32768 tokens 1428 -> 820; 8/1 heads, one sequence of 16384
+// tokens 3070 -> 1262; 32/8 heads, 1024 tokens 98 -> 42 to 54, 2048 tokens 115 -> 65 to 76, 4096 tokens 307 -> 229, 8192
+// tokens 415 -> 406.  kPartSteps 12 / 24 / 40: 1024 tokens 43 / 54 / 74, 2048 tokens 76 / 65 / 81.
+constexpr int kPartSteps = 16;
+void set_parts(SchedView& sv, int limit, int T, int nseq, int max_seqlen, int hq, int hkv, int wgs) {
+    const double nm = (double)max_seqlen / kKvBN, m = nseq > 1 ? nseq - 1 : 1, nr = (double)(T - max_seqlen) / m / kKvBN;
+    const double share = (double)hq * (nm * (nm + 1) + m * nr * (nr + 1)) / wgs;       // steps of 64 query rows
+    sv.steps_per_level = kKvBN / kKvBM * (hq / hkv);
+    const double longest = (double)sv.n_lev * sv.steps_per_level;
+    if (limit <= 1 || longest < 1.6 * share || longest < 2 * kPartSteps) return;
+    double q = share / 2 > kPartSteps ? share / 2 : kPartSteps;
+    if (q < longest / limit) q = longest / limit;
+    sv.part_q = (int)ceil(q);
+    sv.part_max = item_parts(sv.n_lev, sv.steps_per_level, sv.part_q, limit);
 }
 
 int persistent_grid(const DeviceInfo& d, int occ, long long work_upper_bound) {
@@ -445,12 +485,13 @@ hyd_status bwd_impl(const void* q, const void* k, const void* v, const void* o, 
     const int lh = ranged ? 0 : split_lh(dt, total_tokens, hq, hkv, false);
     const int units = hq >> lh;
     const bool grouped = hq >= 4 * hkv;
-    const SchedView sv_kv = make_view(ws, w.sched[0], tile_kv(dt), 0, max_seqlen, dt, hkv, dev->cus * occ_kv, grouped);
+    SchedView sv_kv = make_view(ws, w.sched[0], tile_kv(dt), 0, max_seqlen, dt, hkv, dev->cus * occ_kv, grouped);
+    if (dt == HYD_BF16) set_parts(sv_kv, w.part_max, total_tokens, num_seqs, max_seqlen, hq, hkv, dev->cus * occ_kv);
     const SchedView sv_whole = make_view(ws, w.sched[1], tile_q(dt), 0, max_seqlen, dt, units, dev->cus * occ_q, grouped);
     const SchedView sv_q = lh ? make_view(ws, w.split, (256 >> lh), lh, max_seqlen, dt, units, dev->cus * occ_q, grouped) : sv_whole;
     float* Dvec = reinterpret_cast<float*>(ws + w.stat[0]);
     double* rope_tab = rope_base != 0.f ? reinterpret_cast<double*>(ws + w.rope_tab) : nullptr;
-    const long long work_q = (long long)sv_q.max_items * units, work_kv = (long long)sv_kv.max_items * hkv;
+    const long long work_q = (long long)sv_q.max_items * units, work_kv = (long long)sv_kv.max_items * sv_kv.part_max * hkv;
     if (dt == HYD_BF16) {
         BwdScratch sc;
         sc.Dq = Dvec;
@@ -502,7 +543,8 @@ hyd_status bwd_impl(const void* q, const void* k, const void* v, const void* o, 
             hipLaunchKernelGGL(kDqKernels[ranged ? 1 : lh][head_dim == 64], grid, dim3(kDqThreads), kDqLds, st, p);
         }
         {
-            p.hdr = sv_kv.hdr; p.items = sv_kv.exec;
+            p.hdr = sv_kv.hdr + kHdrExec; p.items = sv_kv.exec;
+            p.part = reinterpret_cast<float*>(ws + w.part); p.part_max = sv_kv.part_max;
             p.cursors = sv_kv.hdr + kHdrCursor;
             const dim3 grid(persistent_grid(*dev, occ_kv, work_kv));
             p.hm = head_map_kv(hkv, grid.x);
@@ -512,6 +554,19 @@ hyd_status bwd_impl(const void* q, const void* k, const void* v, const void* o, 
                 else hipLaunchKernelGGL((hyd_bwd_dkdv_bf16_kernel<false, 64>), grid, dim3(kKvThreads), kKvLds, st, p);
             } else if (ranged) hipLaunchKernelGGL(hyd_bwd_dkdv_bf16_kernel<true>, grid, dim3(kKvThreads), kKvLds, st, p);
             else hipLaunchKernelGGL(hyd_bwd_dkdv_bf16_kernel<false>, grid, dim3(kKvThreads), kKvLds, st, p);
+        }
+        if (sv_kv.part_max > 1) {
+            SumParams sp;
+            sp.part = p.part; sp.dk = p.dk; sp.dv = p.dv; sp.T = total_tokens; sp.hkv = hkv;
+            sp.part_max = sv_kv.part_max; sp.part_q = sv_kv.part_q; sp.steps_per_level = sv_kv.steps_per_level;
+            sp.hdr = sv_kv.hdr; sp.items = sv_kv.items; sp.ranges = p.ranges;
+            // items in parts are the first of the list: those of levels above `low`, of sequences longer than low tiles
+            const long long low = sp.part_q / sp.steps_per_level, tiles = total_tokens / kKvBN + 1;
+            const long long bound = low > 0 ? tiles + tiles / low + 1 : sv_kv.max_items;
+            const dim3 grid((unsigned)(bound < sv_kv.max_items ? bound : sv_kv.max_items), (unsigned)hkv, 2 * kKvBN / kSumRows);
+            KernelTimer kt("bwd_sum_parts", st);
+            if (head_dim == 64) hipLaunchKernelGGL(hyd_bwd_sum_parts_kernel<64>, grid, dim3(kSumThreads), 0, st, sp);
+            else hipLaunchKernelGGL(hyd_bwd_sum_parts_kernel<128>, grid, dim3(kSumThreads), 0, st, sp);
         }
     } else {
         F32Params p;

@@ -237,6 +237,8 @@ struct BwdParams {
     BwdScratch sc;
     uint16_t* dq; uint16_t* dk; uint16_t* dv;
     int T, hq, hkv;
+    float* part;                      // dK/dV: [2][part_max][T][Hkv][d] sums of the items in parts (dK first)
+    int part_max;
     float scale, scale_log2;
     const int* hdr; int* cursors; const int* items;
     HeadMap hm;
@@ -647,7 +649,8 @@ __global__ void __launch_bounds__(kKvThreads, 1) hyd_bwd_dkdv_bf16_kernel(BwdPar
     const float unscale = pow2i(-pm.shift());                         // 2^-kg
     while (have) {
         ++n_done;
-        const int lev = wi.lev, g = wi.head, row0 = wi.row0, L = wi.len;
+        const int lev = wi.lev & ((1 << kLevBits) - 1), g = wi.head, row0 = wi.row0, L = wi.len;
+        const int part = (wi.lev >> kLevBits) & (kPartsMax - 1), n_parts = ((wi.lev >> (kLevBits + 3)) & (kPartsMax - 1)) + 1;
         const int n_tiles = (L + kKvBN - 1) / kKvBN;
         const int j0 = (n_tiles - lev) * kKvBN;               // first key of the item
         int Lq = L, Lk = L, qb = 0;                           // query rows [qb, Lq), keys [.., Lk)
@@ -664,7 +667,10 @@ __global__ void __launch_bounds__(kKvThreads, 1) hyd_bwd_dkdv_bf16_kernel(BwdPar
         const bool active = wkey0 < Lk;
         const int qt_first = max(j0, qb) / kKvBM;             // first query tile that sees key j0
         const int n_qt = max((Lq + kKvBM - 1) / kKvBM - qt_first, 0);
-        const int n_iter = n_qt * G;
+        const int n_all = n_qt * G;                           // steps of the whole item; this part takes [it0, it0 + n_iter)
+        const int it0 = n_parts == 1 ? 0 : (int)((long long)n_all * part / n_parts);
+        const int n_iter = n_parts == 1 ? n_all : (int)((long long)n_all * (part + 1) / n_parts) - it0;
+        const int qt0_part = qt_first + it0 / G, h0_part = it0 % G;
         // rows past the query range read as zeros (as rows past the sequence do)
         const uint32_t q_bytes = (uint32_t)(max(Lq, 1) - 1) * q_stride_b + kRowB;
         const uint32_t stat_bytes = (uint32_t)Lq * 4;
@@ -676,7 +682,7 @@ __global__ void __launch_bounds__(kKvThreads, 1) hyd_bwd_dkdv_bf16_kernel(BwdPar
         constexpr int kDmaPerStage = 2 * (16 / kKvWaves) + 1;
         // the loads are issued for it = 0, 1, 2, ... in turn: (tile, head) advance with them instead
         // of being divided out of `it` every time
-        int ld_qt = qt_first, ld_h = 0;
+        int ld_qt = qt0_part, ld_h = h0_part;
         auto dma_stage = [&](int stage) {
             const int h = g * G + ld_h;
             const int qt = ld_qt;
@@ -853,7 +859,7 @@ __global__ void __launch_bounds__(kKvThreads, 1) hyd_bwd_dkdv_bf16_kernel(BwdPar
             }
             if (kB) __builtin_amdgcn_s_setprio(0);
         };
-        int cp_qt = qt_first, cp_h = 0;
+        int cp_qt = qt0_part, cp_h = h0_part;
         auto step = [&](auto role_tag, auto stage_tag, int it) {
             constexpr int ST = decltype(stage_tag)::value;
             constexpr int ST2 = (ST + 2) % kKvStages;
@@ -882,12 +888,63 @@ __global__ void __launch_bounds__(kKvThreads, 1) hyd_bwd_dkdv_bf16_kernel(BwdPar
         else tiles(std::false_type{});
         wf.claim(p.hm, p.cursors);
         __syncthreads();                                      // every wave is done with the ring
-        if (active)
-            store_rows_via_lds<D>((role_b ? p.dk : p.dv) + (int64_t)(row0 + wkey0) * kv_stride + (int64_t)g * D, kv_stride,
-                               Lk - wkey0, acc, (role_b ? p.scale : 1.f) * unscale, o_stage, lane);
+        const int64_t out = (int64_t)(row0 + wkey0) * kv_stride + (int64_t)g * D;
+        const float mul = (role_b ? p.scale : 1.f) * unscale;
+        if (active && n_parts == 1)
+            store_rows_via_lds<D>((role_b ? p.dk : p.dv) + out, kv_stride, Lk - wkey0, acc, mul, o_stage, lane);
+        else if (active)
+            store_rows_f32_via_lds<D>(p.part + ((role_b ? 0 : p.part_max) + part) * (int64_t)p.T * kv_stride + out, kv_stride,
+                                      Lk - wkey0, acc, mul, o_stage, lane);
         have = wf.next(p.hm, p.cursors, p.items, slot, wi);
     }
     trace_write(p.tr, 1, t_start, n_done);
+}
+
+// ---------------------------------------------------------------------------------------------
+// dK and dV of the items that dK/dV took in parts: the parts' fp32 sums added in the order of the
+// parts and rounded once.  A workgroup takes 32 keys of an item and KV head, of dK or of dV; the others
+// leave at once.  Bound by HBM: part_max reads of 4 bytes and one write of 2 per element.
+// ---------------------------------------------------------------------------------------------
+constexpr int kSumThreads = 256, kSumRows = 32;
+struct SumParams {
+    const float* part; uint16_t* dk; uint16_t* dv;
+    int T, hkv, part_max, part_q, steps_per_level;
+    const int* hdr; const int* items;
+    const int32_t* ranges;                 // range variant, else NULL
+};
+template <int D>
+__global__ void __launch_bounds__(kSumThreads) hyd_bwd_sum_parts_kernel(SumParams p) {
+    const int item = blockIdx.x, g = blockIdx.y, which = blockIdx.z / (kKvBN / kSumRows);
+    if (item >= p.hdr[0]) return;
+    const i32x4 rec = *reinterpret_cast<const i32x4*>(p.items + 4 * item);
+    const int n = item_parts(rec[1], p.steps_per_level, p.part_q, p.part_max);
+    if (n == 1) return;
+    const int L = rec[3], j0 = ((L + kKvBN - 1) / kKvBN - rec[1]) * kKvBN;
+    int Lk = L;
+    if (p.ranges) {
+        const i32x4 rg = *reinterpret_cast<const i32x4*>(p.ranges + 4 * rec[0]);
+        Lk = min(L, rg[3]);
+        if (j0 < rg[2]) return;
+    }
+    constexpr int kLanes = D / 4, kGrps = kSumThreads / kLanes;
+    const int c = threadIdx.x % kLanes, first = j0 + kSumRows * (blockIdx.z % (kKvBN / kSumRows));
+    const int64_t stride = (int64_t)p.hkv * D, plane = (int64_t)p.T * stride;
+    const float* src = p.part + (int64_t)(which ? p.part_max : 0) * plane;
+    uint16_t* dst = which ? p.dv : p.dk;
+    for (int r = threadIdx.x / kLanes; r < kSumRows; r += kGrps) {
+        if (first + r >= Lk) break;
+        const int64_t at = (int64_t)(rec[2] + first + r) * stride + (int64_t)g * D + 4 * c;
+        f32x4 x[kPartsMax];
+#pragma unroll
+        for (int i = 0; i < kPartsMax; ++i)
+            if (i < n) x[i] = *reinterpret_cast<const f32x4*>(src + i * plane + at);
+        f32x4 sum = x[0];
+#pragma unroll
+        for (int i = 1; i < kPartsMax; ++i)
+            if (i < n) sum += x[i];
+        const u32x2 w = {pack_bf16(sum[0], sum[1]), pack_bf16(sum[2], sum[3])};
+        *reinterpret_cast<u32x2*>(dst + at) = w;
+    }
 }
 
 }  // namespace hyd

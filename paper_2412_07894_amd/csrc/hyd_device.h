@@ -229,6 +229,36 @@ __device__ __forceinline__ void store_rows_via_lds(uint16_t* dst, int64_t row_st
     }
 }
 
+// The same rows in fp32: 64 elements (256 bytes) of each row at a time through the same 8 KB.
+template <int D>
+__device__ __forceinline__ void store_rows_f32_via_lds(float* dst, int64_t row_stride, int rows_valid,
+                                                       const f32x16 (&acc)[D / 32], float mul, uint32_t stage, int lane) {
+    typedef __attribute__((address_space(3))) f32x4 lds_f32x4;
+    asm volatile("" : "+v"(lane));
+    const int l32 = lane & 31, half = lane >> 5, c16 = lane & 15, r4 = lane >> 4;
+    const uint32_t wbase = stage + (uint32_t)(l32 * kRowBytes);
+    const int wswz = swz(l32);
+    float* ob = dst + (int64_t)r4 * row_stride + 4 * c16;
+    const uint32_t rbase = stage + (uint32_t)(r4 * kRowBytes);
+#pragma unroll
+    for (int h = 0; h < D / 64; ++h) {
+#pragma unroll
+        for (int db = 0; db < 2; ++db) {
+#pragma unroll
+            for (int rq = 0; rq < 4; ++rq) {
+                const f32x4 w = {acc[2 * h + db][4 * rq] * mul, acc[2 * h + db][4 * rq + 1] * mul,
+                                 acc[2 * h + db][4 * rq + 2] * mul, acc[2 * h + db][4 * rq + 3] * mul};
+                *(lds_f32x4*)(uintptr_t)(wbase + (uint32_t)(((8 * db + 2 * rq + half) ^ wswz) << 4)) = w;
+            }
+        }
+#pragma unroll
+        for (int k = 0; k < 8; ++k) {
+            const f32x4 w = *(lds_f32x4*)(uintptr_t)(rbase + (uint32_t)(4 * k * kRowBytes + ((c16 ^ (((r4 & 3) << 2) | (k & 3))) << 4)));
+            if (4 * k + r4 < rows_valid) *reinterpret_cast<f32x4*>(ob + (int64_t)(4 * k) * row_stride + 64 * h) = w;
+        }
+    }
+}
+
 // Per-lane byte offset of a direct-to-LDS row load: lane i of a 64-lane instruction fills LDS
 // position i%16 of tile row `row`, which in the swizzled layout holds chunk (i%16) ^ swz(row) of
 // the row.  A head dimension of 64 has only chunks 0..7: the other lanes point far outside the

@@ -22,13 +22,13 @@ namespace hyd {
 constexpr int kQueues = 8;
 typedef __attribute__((ext_vector_type(4))) int i32x4;
 
-// header (ints): [0] n_items, [1] kSched* flags about cu_seqlens as the prelude saw it, the rest
-// zeros; then the cursors of the eight queues, 256 bytes apart: the workgroups of all XCDs claim
+// header (ints): [0] n_items, [1] kSched* flags about cu_seqlens as the prelude saw it, [2] records
+// handed out, the rest zeros; then the cursors of the eight queues, 256 bytes apart: the workgroups of all XCDs claim
 // through them with device-scope atomics, which a shared line serialises (one line for all eight:
 // forward of 26177 tokens in sequences of 64-1024, 32 heads, d = 64: 227 us, apart 216)
 constexpr int kHdrInts = 64, kCursorStride = 64;
 constexpr int kHdrCursor = kHdrInts, kHdrTotal = kHdrInts + kQueues * kCursorStride;
-constexpr int kHdrFlags = 1;
+constexpr int kHdrFlags = 1, kHdrExec = 2;
 constexpr int kSchedTooLong = 1;          // a sequence is longer than max_seqlen: its tiles beyond that bound got no item
 constexpr int kSchedBadSeqlens = 2;       // cu_seqlens does not start at 0, does not end at T, or decreases
 
@@ -42,7 +42,18 @@ struct SchedView {            // device pointers into the workspace (all int32)
     float group_share;        // ... and at most (sum of all levels) * group_share
     int n_lev;                // upper bound on tiles per sequence
     int max_items;
+    int part_max, part_q, steps_per_level;     // items in parts (see item_parts); part_max = 1: whole
 };
+
+// An item can be handed out in parts (dK/dV kernel): level c, with c * steps_per_level steps, in
+// ceil(steps / part_q) of them, at most part_max.  exec then holds a record per part, which carries its
+// index and the number of parts in the level's upper bits.
+constexpr int kLevBits = 24, kPartsMax = 8;
+__host__ __device__ __forceinline__ int item_parts(int c, int steps_per_level, int part_q, int part_max) {
+    if (part_max <= 1) return 1;
+    const long long n = ((long long)c * steps_per_level + part_q - 1) / part_q;
+    return n < part_max ? (int)n : part_max;
+}
 
 struct HeadMap {              // how (item, head) pairs are spread over the queues
     int striped;              // 0: heads partitioned over the queues; 1: items striped
@@ -148,6 +159,15 @@ __device__ __forceinline__ void build_schedule(const int32_t* __restrict__ cu, i
     __syncthreads();
     // Level c (reversed index r = nl - c) holds the sequences of rank < cnt[r] at the list
     // positions [offs[r] - cnt[r], offs[r]): one thread per position finds its level by bisection.
+    const bool parts = sv.part_max > 1 && nl > 0 && offs[nl - 1] <= sv.max_items;
+    if (parts) {
+        if (tid < 64) {                        // hist[r]: records handed out up to level nl - r
+            for (int r = tid; r < nl; r += 64) hist[r] = cnt[r] * item_parts(nl - r, sv.steps_per_level, sv.part_q, sv.part_max);
+            wave_inclusive_scan(hist, nl, tid);
+        }
+        __syncthreads();
+    }
+    if (tid == 0) sv.hdr[kHdrExec] = parts ? hist[nl - 1] : n_items;
     for (int pos = tid; pos < n_items; pos += nthreads) {
         int lo = 0, hi = nl - 1;               // first r with offs[r] > pos
         while (lo < hi) {
@@ -159,7 +179,13 @@ __device__ __forceinline__ void build_schedule(const int32_t* __restrict__ cu, i
         const int a = cu[s], L = cu[s + 1] - a;
         const i32x4 rec = {s, c, a, L};
         *reinterpret_cast<i32x4*>(sv.items + 4 * pos) = rec;
-        if (sv.exec != sv.items) {
+        if (parts) {
+            const int n = item_parts(c, sv.steps_per_level, sv.part_q, sv.part_max);
+            for (int x = 0; x < n; ++x) {
+                const i32x4 part = {s, c | (x << kLevBits) | ((n - 1) << (kLevBits + 3)), a, L};
+                *reinterpret_cast<i32x4*>(sv.exec + 4 * (hist[lo] - (cnt[lo] - rank) * n + x)) = part;
+            }
+        } else if (sv.exec != sv.items) {
             int e = pos;
             if (c <= C) {
                 // items of higher levels, then the C lowest levels of the sequences of lower rank

@@ -1,0 +1,64 @@
+"""dK/dV items taken in parts (few KV heads or few tokens): fp32 sums of the parts added in a pass of
+their own.  Against the fp64 oracle with the bars of the other parity tests, over the number of parts, the
+remainders of steps per part, and the range variant; twice the same bits; rows that get no item stay."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import attn_oracle as orc
+from paper_2412_07894_amd import binding, workloads as wl
+import gpu_util as gu
+
+pytestmark = pytest.mark.gpu
+
+
+def setup(lens, hq, hkv, d, seed):
+    cu, q, k, v, do = wl.custom(lens, hq, hkv, d, "bf16", seed)
+    if hq // hkv > 16:          # a sum over 32 heads reaches 12, where rounding to bf16 alone (2^-5 above 8) passes
+        do = do * 0.25          # the absolute bar of 2e-2; the gradients follow a power of two exactly
+    scale = 1.0 / float(np.sqrt(d))
+    dev = [gu.to_dev(x, "bf16") for x in (q, k, v, do)]
+    cu_d = torch.from_numpy(cu).cuda()
+    o, lse = binding.varlen_attn_fwd(*dev[:3], cu_d, max(lens), scale)
+    return cu, (q, k, v, do), scale, dev, cu_d, o, lse
+
+
+def names_of(run):
+    binding.enable_kernel_timing(True)
+    try:
+        run()
+        return [n for n, _ in binding.kernel_times()]
+    finally:
+        binding.enable_kernel_timing(False)
+
+
+@pytest.mark.parametrize("lens,hq,hkv,d,parts", [
+    ([1300, 7, 129], 8, 1, 128, True), ([1300, 7, 129], 16, 2, 64, True), ([2200], 4, 4, 64, True), ([257, 1000], 32, 8, 128, True),
+    ([3, 900, 128], 6, 2, 128, True), ([100, 31], 8, 8, 128, False), ([128, 127], 32, 1, 64, True)])
+def test_items_in_parts_match_the_oracle(lens, hq, hkv, d, parts):
+    print(f"\nparts: {lens} {hq}/{hkv} d = {d}", flush=True)
+    cu, host, scale, (q, k, v, do), cu_d, o, lse = setup(lens, hq, hkv, d, 71)
+    run = lambda: binding.varlen_attn_bwd(q, k, v, o, lse, do, cu_d, max(lens), scale)
+    assert ("bwd_sum_parts" in names_of(run)) == parts
+    (dq, dk, dv), again = run(), run()
+    for x, y in zip((dq, dk, dv), again):
+        assert torch.equal(x, y)
+    rdq, rdk, rdv = orc.bwd(*host, cu, scale)
+    for name, got, ref in (("dq", dq, rdq), ("dk", dk, rdk), ("dv", dv, rdv)):
+        gu.check(name, gu.to_np(got), ref, "bf16")
+
+
+def test_items_in_parts_of_a_key_range():
+    lens, hq, hkv, d = [1500, 300], 8, 1, 128
+    cu, host, scale, (q, k, v, do), cu_d, o, lse = setup(lens, hq, hkv, d, 72)
+    _, rdk, rdv = orc.bwd(*host, cu, scale)
+    ranges = torch.tensor([[0, 4096, 256, 1024], [0, 4096, 256, 1024]], dtype=torch.int32, device="cuda")
+    dq, dk, dv = (torch.full_like(x, 7.0) for x in (q, k, v))
+    run = lambda: binding.varlen_attn_bwd_range(q, k, v, o, lse, do, cu_d, ranges, max(lens), scale, dq=dq, dk=dk, dv=dv)
+    assert "bwd_sum_parts" in names_of(run)
+    inside = np.r_[256:1024, 1756:1800]
+    outside = np.setdiff1d(np.arange(1800), inside)
+    for name, got, ref in (("dk", dk, rdk), ("dv", dv, rdv)):
+        got = gu.to_np(got)
+        gu.check(name, got[inside], ref[inside], "bf16")
+        assert np.all(got[outside] == 7.0), name
