@@ -28,23 +28,23 @@ constexpr int kBwdStatVecs = 4;
 struct SchedLayout { size_t hdr, lev, order, items, exec; int n_lev, max_items; };
 struct WsLayout {
     SchedLayout sched[2];
-    SchedLayout split;      // query side by QuerySplit tiles, where an item takes several heads (lh > 0)
+    SchedLayout split;      // query side by QuerySplit tiles, where an item is not a whole tile (split > 0)
     int n_sched;
     int part_max;           // dK/dV items in parts: their number at most, and the parts' sums
     size_t stat[kBwdStatVecs], q16, do16, k16, absmax, rope_tab, part, total;
 };
 constexpr int kRopeTabEntries = 64;       // head_dim / 2 at most
 
-// levels of a sequence of `len` rows, in whole multiples of 2^lh tiles: a list of split tiles covers
+// levels of a sequence of `len` rows, in whole multiples of 2^split tiles: a list of split tiles covers
 // the same rows as the list of whole ones for every bound on the sequence length
-int levels(int len, int tile, int lh) {
-    const int whole = tile << lh, n = (len + whole - 1) / whole;
-    return (n < 1 ? 1 : n) << lh;
+int levels(int len, int tile, int split) {
+    const int whole = tile << split, n = (len + whole - 1) / whole;
+    return (n < 1 ? 1 : n) << split;
 }
 
 // `compact`: the records are handed out in list order, without a second copy of them
-size_t sched_layout(SchedLayout& v, size_t at, int T, int nseq, int tile, int lh, bool compact, int part_max = 1) {
-    v.n_lev = levels(T, tile, lh);
+size_t sched_layout(SchedLayout& v, size_t at, int T, int nseq, int tile, int split, bool compact, int part_max = 1) {
+    v.n_lev = levels(T, tile, split);
     v.max_items = T / tile + nseq + 1;
     v.hdr = at;   at += align_up(sizeof(int) * kHdrTotal);
     v.lev = at;   at += align_up(sizeof(int) * 3 * (size_t)(v.n_lev + 2));
@@ -65,15 +65,16 @@ int part_limit(int T, int hkv, int head_dim) {
     return n;
 }
 
-// lh: of the query side (the last list)
-WsLayout ws_layout(int T, int nseq, int tile0, int tile1, int lh, int hq, int hkv, int head_dim, hyd_dtype dt, bool bwd, bool compact = false) {
+// split: finest form of the query side's items (the last list).  The list of whole tiles has its order of
+// execution only where that differs from it (make_view).
+WsLayout ws_layout(int T, int nseq, int tile0, int tile1, int split, int hq, int hkv, int head_dim, hyd_dtype dt, bool bwd, bool compact = false) {
     WsLayout w;
     w.part_max = bwd && dt == HYD_BF16 ? part_limit(T, hkv, head_dim) : 1;
-    size_t at = sched_layout(w.sched[0], 0, T, nseq, tile0, 0, compact || (!bwd && lh > 0), w.part_max);
+    size_t at = sched_layout(w.sched[0], 0, T, nseq, tile0, 0, compact || (!bwd && hq >= 4 * hkv), w.part_max);
     w.n_sched = bwd ? 2 : 1;
-    if (bwd) at = sched_layout(w.sched[1], at, T, nseq, tile1, 0, lh > 0);
+    if (bwd) at = sched_layout(w.sched[1], at, T, nseq, tile1, 0, hq >= 4 * hkv);
     else w.sched[1] = w.sched[0];
-    if (lh > 0) at = sched_layout(w.split, at, T, nseq, (bwd ? tile1 : tile0) >> lh, lh, true);
+    if (split > 0) at = sched_layout(w.split, at, T, nseq, (bwd ? tile1 : tile0) >> split, split, true);
     else w.split = w.sched[1];
     const int n_stat = !bwd ? 0 : (dt == HYD_BF16 ? kBwdStatVecs : 1);
     for (int i = 0; i < kBwdStatVecs; ++i) {
@@ -95,25 +96,47 @@ WsLayout ws_layout(int T, int nseq, int tile0, int tile1, int lh, int hq, int hk
 static_assert(kFwdBM == 256 && kDqBM == 256, "QuerySplit");
 int tile_q(hyd_dtype dt) { return dt == HYD_BF16 ? 256 : kF32BM; }
 int tile_kv(hyd_dtype dt) { return dt == HYD_BF16 ? kKvBN : kF32KvBN; }
-// LH of QuerySplit: four heads per item where the query heads of a KV head come in fours and there
+// Form of the query side's items (QuerySplit) in a call without ranges.
+//
+// Half tiles where a launch lasts as long as its longest item: that item's steps are 2.5 times a
+// workgroup's share of all steps or more, the work bounded from below as in set_parts.  (Half / whole,
+// forward and dQ, log-normal lengths unless noted: 8 heads, 2048 tokens, 7 shares 0.85 / 0.82, 4096 tokens, 4.4
+// shares 0.72 / 0.75, 8192 tokens, 2.9 shares 0.69 / 0.69; 10 heads, one sequence of 4096, 3.0 shares 0.70 /
+// 0.71; 32 heads, 1536 tokens, 2.5 shares 0.83 / 0.82; 8 heads, 8192 tokens of 64-1024, 2.4 shares 1.08 / 1.02; 32
+// heads, 2048 tokens, 1.75 shares 1.05 / 1.04, 4096 tokens, 1.1 shares 1.20 / 1.15.)
+//
+// Four heads per item where the query heads of a KV head come in fours and there
 // are items for two rounds of workgroups.  With fewer, a launch lasts as long as its longest items,
 // and those are shorter with 256-row tiles, whose waves drop out one by one on the diagonal (32/8 heads,
-// log-normal lengths, forward / dQ in us, whole -> split: 2048 tokens 37.1 / 51.1 -> 40.2 / 54.1; 4096
+// log-normal lengths, forward / dQ in us, whole -> four heads: 2048 tokens 37.1 / 51.1 -> 40.2 / 54.1; 4096
 // tokens 99.5 / 137.6 -> 99.0 / 136.2; 6144 143.8 / 202 -> 140.8 / 197.5; 32768 tokens of 64-1024 336.5 /
 // 478 -> 319 / 452; 64/8 heads, 16384 tokens 654 / 885 -> 612 / 852; 16/2 heads, 32768 tokens 449 / 594 ->
-// 421 / 569).  The range variants, whose rows are a part
-// of the tokens, keep whole tiles (a context-parallel ring of four, 16384 tokens: 2980 us, split 3018).
+// 421 / 569).  The range variants, whose rows are a part of the tokens, keep whole tiles (a
+// context-parallel ring of four, 16384 tokens: 2980 us, four heads 3018).
+//
 // `compact`: whole tiles, which need the fewest records.
-constexpr long long kSplitPairs = 2 * 256 * 256;           // (token, head) pairs of two items for each of 256 CUs
-int split_lh(hyd_dtype dt, int T, int hq, int hkv, bool compact) {
-    return dt == HYD_BF16 && !compact && (hq / hkv) % 4 == 0 && (long long)T * hq >= kSplitPairs ? 2 : 0;
+constexpr long long kFourHeadPairs = 2 * 256 * 256;        // (token, head) pairs of two items for each of 256 CUs
+double share_of_work(double tile, double steps_per_level, int T, int nseq, int max_seqlen, int heads, int wgs) {
+    const double nm = max_seqlen / tile, m = nseq > 1 ? nseq - 1 : 1, nr = (T - max_seqlen) / m / tile;
+    return heads * steps_per_level * (nm * (nm + 1) + m * nr * (nr + 1)) / 2 / wgs;
 }
+int query_split(hyd_dtype dt, int T, int nseq, int max_seqlen, int hq, int hkv, bool compact) {
+    if (dt != HYD_BF16 || compact) return 0;
+    const double steps = 256 / kFwdBN;                     // per level of a whole tile
+    if (max_seqlen / 256.0 * steps >= 2.5 * share_of_work(256, steps, T, nseq, max_seqlen, hq, 256)) return 1;
+    return (hq / hkv) % 4 == 0 && (long long)T * hq >= kFourHeadPairs ? 2 : 0;
+}
+// the finest tile that a call of these sizes may choose, for the workspace
+int finest_split(hyd_dtype dt, int hq, int hkv, bool compact) {
+    return dt != HYD_BF16 || compact ? 0 : ((hq / hkv) % 4 == 0 ? 2 : 1);
+}
+int item_heads(int split) { return split == 2 ? 4 : 1; }
 
 WsLayout fwd_layout(int T, int nseq, int hq, int hkv, int head_dim, hyd_dtype dt, bool compact) {
-    return ws_layout(T, nseq, tile_q(dt), tile_q(dt), split_lh(dt, T, hq, hkv, compact), hq, hkv, head_dim, dt, false, compact);
+    return ws_layout(T, nseq, tile_q(dt), tile_q(dt), finest_split(dt, hq, hkv, compact), hq, hkv, head_dim, dt, false, compact);
 }
 WsLayout bwd_layout(int T, int nseq, int hq, int hkv, int head_dim, hyd_dtype dt) {
-    return ws_layout(T, nseq, tile_kv(dt), tile_q(dt), split_lh(dt, T, hq, hkv, false), hq, hkv, head_dim, dt, true);
+    return ws_layout(T, nseq, tile_kv(dt), tile_q(dt), finest_split(dt, hq, hkv, false), hq, hkv, head_dim, dt, true);
 }
 
 bool head_dim_ok(hyd_dtype dt, int d) { (void)dt; return d == 64 || d == 128; }
@@ -229,15 +252,17 @@ bool prep_f32(int* occ) {
            prep_kernel(hyd_bwd_dkdv_fp32_kernel<D>, 64 * kF32KvWaves, f32_lds<D>(), occ + 2);
 }
 
-// [whole tiles, range variant, split tiles][head_dim == 64]
+// [form of the items, then range variant][head_dim == 64]
 typedef void (*FwdKernel)(FwdParams);
 typedef void (*BwdKernel)(BwdParams);
-constexpr FwdKernel kFwdKernels[3][2] = {{hyd_fwd_bf16_kernel<false, 128, 0>, hyd_fwd_bf16_kernel<false, 64, 0>},
-                                         {hyd_fwd_bf16_kernel<true, 128, 0>, hyd_fwd_bf16_kernel<true, 64, 0>},
-                                         {hyd_fwd_bf16_kernel<false, 128, 2>, hyd_fwd_bf16_kernel<false, 64, 2>}};
-constexpr BwdKernel kDqKernels[3][2] = {{hyd_bwd_dq_bf16_kernel<false, 128, 0>, hyd_bwd_dq_bf16_kernel<false, 64, 0>},
-                                        {hyd_bwd_dq_bf16_kernel<true, 128, 0>, hyd_bwd_dq_bf16_kernel<true, 64, 0>},
-                                        {hyd_bwd_dq_bf16_kernel<false, 128, 2>, hyd_bwd_dq_bf16_kernel<false, 64, 2>}};
+constexpr FwdKernel kFwdKernels[4][2] = {{hyd_fwd_bf16_kernel<false, 128, 0>, hyd_fwd_bf16_kernel<false, 64, 0>},
+                                         {hyd_fwd_bf16_kernel<false, 128, 1>, hyd_fwd_bf16_kernel<false, 64, 1>},
+                                         {hyd_fwd_bf16_kernel<false, 128, 2>, hyd_fwd_bf16_kernel<false, 64, 2>},
+                                         {hyd_fwd_bf16_kernel<true, 128, 0>, hyd_fwd_bf16_kernel<true, 64, 0>}};
+constexpr BwdKernel kDqKernels[4][2] = {{hyd_bwd_dq_bf16_kernel<false, 128, 0>, hyd_bwd_dq_bf16_kernel<false, 64, 0>},
+                                        {hyd_bwd_dq_bf16_kernel<false, 128, 1>, hyd_bwd_dq_bf16_kernel<false, 64, 1>},
+                                        {hyd_bwd_dq_bf16_kernel<false, 128, 2>, hyd_bwd_dq_bf16_kernel<false, 64, 2>},
+                                        {hyd_bwd_dq_bf16_kernel<true, 128, 0>, hyd_bwd_dq_bf16_kernel<true, 64, 0>}};
 
 hyd_status device_info(DeviceInfo** out) {
     int dev = 0;
@@ -251,7 +276,7 @@ hyd_status device_info(DeviceInfo** out) {
         d.ok = strncmp(prop.gcnArchName, "gfx950", 6) == 0;
         d.cus = prop.multiProcessorCount;
         if (d.ok) {
-            for (int i = 0; i < 6; ++i)          // (the LDS of all variants allows one workgroup per CU)
+            for (int i = 0; i < 8; ++i)          // (the LDS of all variants allows one workgroup per CU)
                 if (!prep_kernel(kFwdKernels[i / 2][i % 2], kFwdThreads, kFwdLds, &d.occ_fwd) ||
                     !prep_kernel(kDqKernels[i / 2][i % 2], kDqThreads, kDqLds, &d.occ_dq))
                     return HYD_ERR_LAUNCH;
@@ -299,17 +324,17 @@ struct KernelTimer {       // brackets one launch with events when timing is on
     }
 };
 
-// View of a schedule of `tile` rows (a 2^lh-th of the kernel's tile); its level count is bounded by the caller's max_seqlen.
+// View of a schedule of `tile` rows (a 2^split-th of the kernel's tile); its level count is bounded by the caller's max_seqlen.
 // `heads` work items per record are shared by `wgs` workgroups.  Sequences are grouped up to
 // 1024 bf16 (512 fp32) rows, 512 KB of K and V for a head, unless four or more query heads share
 // a KV head: their workgroups share its stream already, and the list's own order is balanced best.
-SchedView make_view(char* ws, const SchedLayout& v, int tile, int lh, int max_seqlen, hyd_dtype dt, int heads, int wgs, bool grouped_heads) {
+SchedView make_view(char* ws, const SchedLayout& v, int tile, int split, int max_seqlen, hyd_dtype dt, int heads, int wgs, bool grouped_heads) {
     SchedView sv;
     sv.hdr = reinterpret_cast<int*>(ws + v.hdr);
     sv.lev = reinterpret_cast<int*>(ws + v.lev);
     sv.order = reinterpret_cast<int*>(ws + v.order);
     sv.items = reinterpret_cast<int*>(ws + v.items);
-    const int by_len = levels(max_seqlen, tile, lh);
+    const int by_len = levels(max_seqlen, tile, split);
     sv.n_lev = by_len < v.n_lev ? by_len : v.n_lev;
     sv.max_items = v.max_items;
     sv.exec = reinterpret_cast<int*>(ws + v.exec);
@@ -334,9 +359,8 @@ SchedView make_view(char* ws, const SchedLayout& v, int tile, int lh, int max_se
 // tokens 415 -> 406.  kPartSteps 12 / 24 / 40: 1024 tokens 43 / 54 / 74, 2048 tokens 76 / 65 / 81.
 constexpr int kPartSteps = 16;
 void set_parts(SchedView& sv, int limit, int T, int nseq, int max_seqlen, int hq, int hkv, int wgs) {
-    const double nm = (double)max_seqlen / kKvBN, m = nseq > 1 ? nseq - 1 : 1, nr = (double)(T - max_seqlen) / m / kKvBN;
-    const double share = (double)hq * (nm * (nm + 1) + m * nr * (nr + 1)) / wgs;       // steps of 64 query rows
     sv.steps_per_level = kKvBN / kKvBM * (hq / hkv);
+    const double share = share_of_work(kKvBN, sv.steps_per_level, T, nseq, max_seqlen, hkv, wgs);
     const double longest = (double)sv.n_lev * sv.steps_per_level;
     if (limit <= 1 || longest < 1.6 * share || longest < 2 * kPartSteps) return;
     double q = share / 2 > kPartSteps ? share / 2 : kPartSteps;
@@ -409,20 +433,20 @@ hyd_status fwd_impl(const void* q, const void* k, const void* v, const int32_t* 
     if (ds != HYD_OK) return ds;
     hipStream_t st = static_cast<hipStream_t>(hip_stream);
 
-    const int lh = ranged ? 0 : split_lh(dt, total_tokens, hq, hkv, compact);
-    const int tile = tile_q(dt), units = hq >> lh;
+    const int split = ranged ? 0 : query_split(dt, total_tokens, num_seqs, max_seqlen, hq, hkv, compact);
+    const int tile = tile_q(dt), units = hq / item_heads(split);
     const WsLayout w = fwd_layout(total_tokens, num_seqs, hq, hkv, head_dim, dt, compact);
     const int occ = dt == HYD_BF16 ? dev->occ_fwd : dev->occ_f32[head_dim == 128][0];
-    // where items take several heads, the list of whole tiles is built too, next to the one that is
+    // where items are not whole tiles, the list of whole tiles is built too, next to the one that is
     // handed out (hyd_varlen_attn_schedule_layout shows it)
     const bool grouped = hq >= 4 * hkv;
     const SchedView sv_whole = make_view(static_cast<char*>(workspace), w.sched[0], tile, 0, max_seqlen, dt, units, dev->cus * occ, grouped);
-    const SchedView sv = lh ? make_view(static_cast<char*>(workspace), w.split, (256 >> lh), lh, max_seqlen, dt, units, dev->cus * occ, grouped) : sv_whole;
+    const SchedView sv = split ? make_view(static_cast<char*>(workspace), w.split, 256 >> split, split, max_seqlen, dt, units, dev->cus * occ, grouped) : sv_whole;
     double* rope_tab = rope_base != 0.f ? reinterpret_cast<double*>(static_cast<char*>(workspace) + w.rope_tab) : nullptr;
     {
         KernelTimer kt("schedule_prelude", st);
-        hipLaunchKernelGGL(hyd_schedule_prelude, dim3(lh ? 2 : 1), dim3(kPreludeThreads), schedule_lds_max(sv_whole.n_lev, sv.n_lev), st, cu_seqlens, num_seqs,
-                           total_tokens, tile, sv_whole, tile >> lh, sv,
+        hipLaunchKernelGGL(hyd_schedule_prelude, dim3(split ? 2 : 1), dim3(kPreludeThreads), schedule_lds_max(sv_whole.n_lev, sv.n_lev), st, cu_seqlens, num_seqs,
+                           total_tokens, tile, sv_whole, tile >> split, sv,
                            rope_tab, head_dim / 2, rope_base != 0.f ? log2((double)rope_base) : 0.0);
     }
     const long long work = (long long)sv.max_items * units;
@@ -438,7 +462,7 @@ hyd_status fwd_impl(const void* q, const void* k, const void* v, const int32_t* 
         const dim3 grid(persistent_grid(*dev, occ, work));
         p.hm = head_map_q(units, hkv, grid.x);
         KernelTimer kt(ranged ? "fwd_range_bf16" : "fwd_bf16", st);
-        hipLaunchKernelGGL(kFwdKernels[ranged ? 1 : lh][head_dim == 64], grid, dim3(kFwdThreads), kFwdLds, st, p);
+        hipLaunchKernelGGL(kFwdKernels[ranged ? 3 : split][head_dim == 64], grid, dim3(kFwdThreads), kFwdLds, st, p);
     } else {
         F32Params p;
         memset(&p, 0, sizeof(p));
@@ -482,13 +506,13 @@ hyd_status bwd_impl(const void* q, const void* k, const void* v, const void* o, 
     char* ws = static_cast<char*>(workspace);
     const int occ_q = dt == HYD_BF16 ? dev->occ_dq : dev->occ_f32[head_dim == 128][1];
     const int occ_kv = dt == HYD_BF16 ? dev->occ_kv : dev->occ_f32[head_dim == 128][2];
-    const int lh = ranged ? 0 : split_lh(dt, total_tokens, hq, hkv, false);
-    const int units = hq >> lh;
+    const int split = ranged ? 0 : query_split(dt, total_tokens, num_seqs, max_seqlen, hq, hkv, false);
+    const int units = hq / item_heads(split);
     const bool grouped = hq >= 4 * hkv;
     SchedView sv_kv = make_view(ws, w.sched[0], tile_kv(dt), 0, max_seqlen, dt, hkv, dev->cus * occ_kv, grouped);
     if (dt == HYD_BF16) set_parts(sv_kv, w.part_max, total_tokens, num_seqs, max_seqlen, hq, hkv, dev->cus * occ_kv);
     const SchedView sv_whole = make_view(ws, w.sched[1], tile_q(dt), 0, max_seqlen, dt, units, dev->cus * occ_q, grouped);
-    const SchedView sv_q = lh ? make_view(ws, w.split, (256 >> lh), lh, max_seqlen, dt, units, dev->cus * occ_q, grouped) : sv_whole;
+    const SchedView sv_q = split ? make_view(ws, w.split, 256 >> split, split, max_seqlen, dt, units, dev->cus * occ_q, grouped) : sv_whole;
     float* Dvec = reinterpret_cast<float*>(ws + w.stat[0]);
     double* rope_tab = rope_base != 0.f ? reinterpret_cast<double*>(ws + w.rope_tab) : nullptr;
     const long long work_q = (long long)sv_q.max_items * units, work_kv = (long long)sv_kv.max_items * sv_kv.part_max * hkv;
@@ -511,8 +535,8 @@ hyd_status bwd_impl(const void* q, const void* k, const void* v, const void* o, 
             pp.sc = sc;
             pp.cu = cu_seqlens; pp.nseq = num_seqs;
             pp.ranges = ranged ? ranges : nullptr;
-            pp.n_sched = lh ? 3 : 2;
-            pp.tile[0] = tile_kv(dt); pp.tile[1] = tile_q(dt); pp.tile[2] = tile_q(dt) >> lh;
+            pp.n_sched = split ? 3 : 2;
+            pp.tile[0] = tile_kv(dt); pp.tile[1] = tile_q(dt); pp.tile[2] = tile_q(dt) >> split;
             pp.sv[0] = sv_kv; pp.sv[1] = sv_whole; pp.sv[2] = sv_q;
             pp.rope_tab = rope_tab; pp.log2_base = rope_tab ? log2((double)rope_base) : 0.0;
             const dim3 grid((unsigned)(pp.n_sched + sc.n_absmax)), block(kPrepThreads);
@@ -540,7 +564,7 @@ hyd_status bwd_impl(const void* q, const void* k, const void* v, const void* o, 
             const dim3 grid(persistent_grid(*dev, occ_q, work_q));
             p.hm = head_map_q(units, hkv, grid.x);
             KernelTimer kt(ranged ? "bwd_dq_range_bf16" : "bwd_dq_bf16", st);
-            hipLaunchKernelGGL(kDqKernels[ranged ? 1 : lh][head_dim == 64], grid, dim3(kDqThreads), kDqLds, st, p);
+            hipLaunchKernelGGL(kDqKernels[ranged ? 3 : split][head_dim == 64], grid, dim3(kDqThreads), kDqLds, st, p);
         }
         {
             p.hdr = sv_kv.hdr + kHdrExec; p.items = sv_kv.exec;

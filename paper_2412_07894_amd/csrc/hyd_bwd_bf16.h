@@ -249,7 +249,7 @@ struct BwdParams {
 };
 
 // ---------------------------------------------------------------------------------------------
-// dQ.  Work item = (sequence, query tile, query heads), 256 (row, head) pairs (see QuerySplit); each of 8
+// dQ.  Work item = (sequence, query tile, query heads), 256 or 128 (row, head) pairs (see QuerySplit); each of 8
 // waves owns 32 rows of one head.
 // Same orientation, K/V ring and causal structure as the forward kernel: S^T[key][q] = K Q^T and
 // dP^T[key][q] = V dO^T put one query row in each lane, so LSE_i and D_i are per-lane scalars;
@@ -352,9 +352,9 @@ __device__ __forceinline__ void dq_block(int Kt, int Vt, const FragAddr& fa, int
 
 // R: range variant (see the forward kernel): query tiles outside the query range are skipped,
 // the tile loop covers the key range only, dQ holds that key range's contribution.
-template <bool R, int D = kHeadDim, int LH = 0>
+template <bool R, int D = kHeadDim, int S = 0>
 __global__ void __launch_bounds__(kDqThreads, 1) hyd_bwd_dq_bf16_kernel(BwdParams p) {
-    using QS = QuerySplit<LH>;
+    using QS = QuerySplit<S>;
     static_assert(D == 128 || D == 64, "head dimension");
     constexpr int kRowB = D * 2;                                      // bytes of a row in global memory
     static_assert(kDqBM == 256 && kDqStages == 3, "the Q / dO staging assumes a 256-row tile and a 3-stage ring");
@@ -393,7 +393,7 @@ __global__ void __launch_bounds__(kDqThreads, 1) hyd_bwd_dq_bf16_kernel(BwdParam
     while (have) {
         ++n_done;
         __syncthreads();                                  // everybody has read the work slot: its bytes may be overwritten
-        const int lev = wi.lev, head0 = wi.head << LH, row0 = wi.row0, L = wi.len;
+        const int lev = wi.lev, head0 = wi.head << QS::kLh, row0 = wi.row0, L = wi.len;
         const int q0 = (lev - 1) * QS::kRows;
         int Lq = L, kb = 0, kcap = L;                     // query rows [.., Lq), keys [kb, kcap)
         if (R) {
@@ -440,13 +440,13 @@ __global__ void __launch_bounds__(kDqThreads, 1) hyd_bwd_dq_bf16_kernel(BwdParam
         };
         dma_tile(t_lo, 0);
         {   // the item's rows of Q and dO; rows past the query range read as zeros
-            const uint32_t q_bytes = (uint32_t)(min(Lq - q0, QS::kRows) - 1) * q_stride_b + (kRowB << LH);
+            const uint32_t q_bytes = (uint32_t)(min(Lq - q0, QS::kRows) - 1) * q_stride_b + (kRowB << QS::kLh);
             const int64_t off = (int64_t)(row0 + q0) * q_stride + (int64_t)head0 * D;
             auto tile_at = [&](int j) { return QS::tile_at(j, q_stride_b, kRowB); };
             dma_rows<kDqWaves>(make_rsrc(p.q + off, q_bytes), smem + kDqQxOff, [](int j) { return j * kDqTileBytes; },
-                               kDqBM / 64, q_stride_b, tile_at, wave, dma_voff_q);
+                               QS::kTiles, q_stride_b, tile_at, wave, dma_voff_q);
             dma_rows<kDqWaves>(make_rsrc(p.d_o + off, q_bytes), smem + kDqStageBytes, [](int j) { return j * kDqTileBytes; },
-                               kDqBM / 64, q_stride_b, tile_at, wave, dma_voff_q);
+                               QS::kTiles, q_stride_b, tile_at, wave, dma_voff_q);
         }
         float lse2 = 0.f, Dq = 0.f, unshift = 0.f;
         if (qvalid) {

@@ -1,6 +1,6 @@
 // bf16 forward kernel: block-diagonal causal flash-style tile loop on MFMA with fp32 accumulation.
 //
-// Work item = (sequence, query tile, query heads of one KV head), 256 (row, head) pairs in all (see
+// Work item = (sequence, query tile, query heads of one KV head), 256 or 128 (row, head) pairs in all (see
 // QuerySplit).  A workgroup has 8 waves; a wave owns 32 query rows of one head for the whole item, so
 // the online softmax never crosses waves.  K/V tiles of 64 keys travel global -> LDS by direct-to-LDS buffer loads (no staging
 // registers, no LDS store instructions) into a ring of three stages shared by the waves: while
@@ -190,9 +190,9 @@ __device__ __forceinline__ void fwd_tile(int Kt, int Vt, const FragAddr& fa, con
 // outside the query range are skipped, the tile loop starts at the key range's first tile and
 // stops at its end, and a row that sees no key of the range gets O = 0 and LSE = -inf (the
 // neutral element of the log-sum-exp merge of partial results).
-template <bool R, int D = kHeadDim, int LH = 0>
+template <bool R, int D = kHeadDim, int S = 0>
 __global__ void __launch_bounds__(kFwdThreads, 1) hyd_fwd_bf16_kernel(FwdParams p) {
-    using QS = QuerySplit<LH>;
+    using QS = QuerySplit<S>;
     static_assert(D == 128 || D == 64, "head dimension");
     constexpr int kRowB = D * 2;                                      // bytes of a row in global memory
     extern __shared__ __attribute__((aligned(16))) char smem[];
@@ -231,7 +231,7 @@ __global__ void __launch_bounds__(kFwdThreads, 1) hyd_fwd_bf16_kernel(FwdParams 
     bool have = wf.first(p.hm, p.hdr, p.cursors, p.items, slot, wi);
     while (have) {
         ++n_done;
-        const int lev = wi.lev, head0 = wi.head << LH, row0 = wi.row0, L = wi.len;
+        const int lev = wi.lev, head0 = wi.head << QS::kLh, row0 = wi.row0, L = wi.len;
         const int q0 = (lev - 1) * QS::kRows;
         int Lq = L, kb = 0, kcap = L;                     // query rows [.., Lq), keys [kb, kcap)
         if (R) {
@@ -282,9 +282,9 @@ __global__ void __launch_bounds__(kFwdThreads, 1) hyd_fwd_bf16_kernel(FwdParams 
         if (t_lo + 1 < n_kt) dma_tile(t_lo + 1, 1);
 
         {   // the item's Q rows; rows past the query range read as zeros (the last row ends with its last head)
-            const uint32_t q_bytes = (uint32_t)(min(Lq - q0, QS::kRows) - 1) * q_stride_b + (kRowB << LH);
+            const uint32_t q_bytes = (uint32_t)(min(Lq - q0, QS::kRows) - 1) * q_stride_b + (kRowB << QS::kLh);
             dma_rows<kFwdWaves>(make_rsrc(p.q + (int64_t)(row0 + q0) * q_stride + (int64_t)head0 * D, q_bytes), smem,
-                                [](int j) { return fwd_q_stage_off(j); }, kFwdBM / 64, q_stride_b,
+                                [](int j) { return fwd_q_stage_off(j); }, QS::kTiles, q_stride_b,
                                 [&](int j) { return QS::tile_at(j, q_stride_b, kRowB); }, wave, dma_voff_q);
         }
         if (tid == 0) *redo = 0;

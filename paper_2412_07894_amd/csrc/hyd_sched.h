@@ -208,19 +208,26 @@ __global__ void __launch_bounds__(kPreludeThreads) hyd_schedule_prelude(const in
     build_schedule(cu, nseq, T, second ? tile1 : tile0, second ? sv1 : sv0, lds_lev, kPreludeThreads);
 }
 
-// Query side of an item of the bf16 forward and dQ kernels: 8 waves of 32 rows each, split as 2^LH
-// query heads of one KV head x 256 >> LH rows.  Waves that share 64 rows walk the same key tiles, so
-// with four heads (LH = 2) no wave of a workgroup idles behind the diagonal of another one, and a
-// sequence's last tile pads it to 64 rows instead of 256: a workgroup takes 136 steps of 64 keys
-// instead of 160 for four heads of a 1024-token sequence, 45 instead of 84 for 544 tokens.
-template <int LH>
+// Query side of an item of the bf16 forward and dQ kernels, 32 rows of a head per wave; rows = 256 >> S.
+//   S = 0: 256 rows of one head.
+//   S = 1: 128 rows of one head on four of the eight waves, one per SIMD; the others help with the loads.
+//     For launches with less than a workgroup's worth of work per CU, which last as long as their longest
+//     item: a wave that has its SIMD to itself takes two thirds of the time for a step.
+//   S = 2: 64 rows of four query heads of one KV head.  All waves walk the same key tiles, none idles
+//     behind the diagonal of another one, and a sequence's last tile pads it to 64 rows instead of 256: a
+//     workgroup takes 136 steps of 64 keys instead of 160 for four heads of a 1024-token sequence, 45
+//     instead of 84 for 544 tokens.
+template <int S>
 struct QuerySplit {
-    static constexpr int kRows = 256 >> LH;
-    __device__ __forceinline__ static int head_of(int wave) { return wave >> (3 - LH); }
-    __device__ __forceinline__ static int row_of(int wave) { return 32 * (wave & ((8 >> LH) - 1)); }
+    static_assert(S >= 0 && S <= 2, "whole, half, four heads");
+    static constexpr int kRows = 256 >> S, kLh = S == 2 ? 2 : 0;      // rows; log2 of the heads
+    static constexpr int kTiles = S == 1 ? 2 : 4;                     // 64-row tiles to stage
+    __device__ __forceinline__ static int head_of(int wave) { return S == 2 ? wave >> 1 : 0; }
+    // first row of a wave; that of an idle wave lies behind every sequence
+    __device__ __forceinline__ static int row_of(int wave) { return S == 2 ? 32 * (wave & 1) : (S == 1 && wave >= 4 ? 1 << 30 : 32 * wave); }
     // byte offset of the item's 64-row tile j (tiles by head, then by row) from row 0 of its first head
     __device__ __forceinline__ static uint32_t tile_at(int j, uint32_t row_stride_b, uint32_t row_b) {
-        return (uint32_t)(j >> (2 - LH)) * row_b + (uint32_t)(64 * (j & ((4 >> LH) - 1))) * row_stride_b;
+        return S == 2 ? (uint32_t)j * row_b : (uint32_t)(64 * j) * row_stride_b;
     }
 };
 

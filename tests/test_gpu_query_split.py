@@ -49,11 +49,12 @@ def test_split_heads_equal_repeated_kv_heads(hq, hkv, d, call):
         assert rel < 2.0 ** -8, (name, rel)
 
 
+@pytest.mark.parametrize("copies", [1, 13])
 @pytest.mark.parametrize("max_seqlen", [100, 256, 300, 1000])
-def test_a_bound_below_the_longest_sequence_covers_whole_tiles(max_seqlen):
+def test_a_bound_below_the_longest_sequence_covers_whole_tiles(max_seqlen, copies):
     """A sequence longer than max_seqlen gets its first ceil(max_seqlen / 256) tiles of 256 rows, with
-    split heads as without."""
-    lens, hq, hkv, d = [1000, 40, 256] * 13, 8, 2, 128
+    split heads and half tiles as without."""
+    lens, hq, hkv, d = [1000, 40, 256] * copies, 8, 2, 128
     T = sum(lens)
     cu = torch.from_numpy(wl.cu_seqlens(lens)).cuda()
     g = torch.Generator(device="cuda")
@@ -66,3 +67,30 @@ def test_a_bound_below_the_longest_sequence_covers_whole_tiles(max_seqlen):
     covered = min(1000, -(-max_seqlen // 256) * 256)
     assert torch.equal(o[:covered], full[:covered]) and torch.equal(o[1000:1296], full[1000:1296])
     assert bool((o[covered:1000] == 7.0).all())
+
+
+@pytest.mark.parametrize("hq,hkv,d", [(2, 2, 128), (3, 1, 64), (8, 2, 128)])
+@pytest.mark.parametrize("rope_base", [None, 1e4])
+def test_half_tiles_equal_the_tiles_of_a_larger_batch(hq, hkv, d, rope_base):
+    """A batch below the limit of the 128-row items against the same sequences in a batch far above it."""
+    T = sum(EDGES)
+    copies = 1 + 600000 // (T * hq)
+    g = torch.Generator(device="cuda")
+    g.manual_seed(31)
+    mk = lambda h: torch.randn((T, h, d), device="cuda", generator=g).to(torch.bfloat16)
+    q, k, v, do = mk(hq), mk(hkv), mk(hkv), mk(hq)
+
+    def run(n):
+        lens = EDGES * n
+        cu = torch.from_numpy(wl.cu_seqlens(lens)).cuda()
+        x = [t.repeat(n, 1, 1) for t in (q, k, v, do)]
+        o, lse = binding.varlen_attn_fwd(*x[:3], cu, max(lens), d ** -0.5, rope_base=rope_base)
+        dq, dk, dv = binding.varlen_attn_bwd(*x[:3], o, lse, x[3], cu, max(lens), d ** -0.5, rope_base=rope_base)
+        return o[:T], lse[:, :T], dq[:T], dk[:T], dv[:T]
+
+    small, large = run(1), run(copies)
+    for name, x, y in zip(("o", "lse", "dq"), small, large):
+        assert torch.isfinite(x.float()).all() and torch.equal(x, y), name
+    for name, x, y in zip(("dk", "dv"), small[3:], large[3:]):       # sums in another order, rounded to bf16
+        rel = float((x.double() - y.double()).norm() / y.double().norm())
+        assert rel < 2.0 ** -8, (name, rel)
