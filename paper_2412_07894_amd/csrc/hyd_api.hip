@@ -222,7 +222,9 @@ hyd_status validate_ranges(const int32_t* ranges, const int32_t* ranges_host, co
 // array's name is only a handle for hipGetSymbolAddress: the address kernels and memory calls use
 // is DeviceInfo::scratch, looked up once per device.
 constexpr size_t kScratchBytes = 2u << 20;
-static __device__ __align__(256) unsigned char scratch[kScratchBytes];
+// (the cursors, 256 bytes apart, come on top of what callers size their batches for)
+constexpr size_t kScratchAll = kScratchBytes + sizeof(int) * kQueues * kCursorStride;
+static __device__ __align__(256) unsigned char scratch[kScratchAll];
 
 // ---- per-device state -------------------------------------------------------------------------
 struct DeviceInfo {
@@ -674,10 +676,10 @@ hyd_status hyd_varlen_attn_fwd_noalloc(const void* q, const void* k, const void*
     if (!head_dim_ok(dt, head_dim)) return HYD_ERR_HEADDIM;
     // (if need be with 256-row tiles and without the second copy of the item records)
     const bool compact = fwd_layout(total_tokens, num_seqs, hq, hkv, head_dim, dt, false).total > kScratchBytes;
-    if (compact && fwd_layout(total_tokens, num_seqs, hq, hkv, head_dim, dt, true).total > kScratchBytes) return HYD_ERR_WORKSPACE;
+    if (compact && fwd_layout(total_tokens, num_seqs, hq, hkv, head_dim, dt, true).total > kScratchAll) return HYD_ERR_WORKSPACE;
     // the rest of the argument checks, still before any HIP call (a stand-in for the workspace pointer)
     const hyd_status vs = validate_common(cu_seqlens, num_seqs, cu_seqlens_host, total_tokens, max_seqlen, hq, hkv, head_dim,
-                                          dt, reinterpret_cast<const void*>(kAlign), kScratchBytes, false, compact);
+                                          dt, reinterpret_cast<const void*>(kAlign), kScratchAll, false, compact);
     if (vs != HYD_OK) return vs;
     if (total_tokens == 0 || num_seqs == 0) return HYD_OK;
     if (!q || !k || !v || !o || !lse) return HYD_ERR_NULL;
@@ -685,7 +687,7 @@ hyd_status hyd_varlen_attn_fwd_noalloc(const void* q, const void* k, const void*
     const hyd_status ds = device_info(&dev);          // first call on a device: looks the array's address up
     if (ds != HYD_OK) return ds;
     return fwd_impl(q, k, v, cu_seqlens, num_seqs, cu_seqlens_host, nullptr, nullptr, false, total_tokens, max_seqlen,
-                    hq, hkv, head_dim, softmax_scale, dt, o, lse, dev->scratch, kScratchBytes, hip_stream, 0.f, compact);
+                    hq, hkv, head_dim, softmax_scale, dt, o, lse, dev->scratch, kScratchAll, hip_stream, 0.f, compact);
 }
 
 hyd_status hyd_varlen_attn_bwd(const void* q, const void* k, const void* v, const void* o, const float* lse,

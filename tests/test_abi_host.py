@@ -190,6 +190,21 @@ def test_noalloc_forward_checks_sizes_and_arguments_before_any_hip_call(lib):
     assert call(T=0, nseq=0, q=None, k=None, v=None, cu=None, o=None, lse=None) == 0
 
 
+def test_noalloc_forward_takes_what_fits_two_mebibytes_of_schedule(lib):
+    """256 bytes of header, three level arrays, a rank and a 16-byte record per sequence and 256-row tile,
+    512 bytes for the rotary table: a batch whose schedule takes 2 MiB to the byte is accepted (the NULL query
+    pointer is found, error 1), one more page of records is not."""
+    P, N = ctypes.c_void_p(1 << 20), None
+    lib.hyd_varlen_attn_fwd_noalloc.restype = ctypes.c_int
+    call = lambda n, hq, hkv: lib.hyd_varlen_attn_fwd_noalloc(N, P, P, P, n, N, 1 << 20, 4096, hq, hkv, 128, ctypes.c_float(0.1), 0, P, P, N)
+    up = lambda x: (x + 255) // 256 * 256
+    need = lambda n: 256 + up(12 * (4096 + 2)) + up(4 * n) + up(16 * (4096 + n + 1)) + 512
+    assert need(99071) == 2 << 20
+    for hq, hkv in ((8, 8), (8, 2)):
+        assert call(99071, hq, hkv) == 1
+        assert call(99071 + 64, hq, hkv) == 7
+
+
 def test_schedule_layout_and_status_argument_errors(lib):
     sz, ci = ctypes.c_size_t, ctypes.c_int
     h, it, cap, tile = sz(0), sz(0), ci(0), ci(0)
