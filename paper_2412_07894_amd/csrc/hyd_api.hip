@@ -447,7 +447,7 @@ hyd_status fwd_impl(const void* q, const void* k, const void* v, const int32_t* 
     double* rope_tab = rope_base != 0.f ? reinterpret_cast<double*>(static_cast<char*>(workspace) + w.rope_tab) : nullptr;
     {
         KernelTimer kt("schedule_prelude", st);
-        hipLaunchKernelGGL(hyd_schedule_prelude, dim3(split ? 2 : 1), dim3(kPreludeThreads), schedule_lds_max(sv_whole.n_lev, sv.n_lev), st, cu_seqlens, num_seqs,
+        hipLaunchKernelGGL(hyd_schedule_prelude, dim3(split ? 2 : 1), dim3(kPreludeThreads), schedule_lds(sv_whole.n_lev, sv.n_lev), st, cu_seqlens, num_seqs,
                            total_tokens, tile, sv_whole, tile >> split, sv,
                            rope_tab, head_dim / 2, rope_base != 0.f ? log2((double)rope_base) : 0.0);
     }
@@ -542,7 +542,7 @@ hyd_status bwd_impl(const void* q, const void* k, const void* v, const void* o, 
             pp.sv[0] = sv_kv; pp.sv[1] = sv_whole; pp.sv[2] = sv_q;
             pp.rope_tab = rope_tab; pp.log2_base = rope_tab ? log2((double)rope_base) : 0.0;
             const dim3 grid((unsigned)(pp.n_sched + sc.n_absmax)), block(kPrepThreads);
-            const size_t lds = prep_lds(hq, pp.tok, schedule_lds_max(sv_kv.n_lev, sv_q.n_lev));
+            const size_t lds = prep_lds(hq, pp.tok, schedule_lds(sv_kv.n_lev, sv_whole.n_lev, sv_q.n_lev));
             KernelTimer kt("bwd_prep_bf16", st);
             if (head_dim == 64) {
                 if (ranged) hipLaunchKernelGGL((hyd_bwd_prep_bf16_kernel<true, 64>), grid, block, lds, st, pp);
@@ -605,7 +605,7 @@ hyd_status bwd_impl(const void* q, const void* k, const void* v, const void* o, 
         p.tr = t_trace;
         {   // one launch builds both item lists, one workgroup each
             KernelTimer kt("schedule_prelude", st);
-            hipLaunchKernelGGL(hyd_schedule_prelude, dim3(w.n_sched), dim3(kPreludeThreads), schedule_lds_max(sv_kv.n_lev, sv_q.n_lev), st, cu_seqlens,
+            hipLaunchKernelGGL(hyd_schedule_prelude, dim3(w.n_sched), dim3(kPreludeThreads), schedule_lds(sv_kv.n_lev, sv_q.n_lev), st, cu_seqlens,
                                num_seqs, total_tokens, tile_kv(dt), sv_kv, tile_q(dt), sv_q, nullptr, 0, 0.0);
         }
         const dim3 grid_q(persistent_grid(*dev, occ_q, work_q)), grid_kv(persistent_grid(*dev, occ_kv, work_kv));

@@ -94,3 +94,28 @@ def test_half_tiles_equal_the_tiles_of_a_larger_batch(hq, hkv, d, rope_base):
     for name, x, y in zip(("dk", "dv"), small[3:], large[3:]):       # sums in another order, rounded to bf16
         rel = float((x.double() - y.double()).norm() / y.double().norm())
         assert rel < 2.0 ** -8, (name, rel)
+
+
+def test_lists_with_levels_inside_and_outside_lds():
+    """With max_seqlen = T the lists of 64-row and 128-row tiles have more levels than fit LDS and the list of
+    whole tiles has not; all of them are right, and the bound does not change a bit."""
+    from oracle import sched_oracle as so
+    lens, hq, hkv, d = [640, 511, 769] * 370, 4, 1, 64
+    T, code = sum(lens), binding.HYD_BF16
+    assert 4096 * 128 < T < 4096 * 256
+    cu = torch.from_numpy(wl.cu_seqlens(lens)).cuda()
+    g = torch.Generator(device="cuda")
+    g.manual_seed(37)
+    mk = lambda h: torch.randn((T, h, d), device="cuda", generator=g, dtype=torch.float32).to(torch.bfloat16)
+    q, k, v, do = mk(hq), mk(hkv), mk(hkv), mk(hq)
+    size = binding.workspace_bytes(T, len(lens), hq, hkv, d, code, 1)
+    out = []
+    for bound in (T, max(lens)):
+        ws = torch.empty(size, dtype=torch.uint8, device="cuda")
+        o, lse = binding.varlen_attn_fwd(q, k, v, cu, bound, d ** -0.5)
+        out.append((o, lse) + tuple(binding.varlen_attn_bwd(q, k, v, o, lse, do, cu, bound, d ** -0.5, workspace=ws)))
+        for which in (0, 1):
+            tile, rec = binding.schedule_items(ws, T, len(lens), hq, hkv, d, code, 1, which)
+            assert sorted(map(tuple, rec.tolist())) == sorted(so.records(lens, tile)), (bound, which)
+    for x, y in zip(*out):
+        assert torch.equal(x, y)
