@@ -357,8 +357,9 @@ SchedView make_view(char* ws, const SchedLayout& v, int tile, int split, int max
 // heads, 1.05 shares: 1068 -> 1083).
 // Measured (log-normal lengths, dK/dV + adding pass in us, before -> now): 8/1 heads, 8192 tokens 650 ->
 // 123; 16/2 heads, 8192 tokens 666 -> 233, 32768 tokens 1428 -> 820; 8/1 heads, one sequence of 16384
-// tokens 3070 -> 1262; 32/8 heads, 1024 tokens 98 -> 42 to 54, 2048 tokens 115 -> 65 to 76, 4096 tokens 307 -> 229, 8192
-// tokens 415 -> 406.  kPartSteps 12 / 24 / 40: 1024 tokens 43 / 54 / 74, 2048 tokens 76 / 65 / 81.
+// tokens 3070 -> 1262; 32/8 heads, 512 tokens 54 -> 41, 1024 tokens 98 -> 47, 2048 tokens 115 -> 78, 4096 tokens 307 -> 221,
+// 8192 tokens 415 -> 406.  kPartSteps 12 / 16 / 24 / 40: 512 tokens 36 / 41 / 50 / 54, 1024 tokens 43 / 47 / 54 / 74, 2048 tokens 76 /
+// 78 / 65 / 81; with 12 a batch of 8/8 heads and 2048 tokens is cut too, for nothing (37 -> 37).
 constexpr int kPartSteps = 16;
 void set_parts(SchedView& sv, int limit, int T, int nseq, int max_seqlen, int hq, int hkv, int wgs) {
     sv.steps_per_level = kKvBN / kKvBM * (hq / hkv);
