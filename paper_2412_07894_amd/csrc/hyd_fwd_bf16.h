@@ -174,7 +174,8 @@ __device__ __forceinline__ void fwd_tile(int Kt, int Vt, const FragAddr& fa, con
 #pragma unroll
             for (int r = 0; r < 16; ++r) big = max(big, __float_as_uint(acc_o[db][r]) & 0x7fffffffu);
         if (big >= 0x7f800000u) overflow = true;
-        const int k = e > 127u && big < 0x7f800000u ? (int)e - 127 : 0;
+        // (126 at most: 2^-126 is the smallest power of two with an exponent of its own, and leaves l below 4)
+        const int k = e > 127u && big < 0x7f800000u ? min((int)e - 127, 126) : 0;
         const float alpha = __uint_as_float((uint32_t)(127 - k) << 23);
         l_run *= alpha;
         m_ref += (float)k;

@@ -4,9 +4,10 @@ back), by so much that a probability overflows (the item is repeated with the tr
 any tile, also the diagonal one, and next to rows and heads where nothing happens."""
 import numpy as np
 import pytest
+import torch
 
 from oracle import attn_oracle as orc
-from paper_2412_07894_amd import workloads as wl
+from paper_2412_07894_amd import binding, workloads as wl
 import gpu_util as gu
 
 pytestmark = pytest.mark.gpu
@@ -28,3 +29,34 @@ def test_scores_that_rise_after_the_first_tile(gain, first_key, d):
     # LSE is as large as the scores here: fp32 sums of d products of that size
     tol = max(2e-2, 2.0 ** -23 * np.sqrt(d) * np.max(np.abs(lse)) * 4)
     assert np.max(np.abs(got["lse"] - lse)) <= tol
+
+
+def forward(lengths, q, k, v, scale):
+    """Forward over bf16-exact float32 inputs: O and LSE as float64, then the oracle's."""
+    cu = wl.cu_seqlens(lengths)
+    for x in (q, k, v):
+        assert np.array_equal(x, wl.bf16_bits_to_f32(wl.f32_to_bf16_bits(x))), "inputs are bf16 values"
+    dev = [gu.to_dev(x, "bf16") for x in (q, k, v)]
+    o, lse = binding.varlen_attn_fwd(*dev, torch.from_numpy(cu).cuda(), max(lengths), scale)
+    return gu.to_np(o), gu.to_np(lse), *orc.fwd(q, k, v, cu, float(np.float32(scale)))
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("key,L", [(100, 128), (100, 192), (100, 700), (300, 700)])     # in the row's last tile, in an earlier one
+@pytest.mark.parametrize("rise", [100.0, 126.0, 126.5, 127.0, 127.5, 127.99, 128.5, 200.0])
+def test_one_key_far_above_the_first_tile(rise, key, L, d):
+    """One key scores `rise` (log2 units) above all others, which score 0, with V of at most 0.5: the row sum runs up
+    to the largest finite values and O with it.  The row is that key's V from then on."""
+    hq, hkv, scale = 4, 2, d ** -0.5
+    rng = np.random.default_rng(5)
+    q, k = np.zeros((L, hq, d), np.float32), np.zeros((L, hkv, d), np.float32)
+    v = wl.bf16_bits_to_f32(wl.f32_to_bf16_bits(rng.uniform(-0.5, 0.5, (L, hkv, d)).astype(np.float32)))
+    q[:, :, :3] = 16.0
+    want = rise / (16.0 * scale * np.log2(np.e))
+    for c in range(3):                                     # three bf16 pieces: the score is right to 2^-16
+        k[key, 0, c] = wl.bf16_bits_to_f32(wl.f32_to_bf16_bits(np.array([want], np.float32)))[0]
+        want -= float(k[key, 0, c])
+    o, lse, ro, rlse = forward([L], q, k, v, scale)
+    assert abs(rlse[0, key] * np.log2(np.e) - rise) < 2e-3
+    gu.check("o", o, ro, "bf16")
+    assert np.max(np.abs(lse - rlse)) <= 2e-2
