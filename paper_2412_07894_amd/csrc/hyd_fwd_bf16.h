@@ -20,9 +20,9 @@
 // row maximum is taken over the FIRST tile only, and later tiles are not searched for a larger
 // score (16 three-way maxima and an exchange per tile and wave, 6 % of the kernel): what a larger
 // score does to the row sum l is looked at afterwards.  When l has passed 2^kRefSlack, O and l are
-// scaled back by a power of two and m_ref moves up by its exponent, exactly.  A score more than about
-// 100 (log2 units) above everything before it overflows on the spot; the check finds O or l
-// non-finite then, and the workgroup repeats the item with m_ref set to the true row maximum, from a
+// scaled back by a power of two and m_ref moves up by its exponent (beyond 2^24, where a float no longer
+// holds every integer, by what it can, and O and l by as much).  A probability or an O that reaches 2^128
+// overflows on the spot; the check finds O or l non-finite then, and the workgroup repeats the item with m_ref set to the true row maximum, from a
 // pass over the scores.  Measured (forward, MI355X): 131072 tokens, 40 heads, d = 128,
 // 12.65 -> 12.37 ms; 32768 tokens, 32 heads, d = 64, 1.089 -> 1.033 ms.  Starting the exponentials of key
 // block 0 under the score product of block 1, which no longer has to wait for a maximum, is 1.5-4 %
@@ -173,12 +173,15 @@ __device__ __forceinline__ void fwd_tile(int Kt, int Vt, const FragAddr& fa, con
         for (int db = 0; db < NDB; ++db)
 #pragma unroll
             for (int r = 0; r < 16; ++r) big = max(big, __float_as_uint(acc_o[db][r]) & 0x7fffffffu);
-        if (big >= 0x7f800000u) overflow = true;
-        // (126 at most: 2^-126 is the smallest power of two with an exponent of its own, and leaves l below 4)
-        const int k = e > 127u && big < 0x7f800000u ? min((int)e - 127, 126) : 0;
-        const float alpha = __uint_as_float((uint32_t)(127 - k) << 23);
+        // O and l are scaled by what the reference moves: by 2^-k, unless m_ref is so large that it holds no such
+        // sum.  2^-126 is the smallest power of two with an exponent of its own; more is left to the repeat.
+        const int k = e > 127u ? min((int)e - 127, 126) : 0;
+        const float m_new = m_ref + (float)k, moved = m_new - m_ref;
+        const bool ok = big < 0x7f800000u && moved <= 126.f;
+        const float alpha = ok ? __builtin_amdgcn_exp2f(-moved) : 1.f;
+        if (!ok) overflow = true;
         l_run *= alpha;
-        m_ref += (float)k;
+        m_ref = ok ? m_new : m_ref;
 #pragma unroll
         for (int db = 0; db < NDB; ++db)
 #pragma unroll

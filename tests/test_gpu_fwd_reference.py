@@ -60,3 +60,21 @@ def test_one_key_far_above_the_first_tile(rise, key, L, d):
     assert abs(rlse[0, key] * np.log2(np.e) - rise) < 2e-3
     gu.check("o", o, ro, "bf16")
     assert np.max(np.abs(lse - rlse)) <= 2e-2
+
+
+@pytest.mark.parametrize("d", [64, 128])
+def test_scores_beyond_the_integers_of_a_float(d):
+    """Scores of 2^26 (log2 units), where a float holds every eighth integer: three keys 24 above the first tile with
+    V = 0.5, three more of the same score in the tile after with V = -0.5, so O is 0 from there on.  The reference can
+    only move by what it holds, and O and l have to be scaled by exactly that."""
+    L, hq, hkv = 256, 2, 1
+    scale = float(np.float32(np.log(2.0)))
+    q, k = np.zeros((L, hq, d), np.float32), np.zeros((L, hkv, d), np.float32)
+    v = np.zeros((L, hkv, d), np.float32)
+    q[:, :, 0], q[:, :, 1] = 2.0 ** 13, 8.0
+    k[:, 0, 0] = 2.0 ** 13
+    for at, val in ((64, 0.5), (128, -0.5)):
+        k[at:at + 3, 0, 1] = 3.0
+        v[at:at + 3] = val
+    o, _, ro, _ = forward([L], q, k, v, scale)
+    assert np.max(np.abs(o[131:] - ro[131:])) <= 2e-2 and np.max(np.abs(ro[131:])) < 1e-4
