@@ -22,8 +22,10 @@
 // score does to the row sum l is looked at afterwards.  When l has passed 2^kRefSlack, O and l are
 // scaled back by a power of two and m_ref moves up by its exponent (beyond 2^24, where a float no longer
 // holds every integer, by what it can, and O and l by as much).  A probability or an O that reaches 2^128
-// overflows on the spot; the check finds O or l non-finite then, and the workgroup repeats the item with m_ref set to the true row maximum, from a
-// pass over the scores.  Measured (forward, MI355X): 131072 tokens, 40 heads, d = 128,
+// overflows on the spot; the checks there and, for sums between 2^8 and 2^24, behind the item's last tile find O or l
+// non-finite then, and the workgroup repeats the item with m_ref set to the true row maximum, from a
+// pass over the scores.  (No probability exceeds a sum below 2^8: O cannot overflow but for the last
+// bits of V's range.)  Measured (forward, MI355X): 131072 tokens, 40 heads, d = 128,
 // 12.65 -> 12.37 ms; 32768 tokens, 32 heads, d = 64, 1.089 -> 1.033 ms.  Starting the exponentials of key
 // block 0 under the score product of block 1, which no longer has to wait for a maximum, is 1.5-4 %
 // slower than this order.
@@ -55,6 +57,7 @@ __device__ __forceinline__ constexpr int fwd_q_stage_off(int j) {
     return j < 2 ? kFwdQxOff + j * kFwdTileBytes : (kFwdStages - 1) * kFwdStageBytes + (j - 2) * kFwdTileBytes;
 }
 constexpr float kRefSlack = 16777216.f;                           // 2^24, see "Reference"
+constexpr float kRefQuiet = 256.f;
 
 struct FwdParams {
     const uint16_t* q; const uint16_t* k; const uint16_t* v;
@@ -69,6 +72,18 @@ struct FwdParams {
 };
 
 typedef __attribute__((address_space(3))) void lds_void;
+
+// Largest magnitude as a bit pattern; non-finite values have all exponent bits set.
+constexpr uint32_t kInfBits = 0x7f800000u;
+template <int N>
+__device__ __forceinline__ uint32_t largest_bits(const f32x16 (&a)[N]) {
+    uint32_t big = 0;
+#pragma unroll
+    for (int i = 0; i < N; ++i)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) big = max(big, __float_as_uint(a[i][r]) & 0x7fffffffu);
+    return big;
+}
 
 // One 64-key tile for the 32 rows of a wave.  There is ONE body for all tiles (separate bodies for
 // masked and unmasked tiles make the compiler keep the accumulators twice and copy them at every
@@ -168,16 +183,12 @@ __device__ __forceinline__ void fwd_tile(int Kt, int Vt, const FragAddr& fa, con
         float lo, hi;
         both_halves(l_run, lo, hi);                    // O is shared by the halves of a row, so its scale is too
         const uint32_t e = __float_as_uint(fmaxf(lo, hi)) >> 23;       // l > 0: biased exponent
-        uint32_t big = e << 23;                        // non-finite values have all exponent bits set
-#pragma unroll
-        for (int db = 0; db < NDB; ++db)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) big = max(big, __float_as_uint(acc_o[db][r]) & 0x7fffffffu);
+        const uint32_t big = max(e << 23, largest_bits(acc_o));
         // O and l are scaled by what the reference moves: by 2^-k, unless m_ref is so large that it holds no such
         // sum.  2^-126 is the smallest power of two with an exponent of its own; more is left to the repeat.
         const int k = e > 127u ? min((int)e - 127, 126) : 0;
         const float m_new = m_ref + (float)k, moved = m_new - m_ref;
-        const bool ok = big < 0x7f800000u && moved <= 126.f;
+        const bool ok = big < kInfBits && moved <= 126.f;
         const float alpha = ok ? __builtin_amdgcn_exp2f(-moved) : 1.f;
         if (!ok) overflow = true;
         l_run *= alpha;
@@ -333,7 +344,6 @@ __global__ void __launch_bounds__(kFwdThreads, 1) hyd_fwd_bf16_kernel(FwdParams 
                 if (active && t <= td)
                     fwd_tile<D>(Kt, Vt, fa, qf, acc_o, m_ref, l_run, scale_log2, t * kFwdBN + koff0, t == td,
                                 pass == 1 || (pass == 0 && t == t_lo), overflow);
-                if (!more2 && __any(overflow)) *redo = 1;                               // seen by all behind the last barrier
                 if (more2) __builtin_amdgcn_s_waitcnt(0x0070 | (kDmaPerTile & 15));     // vmcnt(kDmaPerTile), lgkmcnt(0)
                 else __builtin_amdgcn_s_waitcnt(0x0070);                                // vmcnt(0), lgkmcnt(0)
                 __builtin_amdgcn_s_barrier();
@@ -343,6 +353,10 @@ __global__ void __launch_bounds__(kFwdThreads, 1) hyd_fwd_bf16_kernel(FwdParams 
                 if (t + 1 < n_kt) step(std::integral_constant<int, 1>{}, t + 1);
                 if (t + 2 < n_kt) step(std::integral_constant<int, 2>{}, t + 2);
             }
+            // (behind the loop, with a barrier of its own: in the last step it cost the long items 1 %)
+            if (__any(l_run > kRefQuiet)) overflow |= largest_bits(acc_o) >= kInfBits;
+            if (__any(overflow)) *redo = 1;
+            __syncthreads();
             if (__builtin_expect(pass == 0 ? *redo == 0 : pass == 2, 1)) break;
             ++pass;
             __syncthreads();

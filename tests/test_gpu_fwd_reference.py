@@ -78,3 +78,19 @@ def test_scores_beyond_the_integers_of_a_float(d):
         v[at:at + 3] = val
     o, _, ro, _ = forward([L], q, k, v, scale)
     assert np.max(np.abs(o[131:] - ro[131:])) <= 2e-2 and np.max(np.abs(ro[131:])) < 1e-4
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("key,L", [(100, 128), (100, 300), (299, 300)])
+def test_large_values_times_a_large_probability(key, L, d):
+    """V of 2^105 and one key 23.5 (log2 units) above all others: O passes the largest float while the row sum
+    stays below the limit from which it is scaled back.  O itself is no larger than V."""
+    hq, hkv, scale = 4, 2, d ** -0.5
+    rng = np.random.default_rng(6)
+    q, k = np.zeros((L, hq, d), np.float32), np.zeros((L, hkv, d), np.float32)
+    unit = wl.bf16_bits_to_f32(wl.f32_to_bf16_bits(rng.uniform(0.75, 1.0, (L, hkv, d)).astype(np.float32)))
+    q[:, :, 0] = 16.0
+    k[key, 0, 0] = wl.bf16_bits_to_f32(wl.f32_to_bf16_bits(np.array([23.5 / (16.0 * scale * np.log2(np.e))], np.float32)))[0]
+    o, lse, ro, rlse = forward([L], q, k, unit * np.float32(2.0 ** 105), scale)
+    gu.check("o / 2^105", o * 2.0 ** -105, ro * 2.0 ** -105, "bf16")
+    assert np.max(np.abs(lse - rlse)) <= 2e-2
