@@ -23,8 +23,13 @@
 // scaled back by a power of two and m_ref moves up by its exponent (beyond 2^24, where a float no longer
 // holds every integer, by what it can, and O and l by as much).  A probability or an O that reaches 2^128
 // overflows on the spot; the checks there and, for sums between 2^8 and 2^24, behind the item's last tile find O or l
-// non-finite then, and the workgroup repeats the item with m_ref set to the true row maximum, from a
-// pass over the scores.  (No probability exceeds a sum below 2^8: O cannot overflow but for the last
+// non-finite then, and the workgroup repeats the item with care: every tile is searched, and where a
+// row's maximum exceeds m_ref by more than 8, O and l are rescaled before the exponentials.  A wave
+// goes on with care from its first tile on if the scores of a row there are more than kRefSpread apart: later
+// ones are bound to rise then (of 131072 normal scores the largest is 0.45 of the spread of the first 64
+// above their maximum, 72 for a spread of 160: this side of that nothing overflows).  Measured, 4 x 4096 tokens, 32
+// heads, scores of standard deviation 100 / 40 / 16 nats: 547 / 558 / 584 us; without the look at the spread 1140 /
+// 930 / 583; with the maximum of every tile of every item 553 / 561 / 586.  (No probability exceeds a sum below 2^8: O cannot overflow but for the last
 // bits of V's range.)  Measured (forward, MI355X): 131072 tokens, 40 heads, d = 128,
 // 12.65 -> 12.37 ms; 32768 tokens, 32 heads, d = 64, 1.089 -> 1.033 ms.  Starting the exponentials of key
 // block 0 under the score product of block 1, which no longer has to wait for a maximum, is 1.5-4 %
@@ -35,6 +40,8 @@
 // masked).  A wave's diagonal tile is its last, and every tile it computes holds at least one
 // visible key for every row, so row maxima are finite.
 #pragma once
+#include <limits.h>
+
 #include <type_traits>
 
 #include "hyd_sched.h"
@@ -57,7 +64,8 @@ __device__ __forceinline__ constexpr int fwd_q_stage_off(int j) {
     return j < 2 ? kFwdQxOff + j * kFwdTileBytes : (kFwdStages - 1) * kFwdStageBytes + (j - 2) * kFwdTileBytes;
 }
 constexpr float kRefSlack = 16777216.f;                           // 2^24, see "Reference"
-constexpr float kRefQuiet = 256.f;
+constexpr float kRefQuiet = 256.f;                                // 2^kRefStep
+constexpr float kRefStep = 8.f, kRefSpread = 160.f;               // log2 units
 
 struct FwdParams {
     const uint16_t* q; const uint16_t* k; const uint16_t* v;
@@ -93,7 +101,8 @@ __device__ __forceinline__ uint32_t largest_bits(const f32x16 (&a)[N]) {
 template <int D>
 __device__ __forceinline__ void fwd_tile(int Kt, int Vt, const FragAddr& fa, const bf16x8 (&qf)[D / 16],
                                          f32x16 (&acc_o)[D / 32], float& m_ref, float& l_run, float scale_log2,
-                                         int koff, bool diag, bool find_max, bool& overflow) {
+                                         int koff, bool diag, int t, int& t_find, bool& overflow) {
+    // t_find: the wave's last tile that is searched for row maxima, the first one unless it works with care
     constexpr int NK = D / 16, NDB = D / 32;
     // The instruction order below is pinned with scheduling fences: left alone, the compiler sinks
     // every LDS read next to its use and serialises read -> wait -> MFMA.
@@ -135,17 +144,34 @@ __device__ __forceinline__ void fwd_tile(int Kt, int Vt, const FragAddr& fa, con
             for (int r = 0; r < 16; ++r)
                 if (32 * kb + 8 * (r >> 2) + (r & 3) + k0 > 0) s[kb][r] = -INFINITY;
     }
-    if (find_max) {
+    if (t <= t_find) {
         // row maximum of the raw scores (a negative softmax scale has been folded into the sign of
         // the Q fragments, so the largest raw score is the largest scaled score)
-        float mx = s[0][0];
+        float mx = s[0][0], lo, hi;
 #pragma unroll
         for (int kb = 0; kb < 2; ++kb)
 #pragma unroll
             for (int r = 0; r < 16; ++r) mx = fmaxf(mx, s[kb][r]);
-        float lo, hi;
         both_halves(mx, lo, hi);
-        m_ref = fmaxf(m_ref, fmaxf(lo, hi) * scale_log2);
+        const float cand = fmaxf(lo, hi) * scale_log2;
+        if (t == t_find) {
+            m_ref = cand;
+            float mn = s[0][0];
+#pragma unroll
+            for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) mn = fminf(mn, s[kb][r]);
+            if (__any(cand - mn * scale_log2 > kRefSpread)) t_find = INT_MAX;
+        } else if (__any(cand > m_ref + kRefStep)) {
+            const float m_new = fmaxf(m_ref, cand);
+            const float alpha = __builtin_amdgcn_exp2f(m_ref - m_new);
+            l_run *= alpha;
+#pragma unroll
+            for (int db = 0; db < NDB; ++db)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) acc_o[db][r] *= alpha;
+            m_ref = m_new;
+        }
     }
     // P V: the exponentials of key step b+1 (8 scores) issue under the NDB MFMAs of step b (two
     // scores per MFMA for D = 128, four for D = 64); V fragments are read kVAhead MFMAs ahead.
@@ -321,11 +347,11 @@ __global__ void __launch_bounds__(kFwdThreads, 1) hyd_fwd_bf16_kernel(FwdParams 
         __builtin_amdgcn_s_barrier();                     // the staged Q may be overwritten (tile t_lo+2 goes there)
 
         f32x16 acc_o[D / 32];
-        float m_ref = -INFINITY, l_run;
+        float m_ref, l_run;
         bool overflow = false;
-        int pass = 0;            // 0: reference from the first tile; after an overflow 1: row maxima of all tiles, 2: with those
+        int t_find = t_lo;       // last tile that is searched for row maxima
         while (true) {
-            if (pass == 1) m_ref = -INFINITY;
+            m_ref = -INFINITY;
             l_run = 0.f;
 #pragma unroll
             for (int db = 0; db < D / 32; ++db)
@@ -343,7 +369,7 @@ __global__ void __launch_bounds__(kFwdThreads, 1) hyd_fwd_bf16_kernel(FwdParams 
                 if (more2) dma_tile(t + 2, ST2);
                 if (active && t <= td)
                     fwd_tile<D>(Kt, Vt, fa, qf, acc_o, m_ref, l_run, scale_log2, t * kFwdBN + koff0, t == td,
-                                pass == 1 || (pass == 0 && t == t_lo), overflow);
+                                t, t_find, overflow);
                 if (more2) __builtin_amdgcn_s_waitcnt(0x0070 | (kDmaPerTile & 15));     // vmcnt(kDmaPerTile), lgkmcnt(0)
                 else __builtin_amdgcn_s_waitcnt(0x0070);                                // vmcnt(0), lgkmcnt(0)
                 __builtin_amdgcn_s_barrier();
@@ -355,10 +381,10 @@ __global__ void __launch_bounds__(kFwdThreads, 1) hyd_fwd_bf16_kernel(FwdParams 
             }
             // (behind the loop, with a barrier of its own: in the last step it cost the long items 1 %)
             if (__any(l_run > kRefQuiet)) overflow |= largest_bits(acc_o) >= kInfBits;
-            if (__any(overflow)) *redo = 1;
+            if (t_find == t_lo && __any(overflow)) *redo = 1;
             __syncthreads();
-            if (__builtin_expect(pass == 0 ? *redo == 0 : pass == 2, 1)) break;
-            ++pass;
+            if (__builtin_expect(*redo == 0, 1)) break;
+            t_find = INT_MAX;
             __syncthreads();
             if (tid == 0) *redo = 0;
             dma_tile(t_lo, 0);
