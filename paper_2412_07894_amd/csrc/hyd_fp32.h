@@ -447,8 +447,8 @@ __global__ void __launch_bounds__(64 * kF32KvWaves, 1) hyd_bwd_dkdv_fp32_kernel(
             if (it == max(n_iter - 2, 0)) wf.claim(p.hm, p.cursors);
             const int i0 = ti + 32 * split;
             const bool work = i0 < L;
-            // statistics of the block's rows (register r: row i0 + 8 (r / 4) + 4 half + r % 4; past the
-            // sequence any finite value will do: Q and dO are zero there)
+            // statistics of the block's rows (register r: row i0 + 8 (r / 4) + 4 half + r % 4); rows past the
+            // sequence repeat its last one and are masked below, as exp(-LSE) need not be finite
             float nl[16], nd[16];
             if (work) {
                 const int64_t at = (int64_t)(g * G + hh) * p.T + row0;
@@ -466,13 +466,20 @@ __global__ void __launch_bounds__(64 * kF32KvWaves, 1) hyd_bwd_dkdv_fp32_kernel(
             if (work) {
                 f32_row_product(s[0], fl, 0, kr);
                 f32_row_product(dp[0], fl, kT, vr);
-                const int rel = j - i0 - 4 * half;               // register r is visible iff its row offset >= rel
+                // register r is visible iff its row offset is in [rel, end): from the key on, inside the sequence
+                const int rel = j - i0 - 4 * half, end = L - i0 - 4 * half;
+                const bool part = i0 == j0 || i0 + 32 > L;       // else the whole block is
 #pragma unroll
                 for (int r = 0; r < 16; ++r) {
+                    const int row = 8 * (r >> 2) + (r & 3);
                     float pr = f32_exp(__builtin_fmaf(p.scale, s[0][r], -nl[r]));
-                    if (i0 == j0) pr = 8 * (r >> 2) + (r & 3) >= rel ? pr : 0.f;       // the diagonal block
+                    float ds = pr * (dp[0][r] - nd[r]);
+                    if (part) {
+                        pr = row >= rel && row < end ? pr : 0.f;
+                        ds = row >= rel && row < end ? ds : 0.f;
+                    }
                     s[0][r] = pr;
-                    dp[0][r] = pr * (dp[0][r] - nd[r]);
+                    dp[0][r] = ds;
                 }
                 f32_col_product(acck, fl, 0, dp[0]);
             }
