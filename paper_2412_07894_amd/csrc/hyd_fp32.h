@@ -137,12 +137,12 @@ __device__ __forceinline__ void f32_col_product(f32x16 (&acc)[D / 32], const F32
     }
 }
 // exp(x) to fp32 accuracy: x log2(e) is formed as hi + lo (lo from the rounding error of the product and
-// the rest of the constant), 2^hi by the hardware instruction, 2^lo = 1 + lo ln(2).  Finite x only: a
-// hidden score is kF32Hidden, whose exponential is 0.
-constexpr float kF32Hidden = -1e30f;
+// the rest of the constant), 2^hi by the hardware instruction, 2^lo = 1 + lo ln(2).  Down to x = -inf, where
+// lo would not be a number (hence the maximum, which keeps a NaN); not for x above 88.7, which no visible pair has.
 __device__ __forceinline__ float f32_exp(float x) {
     constexpr float kL2e = 1.44269504088896340736f, kL2eRest = 1.44269504088896340736 - (double)kL2e;
     constexpr float kLn2 = 0.69314718055994530942f;
+    x = __builtin_elementwise_maximum(x, -200.f);
     const float hi = x * kL2e;
     const float lo = __builtin_fmaf(x, kL2eRest, __builtin_fmaf(x, kL2e, -hi));
     const float e = __builtin_amdgcn_exp2f(hi);
@@ -236,7 +236,7 @@ __global__ void __launch_bounds__(64 * kF32Waves, 1) hyd_fwd_fp32_kernel(F32Para
         fl.load(rv, smem + kT, 0, stride_b);
         f32x16 o[NDB];
         f32_zero(o);
-        float m = kF32Hidden, l = 0.f;
+        float m = -INFINITY, l = 0.f;
         for (int t = 0; t < n_kt; ++t) {
             const uint32_t nxt = (uint32_t)(t + 1) * kF32Tile * stride_b;
             const bool more = t + 1 < n_kt;
@@ -256,7 +256,7 @@ __global__ void __launch_bounds__(64 * kF32Waves, 1) hyd_fwd_fp32_kernel(F32Para
                 if (key0 == wrow0) {                             // the diagonal block
 #pragma unroll
                     for (int r = 0; r < 16; ++r)
-                        if (8 * (r >> 2) + (r & 3) > rel) s[0][r] = kF32Hidden;
+                        if (8 * (r >> 2) + (r & 3) > rel) s[0][r] = -INFINITY;
                 }
                 float mx = s[0][0];
 #pragma unroll
@@ -264,11 +264,13 @@ __global__ void __launch_bounds__(64 * kF32Waves, 1) hyd_fwd_fp32_kernel(F32Para
                 float lo, hi;
                 both_halves(mx, lo, hi);
                 const float m_new = fmaxf(m, fmaxf(lo, hi));
-                const float alpha = f32_exp(m - m_new);
+                // (a row that has seen no score but -inf yet: every probability is 0)
+                const float ref = m_new == -INFINITY ? 0.f : m_new;
+                const float alpha = f32_exp(m - ref);
                 m = m_new;
                 float sum = 0.f;
 #pragma unroll
-                for (int r = 0; r < 16; ++r) { s[0][r] = f32_exp(s[0][r] - m); sum += s[0][r]; }
+                for (int r = 0; r < 16; ++r) { s[0][r] = f32_exp(s[0][r] - ref); sum += s[0][r]; }
                 l = l * alpha + sum;
                 if (__any(alpha != 1.f)) {
 #pragma unroll
@@ -295,7 +297,7 @@ __global__ void __launch_bounds__(64 * kF32Waves, 1) hyd_fwd_fp32_kernel(F32Para
         ml[wave * 128 + 64 + lane] = l;
         __syncthreads();
         if (split == 0 && wrow0 < L) {
-            float mt = m, lt = 0.f;                              // finite: split 0 saw key 0
+            float mt = m, lt = 0.f;                              // (a split that saw no key has m = -inf and l = 0)
 #pragma unroll
             for (int x = 1; x < kF32Splits; ++x) mt = fmaxf(mt, ml[(2 * x + rg) * 128 + lane]);
             float w = f32_exp(m - mt);

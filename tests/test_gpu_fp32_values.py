@@ -1,5 +1,5 @@
-"""fp32 kernels on what unit-normal inputs never show: rows whose scores are strongly negative, and buffers
-that are only aligned to a float."""
+"""fp32 kernels on what unit-normal inputs never show: rows whose scores are strongly negative,
+scores of -inf or below every finite mask value, and buffers that are only aligned to a float."""
 import numpy as np
 import pytest
 import torch
@@ -37,6 +37,35 @@ def test_last_row_with_strongly_negative_scores(low, L, d):
         print(f"{name}: max-abs {max_abs:.2e} rel-L2 {rel:.2e}", flush=True)
         # a score of size |low| is a sum of d products: 2^-24 |low| sqrt(d) of absolute error in the exponent of P
         assert np.all(np.isfinite(got[name])) and rel <= 1e-5 + 2.0 ** -23 * abs(low) * np.sqrt(d), name
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("at", [20, 40, 130])
+def test_a_score_of_minus_infinity_is_a_probability_of_zero(at, d):
+    """q . k overflows to -inf for one key: that key is not attended to."""
+    L, hq, hkv, scale = 200, 2, 1, d ** -0.5
+    cu, q, k, v, do = wl.custom([L], hq, hkv, d, "fp32", seed=32)
+    q[:, :, 0], k[:, :, 0] = 1e30, 0.0
+    k[at, :, 0] = -1e30
+    got = run([L], q, k, v, do, scale)
+    o, lse = orc.fwd(q, k, v, cu, scale)
+    dq, dk, dv = orc.bwd(q, k, v, do, cu, scale)
+    for name, x, ref in (("o", got["o"], o), ("lse", got["lse"], lse), ("dq", got["dq"][:, :, 1:], dq[:, :, 1:]), ("dv", got["dv"], dv)):
+        assert np.all(np.isfinite(x)) and gu.errors(x, ref)[1] <= 1e-5, name
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("score", [-1e31, -1e38])
+def test_scores_below_any_mask_value(score, d):
+    """All scores equal and hugely negative: every row is the mean of the V up to it."""
+    L, hq, hkv = 100, 2, 1
+    cu, q, k, v, do = wl.custom([L], hq, hkv, d, "fp32", seed=33)
+    q[:], k[:] = 0.0, 0.0
+    q[:, :, 0], k[:, :, 0] = score, 1.0
+    dev = [torch.from_numpy(x).cuda() for x in (q, k, v)]
+    o, lse = binding.varlen_attn_fwd(*dev, torch.from_numpy(cu).cuda(), L, 1.0)
+    ro, rlse = orc.fwd(q, k, v, cu, 1.0)
+    assert gu.errors(gu.to_np(o), ro)[1] <= 1e-5 and gu.errors(gu.to_np(lse), rlse)[1] <= 1e-5
 
 
 @pytest.mark.parametrize("d", [64, 128])
