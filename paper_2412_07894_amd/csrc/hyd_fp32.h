@@ -18,6 +18,8 @@
 //   one sequence of 8192, 16 heads, d = 128          109 / 120 / 98 TFLOP/s of useful products
 //                                                    (a large fp32 library product: 151)
 #pragma once
+#include <float.h>
+
 #include "hyd_sched.h"
 
 namespace hyd {
@@ -26,7 +28,7 @@ constexpr int kF32BM = 64, kF32KvBN = 32;        // rows of an item: forward and
 constexpr int kF32Splits = 4, kF32Tile = 32 * kF32Splits;      // rows of a streamed tile, a 32-row block for each split
 constexpr int kF32Waves = 8, kF32KvWaves = 4;
 template <int D> constexpr int f32_tile_bytes() { return kF32Tile * D * 4; }
-template <int D> constexpr int f32_lds() { return 2 * f32_tile_bytes<D>() + 64; }       // two operand tiles + work slot
+template <int D> constexpr int f32_lds() { return 2 * f32_tile_bytes<D>() + 128; }      // two operand tiles, work slot, repeat flag
 
 struct F32Params {
     const float* q; const float* k; const float* v; const float* o; const float* d_o;
@@ -207,6 +209,167 @@ __device__ __forceinline__ void f32_release() {
     asm volatile("" ::: "memory");
 }
 
+// ---- one row at a time
+//
+// Infinities and NaN.  A product over tile rows takes a hidden pair as 0 * x, which is none if x is not finite: a bad row of
+// the streamed side would reach all 32 lanes of the block where some lanes see it and others do not (the
+// diagonal one, and in dK/dV the one that runs past the sequence).  The tile loop does not look for that.  At the end of an
+// item, a wave whose sums are not finite looks at those blocks, and if there is a bad row among them the
+// workgroup takes the rows of the item again, pair by pair, visible pairs only.
+//
+// The functions below take one row: the wave's lanes hold its elements, D / 64 each, and the other side's rows follow one after
+// the other, kU in flight.
+template <int D> struct F32Part { float v[D / 64]; };
+template <int D>
+__device__ __forceinline__ F32Part<D> f32_part(const float* row, int lane) {
+    F32Part<D> x;
+#pragma unroll
+    for (int e = 0; e < D / 64; ++e) x.v[e] = row[64 * e + lane];
+    return x;
+}
+template <int D>
+__device__ __forceinline__ float f32_part_dot(const F32Part<D>& a, const F32Part<D>& b) {
+    float s = 0.f;
+#pragma unroll
+    for (int e = 0; e < D / 64; ++e) s = __builtin_fmaf(a.v[e], b.v[e], s);
+#pragma unroll
+    for (int m = 1; m < 64; m <<= 1) s += __shfl_xor(s, m, 64);
+    return s;
+}
+template <int D>
+__device__ __forceinline__ void f32_part_add(F32Part<D>& acc, float f, const F32Part<D>& x) {
+#pragma unroll
+    for (int e = 0; e < D / 64; ++e) acc.v[e] = __builtin_fmaf(f, x.v[e], acc.v[e]);
+}
+template <int D>
+__device__ __forceinline__ void f32_part_store(float* row, const F32Part<D>& x, float mul, int lane) {
+#pragma unroll
+    for (int e = 0; e < D / 64; ++e) row[64 * e + lane] = x.v[e] * mul;
+}
+constexpr int kF32RowsU = 4;
+
+template <int D>
+__device__ __forceinline__ void f32_row_fwd(const F32Params& p, int row0, int i, int head, int lane) {
+    asm volatile("" : "+v"(lane));           // (addresses are formed here: hoisted out of the item loop they spill registers in the tile loop)
+    const int64_t at = ((int64_t)(row0 + i) * p.hq + head) * D, kv_stride = (int64_t)p.hkv * D;
+    const int64_t kv = (int64_t)row0 * kv_stride + (int64_t)(head / (p.hq / p.hkv)) * D;
+    const F32Part<D> q = f32_part<D>(p.q + at, lane);
+    F32Part<D> o = {};
+    float m = -INFINITY, l = 0.f;
+    for (int j0 = 0; j0 <= i; j0 += kF32RowsU) {
+        F32Part<D> k[kF32RowsU], v[kF32RowsU];
+        float s[kF32RowsU];
+#pragma unroll
+        for (int u = 0; u < kF32RowsU; ++u) {
+            const int64_t row = kv + min(j0 + u, i) * kv_stride;
+            k[u] = f32_part<D>(p.k + row, lane);
+            v[u] = f32_part<D>(p.v + row, lane);
+        }
+#pragma unroll
+        for (int u = 0; u < kF32RowsU; ++u) s[u] = p.scale * f32_part_dot<D>(q, k[u]);
+        float m_new = m;
+#pragma unroll
+        for (int u = 0; u < kF32RowsU; ++u) m_new = fmaxf(m_new, s[u]);        // (the row repeated past i changes nothing)
+        const float ref = m_new == -INFINITY ? 0.f : m_new, alpha = f32_exp(m - ref);
+        m = m_new;
+        l *= alpha;
+#pragma unroll
+        for (int e = 0; e < D / 64; ++e) o.v[e] *= alpha;
+#pragma unroll
+        for (int u = 0; u < kF32RowsU; ++u)
+            if (j0 + u <= i) {
+                const float pr = f32_exp(s[u] - ref);
+                l += pr;
+                f32_part_add<D>(o, pr, v[u]);
+            }
+    }
+    f32_part_store<D>(p.o_out + at, o, 1.f / l, lane);
+    if (lane == 0) p.lse_out[(int64_t)head * p.T + row0 + i] = m + logf(l);
+}
+
+template <int D>
+__device__ __forceinline__ void f32_row_dq(const F32Params& p, int row0, int i, int head, int lane) {
+    asm volatile("" : "+v"(lane));           // (addresses are formed here: hoisted out of the item loop they spill registers in the tile loop)
+    const int64_t at = ((int64_t)(row0 + i) * p.hq + head) * D, st = (int64_t)head * p.T + row0 + i, kv_stride = (int64_t)p.hkv * D;
+    const int64_t kv = (int64_t)row0 * kv_stride + (int64_t)(head / (p.hq / p.hkv)) * D;
+    const F32Part<D> q = f32_part<D>(p.q + at, lane), g = f32_part<D>(p.d_o + at, lane);
+    const float Di = f32_part_dot<D>(f32_part<D>(p.o + at, lane), g), lse = p.lse_in[st];
+    if (lane == 0) p.D[st] = Di;
+    F32Part<D> acc = {};
+    for (int j0 = 0; j0 <= i; j0 += kF32RowsU) {
+        F32Part<D> k[kF32RowsU];
+        float s[kF32RowsU], dp[kF32RowsU];
+#pragma unroll
+        for (int u = 0; u < kF32RowsU; ++u) {
+            const int64_t row = kv + min(j0 + u, i) * kv_stride;
+            k[u] = f32_part<D>(p.k + row, lane);
+            s[u] = f32_part_dot<D>(q, k[u]);
+            dp[u] = f32_part_dot<D>(g, f32_part<D>(p.v + row, lane));
+        }
+#pragma unroll
+        for (int u = 0; u < kF32RowsU; ++u)
+            if (j0 + u <= i) f32_part_add<D>(acc, f32_exp(__builtin_fmaf(p.scale, s[u], -lse)) * (dp[u] - Di), k[u]);
+    }
+    f32_part_store<D>(p.dq + at, acc, p.scale, lane);
+}
+
+template <int D>
+__device__ __forceinline__ void f32_row_dkdv(const F32Params& p, int row0, int L, int j, int g, int lane) {
+    asm volatile("" : "+v"(lane));           // (addresses are formed here: hoisted out of the item loop they spill registers in the tile loop)
+    const int G = p.hq / p.hkv;
+    const int64_t at = ((int64_t)(row0 + j) * p.hkv + g) * D, q_stride = (int64_t)p.hq * D;
+    const F32Part<D> k = f32_part<D>(p.k + at, lane), v = f32_part<D>(p.v + at, lane);
+    F32Part<D> dk = {}, dv = {};
+    for (int h = g * G; h < (g + 1) * G; ++h)
+        for (int i0 = j; i0 < L; i0 += kF32RowsU) {
+            F32Part<D> q[kF32RowsU], d_o[kF32RowsU];
+            float s[kF32RowsU], dp[kF32RowsU], lse[kF32RowsU], Di[kF32RowsU];
+#pragma unroll
+            for (int u = 0; u < kF32RowsU; ++u) {
+                const int i = min(i0 + u, L - 1);
+                const int64_t row = (int64_t)(row0 + i) * q_stride + (int64_t)h * D, st = (int64_t)h * p.T + row0 + i;
+                q[u] = f32_part<D>(p.q + row, lane);
+                d_o[u] = f32_part<D>(p.d_o + row, lane);
+                s[u] = f32_part_dot<D>(q[u], k);
+                dp[u] = f32_part_dot<D>(d_o[u], v);
+                lse[u] = p.lse_in[st];
+                Di[u] = p.D[st];
+            }
+#pragma unroll
+            for (int u = 0; u < kF32RowsU; ++u)
+                if (i0 + u < L) {
+                    const float pr = f32_exp(__builtin_fmaf(p.scale, s[u], -lse[u]));
+                    f32_part_add<D>(dv, pr, d_o[u]);
+                    f32_part_add<D>(dk, pr * (dp[u] - Di[u]), q[u]);
+                }
+        }
+    f32_part_store<D>(p.dk + at, dk, p.scale, lane);
+    f32_part_store<D>(p.dv + at, dv, 1.f, lane);
+}
+
+template <int N>
+__device__ __forceinline__ bool f32_all_finite(const f32x16 (&acc)[N]) {
+    float z = 0.f;                                               // (these maxima keep a NaN)
+#pragma unroll
+    for (int i = 0; i < N; ++i)
+#pragma unroll
+        for (int r = 0; r < 16; r += 2) z = __builtin_elementwise_maximum(__builtin_elementwise_maximum(fabsf(acc[i][r]), fabsf(acc[i][r + 1])), z);
+    return !__any(!(z <= FLT_MAX));
+}
+// rows [first, min(first + 32, L)) of a tensor [.][stride] from `base` hold finite values only
+template <int D>
+__device__ __forceinline__ bool f32_rows_finite(const float* base, int64_t stride, int first, int L, int lane) {
+    asm volatile("" : "+v"(lane));           // (addresses are formed here: hoisted out of the item loop they spill registers in the tile loop)
+    float z = 0.f;
+#pragma unroll 1
+    for (int r = first; r < min(first + 32, L); ++r) {
+        const F32Part<D> x = f32_part<D>(base + r * stride, lane);
+#pragma unroll
+        for (int e = 0; e < D / 64; ++e) z = __builtin_fmaf(x.v[e], 0.f, z);
+    }
+    return !__any(z != 0.f);
+}
+
 // Forward.  S^T[key][q] = K Q^T (one query row per lane), O^T[d][q] += V^T P^T.
 template <int D>
 __global__ void __launch_bounds__(64 * kF32Waves, 1) hyd_fwd_fp32_kernel(F32Params p) {
@@ -214,6 +377,7 @@ __global__ void __launch_bounds__(64 * kF32Waves, 1) hyd_fwd_fp32_kernel(F32Para
     constexpr int kT = f32_tile_bytes<D>(), NDB = D / 32, kL = F32Lds<D, kF32Waves>::kLoads;
     constexpr int kAcc = NDB * 64 * 64;                          // bytes of a wave's accumulators
     int* slot = reinterpret_cast<int*>(smem + 2 * kT);
+    volatile int* bad = slot + kSlotInts;                        // see "one row at a time"
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int rg = wave & 1, split = wave >> 1, l32 = lane & 31, half = lane >> 5;
@@ -236,6 +400,7 @@ __global__ void __launch_bounds__(64 * kF32Waves, 1) hyd_fwd_fp32_kernel(F32Para
         fl.load(rv, smem + kT, 0, stride_b);
         f32x16 o[NDB];
         f32_zero(o);
+        if (tid == 0) *bad = 0;
         float m = -INFINITY, l = 0.f;
         for (int t = 0; t < n_kt; ++t) {
             const uint32_t nxt = (uint32_t)(t + 1) * kF32Tile * stride_b;
@@ -295,6 +460,8 @@ __global__ void __launch_bounds__(64 * kF32Waves, 1) hyd_fwd_fp32_kernel(F32Para
         if (split) f32_put(smem + (2 * (split - 1) + rg) * kAcc, o, lane);
         ml[wave * 128 + lane] = m;
         ml[wave * 128 + 64 + lane] = l;
+        if (split == ((wrow0 >> 5) & (kF32Splits - 1)) && wrow0 < L && __builtin_expect(!f32_all_finite(o), 0))
+            if (!f32_rows_finite<D>(p.v + ((int64_t)row0 * p.hkv + g) * D, (int64_t)p.hkv * D, wrow0, L, lane)) *bad = 1;
         __syncthreads();
         if (split == 0 && wrow0 < L) {
             float mt = m, lt = 0.f;                              // (a split that saw no key has m = -inf and l = 0)
@@ -314,6 +481,10 @@ __global__ void __launch_bounds__(64 * kF32Waves, 1) hyd_fwd_fp32_kernel(F32Para
                 if (half == 0) p.lse_out[(int64_t)head * p.T + row0 + i] = mt + logf(lt);
             }
         }
+        if (__builtin_expect(*bad, 0)) {
+            __syncthreads();
+            for (int r = q0 + wave; r < kv_end; r += kF32Waves) f32_row_fwd<D>(p, row0, r, head, lane);
+        }
     }
 }
 
@@ -325,6 +496,7 @@ __global__ void __launch_bounds__(64 * kF32Waves, 1) hyd_bwd_dq_fp32_kernel(F32P
     constexpr int kT = f32_tile_bytes<D>(), NDB = D / 32, kL = F32Lds<D, kF32Waves>::kLoads;
     constexpr int kAcc = NDB * 64 * 64;
     int* slot = reinterpret_cast<int*>(smem + 2 * kT);
+    volatile int* bad = slot + kSlotInts;                        // see "one row at a time"
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int rg = wave & 1, split = wave >> 1, l32 = lane & 31, half = lane >> 5;
@@ -363,6 +535,7 @@ __global__ void __launch_bounds__(64 * kF32Waves, 1) hyd_bwd_dq_fp32_kernel(F32P
         fl.load(rv, smem + kT, 0, stride_b);
         f32x16 acc[NDB];
         f32_zero(acc);
+        if (tid == 0) *bad = 0;
         for (int t = 0; t < n_kt; ++t) {
             const uint32_t nxt = (uint32_t)(t + 1) * kF32Tile * stride_b;
             const bool more = t + 1 < n_kt;
@@ -393,11 +566,17 @@ __global__ void __launch_bounds__(64 * kF32Waves, 1) hyd_bwd_dq_fp32_kernel(F32P
             if (more) fl.load(rk, smem, nxt, stride_b);
         }
         if (split) f32_put(smem + (2 * (split - 1) + rg) * kAcc, acc, lane);
+        if (split == ((wrow0 >> 5) & (kF32Splits - 1)) && wrow0 < L && __builtin_expect(!f32_all_finite(acc), 0))
+            if (!f32_rows_finite<D>(p.k + ((int64_t)row0 * p.hkv + g) * D, (int64_t)p.hkv * D, wrow0, L, lane)) *bad = 1;
         __syncthreads();
         if (split == 0 && wrow0 < L) {
 #pragma unroll
             for (int x = 1; x < kF32Splits; ++x) f32_add(acc, 1.f, smem + (2 * (x - 1) + rg) * kAcc, 1.f, lane);
             if (i < L) f32_store_row<D>(p.dq + roff, acc, p.scale, half);
+        }
+        if (__builtin_expect(*bad, 0)) {
+            __syncthreads();
+            for (int r = q0 + wave; r < kv_end; r += kF32Waves) f32_row_dq<D>(p, row0, r, head, lane);
         }
     }
 }
@@ -411,6 +590,7 @@ __global__ void __launch_bounds__(64 * kF32KvWaves, 1) hyd_bwd_dkdv_fp32_kernel(
     constexpr int kT = f32_tile_bytes<D>(), NDB = D / 32;
     constexpr int kAcc = NDB * 64 * 64;
     int* slot = reinterpret_cast<int*>(smem + 2 * kT);
+    volatile int* bad = slot + kSlotInts;                        // see "one row at a time"
     const int tid = threadIdx.x, lane = tid & 63;
     const int split = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int l32 = lane & 31, half = lane >> 5;
@@ -442,6 +622,7 @@ __global__ void __launch_bounds__(64 * kF32KvWaves, 1) hyd_bwd_dkdv_fp32_kernel(
         f32x16 acck[NDB], accv[NDB];
         f32_zero(acck);
         f32_zero(accv);
+        if (tid == 0) *bad = 0;
         const int n_iter = (L - j0 + kF32Tile - 1) / kF32Tile * G;
         int ti = j0, hh = 0;
         for (int it = 0; it < n_iter; ++it) {
@@ -496,6 +677,17 @@ __global__ void __launch_bounds__(64 * kF32KvWaves, 1) hyd_bwd_dkdv_fp32_kernel(
             f32_put(smem + 2 * (split - 1) * kAcc, acck, lane);
             f32_put(smem + (2 * (split - 1) + 1) * kAcc, accv, lane);
         }
+        if (__builtin_expect(!f32_all_finite(acck) || !f32_all_finite(accv), 0)) {
+            const int last = j0 + (L - 1 - j0) / 32 * 32;        // the blocks in question: split 0's first, and the last one
+            bool finite = true;
+            for (int h = 0; h < G; ++h) {
+                const int64_t q_stride = (int64_t)p.hq * D, at = ((int64_t)row0 * p.hq + g * G + h) * D;
+                if (split == 0) finite = finite && f32_rows_finite<D>(p.q + at, q_stride, j0, L, lane) && f32_rows_finite<D>(p.d_o + at, q_stride, j0, L, lane);
+                if (((last - j0) / 32) % kF32Splits == split)
+                    finite = finite && f32_rows_finite<D>(p.q + at, q_stride, last, L, lane) && f32_rows_finite<D>(p.d_o + at, q_stride, last, L, lane);
+            }
+            if (!finite) *bad = 1;
+        }
         __syncthreads();
         if (split == 0) {
 #pragma unroll
@@ -507,6 +699,10 @@ __global__ void __launch_bounds__(64 * kF32KvWaves, 1) hyd_bwd_dkdv_fp32_kernel(
                 f32_store_row<D>(p.dk + koff, acck, p.scale, half);
                 f32_store_row<D>(p.dv + koff, accv, 1.f, half);
             }
+        }
+        if (__builtin_expect(*bad, 0)) {
+            __syncthreads();
+            for (int r = j0 + split; r < min(L, j0 + kF32KvBN); r += kF32KvWaves) f32_row_dkdv<D>(p, row0, L, r, g, lane);
         }
     }
 }

@@ -1,5 +1,6 @@
 """fp32 kernels on what unit-normal inputs never show: rows whose scores are strongly negative,
-scores of -inf or below every finite mask value, and buffers that are only aligned to a float."""
+scores of -inf or below every finite mask value, tokens with infinities or NaN (which may reach their own
+row and later ones, never an earlier one), and buffers that are only aligned to a float."""
 import numpy as np
 import pytest
 import torch
@@ -66,6 +67,26 @@ def test_scores_below_any_mask_value(score, d):
     o, lse = binding.varlen_attn_fwd(*dev, torch.from_numpy(cu).cuda(), L, 1.0)
     ro, rlse = orc.fwd(q, k, v, cu, 1.0)
     assert gu.errors(gu.to_np(o), ro)[1] <= 1e-5 and gu.errors(gu.to_np(lse), rlse)[1] <= 1e-5
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("bad", [np.inf, -np.inf, np.nan])
+@pytest.mark.parametrize("at", [5, 31, 32, 70, 149])
+def test_a_bad_token_stays_out_of_earlier_rows(at, bad, d):
+    """Row `at` of one tensor at a time holds `bad`.  O, LSE and dQ of earlier rows depend on Q, K and V up to
+    themselves, dK and dV of later keys on rows of Q and dO from themselves on: they are what they are without it."""
+    L, hq, hkv, scale = 150, 4, 2, d ** -0.5
+    _, q, k, v, do = wl.custom([L], hq, hkv, d, "fp32", seed=34)
+    clean = run([L], q, k, v, do, scale)
+    for name in ("q", "k", "v", "do"):
+        x = {"q": q.copy(), "k": k.copy(), "v": v.copy(), "do": do.copy()}
+        x[name][at, :, 3] = bad
+        got = run([L], x["q"], x["k"], x["v"], x["do"], scale)
+        parts = [("o", got["o"][:at], clean["o"][:at]), ("lse", got["lse"][:, :at], clean["lse"][:, :at]), ("dq", got["dq"][:at], clean["dq"][:at])]
+        if name in ("q", "do"):                            # K and V of one key reach all rows from it on, and with them every key
+            parts += [(out, got[out][at + 1:], clean[out][at + 1:]) for out in ("dk", "dv")]
+        for out, a, b in parts:                            # (the sums of one block in another order: no more than the kernels' bar)
+            assert np.all(np.isfinite(a)) and (a.size == 0 or gu.errors(a, b)[1] <= 1e-6), (name, out)
 
 
 @pytest.mark.parametrize("d", [64, 128])
