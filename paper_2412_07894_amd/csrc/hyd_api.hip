@@ -609,18 +609,21 @@ hyd_status bwd_impl(const void* q, const void* k, const void* v, const void* o, 
             hipLaunchKernelGGL(hyd_schedule_prelude, dim3(w.n_sched), dim3(kPreludeThreads), schedule_lds(sv_kv.n_lev, sv_q.n_lev), st, cu_seqlens,
                                num_seqs, total_tokens, tile_kv(dt), sv_kv, tile_q(dt), sv_q, nullptr, 0, 0.0);
         }
+        const bool short_rows = max_seqlen <= kF32Short;
         const dim3 grid_q(persistent_grid(*dev, occ_q, work_q)), grid_kv(persistent_grid(*dev, occ_kv, work_kv));
         // dQ first: it also writes the row sums D that dK/dV reads
         {
             p.hdr = sv_q.hdr; p.items = sv_q.exec; p.cursors = sv_q.hdr + kHdrCursor; p.hm = head_map_q(hq, hkv, grid_q.x);
             KernelTimer kt("bwd_dq_fp32", st);
             if (head_dim == 64) hipLaunchKernelGGL(hyd_bwd_dq_fp32_kernel<64>, grid_q, dim3(64 * kF32Waves), f32_lds<64>(), st, p);
+            else if (short_rows) hipLaunchKernelGGL((hyd_bwd_dq_fp32_kernel<128, true>), grid_q, dim3(64 * kF32Waves), f32_rows_lds(), st, p);
             else hipLaunchKernelGGL(hyd_bwd_dq_fp32_kernel<128>, grid_q, dim3(64 * kF32Waves), f32_lds<128>(), st, p);
         }
         {
             p.hdr = sv_kv.hdr; p.items = sv_kv.exec; p.cursors = sv_kv.hdr + kHdrCursor; p.hm = head_map_kv(hkv, grid_kv.x);
             KernelTimer kt("bwd_dkdv_fp32", st);
             if (head_dim == 64) hipLaunchKernelGGL(hyd_bwd_dkdv_fp32_kernel<64>, grid_kv, dim3(64 * kF32KvWaves), f32_lds<64>(), st, p);
+            else if (short_rows) hipLaunchKernelGGL((hyd_bwd_dkdv_fp32_kernel<128, true>), grid_kv, dim3(64 * kF32KvWaves), f32_rows_lds(), st, p);
             else hipLaunchKernelGGL(hyd_bwd_dkdv_fp32_kernel<128>, grid_kv, dim3(64 * kF32KvWaves), f32_lds<128>(), st, p);
         }
     }

@@ -247,6 +247,13 @@ __device__ __forceinline__ void f32_part_store(float* row, const F32Part<D>& x, 
     for (int e = 0; e < D / 64; ++e) row[64 * e + lane] = x.v[e] * mul;
 }
 constexpr int kF32RowsU = 4;
+// Sequences of up to kF32Short rows are taken this way from the start, a row per wave: an item of the tile path takes about 10 us
+// however short it is.  The tile loops of the backward have no registers to spare at D = 128 (this path beside them
+// costs 3 %), so there it is a kernel of its own, for batches that hold nothing longer.  Measured, 4096 sequences of one
+// token, forward / backward in us, tile path -> this: 8 heads, d = 128 1202 / 3857 -> 337 / 517; 8/2 heads, d = 64 732 /
+// 1700 -> 271 / 601; 1300 sequences of three tokens, 8 heads, d = 128 397 / 1266 -> 115 / 190.
+constexpr int kF32Short = kF32Waves;
+constexpr int f32_rows_lds() { return 128; }
 
 template <int D>
 __device__ __forceinline__ void f32_row_fwd(const F32Params& p, int row0, int i, int head, int lane) {
@@ -389,113 +396,119 @@ __global__ void __launch_bounds__(64 * kF32Waves, 1) hyd_fwd_fp32_kernel(F32Para
     WorkItem wi;
     for (bool have = wf.first(p.hm, p.hdr, p.cursors, p.items, slot, wi); have; have = wf.next(p.hm, p.cursors, p.items, slot, wi)) {
         const int head = wi.head, row0 = wi.row0, L = wi.len;
-        const int q0 = (wi.lev - 1) * kF32BM, kv_end = min(L, q0 + kF32BM), n_kt = (kv_end + kF32Tile - 1) / kF32Tile;
-        const int g = head / G, wrow0 = q0 + 32 * rg, i = wrow0 + l32;
-        const uint32_t kv_bytes = (uint32_t)(kv_end - 1) * stride_b + D * 4;
-        const __amdgpu_buffer_rsrc_t rk = make_rsrc(p.k + ((int64_t)row0 * p.hkv + g) * D, kv_bytes);
-        const __amdgpu_buffer_rsrc_t rv = make_rsrc(p.v + ((int64_t)row0 * p.hkv + g) * D, kv_bytes);
-        fl.load(rk, smem, 0, stride_b);
-        f32x4 q[D / 8];
-        f32_load_row<D>(q, p.q + ((int64_t)(row0 + min(i, L - 1)) * p.hq + head) * D, half);
-        fl.load(rv, smem + kT, 0, stride_b);
-        f32x16 o[NDB];
-        f32_zero(o);
-        if (tid == 0) *bad = 0;
-        float m = -INFINITY, l = 0.f;
-        for (int t = 0; t < n_kt; ++t) {
-            const uint32_t nxt = (uint32_t)(t + 1) * kF32Tile * stride_b;
-            const bool more = t + 1 < n_kt;
-            if (t == max(n_kt - 2, 0)) wf.claim(p.hm, p.cursors);
-            const int key0 = t * kF32Tile + 32 * split;
-            const bool work = key0 <= wrow0 && wrow0 < L;        // else the block is hidden from all rows of the wave
-            f32_arrive<kL>();                                    // K tile t is there
-            f32x16 s[1];
-            f32_zero(s);
-            if (work) f32_row_product(s[0], fl, 0, q);
-            f32_release();
-            if (more) fl.load(rk, smem, nxt, stride_b);
-            if (work) {
-                const int rel = i - key0 - 4 * half;             // register r is visible iff its key offset <= rel
+        bool rows = L <= kF32Short;
+        if (rows) {
+            wf.claim(p.hm, p.cursors);
+        } else {
+            const int q0 = (wi.lev - 1) * kF32BM, kv_end = min(L, q0 + kF32BM), n_kt = (kv_end + kF32Tile - 1) / kF32Tile;
+            const int g = head / G, wrow0 = q0 + 32 * rg, i = wrow0 + l32;
+            const uint32_t kv_bytes = (uint32_t)(kv_end - 1) * stride_b + D * 4;
+            const __amdgpu_buffer_rsrc_t rk = make_rsrc(p.k + ((int64_t)row0 * p.hkv + g) * D, kv_bytes);
+            const __amdgpu_buffer_rsrc_t rv = make_rsrc(p.v + ((int64_t)row0 * p.hkv + g) * D, kv_bytes);
+            fl.load(rk, smem, 0, stride_b);
+            f32x4 q[D / 8];
+            f32_load_row<D>(q, p.q + ((int64_t)(row0 + min(i, L - 1)) * p.hq + head) * D, half);
+            fl.load(rv, smem + kT, 0, stride_b);
+            f32x16 o[NDB];
+            f32_zero(o);
+            if (tid == 0) *bad = 0;
+            float m = -INFINITY, l = 0.f;
+            for (int t = 0; t < n_kt; ++t) {
+                const uint32_t nxt = (uint32_t)(t + 1) * kF32Tile * stride_b;
+                const bool more = t + 1 < n_kt;
+                if (t == max(n_kt - 2, 0)) wf.claim(p.hm, p.cursors);
+                const int key0 = t * kF32Tile + 32 * split;
+                const bool work = key0 <= wrow0 && wrow0 < L;        // else the block is hidden from all rows of the wave
+                f32_arrive<kL>();                                    // K tile t is there
+                f32x16 s[1];
+                f32_zero(s);
+                if (work) f32_row_product(s[0], fl, 0, q);
+                f32_release();
+                if (more) fl.load(rk, smem, nxt, stride_b);
+                if (work) {
+                    const int rel = i - key0 - 4 * half;             // register r is visible iff its key offset <= rel
 #pragma unroll
-                for (int r = 0; r < 16; ++r) s[0][r] *= p.scale;
-                if (key0 == wrow0) {                             // the diagonal block
+                    for (int r = 0; r < 16; ++r) s[0][r] *= p.scale;
+                    if (key0 == wrow0) {                             // the diagonal block
 #pragma unroll
-                    for (int r = 0; r < 16; ++r)
-                        if (8 * (r >> 2) + (r & 3) > rel) s[0][r] = -INFINITY;
+                        for (int r = 0; r < 16; ++r)
+                            if (8 * (r >> 2) + (r & 3) > rel) s[0][r] = -INFINITY;
+                    }
+                    float mx = s[0][0];
+#pragma unroll
+                    for (int r = 1; r < 16; ++r) mx = fmaxf(mx, s[0][r]);
+                    float lo, hi;
+                    both_halves(mx, lo, hi);
+                    const float m_new = fmaxf(m, fmaxf(lo, hi));
+                    // (a row that has seen no score but -inf yet: every probability is 0)
+                    const float ref = m_new == -INFINITY ? 0.f : m_new;
+                    const float alpha = f32_exp(m - ref);
+                    m = m_new;
+                    float sum = 0.f;
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) { s[0][r] = f32_exp(s[0][r] - ref); sum += s[0][r]; }
+                    l = l * alpha + sum;
+                    if (__any(alpha != 1.f)) {
+#pragma unroll
+                        for (int db = 0; db < NDB; ++db)
+#pragma unroll
+                            for (int r = 0; r < 16; ++r) o[db][r] *= alpha;
+                    }
                 }
-                float mx = s[0][0];
-#pragma unroll
-                for (int r = 1; r < 16; ++r) mx = fmaxf(mx, s[0][r]);
+                if (more) f32_arrive<kL>(); else f32_arrive<0>();    // V tile t is there
+                if (work) f32_col_product(o, fl, kT, s[0]);
+                f32_release();
+                if (more) fl.load(rv, smem + kT, nxt, stride_b);
+            }
+            {   // l is still split over the two halves of the wave
                 float lo, hi;
-                both_halves(mx, lo, hi);
-                const float m_new = fmaxf(m, fmaxf(lo, hi));
-                // (a row that has seen no score but -inf yet: every probability is 0)
-                const float ref = m_new == -INFINITY ? 0.f : m_new;
-                const float alpha = f32_exp(m - ref);
-                m = m_new;
-                float sum = 0.f;
+                both_halves(l, lo, hi);
+                l = lo + hi;
+            }
+            // The splits' results meet in LDS: accumulators of split s > 0 and row group rg at 2 (s - 1) + rg,
+            // (m, l) of every wave in the bytes behind them (the last quarter of the second tile).
+            float* ml = reinterpret_cast<float*>(smem + 2 * kT - kAcc);
+            if (split) f32_put(smem + (2 * (split - 1) + rg) * kAcc, o, lane);
+            ml[wave * 128 + lane] = m;
+            ml[wave * 128 + 64 + lane] = l;
+            if (split == ((wrow0 >> 5) & (kF32Splits - 1)) && wrow0 < L && __builtin_expect(!f32_all_finite(o), 0))
+                if (!f32_rows_finite<D>(p.v + ((int64_t)row0 * p.hkv + g) * D, (int64_t)p.hkv * D, wrow0, L, lane)) *bad = 1;
+            __syncthreads();
+            if (split == 0 && wrow0 < L) {
+                float mt = m, lt = 0.f;                              // (a split that saw no key has m = -inf and l = 0)
 #pragma unroll
-                for (int r = 0; r < 16; ++r) { s[0][r] = f32_exp(s[0][r] - ref); sum += s[0][r]; }
-                l = l * alpha + sum;
-                if (__any(alpha != 1.f)) {
+                for (int x = 1; x < kF32Splits; ++x) mt = fmaxf(mt, ml[(2 * x + rg) * 128 + lane]);
+                float w = f32_exp(m - mt);
+                lt = l * w;
 #pragma unroll
-                    for (int db = 0; db < NDB; ++db)
-#pragma unroll
-                        for (int r = 0; r < 16; ++r) o[db][r] *= alpha;
+                for (int x = 1; x < kF32Splits; ++x) {
+                    const float wx = f32_exp(ml[(2 * x + rg) * 128 + lane] - mt);
+                    lt += ml[(2 * x + rg) * 128 + 64 + lane] * wx;
+                    f32_add(o, w, smem + (2 * (x - 1) + rg) * kAcc, wx, lane);
+                    w = 1.f;
+                }
+                if (i < L) {
+                    f32_store_row<D>(p.o_out + ((int64_t)(row0 + i) * p.hq + head) * D, o, 1.f / lt, half);
+                    if (half == 0) p.lse_out[(int64_t)head * p.T + row0 + i] = mt + logf(lt);
                 }
             }
-            if (more) f32_arrive<kL>(); else f32_arrive<0>();    // V tile t is there
-            if (work) f32_col_product(o, fl, kT, s[0]);
-            f32_release();
-            if (more) fl.load(rv, smem + kT, nxt, stride_b);
+            rows = *bad != 0;
+            if (__builtin_expect(rows, 0)) __syncthreads();      // the rows' stores above come first
         }
-        {   // l is still split over the two halves of the wave
-            float lo, hi;
-            both_halves(l, lo, hi);
-            l = lo + hi;
-        }
-        // The splits' results meet in LDS: accumulators of split s > 0 and row group rg at 2 (s - 1) + rg,
-        // (m, l) of every wave in the bytes behind them (the last quarter of the second tile).
-        float* ml = reinterpret_cast<float*>(smem + 2 * kT - kAcc);
-        if (split) f32_put(smem + (2 * (split - 1) + rg) * kAcc, o, lane);
-        ml[wave * 128 + lane] = m;
-        ml[wave * 128 + 64 + lane] = l;
-        if (split == ((wrow0 >> 5) & (kF32Splits - 1)) && wrow0 < L && __builtin_expect(!f32_all_finite(o), 0))
-            if (!f32_rows_finite<D>(p.v + ((int64_t)row0 * p.hkv + g) * D, (int64_t)p.hkv * D, wrow0, L, lane)) *bad = 1;
-        __syncthreads();
-        if (split == 0 && wrow0 < L) {
-            float mt = m, lt = 0.f;                              // (a split that saw no key has m = -inf and l = 0)
-#pragma unroll
-            for (int x = 1; x < kF32Splits; ++x) mt = fmaxf(mt, ml[(2 * x + rg) * 128 + lane]);
-            float w = f32_exp(m - mt);
-            lt = l * w;
-#pragma unroll
-            for (int x = 1; x < kF32Splits; ++x) {
-                const float wx = f32_exp(ml[(2 * x + rg) * 128 + lane] - mt);
-                lt += ml[(2 * x + rg) * 128 + 64 + lane] * wx;
-                f32_add(o, w, smem + (2 * (x - 1) + rg) * kAcc, wx, lane);
-                w = 1.f;
-            }
-            if (i < L) {
-                f32_store_row<D>(p.o_out + ((int64_t)(row0 + i) * p.hq + head) * D, o, 1.f / lt, half);
-                if (half == 0) p.lse_out[(int64_t)head * p.T + row0 + i] = mt + logf(lt);
-            }
-        }
-        if (__builtin_expect(*bad, 0)) {
-            __syncthreads();
-            for (int r = q0 + wave; r < kv_end; r += kF32Waves) f32_row_fwd<D>(p, row0, r, head, lane);
+        if (__builtin_expect(rows, 0)) {
+            for (int r = (wi.lev - 1) * kF32BM + wave; r < min(L, wi.lev * kF32BM); r += kF32Waves) f32_row_fwd<D>(p, row0, r, head, lane);
         }
     }
 }
 
 // dQ.  S^T = K Q^T, dP^T = V dO^T, dQ^T += K^T dS^T.  Also forms D = rowsum(dO * O) of its rows, which
 // the dK/dV kernel that follows reads.
-template <int D>
+template <int D, bool kRows = false>
 __global__ void __launch_bounds__(64 * kF32Waves, 1) hyd_bwd_dq_fp32_kernel(F32Params p) {
     extern __shared__ __attribute__((aligned(16))) char smem[];
     constexpr int kT = f32_tile_bytes<D>(), NDB = D / 32, kL = F32Lds<D, kF32Waves>::kLoads;
     constexpr int kAcc = NDB * 64 * 64;
-    int* slot = reinterpret_cast<int*>(smem + 2 * kT);
+    int* slot = reinterpret_cast<int*>(smem + (kRows ? 0 : 2 * kT));
     volatile int* bad = slot + kSlotInts;                        // see "one row at a time"
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -508,75 +521,81 @@ __global__ void __launch_bounds__(64 * kF32Waves, 1) hyd_bwd_dq_fp32_kernel(F32P
     WorkItem wi;
     for (bool have = wf.first(p.hm, p.hdr, p.cursors, p.items, slot, wi); have; have = wf.next(p.hm, p.cursors, p.items, slot, wi)) {
         const int head = wi.head, row0 = wi.row0, L = wi.len;
-        const int q0 = (wi.lev - 1) * kF32BM, kv_end = min(L, q0 + kF32BM), n_kt = (kv_end + kF32Tile - 1) / kF32Tile;
-        const int g = head / G, wrow0 = q0 + 32 * rg, i = wrow0 + l32, ic = min(i, L - 1);
-        const uint32_t kv_bytes = (uint32_t)(kv_end - 1) * stride_b + D * 4;
-        const __amdgpu_buffer_rsrc_t rk = make_rsrc(p.k + ((int64_t)row0 * p.hkv + g) * D, kv_bytes);
-        const __amdgpu_buffer_rsrc_t rv = make_rsrc(p.v + ((int64_t)row0 * p.hkv + g) * D, kv_bytes);
-        const int64_t roff = ((int64_t)(row0 + ic) * p.hq + head) * D, at = (int64_t)head * p.T + row0 + ic;
-        fl.load(rk, smem, 0, stride_b);
-        f32x4 q[D / 8], dof[D / 8];
-        f32_load_row<D>(q, p.q + roff, half);
-        f32_load_row<D>(dof, p.d_o + roff, half);
-        float Di = 0.f;
+        bool rows = kRows || (D == 64 && L <= kF32Short);
+        if (rows) {
+            wf.claim(p.hm, p.cursors);
+        } else {
+            const int q0 = (wi.lev - 1) * kF32BM, kv_end = min(L, q0 + kF32BM), n_kt = (kv_end + kF32Tile - 1) / kF32Tile;
+            const int g = head / G, wrow0 = q0 + 32 * rg, i = wrow0 + l32, ic = min(i, L - 1);
+            const uint32_t kv_bytes = (uint32_t)(kv_end - 1) * stride_b + D * 4;
+            const __amdgpu_buffer_rsrc_t rk = make_rsrc(p.k + ((int64_t)row0 * p.hkv + g) * D, kv_bytes);
+            const __amdgpu_buffer_rsrc_t rv = make_rsrc(p.v + ((int64_t)row0 * p.hkv + g) * D, kv_bytes);
+            const int64_t roff = ((int64_t)(row0 + ic) * p.hq + head) * D, at = (int64_t)head * p.T + row0 + ic;
+            fl.load(rk, smem, 0, stride_b);
+            f32x4 q[D / 8], dof[D / 8];
+            f32_load_row<D>(q, p.q + roff, half);
+            f32_load_row<D>(dof, p.d_o + roff, half);
+            float Di = 0.f;
 #pragma unroll
-        for (int a = 0; a < D / 8; ++a) {
-            const f32x4 x = *reinterpret_cast<const f32x4*>(p.o + roff + 8 * a + 4 * half);
+            for (int a = 0; a < D / 8; ++a) {
+                const f32x4 x = *reinterpret_cast<const f32x4*>(p.o + roff + 8 * a + 4 * half);
 #pragma unroll
-            for (int e = 0; e < 4; ++e) Di = __builtin_fmaf(x[e], dof[a][e], Di);
-        }
-        {
-            float lo, hi;
-            both_halves(Di, lo, hi);
-            Di = lo + hi;
-        }
-        if (split == 0 && half == 0 && i < L) p.D[at] = Di;
-        const float lse = p.lse_in[at];
-        fl.load(rv, smem + kT, 0, stride_b);
-        f32x16 acc[NDB];
-        f32_zero(acc);
-        if (tid == 0) *bad = 0;
-        for (int t = 0; t < n_kt; ++t) {
-            const uint32_t nxt = (uint32_t)(t + 1) * kF32Tile * stride_b;
-            const bool more = t + 1 < n_kt;
-            if (t == max(n_kt - 2, 0)) wf.claim(p.hm, p.cursors);
-            const int key0 = t * kF32Tile + 32 * split;
-            const bool work = key0 <= wrow0 && wrow0 < L;
-            f32x16 s[1], dp[1];
-            f32_zero(s);
-            f32_zero(dp);
-            if (t == 0) f32_arrive<kL>(); else f32_arrive<0>();  // K tile t (from the second tile on V was requested first)
-            if (work) f32_row_product(s[0], fl, 0, q);
-            if (t == 0) f32_arrive<0>();                         // V tile t
-            if (work) f32_row_product(dp[0], fl, kT, dof);
-            f32_release();
-            if (more) fl.load(rv, smem + kT, nxt, stride_b);
-            if (work) {
-                const int rel = i - key0 - 4 * half;
-#pragma unroll
-                for (int r = 0; r < 16; ++r) s[0][r] = f32_exp(__builtin_fmaf(p.scale, s[0][r], -lse)) * (dp[0][r] - Di);
-                if (key0 == wrow0) {                             // the diagonal block
-#pragma unroll
-                    for (int r = 0; r < 16; ++r)
-                        if (8 * (r >> 2) + (r & 3) > rel) s[0][r] = 0.f;
-                }
-                f32_col_product(acc, fl, 0, s[0]);
+                for (int e = 0; e < 4; ++e) Di = __builtin_fmaf(x[e], dof[a][e], Di);
             }
-            f32_release();
-            if (more) fl.load(rk, smem, nxt, stride_b);
-        }
-        if (split) f32_put(smem + (2 * (split - 1) + rg) * kAcc, acc, lane);
-        if (split == ((wrow0 >> 5) & (kF32Splits - 1)) && wrow0 < L && __builtin_expect(!f32_all_finite(acc), 0))
-            if (!f32_rows_finite<D>(p.k + ((int64_t)row0 * p.hkv + g) * D, (int64_t)p.hkv * D, wrow0, L, lane)) *bad = 1;
-        __syncthreads();
-        if (split == 0 && wrow0 < L) {
+            {
+                float lo, hi;
+                both_halves(Di, lo, hi);
+                Di = lo + hi;
+            }
+            if (split == 0 && half == 0 && i < L) p.D[at] = Di;
+            const float lse = p.lse_in[at];
+            fl.load(rv, smem + kT, 0, stride_b);
+            f32x16 acc[NDB];
+            f32_zero(acc);
+            if (tid == 0) *bad = 0;
+            for (int t = 0; t < n_kt; ++t) {
+                const uint32_t nxt = (uint32_t)(t + 1) * kF32Tile * stride_b;
+                const bool more = t + 1 < n_kt;
+                if (t == max(n_kt - 2, 0)) wf.claim(p.hm, p.cursors);
+                const int key0 = t * kF32Tile + 32 * split;
+                const bool work = key0 <= wrow0 && wrow0 < L;
+                f32x16 s[1], dp[1];
+                f32_zero(s);
+                f32_zero(dp);
+                if (t == 0) f32_arrive<kL>(); else f32_arrive<0>();  // K tile t (from the second tile on V was requested first)
+                if (work) f32_row_product(s[0], fl, 0, q);
+                if (t == 0) f32_arrive<0>();                         // V tile t
+                if (work) f32_row_product(dp[0], fl, kT, dof);
+                f32_release();
+                if (more) fl.load(rv, smem + kT, nxt, stride_b);
+                if (work) {
+                    const int rel = i - key0 - 4 * half;
 #pragma unroll
-            for (int x = 1; x < kF32Splits; ++x) f32_add(acc, 1.f, smem + (2 * (x - 1) + rg) * kAcc, 1.f, lane);
-            if (i < L) f32_store_row<D>(p.dq + roff, acc, p.scale, half);
-        }
-        if (__builtin_expect(*bad, 0)) {
+                    for (int r = 0; r < 16; ++r) s[0][r] = f32_exp(__builtin_fmaf(p.scale, s[0][r], -lse)) * (dp[0][r] - Di);
+                    if (key0 == wrow0) {                             // the diagonal block
+#pragma unroll
+                        for (int r = 0; r < 16; ++r)
+                            if (8 * (r >> 2) + (r & 3) > rel) s[0][r] = 0.f;
+                    }
+                    f32_col_product(acc, fl, 0, s[0]);
+                }
+                f32_release();
+                if (more) fl.load(rk, smem, nxt, stride_b);
+            }
+            if (split) f32_put(smem + (2 * (split - 1) + rg) * kAcc, acc, lane);
+            if (split == ((wrow0 >> 5) & (kF32Splits - 1)) && wrow0 < L && __builtin_expect(!f32_all_finite(acc), 0))
+                if (!f32_rows_finite<D>(p.k + ((int64_t)row0 * p.hkv + g) * D, (int64_t)p.hkv * D, wrow0, L, lane)) *bad = 1;
             __syncthreads();
-            for (int r = q0 + wave; r < kv_end; r += kF32Waves) f32_row_dq<D>(p, row0, r, head, lane);
+            if (split == 0 && wrow0 < L) {
+#pragma unroll
+                for (int x = 1; x < kF32Splits; ++x) f32_add(acc, 1.f, smem + (2 * (x - 1) + rg) * kAcc, 1.f, lane);
+                if (i < L) f32_store_row<D>(p.dq + roff, acc, p.scale, half);
+            }
+            rows = *bad != 0;
+            if (__builtin_expect(rows, 0)) __syncthreads();      // the rows' stores above come first
+        }
+        if (__builtin_expect(rows, 0)) {
+            for (int r = (wi.lev - 1) * kF32BM + wave; r < min(L, wi.lev * kF32BM); r += kF32Waves) f32_row_dq<D>(p, row0, r, head, lane);
         }
     }
 }
@@ -584,12 +603,12 @@ __global__ void __launch_bounds__(64 * kF32Waves, 1) hyd_bwd_dq_fp32_kernel(F32P
 // dK/dV.  S[i][j] = Q K^T and dP[i][j] = dO V^T (one key per lane), dV^T += dO^T P, dK^T += Q^T dS.  K and V
 // rows of the item stay in registers next to both accumulator sets; that takes more than 256
 // registers, so one wave per SIMD.
-template <int D>
+template <int D, bool kRows = false>
 __global__ void __launch_bounds__(64 * kF32KvWaves, 1) hyd_bwd_dkdv_fp32_kernel(F32Params p) {
     extern __shared__ __attribute__((aligned(16))) char smem[];
     constexpr int kT = f32_tile_bytes<D>(), NDB = D / 32;
     constexpr int kAcc = NDB * 64 * 64;
-    int* slot = reinterpret_cast<int*>(smem + 2 * kT);
+    int* slot = reinterpret_cast<int*>(smem + (kRows ? 0 : 2 * kT));
     volatile int* bad = slot + kSlotInts;                        // see "one row at a time"
     const int tid = threadIdx.x, lane = tid & 63;
     const int split = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -602,106 +621,113 @@ __global__ void __launch_bounds__(64 * kF32KvWaves, 1) hyd_bwd_dkdv_fp32_kernel(
     WorkItem wi;
     for (bool have = wf.first(p.hm, p.hdr, p.cursors, p.items, slot, wi); have; have = wf.next(p.hm, p.cursors, p.items, slot, wi)) {
         const int g = wi.head, row0 = wi.row0, L = wi.len;
-        const int j0 = ((L + kF32KvBN - 1) / kF32KvBN - wi.lev) * kF32KvBN, j = j0 + l32;
-        const int64_t koff = ((int64_t)(row0 + min(j, L - 1)) * p.hkv + g) * D;
-        const uint32_t q_bytes = (uint32_t)(L - 1) * stride_b + D * 4;
-        // iterations: tiles of query rows from j0 on outer, the group's heads inner
-        int ld_i = j0, ld_h = 0;
-        auto load_q = [&]() {
-            fl.load(make_rsrc(p.q + ((int64_t)row0 * p.hq + g * G + ld_h) * D, q_bytes), smem, (uint32_t)ld_i * stride_b, stride_b);
-        };
-        auto load_do = [&]() {                                   // follows load_q of the same iteration
-            fl.load(make_rsrc(p.d_o + ((int64_t)row0 * p.hq + g * G + ld_h) * D, q_bytes), smem + kT, (uint32_t)ld_i * stride_b, stride_b);
-            if (++ld_h == G) { ld_h = 0; ld_i += kF32Tile; }
-        };
-        load_q();
-        f32x4 kr[D / 8], vr[D / 8];
-        f32_load_row<D>(kr, p.k + koff, half);
-        f32_load_row<D>(vr, p.v + koff, half);
-        load_do();
-        f32x16 acck[NDB], accv[NDB];
-        f32_zero(acck);
-        f32_zero(accv);
-        if (tid == 0) *bad = 0;
-        const int n_iter = (L - j0 + kF32Tile - 1) / kF32Tile * G;
-        int ti = j0, hh = 0;
-        for (int it = 0; it < n_iter; ++it) {
-            const bool more = it + 1 < n_iter;
-            if (it == max(n_iter - 2, 0)) wf.claim(p.hm, p.cursors);
-            const int i0 = ti + 32 * split;
-            const bool work = i0 < L;
-            // statistics of the block's rows (register r: row i0 + 8 (r / 4) + 4 half + r % 4); rows past the
-            // sequence repeat its last one and are masked below, as exp(-LSE) need not be finite
-            float nl[16], nd[16];
-            if (work) {
-                const int64_t at = (int64_t)(g * G + hh) * p.T + row0;
+        bool rows = kRows || (D == 64 && L <= kF32Short);
+        if (rows) {
+            wf.claim(p.hm, p.cursors);
+        } else {
+            const int j0 = ((L + kF32KvBN - 1) / kF32KvBN - wi.lev) * kF32KvBN, j = j0 + l32;
+            const int64_t koff = ((int64_t)(row0 + min(j, L - 1)) * p.hkv + g) * D;
+            const uint32_t q_bytes = (uint32_t)(L - 1) * stride_b + D * 4;
+            // iterations: tiles of query rows from j0 on outer, the group's heads inner
+            int ld_i = j0, ld_h = 0;
+            auto load_q = [&]() {
+                fl.load(make_rsrc(p.q + ((int64_t)row0 * p.hq + g * G + ld_h) * D, q_bytes), smem, (uint32_t)ld_i * stride_b, stride_b);
+            };
+            auto load_do = [&]() {                                   // follows load_q of the same iteration
+                fl.load(make_rsrc(p.d_o + ((int64_t)row0 * p.hq + g * G + ld_h) * D, q_bytes), smem + kT, (uint32_t)ld_i * stride_b, stride_b);
+                if (++ld_h == G) { ld_h = 0; ld_i += kF32Tile; }
+            };
+            load_q();
+            f32x4 kr[D / 8], vr[D / 8];
+            f32_load_row<D>(kr, p.k + koff, half);
+            f32_load_row<D>(vr, p.v + koff, half);
+            load_do();
+            f32x16 acck[NDB], accv[NDB];
+            f32_zero(acck);
+            f32_zero(accv);
+            if (tid == 0) *bad = 0;
+            const int n_iter = (L - j0 + kF32Tile - 1) / kF32Tile * G;
+            int ti = j0, hh = 0;
+            for (int it = 0; it < n_iter; ++it) {
+                const bool more = it + 1 < n_iter;
+                if (it == max(n_iter - 2, 0)) wf.claim(p.hm, p.cursors);
+                const int i0 = ti + 32 * split;
+                const bool work = i0 < L;
+                // statistics of the block's rows (register r: row i0 + 8 (r / 4) + 4 half + r % 4); rows past the
+                // sequence repeat its last one and are masked below, as exp(-LSE) need not be finite
+                float nl[16], nd[16];
+                if (work) {
+                    const int64_t at = (int64_t)(g * G + hh) * p.T + row0;
 #pragma unroll
-                for (int r = 0; r < 16; ++r) {
-                    const int ii = min(i0 + 8 * (r >> 2) + 4 * half + (r & 3), L - 1);
-                    nl[r] = p.lse_in[at + ii];
-                    nd[r] = p.D[at + ii];
-                }
-            }
-            f32x16 s[1], dp[1];
-            f32_zero(s);
-            f32_zero(dp);
-            f32_arrive<0>();                                     // Q and dO tiles of this iteration
-            if (work) {
-                f32_row_product(s[0], fl, 0, kr);
-                f32_row_product(dp[0], fl, kT, vr);
-                // register r is visible iff its row offset is in [rel, end): from the key on, inside the sequence
-                const int rel = j - i0 - 4 * half, end = L - i0 - 4 * half;
-                const bool part = i0 == j0 || i0 + 32 > L;       // else the whole block is
-#pragma unroll
-                for (int r = 0; r < 16; ++r) {
-                    const int row = 8 * (r >> 2) + (r & 3);
-                    float pr = f32_exp(__builtin_fmaf(p.scale, s[0][r], -nl[r]));
-                    float ds = pr * (dp[0][r] - nd[r]);
-                    if (part) {
-                        pr = row >= rel && row < end ? pr : 0.f;
-                        ds = row >= rel && row < end ? ds : 0.f;
+                    for (int r = 0; r < 16; ++r) {
+                        const int ii = min(i0 + 8 * (r >> 2) + 4 * half + (r & 3), L - 1);
+                        nl[r] = p.lse_in[at + ii];
+                        nd[r] = p.D[at + ii];
                     }
-                    s[0][r] = pr;
-                    dp[0][r] = ds;
                 }
-                f32_col_product(acck, fl, 0, dp[0]);
-            }
-            f32_release();
-            if (more) load_q();                                  // under the dV product
-            if (work) f32_col_product(accv, fl, kT, s[0]);
-            f32_release();
-            if (more) load_do();
-            if (++hh == G) { hh = 0; ti += kF32Tile; }
-        }
-        if (split) {
-            f32_put(smem + 2 * (split - 1) * kAcc, acck, lane);
-            f32_put(smem + (2 * (split - 1) + 1) * kAcc, accv, lane);
-        }
-        if (__builtin_expect(!f32_all_finite(acck) || !f32_all_finite(accv), 0)) {
-            const int last = j0 + (L - 1 - j0) / 32 * 32;        // the blocks in question: split 0's first, and the last one
-            bool finite = true;
-            for (int h = 0; h < G; ++h) {
-                const int64_t q_stride = (int64_t)p.hq * D, at = ((int64_t)row0 * p.hq + g * G + h) * D;
-                if (split == 0) finite = finite && f32_rows_finite<D>(p.q + at, q_stride, j0, L, lane) && f32_rows_finite<D>(p.d_o + at, q_stride, j0, L, lane);
-                if (((last - j0) / 32) % kF32Splits == split)
-                    finite = finite && f32_rows_finite<D>(p.q + at, q_stride, last, L, lane) && f32_rows_finite<D>(p.d_o + at, q_stride, last, L, lane);
-            }
-            if (!finite) *bad = 1;
-        }
-        __syncthreads();
-        if (split == 0) {
+                f32x16 s[1], dp[1];
+                f32_zero(s);
+                f32_zero(dp);
+                f32_arrive<0>();                                     // Q and dO tiles of this iteration
+                if (work) {
+                    f32_row_product(s[0], fl, 0, kr);
+                    f32_row_product(dp[0], fl, kT, vr);
+                    // register r is visible iff its row offset is in [rel, end): from the key on, inside the sequence
+                    const int rel = j - i0 - 4 * half, end = L - i0 - 4 * half;
+                    const bool part = i0 == j0 || i0 + 32 > L;       // else the whole block is
 #pragma unroll
-            for (int x = 0; x < kF32Splits - 1; ++x) {
-                f32_add(acck, 1.f, smem + 2 * x * kAcc, 1.f, lane);
-                f32_add(accv, 1.f, smem + (2 * x + 1) * kAcc, 1.f, lane);
+                    for (int r = 0; r < 16; ++r) {
+                        const int row = 8 * (r >> 2) + (r & 3);
+                        float pr = f32_exp(__builtin_fmaf(p.scale, s[0][r], -nl[r]));
+                        float ds = pr * (dp[0][r] - nd[r]);
+                        if (part) {
+                            pr = row >= rel && row < end ? pr : 0.f;
+                            ds = row >= rel && row < end ? ds : 0.f;
+                        }
+                        s[0][r] = pr;
+                        dp[0][r] = ds;
+                    }
+                    f32_col_product(acck, fl, 0, dp[0]);
+                }
+                f32_release();
+                if (more) load_q();                                  // under the dV product
+                if (work) f32_col_product(accv, fl, kT, s[0]);
+                f32_release();
+                if (more) load_do();
+                if (++hh == G) { hh = 0; ti += kF32Tile; }
             }
-            if (j < L) {
-                f32_store_row<D>(p.dk + koff, acck, p.scale, half);
-                f32_store_row<D>(p.dv + koff, accv, 1.f, half);
+            if (split) {
+                f32_put(smem + 2 * (split - 1) * kAcc, acck, lane);
+                f32_put(smem + (2 * (split - 1) + 1) * kAcc, accv, lane);
             }
-        }
-        if (__builtin_expect(*bad, 0)) {
+            if (__builtin_expect(!f32_all_finite(acck) || !f32_all_finite(accv), 0)) {
+                const int last = j0 + (L - 1 - j0) / 32 * 32;        // the blocks in question: split 0's first, and the last one
+                bool finite = true;
+                for (int h = 0; h < G; ++h) {
+                    const int64_t q_stride = (int64_t)p.hq * D, at = ((int64_t)row0 * p.hq + g * G + h) * D;
+                    if (split == 0) finite = finite && f32_rows_finite<D>(p.q + at, q_stride, j0, L, lane) && f32_rows_finite<D>(p.d_o + at, q_stride, j0, L, lane);
+                    if (((last - j0) / 32) % kF32Splits == split)
+                        finite = finite && f32_rows_finite<D>(p.q + at, q_stride, last, L, lane) && f32_rows_finite<D>(p.d_o + at, q_stride, last, L, lane);
+                }
+                if (!finite) *bad = 1;
+            }
             __syncthreads();
+            if (split == 0) {
+#pragma unroll
+                for (int x = 0; x < kF32Splits - 1; ++x) {
+                    f32_add(acck, 1.f, smem + 2 * x * kAcc, 1.f, lane);
+                    f32_add(accv, 1.f, smem + (2 * x + 1) * kAcc, 1.f, lane);
+                }
+                if (j < L) {
+                    f32_store_row<D>(p.dk + koff, acck, p.scale, half);
+                    f32_store_row<D>(p.dv + koff, accv, 1.f, half);
+                }
+            }
+            rows = *bad != 0;
+            if (__builtin_expect(rows, 0)) __syncthreads();      // the rows' stores above come first
+        }
+        if (__builtin_expect(rows, 0)) {
+            const int j0 = ((L + kF32KvBN - 1) / kF32KvBN - wi.lev) * kF32KvBN;
             for (int r = j0 + split; r < min(L, j0 + kF32KvBN); r += kF32KvWaves) f32_row_dkdv<D>(p, row0, L, r, g, lane);
         }
     }

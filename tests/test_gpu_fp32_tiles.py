@@ -34,3 +34,20 @@ def test_fp32_tile_edges(lengths, hq, hkv, d):
         max_abs, rel = gu.errors(got[name], ref)
         print(f"{name}: max-abs {max_abs:.3e} (tol {tol:.1e})  rel-L2 {rel:.3e}", flush=True)
         assert np.all(np.isfinite(got[name])) and max_abs <= tol and rel <= 1e-5, name
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("lengths,hq,hkv", [
+    ([8, 1, 0, 7, 5, 8, 3, 2], 4, 2),                       # nothing but short sequences
+    ([8, 9, 1, 40, 7, 16], 8, 2),                           # on both sides of the limit
+    ([1] * 300, 2, 2),                                      # more items than workgroups
+])
+def test_fp32_short_sequences(lengths, hq, hkv, d):
+    cu, q, k, v, do = wl.custom(lengths, hq, hkv, d, "fp32", seed=72)
+    scale = d ** -0.5
+    got = gu.run_gpu(cu, q, k, v, do, "fp32", scale)
+    o, lse = orc.fwd(q, k, v, cu, scale)
+    for name, ref in zip(("o", "lse", "dq", "dk", "dv"), (o, lse) + tuple(orc.bwd(q, k, v, do, cu, scale))):
+        max_abs, rel = gu.errors(got[name], ref)
+        print(f"{name}: max-abs {max_abs:.3e} rel-L2 {rel:.3e}", flush=True)
+        assert np.all(np.isfinite(got[name])) and max_abs <= 1e-5 and rel <= 1e-5, name
