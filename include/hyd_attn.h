@@ -70,9 +70,12 @@ const char* hyd_status_string(hyd_status st);
  * (sequence, tile) items ordered by decreasing cost, and the queue cursors of the persistent
  * workgroups) and, for the backward, float vectors [Hq][T] of row statistics (D = rowsum(dO * O)
  * and LSE in base-2 units, negated, in the forms the two kernels consume) plus, for bf16, fp16
- * copies of Q, dO and K (2 * T * (2 Hq + Hkv) * head_dim bytes) and room for fp32 partial sums of dK
- * and dV (n * 8 * T * Hkv * head_dim bytes, n = 8, 4 or 2 as fits 256 MiB, else none); the contents are
- * private to the library.  Returns 0 for invalid arguments.  Pure host arithmetic: no HIP call.
+ * copies of Q, dO and K (2 * T * (2 Hq + Hkv) * head_dim bytes); the contents are private to the
+ * library.  The bf16 size ends with room for fp32 partial sums of dK and dV, at most 256 MiB, where a batch of these
+ * sizes can use them (n * 8 * T * Hkv * head_dim bytes, n <= 8); a backward call does with less of it or none,
+ * more slowly where it would have used it.  For given head counts, head_dim and dt the size does not fall as
+ * total_tokens or num_seqs grow: a workspace made for the largest batch serves every smaller one.
+ * Returns 0 for invalid arguments.  Pure host arithmetic: no HIP call.
  */
 size_t hyd_varlen_attn_workspace_bytes(int total_tokens, int num_seqs, int hq, int hkv,
                                        int head_dim, hyd_dtype dt, int is_bwd);

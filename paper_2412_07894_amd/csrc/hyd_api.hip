@@ -30,8 +30,9 @@ struct WsLayout {
     SchedLayout sched[2];
     SchedLayout split;      // query side by QuerySplit tiles, where an item is not a whole tile (split > 0)
     int n_sched;
-    int part_max;           // dK/dV items in parts: their number at most, and the parts' sums
-    size_t stat[kBwdStatVecs], q16, do16, k16, absmax, rope_tab, part, total;
+    int part_max;           // dK/dV items in parts: their number at most
+    // need: what a call cannot do without; the parts' sums take what lies behind it, up to total (see part_bytes)
+    size_t stat[kBwdStatVecs], q16, do16, k16, absmax, rope_tab, need, total;
 };
 constexpr int kRopeTabEntries = 64;       // head_dim / 2 at most
 
@@ -55,22 +56,50 @@ size_t sched_layout(SchedLayout& v, size_t at, int T, int nseq, int tile, int sp
     return at;
 }
 
-// Parts that a dK/dV item may be taken in: as many as the sums of all rows fit kPartBytes for.  (Splitting
-// pays where few items keep few compute units busy, which needs a small batch or few KV heads.)
+// Parts of dK/dV items.  An item may be taken in as many parts as the sums of all rows fit behind the rest of the
+// workspace and into kPartBytes (splitting pays where few items keep few compute units busy, which needs a small
+// batch or few KV heads).  A call with a smaller workspace takes fewer parts or none: a workspace made for more tokens does for
+// fewer, whatever a batch could use.  What a batch can use at most, whatever its max_seqlen, is a maximum over the number
+// of key tiles of its longest sequence, so that the size asked for never falls as tokens are added.
 constexpr size_t kPartBytes = 256u << 20;
+constexpr int kPartSteps = 16;                             // see set_parts
 size_t part_bytes(int T, int hkv, int head_dim) { return 2 * sizeof(float) * (size_t)T * (size_t)hkv * (size_t)head_dim; }
-int part_limit(int T, int hkv, int head_dim) {
+int part_limit(size_t bytes, int T, int hkv, int head_dim) {
+    const size_t one = part_bytes(T, hkv, head_dim);
     int n = hkv <= 65535 ? kPartsMax : 1;                  // KV heads are a grid dimension of the summing kernel
-    while (n > 1 && (size_t)n * part_bytes(T, hkv, head_dim) > kPartBytes) n >>= 1;
-    return n;
+    while (n > 1 && (size_t)n * one > kPartBytes) n >>= 1;
+    return (size_t)n * one <= bytes ? n : (int)(bytes / one < 1 ? 1 : bytes / one);
+}
+double share_of_work(double tile, double steps_per_level, int T, int nseq, int max_seqlen, int heads, int wgs) {
+    const double nm = max_seqlen / tile, m = nseq > 1 ? nseq - 1 : 1, nr = (T - max_seqlen) / m / tile;
+    return heads * steps_per_level * (nm * (nm + 1) + m * nr * (nr + 1)) / 2 / wgs;
+}
+// steps of a part, 0: items stay whole (see set_parts)
+double steps_of_part(double longest, double share, int limit) {
+    if (limit <= 1 || longest < 1.6 * share || longest < 2 * kPartSteps) return 0;
+    const double q = share / 2 > kPartSteps ? share / 2 : kPartSteps;
+    return q < longest / limit ? longest / limit : q;
+}
+size_t useful_part_bytes(int T, int hq, int hkv, int head_dim) {
+    if (hkv > 65535) return 0;
+    const int steps = kKvBN / kKvBM * (hq / hkv), levels = (T + kKvBN - 1) / kKvBN;
+    int most = 1;
+    for (int n = 1; n <= levels && most < kPartsMax; ++n) {        // the longest sequence has n tiles, and nothing lies beside it
+        const double share = share_of_work(kKvBN, steps, (n - 1) * kKvBN + 1, 1, (n - 1) * kKvBN + 1, hkv, 256);
+        const double q = steps_of_part((double)n * steps, share, kPartsMax);
+        if (q > 0 && most < (int)ceil(n * steps / q)) most = (int)ceil(n * steps / q);
+        if ((double)n * steps < 1.6 * share) break;                 // and so on: a share grows with n squared
+    }
+    const size_t bytes = most == 1 ? 0 : (size_t)most * part_bytes(T, hkv, head_dim);
+    return bytes < kPartBytes ? bytes : kPartBytes;
 }
 
 // split: finest form of the query side's items (the last list).  The list of whole tiles has its order of
 // execution only where that differs from it (make_view).
-WsLayout ws_layout(int T, int nseq, int tile0, int tile1, int split, int hq, int hkv, int head_dim, hyd_dtype dt, bool bwd, bool compact = false) {
+WsLayout ws_layout(int T, int nseq, int tile0, int tile1, int split, int hq, int hkv, int head_dim, hyd_dtype dt, bool bwd, bool compact = false, size_t bytes = 0) {
     WsLayout w;
-    w.part_max = bwd && dt == HYD_BF16 ? part_limit(T, hkv, head_dim) : 1;
-    size_t at = sched_layout(w.sched[0], 0, T, nseq, tile0, 0, compact || (!bwd && hq >= 4 * hkv), w.part_max);
+    const size_t useful = bwd && dt == HYD_BF16 ? useful_part_bytes(T, hq, hkv, head_dim) : 0;
+    size_t at = sched_layout(w.sched[0], 0, T, nseq, tile0, 0, compact || (!bwd && hq >= 4 * hkv), useful ? kPartsMax : 1);
     w.n_sched = bwd ? 2 : 1;
     if (bwd) at = sched_layout(w.sched[1], at, T, nseq, tile1, 0, hq >= 4 * hkv);
     else w.sched[1] = w.sched[0];
@@ -87,8 +116,9 @@ WsLayout ws_layout(int T, int nseq, int tile0, int tile1, int split, int hq, int
     w.k16 = at;  if (copies) at += align_up(2 * (size_t)T * (size_t)hkv * (size_t)head_dim);
     w.absmax = at; if (copies) at += align_up(sizeof(uint32_t) * kPrepMaxWg);
     w.rope_tab = at; at += align_up(sizeof(double) * kRopeTabEntries);       // rotary frequency table (the *_rope calls)
-    w.part = at; if (w.part_max > 1) at += align_up((size_t)w.part_max * part_bytes(T, hkv, head_dim));
-    w.total = at;
+    w.need = at;
+    w.total = at + align_up(useful);
+    w.part_max = useful && bytes > at ? part_limit(bytes - at, T, hkv, head_dim) : 1;
     return w;
 }
 
@@ -116,10 +146,6 @@ int tile_kv(hyd_dtype dt) { return dt == HYD_BF16 ? kKvBN : kF32KvBN; }
 //
 // `compact`: whole tiles, which need the fewest records.
 constexpr long long kFourHeadPairs = 2 * 256 * 256;        // (token, head) pairs of two items for each of 256 CUs
-double share_of_work(double tile, double steps_per_level, int T, int nseq, int max_seqlen, int heads, int wgs) {
-    const double nm = max_seqlen / tile, m = nseq > 1 ? nseq - 1 : 1, nr = (T - max_seqlen) / m / tile;
-    return heads * steps_per_level * (nm * (nm + 1) + m * nr * (nr + 1)) / 2 / wgs;
-}
 int query_split(hyd_dtype dt, int T, int nseq, int max_seqlen, int hq, int hkv, bool compact) {
     if (dt != HYD_BF16 || compact) return 0;
     const double steps = 256 / kFwdBN;                     // per level of a whole tile
@@ -135,8 +161,8 @@ int item_heads(int split) { return split == 2 ? 4 : 1; }
 WsLayout fwd_layout(int T, int nseq, int hq, int hkv, int head_dim, hyd_dtype dt, bool compact) {
     return ws_layout(T, nseq, tile_q(dt), tile_q(dt), finest_split(dt, hq, hkv, compact), hq, hkv, head_dim, dt, false, compact);
 }
-WsLayout bwd_layout(int T, int nseq, int hq, int hkv, int head_dim, hyd_dtype dt) {
-    return ws_layout(T, nseq, tile_kv(dt), tile_q(dt), finest_split(dt, hq, hkv, false), hq, hkv, head_dim, dt, true);
+WsLayout bwd_layout(int T, int nseq, int hq, int hkv, int head_dim, hyd_dtype dt, size_t bytes = 0) {
+    return ws_layout(T, nseq, tile_kv(dt), tile_q(dt), finest_split(dt, hq, hkv, false), hq, hkv, head_dim, dt, true, false, bytes);
 }
 
 bool head_dim_ok(hyd_dtype dt, int d) { (void)dt; return d == 64 || d == 128; }
@@ -187,7 +213,7 @@ hyd_status validate_common(const int32_t* cu, int num_seqs, const int32_t* cu_ho
         }
         if (longest > max_seqlen) return HYD_ERR_SHAPE;
     }
-    const size_t need = (bwd ? bwd_layout(T, num_seqs, hq, hkv, head_dim, dt) : fwd_layout(T, num_seqs, hq, hkv, head_dim, dt, compact)).total;
+    const size_t need = (bwd ? bwd_layout(T, num_seqs, hq, hkv, head_dim, dt) : fwd_layout(T, num_seqs, hq, hkv, head_dim, dt, compact)).need;
     if (!ws || ((uintptr_t)ws % kAlign) != 0 || ws_bytes < need) return HYD_ERR_WORKSPACE;
     return HYD_OK;
 }
@@ -360,14 +386,12 @@ SchedView make_view(char* ws, const SchedLayout& v, int tile, int split, int max
 // tokens 3070 -> 1262; 32/8 heads, 512 tokens 54 -> 41, 1024 tokens 98 -> 47, 2048 tokens 115 -> 78, 4096 tokens 307 -> 221,
 // 8192 tokens 415 -> 406.  kPartSteps 12 / 16 / 24 / 40: 512 tokens 36 / 41 / 50 / 54, 1024 tokens 43 / 47 / 54 / 74, 2048 tokens 76 /
 // 78 / 65 / 81; with 12 a batch of 8/8 heads and 2048 tokens is cut too, for nothing (37 -> 37).
-constexpr int kPartSteps = 16;
 void set_parts(SchedView& sv, int limit, int T, int nseq, int max_seqlen, int hq, int hkv, int wgs) {
     sv.steps_per_level = kKvBN / kKvBM * (hq / hkv);
     const double share = share_of_work(kKvBN, sv.steps_per_level, T, nseq, max_seqlen, hkv, wgs);
     const double longest = (double)sv.n_lev * sv.steps_per_level;
-    if (limit <= 1 || longest < 1.6 * share || longest < 2 * kPartSteps) return;
-    double q = share / 2 > kPartSteps ? share / 2 : kPartSteps;
-    if (q < longest / limit) q = longest / limit;
+    const double q = steps_of_part(longest, share, limit);
+    if (q == 0) return;
     sv.part_q = (int)ceil(q);
     sv.part_max = item_parts(sv.n_lev, sv.steps_per_level, sv.part_q, limit);
 }
@@ -505,7 +529,7 @@ hyd_status bwd_impl(const void* q, const void* k, const void* v, const void* o, 
     if (ds != HYD_OK) return ds;
     hipStream_t st = static_cast<hipStream_t>(hip_stream);
 
-    const WsLayout w = bwd_layout(total_tokens, num_seqs, hq, hkv, head_dim, dt);
+    const WsLayout w = bwd_layout(total_tokens, num_seqs, hq, hkv, head_dim, dt, workspace_bytes);
     char* ws = static_cast<char*>(workspace);
     const int occ_q = dt == HYD_BF16 ? dev->occ_dq : dev->occ_f32[head_dim == 128][1];
     const int occ_kv = dt == HYD_BF16 ? dev->occ_kv : dev->occ_f32[head_dim == 128][2];
@@ -571,7 +595,7 @@ hyd_status bwd_impl(const void* q, const void* k, const void* v, const void* o, 
         }
         {
             p.hdr = sv_kv.hdr + kHdrExec; p.items = sv_kv.exec;
-            p.part = reinterpret_cast<float*>(ws + w.part); p.part_max = sv_kv.part_max;
+            p.part = reinterpret_cast<float*>(ws + w.need); p.part_max = sv_kv.part_max;
             p.cursors = sv_kv.hdr + kHdrCursor;
             const dim3 grid(persistent_grid(*dev, occ_kv, work_kv));
             p.hm = head_map_kv(hkv, grid.x);
@@ -802,8 +826,8 @@ hyd_status hyd_varlen_attn_schedule_status(const void* workspace, size_t workspa
                                                           &max_items, &tile);
     if (ls != HYD_OK) return ls;
     if (total_tokens == 0 || num_seqs == 0) return HYD_OK;
-    if (!workspace || workspace_bytes < hyd_varlen_attn_workspace_bytes(total_tokens, num_seqs, hq, hkv, head_dim, dt, is_bwd))
-        return HYD_ERR_WORKSPACE;
+    const WsLayout w = is_bwd ? bwd_layout(total_tokens, num_seqs, hq, hkv, head_dim, dt) : fwd_layout(total_tokens, num_seqs, hq, hkv, head_dim, dt, false);
+    if (!workspace || workspace_bytes < w.need) return HYD_ERR_WORKSPACE;
     int head[2] = {0, 0};
     hipStream_t st = static_cast<hipStream_t>(hip_stream);
     if (hipMemcpyAsync(head, static_cast<const char*>(workspace) + hdr, sizeof(head), hipMemcpyDeviceToHost, st) != hipSuccess ||

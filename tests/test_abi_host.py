@@ -205,6 +205,34 @@ def test_noalloc_forward_takes_what_fits_two_mebibytes_of_schedule(lib):
         assert call(99071 + 64, hq, hkv) == 7
 
 
+def test_a_workspace_for_a_larger_batch_serves_smaller_ones(lib):
+    """The size does not fall as tokens or sequences are added, and a backward call on a smaller batch takes such a
+    workspace (the NULL query pointer is found, error 1)."""
+    from paper_2412_07894_amd import binding as b
+    P, N = 1 << 20, None
+    for dt in (0, 1):
+        for hq, hkv in ((32, 8), (32, 32), (8, 8), (8, 1), (16, 2), (64, 8), (10, 10), (5, 5)):
+            for d in (64, 128):
+                top = b.workspace_bytes(40000, 64, hq, hkv, d, dt, 1)
+                last = 0
+                for T in sorted({int(x) for k in range(40) for x in (128 * 1.16 ** k, 128 * 1.16 ** k + 1)} | {4096, 4097, 8192, 8193, 16384, 16385}):
+                    n = b.workspace_bytes(T, 16, hq, hkv, d, dt, 1)
+                    assert n >= last, (dt, hq, hkv, d, T)
+                    last = n
+                    assert b.workspace_bytes(T, 64, hq, hkv, d, dt, 1) >= n
+                    if T <= 40000:
+                        for ml in (T, max(1, T // 5)):
+                            assert lib.hyd_varlen_attn_bwd(N, P, P, P, P, P, P, 16, N, T, ml, hq, hkv, d, ctypes.c_float(0.1), dt,
+                                                           P, P, P, P, ctypes.c_size_t(top), N) == 1, (dt, hq, hkv, d, T)
+
+
+def test_room_for_partial_sums_is_asked_for_where_it_can_be_used(lib):
+    """512 tokens of 32 ungrouped heads never take items in parts: no more than the statistics, copies and lists."""
+    from paper_2412_07894_amd import binding as b
+    T, hq, d = 512, 32, 128
+    assert b.workspace_bytes(T, 16, hq, hq, d, 0, 1) < 2 * T * 3 * hq * d + 4 * 4 * T * hq + (1 << 17)
+
+
 def test_schedule_layout_and_status_argument_errors(lib):
     sz, ci = ctypes.c_size_t, ctypes.c_int
     h, it, cap, tile = sz(0), sz(0), ci(0), ci(0)

@@ -62,3 +62,21 @@ def test_items_in_parts_of_a_key_range():
         got = gu.to_np(got)
         gu.check(name, got[inside], ref[inside], "bf16")
         assert np.all(got[outside] == 7.0), name
+
+
+@pytest.mark.parametrize("room", [0, 1, 3, 8])
+def test_a_smaller_workspace_takes_fewer_parts(room):
+    """A workspace with room for the sums of `room` parts (this batch can use eight): right results whatever the number, no parts without."""
+    lens, hq, hkv, d = [1300, 7, 129], 8, 1, 128
+    T = sum(lens)
+    cu, host, scale, (q, k, v, do), cu_d, o, lse = setup(lens, hq, hkv, d, 73)
+    part, full = 8 * T * hkv * d, binding.workspace_bytes(T, len(lens), hq, hkv, d, binding.HYD_BF16, 1)
+    ws = torch.empty(full - (8 - room) * part + 65536, dtype=torch.uint8, device="cuda")
+    ws[-65536:] = 0x5a
+    run = lambda: binding.varlen_attn_bwd(q, k, v, o, lse, do, cu_d, max(lens), scale, workspace=ws[:-65536])
+    assert ("bwd_sum_parts" in names_of(run)) == (room > 1)
+    _, dk, dv = run()
+    _, rdk, rdv = orc.bwd_given(*host, gu.to_np(o).astype(np.float32), gu.to_np(lse).astype(np.float32), cu, scale)     # of the stored O and LSE
+    gu.check("dk", gu.to_np(dk), rdk, "bf16")
+    gu.check("dv", gu.to_np(dv), rdv, "bf16")
+    assert bool((ws[-65536:] == 0x5a).all())
