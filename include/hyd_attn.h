@@ -74,7 +74,8 @@ const char* hyd_status_string(hyd_status st);
  * library.  The bf16 size ends with room for fp32 partial sums of dK and dV, at most 256 MiB, where a batch of these
  * sizes can use them (n * 8 * T * Hkv * head_dim bytes, n <= 8); a backward call does with less of it or none,
  * more slowly where it would have used it.  For given head counts, head_dim and dt the size does not fall as
- * total_tokens or num_seqs grow: a workspace made for the largest batch serves every smaller one.
+ * total_tokens or num_seqs grow: a workspace made for the largest batch serves every smaller one.  The
+ * forward's size depends on total_tokens, num_seqs and dt only.
  * Returns 0 for invalid arguments.  Pure host arithmetic: no HIP call.
  */
 size_t hyd_varlen_attn_workspace_bytes(int total_tokens, int num_seqs, int hq, int hkv,

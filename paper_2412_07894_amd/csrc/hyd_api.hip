@@ -31,8 +31,8 @@ struct WsLayout {
     SchedLayout split;      // query side by QuerySplit tiles, where an item is not a whole tile (split > 0)
     int n_sched;
     int part_max;           // dK/dV items in parts: their number at most
-    // need: what a call cannot do without; the parts' sums take what lies behind it, up to total (see part_bytes)
-    size_t stat[kBwdStatVecs], q16, do16, k16, absmax, rope_tab, need, total;
+    // used: what the call uses; need: what it demands; the parts' sums take what lies behind, up to total (see part_bytes)
+    size_t stat[kBwdStatVecs], q16, do16, k16, absmax, rope_tab, used, need, total;
 };
 constexpr int kRopeTabEntries = 64;       // head_dim / 2 at most
 
@@ -116,7 +116,7 @@ WsLayout ws_layout(int T, int nseq, int tile0, int tile1, int split, int hq, int
     w.k16 = at;  if (copies) at += align_up(2 * (size_t)T * (size_t)hkv * (size_t)head_dim);
     w.absmax = at; if (copies) at += align_up(sizeof(uint32_t) * kPrepMaxWg);
     w.rope_tab = at; at += align_up(sizeof(double) * kRopeTabEntries);       // rotary frequency table (the *_rope calls)
-    w.need = at;
+    w.used = w.need = at;
     w.total = at + align_up(useful);
     w.part_max = useful && bytes > at ? part_limit(bytes - at, T, hkv, head_dim) : 1;
     return w;
@@ -158,8 +158,16 @@ int finest_split(hyd_dtype dt, int hq, int hkv, bool compact) {
 }
 int item_heads(int split) { return split == 2 ? 4 : 1; }
 
+// The forward's size does not depend on the heads: one workspace serves layers of different head counts.
 WsLayout fwd_layout(int T, int nseq, int hq, int hkv, int head_dim, hyd_dtype dt, bool compact) {
-    return ws_layout(T, nseq, tile_q(dt), tile_q(dt), finest_split(dt, hq, hkv, compact), hq, hkv, head_dim, dt, false, compact);
+    WsLayout w = ws_layout(T, nseq, tile_q(dt), tile_q(dt), finest_split(dt, hq, hkv, compact), hq, hkv, head_dim, dt, false, compact);
+    if (!compact) {
+        SchedLayout v;
+        size_t most = sched_layout(v, 0, T, nseq, tile_q(dt), 0, false);
+        if (dt == HYD_BF16) most = sched_layout(v, most, T, nseq, tile_q(dt) >> 2, 2, true);
+        w.need = w.total = most + align_up(sizeof(double) * kRopeTabEntries);
+    }
+    return w;
 }
 WsLayout bwd_layout(int T, int nseq, int hq, int hkv, int head_dim, hyd_dtype dt, size_t bytes = 0) {
     return ws_layout(T, nseq, tile_kv(dt), tile_q(dt), finest_split(dt, hq, hkv, false), hq, hkv, head_dim, dt, true, false, bytes);
@@ -190,7 +198,7 @@ HeadMap head_map_kv(int hkv, int grid) {
 
 hyd_status validate_common(const int32_t* cu, int num_seqs, const int32_t* cu_host, int T,
                            int max_seqlen, int hq, int hkv, int head_dim, hyd_dtype dt,
-                           const void* ws, size_t ws_bytes, bool bwd, bool compact = false) {
+                           const void* ws, size_t ws_bytes, bool bwd, bool compact = false, bool own = false) {
     if (dt != HYD_BF16 && dt != HYD_FP32) return HYD_ERR_DTYPE;
     if (T < 0 || num_seqs < 0 || max_seqlen < 0) return HYD_ERR_SHAPE;
     if (num_seqs == 0 && T != 0) return HYD_ERR_SHAPE;
@@ -213,7 +221,8 @@ hyd_status validate_common(const int32_t* cu, int num_seqs, const int32_t* cu_ho
         }
         if (longest > max_seqlen) return HYD_ERR_SHAPE;
     }
-    const size_t need = (bwd ? bwd_layout(T, num_seqs, hq, hkv, head_dim, dt) : fwd_layout(T, num_seqs, hq, hkv, head_dim, dt, compact)).need;
+    const WsLayout w = bwd ? bwd_layout(T, num_seqs, hq, hkv, head_dim, dt) : fwd_layout(T, num_seqs, hq, hkv, head_dim, dt, compact);
+    const size_t need = own ? w.used : w.need;             // own: the library's array, made for this call
     if (!ws || ((uintptr_t)ws % kAlign) != 0 || ws_bytes < need) return HYD_ERR_WORKSPACE;
     return HYD_OK;
 }
@@ -443,10 +452,10 @@ hyd_status fwd_impl(const void* q, const void* k, const void* v, const int32_t* 
                     const int32_t* ranges_host, bool ranged, int total_tokens,
                     int max_seqlen, int hq, int hkv, int head_dim, float softmax_scale,
                     hyd_dtype dt, void* o, float* lse, void* workspace,
-                    size_t workspace_bytes, void* hip_stream, float rope_base = 0.f, bool compact = false) {
+                    size_t workspace_bytes, void* hip_stream, float rope_base = 0.f, bool compact = false, bool own = false) {
     if (rope_base != 0.f && (dt != HYD_BF16 || !(rope_base > 1.f))) return dt != HYD_BF16 ? HYD_ERR_DTYPE : HYD_ERR_SHAPE;
     const hyd_status vs = validate_common(cu_seqlens, num_seqs, cu_seqlens_host, total_tokens, max_seqlen,
-                                          hq, hkv, head_dim, dt, workspace, workspace_bytes, false, compact);
+                                          hq, hkv, head_dim, dt, workspace, workspace_bytes, false, compact, own);
     if (vs != HYD_OK) return vs;
     if (ranged) {
         const hyd_status rs = validate_ranges(ranges, ranges_host, cu_seqlens_host, num_seqs, max_seqlen, dt);
@@ -703,11 +712,11 @@ hyd_status hyd_varlen_attn_fwd_noalloc(const void* q, const void* k, const void*
     if (dt != HYD_BF16 && dt != HYD_FP32) return HYD_ERR_DTYPE;
     if (!head_dim_ok(dt, head_dim)) return HYD_ERR_HEADDIM;
     // (if need be with 256-row tiles and without the second copy of the item records)
-    const bool compact = fwd_layout(total_tokens, num_seqs, hq, hkv, head_dim, dt, false).total > kScratchBytes;
-    if (compact && fwd_layout(total_tokens, num_seqs, hq, hkv, head_dim, dt, true).total > kScratchAll) return HYD_ERR_WORKSPACE;
+    const bool compact = fwd_layout(total_tokens, num_seqs, hq, hkv, head_dim, dt, false).used > kScratchBytes;
+    if (compact && fwd_layout(total_tokens, num_seqs, hq, hkv, head_dim, dt, true).used > kScratchAll) return HYD_ERR_WORKSPACE;
     // the rest of the argument checks, still before any HIP call (a stand-in for the workspace pointer)
     const hyd_status vs = validate_common(cu_seqlens, num_seqs, cu_seqlens_host, total_tokens, max_seqlen, hq, hkv, head_dim,
-                                          dt, reinterpret_cast<const void*>(kAlign), kScratchAll, false, compact);
+                                          dt, reinterpret_cast<const void*>(kAlign), kScratchAll, false, compact, true);
     if (vs != HYD_OK) return vs;
     if (total_tokens == 0 || num_seqs == 0) return HYD_OK;
     if (!q || !k || !v || !o || !lse) return HYD_ERR_NULL;
@@ -715,7 +724,7 @@ hyd_status hyd_varlen_attn_fwd_noalloc(const void* q, const void* k, const void*
     const hyd_status ds = device_info(&dev);          // first call on a device: looks the array's address up
     if (ds != HYD_OK) return ds;
     return fwd_impl(q, k, v, cu_seqlens, num_seqs, cu_seqlens_host, nullptr, nullptr, false, total_tokens, max_seqlen,
-                    hq, hkv, head_dim, softmax_scale, dt, o, lse, dev->scratch, kScratchAll, hip_stream, 0.f, compact);
+                    hq, hkv, head_dim, softmax_scale, dt, o, lse, dev->scratch, kScratchAll, hip_stream, 0.f, compact, true);
 }
 
 hyd_status hyd_varlen_attn_bwd(const void* q, const void* k, const void* v, const void* o, const float* lse,

@@ -226,6 +226,13 @@ def test_a_workspace_for_a_larger_batch_serves_smaller_ones(lib):
                                                            P, P, P, P, ctypes.c_size_t(top), N) == 1, (dt, hq, hkv, d, T)
 
 
+def test_the_forward_workspace_does_not_depend_on_the_heads(lib):
+    from paper_2412_07894_amd import binding as b
+    for dt in (0, 1):
+        for T, n in ((1, 1), (1000, 7), (16384, 12), (131072, 400), (1 << 20, 65536)):
+            assert len({b.workspace_bytes(T, n, hq, hkv, d, dt, 0) for hq, hkv in ((32, 32), (32, 8), (8, 1), (10, 10), (6, 2)) for d in (64, 128)}) == 1
+
+
 def test_room_for_partial_sums_is_asked_for_where_it_can_be_used(lib):
     """512 tokens of 32 ungrouped heads never take items in parts: no more than the statistics, copies and lists."""
     from paper_2412_07894_amd import binding as b
