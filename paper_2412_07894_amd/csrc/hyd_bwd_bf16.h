@@ -915,7 +915,8 @@ struct SumParams {
 template <int D>
 __global__ void __launch_bounds__(kSumThreads) hyd_bwd_sum_parts_kernel(SumParams p) {
     const int item = blockIdx.x, g = blockIdx.y, which = blockIdx.z / (kKvBN / kSumRows);
-    if (item >= p.hdr[0]) return;
+    // as many records handed out as items: none was cut (no long sequence, or a malformed cu_seqlens)
+    if (item >= p.hdr[0] || p.hdr[kHdrExec] == p.hdr[0]) return;
     const i32x4 rec = *reinterpret_cast<const i32x4*>(p.items + 4 * item);
     const int n = item_parts(rec[1], p.steps_per_level, p.part_q, p.part_max);
     if (n == 1) return;

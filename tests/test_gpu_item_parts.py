@@ -80,3 +80,28 @@ def test_a_smaller_workspace_takes_fewer_parts(room):
     gu.check("dk", gu.to_np(dk), rdk, "bf16")
     gu.check("dv", gu.to_np(dv), rdv, "bf16")
     assert bool((ws[-65536:] == 0x5a).all())
+
+
+def test_no_sums_are_added_where_no_item_was_cut():
+    """A decreasing cu_seqlens that holds the same rows twice asks for 16 items of 128 keys, and there are records for
+    12: items stay whole although the host expected parts, and the last two tiles get none.  dK and dV are what dK/dV
+    wrote, not sums of whatever the workspace held.  Nothing is written behind the workspace."""
+    T, hq, hkv, d, n, done = 1000, 8, 1, 128, 4, 768
+    cu = torch.tensor([0, T, 0, T, 0], dtype=torch.int32, device="cuda")
+    g = torch.Generator(device="cuda")
+    g.manual_seed(41)
+    mk = lambda h: torch.randn((T, h, d), device="cuda", generator=g).to(torch.bfloat16)
+    q, k, v, do = mk(hq), mk(hkv), mk(hkv), mk(hq)
+    one = torch.tensor([0, T], dtype=torch.int32, device="cuda")
+    o, lse = binding.varlen_attn_fwd(q, k, v, one, T, d ** -0.5)
+    _, rdk, rdv = binding.varlen_attn_bwd(q, k, v, o, lse, do, one, T, d ** -0.5)
+    size = binding.workspace_bytes(T, n, hq, hkv, d, binding.HYD_BF16, 1)
+    ws = torch.full((size + 65536,), 0xff, dtype=torch.uint8, device="cuda")      # every float of it is a NaN
+    dk, dv = torch.zeros_like(k), torch.zeros_like(v)
+    run = lambda: binding.varlen_attn_bwd(q, k, v, o, lse, do, cu, T, d ** -0.5, workspace=ws[:size], dk=dk, dv=dv)
+    assert "bwd_sum_parts" in names_of(run)
+    assert binding.schedule_status(ws, T, n, hq, hkv, d, binding.HYD_BF16, 1) == 6
+    for x, ref in ((dk, rdk), (dv, rdv)):                  # (rounded once in both cases: 2^-9 of each element)
+        assert torch.isfinite(x.float()).all() and bool((x[done:] == 0).all())
+        assert float((x[:done].double() - ref[:done].double()).norm() / ref[:done].double().norm()) < 2.0 ** -8
+    assert bool((ws[size:] == 0xff).all())
