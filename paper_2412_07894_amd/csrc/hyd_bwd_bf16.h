@@ -438,6 +438,8 @@ __global__ void __launch_bounds__(kDqThreads, 1) hyd_bwd_dq_bf16_kernel(BwdParam
                 __builtin_amdgcn_raw_ptr_buffer_load_lds(rv, (lds_void_b*)(d + kDqTileBytes), 16, dma_voff, soff, 0, 0);
             }
         };
+        const bool short_item = n_kt - t_lo <= kShortItem;
+        if (short_item) wf.claim(p.hm, p.cursors);
         dma_tile(t_lo, 0);
         {   // the item's rows of Q and dO; rows past the query range read as zeros
             const uint32_t q_bytes = (uint32_t)(min(Lq - q0, QS::kRows) - 1) * q_stride_b + (kRowB << QS::kLh);
@@ -556,7 +558,7 @@ __global__ void __launch_bounds__(kDqThreads, 1) hyd_bwd_dq_bf16_kernel(BwdParam
             if (t + 1 < n_kt) step(std::integral_constant<int, 1>{}, t + 1);
             if (t + 2 < n_kt) step(std::integral_constant<int, 2>{}, t + 2);
         }
-        wf.claim(p.hm, p.cursors);
+        if (!short_item) wf.claim(p.hm, p.cursors);
         if (active && p.rope_tab) rope_acc_inverse<D>(acc, p.rope_tab, qrow, half);     // gradient of the UNROTATED Q
         if (active)         // dQ leaves through this wave's 8 KB of the ring (free now): whole rows per store
             store_rows_via_lds<D>(p.dq + (int64_t)(row0 + wrow0) * q_stride + (int64_t)head * D, q_stride, Lq - wrow0,
@@ -707,6 +709,8 @@ __global__ void __launch_bounds__(kKvThreads, 1) hyd_bwd_dkdv_bf16_kernel(BwdPar
             __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (lds_void_b*)(smem + stage * kKvStageBytes + 2 * kKvTileBytes + which * kKvBM * 4),
                                                      4, (uint32_t)lane * 4, (uint32_t)qt * kKvBM * 4, 0, 0);
         };
+        const bool short_item = n_iter <= kShortItem;
+        if (short_item) wf.claim(p.hm, p.cursors);
         if (n_iter > 0) dma_stage(0);
         if (n_iter > 1) dma_stage(1);
 
@@ -886,7 +890,7 @@ __global__ void __launch_bounds__(kKvThreads, 1) hyd_bwd_dkdv_bf16_kernel(BwdPar
         };
         if (role_b) tiles(std::true_type{});
         else tiles(std::false_type{});
-        wf.claim(p.hm, p.cursors);
+        if (!short_item) wf.claim(p.hm, p.cursors);
         __syncthreads();                                      // every wave is done with the ring
         const int64_t out = (int64_t)(row0 + wkey0) * kv_stride + (int64_t)g * D;
         const float mul = (role_b ? p.scale : 1.f) * unscale;

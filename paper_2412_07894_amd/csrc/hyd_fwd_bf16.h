@@ -345,6 +345,8 @@ __global__ void __launch_bounds__(kFwdThreads, 1) hyd_fwd_bf16_kernel(FwdParams 
             for (int ks = 0; ks < D / 16; ++ks) qf[ks] = as_bf16x8(qv[ks] ^ sign_flip);
         }
         __builtin_amdgcn_s_barrier();                     // the staged Q may be overwritten (tile t_lo+2 goes there)
+        const bool short_item = n_kt - t_lo <= kShortItem;
+        if (short_item) wf.claim(p.hm, p.cursors);
 
         f32x16 acc_o[D / 32];
         float m_ref, l_run;
@@ -391,7 +393,7 @@ __global__ void __launch_bounds__(kFwdThreads, 1) hyd_fwd_bf16_kernel(FwdParams 
             if (t_lo + 1 < n_kt) dma_tile(t_lo + 1, 1);
             __syncthreads();
         }
-        wf.claim(p.hm, p.cursors);
+        if (!short_item) wf.claim(p.hm, p.cursors);
         // epilogue: normalise, write O (bf16) and LSE (natural log)
         float l_lo, l_hi;
         both_halves(l_run, l_lo, l_hi);

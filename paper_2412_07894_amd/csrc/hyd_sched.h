@@ -292,6 +292,11 @@ __device__ __forceinline__ void decode_work(const HeadMap& hm, int n_items, int 
 // launch: forward of 256 tokens, 32 heads 24.1 us, now 12.3; 2048 tokens, 8 heads 35.6 -> 31.5, dQ 45.3 ->
 // 42, dK/dV 40.8 -> 36.5.
 // Every workgroup ends when all queues are empty (the cursors only grow).
+// Items of up to kShortItem steps have little behind their loop for the atomic to run under, and hold nothing long: they claim before it
+// (forward: behind the barrier that ends its loads, which would wait for the atomic).  Forward / backward in us, claim
+// behind the loop -> before it: 20000 sequences of three tokens, 8 heads, d = 64 2635 / 6077 -> 2608 / 5938; 65536 of 16 tokens
+// 9230 / 21233 -> 9119 / 20843; 2000 of one token, 32/8 heads 1136 / 2105 -> 1115 / 2090.
+constexpr int kShortItem = 2;
 struct WorkItem { int seq, lev, head, row0, len; };
 constexpr int kSlotInts = 16;          // two buffers of 8 ints
 struct WorkFetcher {
