@@ -116,10 +116,13 @@ hyd_status hyd_varlen_attn_fwd(const void* q, const void* k, const void* v,
  *   d_o              device, [T][Hq][d], same dtype
  *   dq, dk, dv       device, outputs, fully overwritten (no atomics: bitwise reproducible)
  *   workspace        device, >= hyd_varlen_attn_workspace_bytes(..., 1) bytes, 256-byte aligned
- * Four kernels are enqueued after the schedule prelude (one launch for both item lists): row
- * statistics (D = rowsum(dO * O), the largest |dO| of each row and of the tensor); fp16 copies of
- * Q, K and dO; dK/dV (one work item per (sequence, key tile, KV head), looping over the group's
- * query heads); dQ (one work item per (sequence, query tile, query head)).
+ * bf16: three kernels are enqueued, four where dK/dV items are taken in parts: preparation (the item lists, row
+ * statistics D = rowsum(dO * O), the largest |dO| of each row and of the tensor, the fp16 copy of K); dQ (work items of
+ * a query tile of one or four heads; it also writes the fp16 copies of Q and dO); dK/dV (one work item per
+ * (sequence, key tile, KV head), looping over the group's query heads, or a part of that loop); the sums of the parts.
+ * Equal calls give equal bits.  Whether and how dK/dV items are cut depends on T, num_seqs, max_seqlen, the heads
+ * and the room in the workspace, so dK and dV of a sequence may differ in their last bit between batches.
+ * fp32: the lists, dQ (with D), dK/dV.
  *
  * Arithmetic of the bf16 path: the tile products run on the fp16 matrix instructions with fp32
  * accumulation, so that the factors formed in registers (P, dS) keep 11 significant bits.  bf16
@@ -191,6 +194,13 @@ hyd_status hyd_varlen_attn_schedule_status(const void* workspace, size_t workspa
  * length of the sequence), by decreasing level (paper Sec. 2.1: the cost of a sequence is
  * quadratic; level c of a sequence is its tile with c tiles of causal work, 1 <= c <=
  * ceil(length / *tile)); at most *max_items records.
+ *
+ * That is the work of the batch in tiles of *tile rows.  What the kernel takes may be cut finer (64 rows of four query
+ * heads, 128 rows, or parts of a dK/dV item) and comes in an order of its own at the cheap end.  The header leads there:
+ * [3] is the distance in bytes from this header to the header of the list that is handed out (0: this one), and in that
+ * header [2] is the number of records handed out, [4] the distance in bytes from it to the first one, [5] the rows of a
+ * tile and [6] the query heads of a record (dK/dV: 1 KV head).  Bits 24-26 of a record's level are the index of a part,
+ * bits 27-29 the number of parts of its item less one.
  */
 hyd_status hyd_varlen_attn_schedule_layout(int total_tokens, int num_seqs, int hq, int hkv,
                                            int head_dim, hyd_dtype dt, int is_bwd, int which,

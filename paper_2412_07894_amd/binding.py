@@ -5,6 +5,7 @@ exception is raised."""
 import ctypes
 import os
 
+import numpy as np
 import torch
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
@@ -317,3 +318,18 @@ def schedule_items(workspace, total_tokens, num_seqs, hq, hkv, head_dim, dtype_c
     assert 0 <= n <= cap.value
     rec = workspace[items.value:items.value + 16 * n].view(torch.int32).reshape(n, 4).cpu().numpy()
     return tile.value, rec
+
+
+def executed_items(workspace, total_tokens, num_seqs, hq, hkv, head_dim, dtype_code, is_bwd, which):
+    """The records that the kernel of a finished call took, in the order in which they were handed out: (rows of a
+    tile, heads of a record, int array [n, 6] of (sequence, level, first packed row, length, part, parts))."""
+    hdr, items, cap, tile = ctypes.c_size_t(0), ctypes.c_size_t(0), ctypes.c_int(0), ctypes.c_int(0)
+    _check(load().hyd_varlen_attn_schedule_layout(total_tokens, num_seqs, hq, hkv, head_dim, dtype_code, int(is_bwd), int(which),
+                                                  ctypes.byref(hdr), ctypes.byref(items), ctypes.byref(cap), ctypes.byref(tile)))
+    torch.cuda.synchronize()
+    words = lambda at, n: workspace[at:at + 4 * n].view(torch.int32).cpu().numpy()
+    at = hdr.value + int(words(hdr.value, 4)[3])
+    h = words(at, 7)
+    rec = words(at + int(h[4]), 4 * int(h[2])).reshape(-1, 4)
+    level, part, parts = rec[:, 1] & 0xffffff, (rec[:, 1] >> 24) & 7, ((rec[:, 1] >> 27) & 7) + 1
+    return int(h[5]), int(h[6]), np.column_stack([rec[:, 0], level, rec[:, 2], rec[:, 3], part, parts])

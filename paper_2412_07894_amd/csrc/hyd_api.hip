@@ -378,6 +378,7 @@ SchedView make_view(char* ws, const SchedLayout& v, int tile, int split, int max
     sv.group_max = v.exec == v.items || grouped_heads ? 0 : (dt == HYD_BF16 ? 1024 : 512) / tile;
     sv.group_share = (float)heads / (16.f * (float)wgs);
     sv.part_max = 1; sv.part_q = 1; sv.steps_per_level = 0;
+    sv.other = 0; sv.rec_heads = item_heads(split);
     return sv;
 }
 
@@ -474,9 +475,10 @@ hyd_status fwd_impl(const void* q, const void* k, const void* v, const int32_t* 
     const WsLayout w = fwd_layout(total_tokens, num_seqs, hq, hkv, head_dim, dt, compact);
     const int occ = dt == HYD_BF16 ? dev->occ_fwd : dev->occ_f32[head_dim == 128][0];
     // where items are not whole tiles, the list of whole tiles is built too, next to the one that is
-    // handed out (hyd_varlen_attn_schedule_layout shows it)
+    // handed out (hyd_varlen_attn_schedule_layout shows the first and its header leads to the second)
     const bool grouped = hq >= 4 * hkv;
-    const SchedView sv_whole = make_view(static_cast<char*>(workspace), w.sched[0], tile, 0, max_seqlen, dt, units, dev->cus * occ, grouped);
+    SchedView sv_whole = make_view(static_cast<char*>(workspace), w.sched[0], tile, 0, max_seqlen, dt, units, dev->cus * occ, grouped);
+    if (split) sv_whole.other = (int)(w.split.hdr - w.sched[0].hdr);
     const SchedView sv = split ? make_view(static_cast<char*>(workspace), w.split, 256 >> split, split, max_seqlen, dt, units, dev->cus * occ, grouped) : sv_whole;
     double* rope_tab = rope_base != 0.f ? reinterpret_cast<double*>(static_cast<char*>(workspace) + w.rope_tab) : nullptr;
     {
@@ -547,7 +549,8 @@ hyd_status bwd_impl(const void* q, const void* k, const void* v, const void* o, 
     const bool grouped = hq >= 4 * hkv;
     SchedView sv_kv = make_view(ws, w.sched[0], tile_kv(dt), 0, max_seqlen, dt, hkv, dev->cus * occ_kv, grouped);
     if (dt == HYD_BF16) set_parts(sv_kv, w.part_max, total_tokens, num_seqs, max_seqlen, hq, hkv, dev->cus * occ_kv);
-    const SchedView sv_whole = make_view(ws, w.sched[1], tile_q(dt), 0, max_seqlen, dt, units, dev->cus * occ_q, grouped);
+    SchedView sv_whole = make_view(ws, w.sched[1], tile_q(dt), 0, max_seqlen, dt, units, dev->cus * occ_q, grouped);
+    if (split) sv_whole.other = (int)(w.split.hdr - w.sched[1].hdr);
     const SchedView sv_q = split ? make_view(ws, w.split, 256 >> split, split, max_seqlen, dt, units, dev->cus * occ_q, grouped) : sv_whole;
     float* Dvec = reinterpret_cast<float*>(ws + w.stat[0]);
     double* rope_tab = rope_base != 0.f ? reinterpret_cast<double*>(ws + w.rope_tab) : nullptr;

@@ -23,12 +23,13 @@ constexpr int kQueues = 8;
 typedef __attribute__((ext_vector_type(4))) int i32x4;
 
 // header (ints): [0] n_items, [1] kSched* flags about cu_seqlens as the prelude saw it, [2] records
-// handed out, the rest zeros; then the cursors of the eight queues, 256 bytes apart: the workgroups of all XCDs claim
+// handed out, [3] bytes from here to the header of the list that is handed out in this one's place (0: this one is), [4] bytes from
+// here to the records handed out, [5] rows of a tile, [6] heads of a record, the rest zeros; then the cursors of the eight queues, 256 bytes apart: the workgroups of all XCDs claim
 // through them with device-scope atomics, which a shared line serialises (one line for all eight:
 // forward of 26177 tokens in sequences of 64-1024, 32 heads, d = 64: 227 us, apart 216)
 constexpr int kHdrInts = 64, kCursorStride = 64;
 constexpr int kHdrCursor = kHdrInts, kHdrTotal = kHdrInts + kQueues * kCursorStride;
-constexpr int kHdrFlags = 1, kHdrExec = 2;
+constexpr int kHdrFlags = 1, kHdrExec = 2, kHdrOther = 3, kHdrRecords = 4, kHdrTile = 5, kHdrHeads = 6;
 constexpr int kSchedTooLong = 1;          // a sequence is longer than max_seqlen: its tiles beyond that bound got no item
 constexpr int kSchedBadSeqlens = 2;       // cu_seqlens does not start at 0, does not end at T, or decreases
 
@@ -43,6 +44,7 @@ struct SchedView {            // device pointers into the workspace (all int32)
     int n_lev;                // upper bound on tiles per sequence
     int max_items;
     int part_max, part_q, steps_per_level;     // items in parts (see item_parts); part_max = 1: whole
+    int other, rec_heads;     // header words kHdrOther, kHdrHeads
 };
 
 // An item can be handed out in parts (dK/dV kernel): level c, with c * steps_per_level steps, in
@@ -146,7 +148,13 @@ __device__ __forceinline__ void build_schedule(const int32_t* __restrict__ cu, i
     const int n_items = nl > 0 ? min(offs[nl - 1], sv.max_items) : 0;
     // more items than any valid cu_seqlens has: positions of the grouped order would lie outside the records
     if (nl > 0 && offs[nl - 1] > sv.max_items) C = 0;
-    if (tid == 0) sv.hdr[0] = n_items;
+    if (tid == 0) {
+        sv.hdr[0] = n_items;
+        sv.hdr[kHdrOther] = sv.other;
+        sv.hdr[kHdrRecords] = (int)((const char*)sv.exec - (const char*)sv.hdr);
+        sv.hdr[kHdrTile] = tile;
+        sv.hdr[kHdrHeads] = sv.rec_heads;
+    }
     for (int i = tid; i < nl + 2; i += nthreads) hist[i] = 0;
     __syncthreads();
     // rank of a sequence with n tiles = (#sequences with more tiles) + arrival order among equals

@@ -176,3 +176,55 @@ def test_prelude_reports_what_it_saw_in_device_seqlens():
     assert binding.schedule_status(ws, T, nseq, hq, hkv, d, code, 0) == 6
     binding.varlen_attn_fwd(q, k, v, cu, 700, 0.1, workspace=ws)         # and a good call clears the flags again
     assert binding.schedule_status(ws, T, nseq, hq, hkv, d, code, 0) == 0
+
+
+@pytest.mark.parametrize("lengths,hq,hkv,dtype,form", [
+    ([700, 64, 1, 300, 0, 129, 256, 257] * 40, 16, 16, "bf16", (256, 1)),       # whole tiles, the cheap end sequence by sequence
+    ([700, 64, 1, 300, 0, 129, 256, 257] * 40, 16, 4, "bf16", (64, 4)),         # four heads
+    ([1000, 40, 7], 8, 8, "bf16", (128, 1)),                                    # half tiles, dK/dV in parts
+    ([1300, 7, 129], 8, 1, "bf16", (128, 1)),
+    ([300, 1, 0, 65] * 30, 4, 2, "fp32", (64, 1)),
+])
+def test_what_is_handed_out_is_the_work_of_the_batch(lengths, hq, hkv, dtype, form, d=64):
+    """The records the kernels took, read back: every tile of every sequence exactly once in the form that is
+    handed out, whole or in all of its parts; by decreasing level but for an end that follows sequence by sequence."""
+    from oracle import sched_oracle as so
+    cu_np = wl.cu_seqlens(lengths)
+    T, nseq, ml = int(cu_np[-1]), len(lengths), int(max(lengths))
+    cu = torch.from_numpy(cu_np).cuda()
+    g = torch.Generator(device="cuda"); g.manual_seed(13)
+    dt, code = (torch.bfloat16, binding.HYD_BF16) if dtype == "bf16" else (torch.float32, binding.HYD_FP32)
+    mk = lambda h: torch.randn((T, h, d), device="cuda", dtype=torch.float32, generator=g).to(dt)
+    q, k, v, do = mk(hq), mk(hkv), mk(hkv), mk(hq)
+    ws_f = torch.empty(binding.workspace_bytes(T, nseq, hq, hkv, d, code, 0), dtype=torch.uint8, device="cuda")
+    ws_b = torch.empty(binding.workspace_bytes(T, nseq, hq, hkv, d, code, 1), dtype=torch.uint8, device="cuda")
+    o, lse = binding.varlen_attn_fwd(q, k, v, cu, ml, 0.1, workspace=ws_f)
+    binding.enable_kernel_timing(True)
+    binding.varlen_attn_bwd(q, k, v, o, lse, do, cu, ml, 0.1, workspace=ws_b)
+    names = [n for n, _ in binding.kernel_times()]
+    binding.enable_kernel_timing(False)
+    for ws, is_bwd, which, name in ((ws_f, 0, 0, "forward"), (ws_b, 1, 0, "dK/dV"), (ws_b, 1, 1, "dQ")):
+        tile, heads, rec = binding.executed_items(ws, T, nseq, hq, hkv, d, code, is_bwd, which)
+        cut = int((rec[:, 5] > 1).sum())
+        print(f"{name}: {len(rec)} records of {tile} rows, {heads} heads, {cut} of them parts", flush=True)
+        assert (tile, heads) == (form if name != "dK/dV" else (128 if dtype == "bf16" else 32, 1)), name
+        assert (cut > 0) == (name == "dK/dV" and "bwd_sum_parts" in names), name
+        whole = [tuple(r[:4]) for r in rec.tolist() if r[4] == 0]
+        assert sorted(whole) == sorted(so.records(lengths, tile)), name
+        for r in rec[rec[:, 5] > 1]:                       # all parts of an item, in turn
+            i = int(np.flatnonzero((rec == r).all(axis=1))[0])
+            assert (rec[i - r[4]:i - r[4] + r[5], 4] == np.arange(r[5])).all() and (rec[i - r[4]:i - r[4] + r[5], :4] == r[:4]).all(), name
+        assert any(_handed_out_in_order(rec, c) for c in range(int(rec[:, 1].max()) + 1)), name
+
+
+def _handed_out_in_order(rec, c):
+    """Records above level c by decreasing level, then those of levels up to c sequence by sequence, highest first."""
+    head = rec[:, 1] > c
+    n = int(head.sum())
+    if not head[:n].all() or (np.diff(rec[:n, 1]) > 0).any():
+        return False
+    want = []
+    for r in rec[n:]:
+        if r[4] == 0 and (not want or want[-1][0] != r[0]):
+            want += [(int(r[0]), x) for x in range(int(r[1]), 0, -1)]
+    return want == [(int(r[0]), int(r[1])) for r in rec[n:] if r[4] == 0]
