@@ -1,9 +1,9 @@
 #!/usr/bin/env python3
 """Benchmark of the hot path: packed varlen causal attention, forward + backward, on one MI355X.
 
-One "step" is one forward call plus one backward call (schedule preludes, forward kernel, row
-statistics and fp16 operand copies, dK/dV kernel, dQ kernel) over one synthetic packed batch that
-is already resident in HBM.  By default the four bf16 configurations of the benchmark spec (2-5) are
+One "step" is one forward call plus one backward call (schedule prelude, forward kernel; item lists, row
+statistics and fp16 copy of K in one launch, dQ kernel, dK/dV kernel) over one synthetic packed batch that
+is already resident in HBM.  By default the four bf16 configurations (2-5 of workloads.py) are
 timed one after the other, each for `--steps` steps after `--warmup` warm-up steps, and the
 headline is the SLOWEST of them (lowest useful TFLOP/s); `--config N` times one configuration
 only (this is what the rocprofv3 runs under profiles/ use).  Prints ONE JSON line:
@@ -125,7 +125,7 @@ def run_gpu(cid, steps, warmup, inputs="randn"):
         per_step = [sum(ms for _, ms in recorded[i * n:(i + 1) * n]) for i in range(steps)]
     ms_per_step = (t1 - t0) * 1e3 / steps
     pairs = wl.causal_pairs(lengths)
-    # per launch; the schedule prelude runs twice per step (forward; backward: one launch builds the lists of dK/dV and dQ)
+    # per launch; the schedule prelude is the forward's (the backward's preparation kernel builds its lists; fp32: a prelude of its own)
     kernels = {n: sum(x) / len(x) for n, x in per_kernel.items()}
     return cfg, lengths, pairs, ms_per_step, kernels, per_step
 
@@ -290,7 +290,7 @@ def config_result(cid, steps, warmup, inputs):
         alg = 6.0 * cfg.d * cfg.hq * pairs
         ach = alg / (kernels[dom] * 1e-3) / 1e12
         peak = PEAK_BF16_TFLOPS if cfg.dtype == "bf16" else 157.3
-        res["roofline"] = {"kernel": dom, "bound": "mfma" if cfg.dtype == "bf16" else "alu", "achieved": ach,
+        res["roofline"] = {"kernel": dom, "bound": "mfma", "achieved": ach,
                            "peak": peak, "unit": "TFLOP/s", "frac": ach / peak, "traffic": measured_traffic(cfg.cid, dom),
                            "avg_ms": kernels[dom]}
     return res

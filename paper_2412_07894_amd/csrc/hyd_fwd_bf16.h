@@ -19,7 +19,7 @@
 // overflows: bf16 and fp32 keep the relative precision of a probability whatever its size.  So the
 // row maximum is taken over the FIRST tile only, and later tiles are not searched for a larger
 // score (16 three-way maxima and an exchange per tile and wave, 6 % of the kernel): what a larger
-// score does to the row sum l is looked at afterwards.  When l has passed 2^kRefSlack, O and l are
+// score does to the row sum l is looked at afterwards.  When l has passed kRefSlack, O and l are
 // scaled back by a power of two and m_ref moves up by its exponent (beyond 2^24, where a float no longer
 // holds every integer, by what it can, and O and l by as much).  A probability or an O that reaches 2^128
 // overflows on the spot; the checks there and, for sums between 2^8 and 2^24, behind the item's last tile find O or l
