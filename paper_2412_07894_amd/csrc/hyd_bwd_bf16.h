@@ -85,8 +85,8 @@ struct PartialMaxima {
 // initial value of its dP accumulator.
 //
 // Bound by HBM on large batches (5 TB/s, the rate of a copy) and by latency on small ones, hence
-// the split by tokens: a workgroup takes 32 of them at most, fewer as soon as that leaves less than
-// kPrepTarget workgroups.  The range variant skips the rows of dO outside a visit's query range and
+// the split by tokens: a workgroup takes 32 of them at most, fewer as long as kPrepTarget workgroups, four
+// for each CU, do (a few more than that make five on some: 32000 tokens, 32 heads in 1033 workgroups 232 us, in 1000 190).  The range variant skips the rows of dO outside a visit's query range and
 // the rows of K outside its key range, which nothing reads.
 // Measured (MI355X, this pass with the item lists; before: 32 tokens per workgroup, one row in
 // flight, sixteen lanes for a 128-byte row too, and a launch of its own for the lists, 7 us):
@@ -98,8 +98,8 @@ constexpr int kPrepThreads = 256, kPrepTarget = 1024;
 inline int prep_tokens(int T, int hq) {
     int t = 4096 / (hq > 0 ? hq : 1);                      // statistics of a workgroup within 32 KB of LDS
     t = t > 32 ? 32 : t;
-    if (t > T / kPrepTarget) t = T / kPrepTarget;
-    return t < 1 ? 1 : t;
+    const int few = (T + kPrepTarget - 1) / kPrepTarget;
+    return t < 1 || few < 1 ? 1 : (t > few ? few : t);
 }
 inline int prep_workgroups(int T, int tok) {
     const int n = (T + tok - 1) / tok;

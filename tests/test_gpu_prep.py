@@ -1,5 +1,5 @@
 """The backward's preparation pass splits the tokens over its workgroups by batch size: one token per
-workgroup below 2048 tokens, a ragged last block, partial maxima of |dO| whose count is no multiple
+workgroup up to 1024 tokens, a ragged last block, partial maxima of |dO| whose count is no multiple
 of four.  The largest |dO| of the tensor sits in the last row, the only one its workgroup sees, and
 is so much larger that dO would leave the range of fp16 if that workgroup's maximum got lost.
 
@@ -19,8 +19,8 @@ pytestmark = pytest.mark.gpu
 @pytest.mark.parametrize("lengths,hq,hkv", [
     ([1], 2, 1),
     ([1000, 23], 4, 2),                  # one token per workgroup
-    ([1500, 1499, 0, 2], 2, 1),          # two per workgroup, a last block of one token (its dK would be zero in a sequence of its own)
-    ([2100, 1030, 993], 3, 3),           # four per workgroup
+    ([1500, 1499, 0, 2], 2, 1),          # three per workgroup, a last block of one token (its dK would be zero in a sequence of its own)
+    ([2100, 1030, 993], 3, 3),           # five per workgroup
 ])
 def test_preparation_pass_splits(lengths, hq, hkv, d):
     cu, q, k, v, do = wl.custom(lengths, hq, hkv, d, "bf16", seed=91)
