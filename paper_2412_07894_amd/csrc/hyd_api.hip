@@ -775,16 +775,13 @@ hyd_status hyd_attn_merge(const void* o_a, const float* lse_a, const void* o_b, 
     const hyd_status ds = device_info(&dev);
     if (ds != HYD_OK) return ds;
     hipStream_t st = static_cast<hipStream_t>(hip_stream);
-    const long long rows = (long long)total_tokens * hq;
     {
         KernelTimer kt("merge_bf16", st);
-        const dim3 mgrid((unsigned)((rows + 15) / 16));
-        if (head_dim == 64)
-            hipLaunchKernelGGL(hyd_merge_bf16_kernel<64>, mgrid, dim3(256), 0, st, static_cast<const uint16_t*>(o_a), lse_a,
-                               static_cast<const uint16_t*>(o_b), lse_b, static_cast<uint16_t*>(o_out), lse_out, total_tokens, hq);
-        else
-            hipLaunchKernelGGL(hyd_merge_bf16_kernel<kHeadDim>, mgrid, dim3(256), 0, st, static_cast<const uint16_t*>(o_a), lse_a,
-                               static_cast<const uint16_t*>(o_b), lse_b, static_cast<uint16_t*>(o_out), lse_out, total_tokens, hq);
+        const int chunks = merge_chunks(hq);
+        const dim3 mgrid((unsigned)((total_tokens + kMergeTok - 1) / kMergeTok) * (unsigned)chunks);
+        const auto kernel = head_dim == 64 ? hyd_merge_bf16_kernel<64> : hyd_merge_bf16_kernel<kHeadDim>;
+        hipLaunchKernelGGL(kernel, mgrid, dim3(kMergeThreads), 0, st, static_cast<const uint16_t*>(o_a), lse_a,
+                           static_cast<const uint16_t*>(o_b), lse_b, static_cast<uint16_t*>(o_out), lse_out, total_tokens, hq, chunks);
     }
     return hipGetLastError() == hipSuccess ? HYD_OK : HYD_ERR_LAUNCH;
 }

@@ -3,46 +3,83 @@
 // the keys of partial x, the softmax over the union of the keys is
 //     LSE = ln(exp(LSE_a) + exp(LSE_b)),   O = exp(LSE_a - LSE) O_a + exp(LSE_b - LSE) O_b;
 // a partial that saw no key carries LSE = -inf and O = 0 and is the neutral element.
-// Purely HBM-bound: 16 lanes per row, 16 bytes per lane, every byte read and written once.
+//
+// Bound by HBM, so rows that need no work are not touched: a visit of a context-parallel ring merges buffers
+// of all T rows of which only the rank's own carry a partial, and where LSE_b = -inf (or LSE_a) a merge in place
+// leaves the other partial's row as it is.  A workgroup takes 32 tokens of up to 8 heads: the weights of its rows are
+// formed first, a thread per row, so that the [Hq][T] vectors are read and written in runs of 32
+// floats; then kLanes lanes per row move 16 bytes each, four rows in flight.  Measured (16384 tokens, 32 heads): a merge
+// in place of 3030 tokens' rows 64 us before (event times), 27 now.
 #pragma once
 #include "hyd_device.h"
 
 namespace hyd {
 
-// o_out / lse_out may alias either input (each lane reads what it overwrites before writing it).
+constexpr int kMergeThreads = 256, kMergeTok = 32, kMergeHeads = 8;
+inline int merge_chunks(int hq) { return (hq + kMergeHeads - 1) / kMergeHeads; }      // of the heads
+
+// o_out / lse_out may alias either input (what is overwritten has been read before).
 template <int D = kHeadDim>
-__global__ void __launch_bounds__(256) hyd_merge_bf16_kernel(const uint16_t* o_a, const float* lse_a,
-                                                            const uint16_t* o_b, const float* lse_b,
-                                                            uint16_t* o_out, float* lse_out, int T, int hq) {
-    const int64_t n_rows = (int64_t)T * hq;
-    const int64_t row = (int64_t)blockIdx.x * 16 + (threadIdx.x >> 4);
-    const int c = threadIdx.x & 15;
-    if (row >= n_rows || (D != kHeadDim && c >= D / 8)) return;
-    const int t = (int)(row / hq), h = (int)(row % hq);
-    const int64_t si = (int64_t)h * T + t;
-    const float la = lse_a[si], lb = lse_b[si];
-    const float m = fmaxf(la, lb);
-    float ca = 0.f, cb = 0.f, lse = -INFINITY;
-    if (m > -INFINITY) {
-        constexpr float kL2e = 1.44269504088896340736f, kLn2 = 0.69314718055994530942f;
-        const float wa = __builtin_amdgcn_exp2f((la - m) * kL2e), wb = __builtin_amdgcn_exp2f((lb - m) * kL2e);
-        const float tot = wa + wb;                        // in [1, 2]
-        lse = m + __builtin_amdgcn_logf(tot) * kLn2;
-        const float inv = 1.f / tot;
-        ca = wa * inv; cb = wb * inv;
+__global__ void __launch_bounds__(kMergeThreads) hyd_merge_bf16_kernel(const uint16_t* o_a, const float* lse_a,
+                                                                       const uint16_t* o_b, const float* lse_b,
+                                                                       uint16_t* o_out, float* lse_out, int T, int hq, int chunks) {
+    __shared__ float wt[2][kMergeTok * kMergeHeads];
+    const int tid = threadIdx.x, per = (hq + chunks - 1) / chunks;             // heads of a chunk
+    const int t0 = (int)(blockIdx.x / (unsigned)chunks) * kMergeTok, h0 = (int)(blockIdx.x % (unsigned)chunks) * per;
+    const int nt = min(kMergeTok, T - t0), nh = min(per, hq - h0);
+    if (nh <= 0) return;
+    {
+        const int tl = tid % kMergeTok, hl = tid / kMergeTok;
+        if (tl < nt && hl < nh) {
+            const int64_t si = (int64_t)(h0 + hl) * T + t0 + tl;
+            const float la = lse_a[si], lb = lse_b[si];
+            const float m = fmaxf(la, lb);
+            float ca = 0.f, cb = 0.f, lse = -INFINITY;
+            if (m > -INFINITY) {
+                constexpr float kL2e = 1.44269504088896340736f, kLn2 = 0.69314718055994530942f;
+                const float wa = __builtin_amdgcn_exp2f((la - m) * kL2e), wb = __builtin_amdgcn_exp2f((lb - m) * kL2e);
+                const float tot = wa + wb;                        // in [1, 2]
+                lse = m + __builtin_amdgcn_logf(tot) * kLn2;
+                const float inv = 1.f / tot;
+                ca = wa * inv; cb = wb * inv;
+            }
+            wt[0][tl * per + hl] = ca;
+            wt[1][tl * per + hl] = cb;
+            lse_out[si] = lse;
+        }
     }
-    const u32x4 a = *reinterpret_cast<const u32x4*>(o_a + row * D + c * 8);
-    const u32x4 b = *reinterpret_cast<const u32x4*>(o_b + row * D + c * 8);
-    u32x4 r;
+    __syncthreads();
+    constexpr int kLanes = D / 8, kGrps = kMergeThreads / kLanes, kU = 4;      // lanes per row, rows at a time, of them in flight
+    const int c = tid % kLanes, n_rows = nt * per;
+    const bool in_a = o_out == o_a, in_b = o_out == o_b;
+    for (int r0 = tid / kLanes; r0 < n_rows; r0 += kGrps * kU) {
+        u32x4 a[kU], b[kU];
+        float ca[kU], cb[kU];
+        int64_t at[kU];
+        bool on[kU];
 #pragma unroll
-    for (int e = 0; e < 4; ++e) {
-        // a weight of zero must also silence a partial whose unwritten rows hold non-finite bits
-        const float lo = (ca != 0.f ? ca * bf16_lo(a[e]) : 0.f) + (cb != 0.f ? cb * bf16_lo(b[e]) : 0.f);
-        const float hi = (ca != 0.f ? ca * bf16_hi(a[e]) : 0.f) + (cb != 0.f ? cb * bf16_hi(b[e]) : 0.f);
-        r[e] = pack_bf16(lo, hi);
+        for (int u = 0; u < kU; ++u) {
+            const int r = r0 + kGrps * u, tl = r / per, hl = r - tl * per;
+            on[u] = r < n_rows && hl < nh;
+            ca[u] = cb[u] = 0.f;
+            if (on[u]) { ca[u] = wt[0][r]; cb[u] = wt[1][r]; }
+            // the whole weight on the row that is there already
+            if ((in_a && ca[u] == 1.f && cb[u] == 0.f) || (in_b && cb[u] == 1.f && ca[u] == 0.f)) on[u] = false;
+            at[u] = ((int64_t)(t0 + tl) * hq + h0 + hl) * D + c * 8;
+            a[u] = b[u] = u32x4{0u, 0u, 0u, 0u};
+            // a weight of zero must also silence a partial whose unwritten rows hold non-finite bits: it is not read
+            if (on[u] && ca[u] != 0.f) a[u] = *reinterpret_cast<const u32x4*>(o_a + at[u]);
+            if (on[u] && cb[u] != 0.f) b[u] = *reinterpret_cast<const u32x4*>(o_b + at[u]);
+        }
+#pragma unroll
+        for (int u = 0; u < kU; ++u) {
+            u32x4 r;
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+                r[e] = pack_bf16(ca[u] * bf16_lo(a[u][e]) + cb[u] * bf16_lo(b[u][e]), ca[u] * bf16_hi(a[u][e]) + cb[u] * bf16_hi(b[u][e]));
+            if (on[u]) *reinterpret_cast<u32x4*>(o_out + at[u]) = r;
+        }
     }
-    *reinterpret_cast<u32x4*>(o_out + row * D + c * 8) = r;
-    if (c == 0) lse_out[si] = lse;
 }
 
 }  // namespace hyd

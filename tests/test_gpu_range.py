@@ -280,3 +280,31 @@ def test_config2_ring_at_full_size():
     idx = torch.from_numpy((cu[s] + cols).astype(np.int64)).cuda()
     gu.check("dk[keys]", gu.to_np(tot[1][idx, g]), rk, "bf16")
     gu.check("dv[keys]", gu.to_np(tot[2][idx, g]), rv, "bf16")
+
+
+@pytest.mark.parametrize("T,hq,d", [(1, 1, 128), (31, 8, 64), (33, 9, 128), (65, 17, 64), (70, 33, 128), (32, 40, 128)])
+def test_merge_rows_without_a_partial_stay(T, hq, d):
+    """Blocks of 32 tokens and up to 8 heads, with remainders of both: in place, a row of weight one keeps its bits
+    (a negative zero among them) next to rows that are merged, and the other partial's row is not looked at."""
+    rng = np.random.default_rng(T + hq)
+    mk = lambda: wl.bf16_bits_to_f32(wl.f32_to_bf16_bits(rng.standard_normal((T, hq, d)).astype(np.float32)))
+    oa, ob = mk(), mk()
+    oa[0, 0, 0] = -0.0
+    la = rng.uniform(-3, 3, size=(hq, T)).astype(np.float32)
+    lb = rng.uniform(-3, 3, size=(hq, T)).astype(np.float32)
+    blind = rng.random((hq, T))
+    blind[0, 0] = 0.0
+    lb[blind < 0.6] = -np.inf
+    la[blind > 0.9] = -np.inf
+    o_ref, l_ref = rorc.merge(oa, la, ob, lb)
+    a, b = gu.to_dev(oa, "bf16"), gu.to_dev(ob, "bf16")
+    a0, keep = a.clone(), torch.from_numpy((blind < 0.6).T.copy()).cuda()
+    b[keep] = float("nan")
+    lda, ldb = torch.from_numpy(la).cuda(), torch.from_numpy(lb).cuda()
+    o, l = binding.attn_merge(a, lda, b, ldb)
+    binding.attn_merge(a, lda, b, ldb, out=a, lse_out=lda)
+    torch.cuda.synchronize()
+    gu.check("o", gu.to_np(o), o_ref, "bf16")
+    assert np.array_equal(np.isneginf(gu.to_np(l)), np.isneginf(l_ref))
+    assert torch.equal(a, o) and torch.equal(lda, l)
+    assert torch.equal(a[keep].view(torch.int16), a0[keep].view(torch.int16))
