@@ -156,6 +156,12 @@ int query_split(hyd_dtype dt, int T, int nseq, int max_seqlen, int hq, int hkv, 
 int finest_split(hyd_dtype dt, int hq, int hkv, bool compact) {
     return dt != HYD_BF16 || compact ? 0 : ((hq / hkv) % 4 == 0 ? 2 : 1);
 }
+// Batches of up to so many (token, head) pairs run dK/dV beside dQ in one launch: each of the two leaves most of the chip
+// idle and lasts as long as its longest item.  dK/dV converts dO itself then, which costs it a fifth where the chip is
+// full.  Backward, one launch after the other -> beside each other (log-normal lengths, d = 128): 8 heads, 1500 tokens 70 -> 51
+// us, 3000 tokens 103 -> 80, 6000 184 -> 164 (8/1 heads 187 -> 191, one sequence 318 -> 383); 32 heads, 700 tokens 56 -> 48, 1500
+// 93 -> 86 (32/8 heads 94 -> 94), 3000 200 -> 208.
+constexpr long long kBothRows = 40960;
 int item_heads(int split) { return split == 2 ? 4 : 1; }
 
 // The forward's size does not depend on the heads: one workspace serves layers of different head counts.
@@ -291,7 +297,7 @@ bool prep_f32(int* occ) {
 
 // [form of the items, then range variant][head_dim == 64]
 typedef void (*FwdKernel)(FwdParams);
-typedef void (*BwdKernel)(BwdParams);
+typedef void (*BwdKernel)(BwdParams, WorkList);
 constexpr FwdKernel kFwdKernels[4][2] = {{hyd_fwd_bf16_kernel<false, 128, 0>, hyd_fwd_bf16_kernel<false, 64, 0>},
                                          {hyd_fwd_bf16_kernel<false, 128, 1>, hyd_fwd_bf16_kernel<false, 64, 1>},
                                          {hyd_fwd_bf16_kernel<false, 128, 2>, hyd_fwd_bf16_kernel<false, 64, 2>},
@@ -300,6 +306,11 @@ constexpr BwdKernel kDqKernels[4][2] = {{hyd_bwd_dq_bf16_kernel<false, 128, 0>, 
                                         {hyd_bwd_dq_bf16_kernel<false, 128, 1>, hyd_bwd_dq_bf16_kernel<false, 64, 1>},
                                         {hyd_bwd_dq_bf16_kernel<false, 128, 2>, hyd_bwd_dq_bf16_kernel<false, 64, 2>},
                                         {hyd_bwd_dq_bf16_kernel<true, 128, 0>, hyd_bwd_dq_bf16_kernel<true, 64, 0>}};
+
+typedef void (*BothKernel)(BwdParams, WorkList, WorkList, int);
+constexpr BothKernel kBothKernels[3][2] = {{hyd_bwd_both_bf16_kernel<128, 0>, hyd_bwd_both_bf16_kernel<64, 0>},
+                                           {hyd_bwd_both_bf16_kernel<128, 1>, hyd_bwd_both_bf16_kernel<64, 1>},
+                                           {hyd_bwd_both_bf16_kernel<128, 2>, hyd_bwd_both_bf16_kernel<64, 2>}};
 
 hyd_status device_info(DeviceInfo** out) {
     int dev = 0;
@@ -317,6 +328,8 @@ hyd_status device_info(DeviceInfo** out) {
                 if (!prep_kernel(kFwdKernels[i / 2][i % 2], kFwdThreads, kFwdLds, &d.occ_fwd) ||
                     !prep_kernel(kDqKernels[i / 2][i % 2], kDqThreads, kDqLds, &d.occ_dq))
                     return HYD_ERR_LAUNCH;
+            for (int i = 0; i < 6; ++i)
+                if (!prep_kernel(kBothKernels[i / 2][i % 2], kKvThreads, kBothLds, nullptr)) return HYD_ERR_LAUNCH;
             if (!prep_kernel(hyd_bwd_dkdv_bf16_kernel<false>, kKvThreads, kKvLds, &d.occ_kv) ||
                 !prep_kernel(hyd_bwd_dkdv_bf16_kernel<true>, kKvThreads, kKvLds, nullptr) ||
                 !prep_kernel(hyd_bwd_dkdv_bf16_kernel<false, 64>, kKvThreads, kKvLds, nullptr) ||
@@ -564,10 +577,12 @@ hyd_status bwd_impl(const void* q, const void* k, const void* v, const void* o, 
         sc.q16 = reinterpret_cast<uint16_t*>(ws + w.q16);
         sc.do16 = reinterpret_cast<uint16_t*>(ws + w.do16);
         sc.k16 = reinterpret_cast<uint16_t*>(ws + w.k16);
+        const bool both = !ranged && !rope_tab && (long long)total_tokens * hq <= kBothRows;
         // item lists of both tile kernels and the row statistics in one launch
         {
             PrepParams pp;
             pp.o = static_cast<const uint16_t*>(o); pp.d_o = static_cast<const uint16_t*>(d_o); pp.lse = lse; pp.k = static_cast<const uint16_t*>(k);
+            pp.q = static_cast<const uint16_t*>(q);
             pp.T = total_tokens; pp.hq = hq; pp.hkv = hkv; pp.tok = prep_tokens(total_tokens, hq);
             sc.absmax = reinterpret_cast<uint32_t*>(ws + w.absmax);
             sc.n_absmax = prep_workgroups(total_tokens, pp.tok);
@@ -581,11 +596,10 @@ hyd_status bwd_impl(const void* q, const void* k, const void* v, const void* o, 
             const dim3 grid((unsigned)(pp.n_sched + sc.n_absmax)), block(kPrepThreads);
             const size_t lds = prep_lds(hq, pp.tok, schedule_lds(sv_kv.n_lev, sv_whole.n_lev, sv_q.n_lev));
             KernelTimer kt("bwd_prep_bf16", st);
-            if (head_dim == 64) {
-                if (ranged) hipLaunchKernelGGL((hyd_bwd_prep_bf16_kernel<true, 64>), grid, block, lds, st, pp);
-                else hipLaunchKernelGGL((hyd_bwd_prep_bf16_kernel<false, 64>), grid, block, lds, st, pp);
-            } else if (ranged) hipLaunchKernelGGL(hyd_bwd_prep_bf16_kernel<true>, grid, block, lds, st, pp);
-            else hipLaunchKernelGGL(hyd_bwd_prep_bf16_kernel<false>, grid, block, lds, st, pp);
+            const auto kernel = both ? (head_dim == 64 ? hyd_bwd_prep_bf16_kernel<false, 64, true> : hyd_bwd_prep_bf16_kernel<false, 128, true>)
+                : ranged ? (head_dim == 64 ? hyd_bwd_prep_bf16_kernel<true, 64> : hyd_bwd_prep_bf16_kernel<true, 128>)
+                         : (head_dim == 64 ? hyd_bwd_prep_bf16_kernel<false, 64> : hyd_bwd_prep_bf16_kernel<false, 128>);
+            hipLaunchKernelGGL(kernel, grid, block, lds, st, pp);
         }
         BwdParams p;
         p.q = static_cast<const uint16_t*>(q); p.v = static_cast<const uint16_t*>(v); p.d_o = static_cast<const uint16_t*>(d_o);
@@ -596,27 +610,31 @@ hyd_status bwd_impl(const void* q, const void* k, const void* v, const void* o, 
         p.tr = t_trace;
         p.ranges = ranged ? ranges : nullptr;
         p.rope_tab = rope_tab;
-        // dQ first: it also writes the fp16 copies of Q and dO that dK/dV streams
-        {
-            p.hdr = sv_q.hdr; p.items = sv_q.exec;
-            p.cursors = sv_q.hdr + kHdrCursor;
-            const dim3 grid(persistent_grid(*dev, occ_q, work_q));
-            p.hm = head_map_q(units, hkv, grid.x);
-            KernelTimer kt(ranged ? "bwd_dq_range_bf16" : "bwd_dq_bf16", st);
-            hipLaunchKernelGGL(kDqKernels[ranged ? 3 : split][head_dim == 64], grid, dim3(kDqThreads), kDqLds, st, p);
-        }
-        {
-            p.hdr = sv_kv.hdr + kHdrExec; p.items = sv_kv.exec;
-            p.part = reinterpret_cast<float*>(ws + w.need); p.part_max = sv_kv.part_max;
-            p.cursors = sv_kv.hdr + kHdrCursor;
-            const dim3 grid(persistent_grid(*dev, occ_kv, work_kv));
-            p.hm = head_map_kv(hkv, grid.x);
+        p.part = reinterpret_cast<float*>(ws + w.need); p.part_max = sv_kv.part_max;
+        const int grid_q = persistent_grid(*dev, occ_q, work_q), grid_kv = persistent_grid(*dev, occ_kv, work_kv);
+        WorkList lq{sv_q.hdr, sv_q.hdr + kHdrCursor, sv_q.exec, head_map_q(units, hkv, grid_q)};
+        WorkList lkv{sv_kv.hdr + kHdrExec, sv_kv.hdr + kHdrCursor, sv_kv.exec, head_map_kv(hkv, grid_kv)};
+        if (both) {
+            // the workgroups of dK/dV: one per item where there is room for all items, else four of seven (its share of the products)
+            int n_kv = dev->cus * 4 / 7;
+            if (n_kv < dev->cus - work_q) n_kv = (int)(dev->cus - work_q);
+            if (n_kv > work_kv) n_kv = (int)work_kv;
+            n_kv = (n_kv + kQueues - 1) / kQueues * kQueues;           // queue by XCD on both sides
+            int n_q = dev->cus - n_kv;
+            if (n_q > work_q) n_q = (int)work_q;
+            if (n_q < 0) n_q = 0;
+            lkv.hm.grid = n_kv; lq.hm.grid = n_q;
+            KernelTimer kt("bwd_both_bf16", st);
+            hipLaunchKernelGGL(kBothKernels[split][head_dim == 64], dim3(n_kv + n_q), dim3(kKvThreads), kBothLds, st, p, lkv, lq, n_kv);
+        } else {
+            {   // dQ first: it also writes the fp16 copies of Q and dO that dK/dV streams
+                KernelTimer kt(ranged ? "bwd_dq_range_bf16" : "bwd_dq_bf16", st);
+                hipLaunchKernelGGL(kDqKernels[ranged ? 3 : split][head_dim == 64], dim3(grid_q), dim3(kDqThreads), kDqLds, st, p, lq);
+            }
             KernelTimer kt(ranged ? "bwd_dkdv_range_bf16" : "bwd_dkdv_bf16", st);
-            if (head_dim == 64) {
-                if (ranged) hipLaunchKernelGGL((hyd_bwd_dkdv_bf16_kernel<true, 64>), grid, dim3(kKvThreads), kKvLds, st, p);
-                else hipLaunchKernelGGL((hyd_bwd_dkdv_bf16_kernel<false, 64>), grid, dim3(kKvThreads), kKvLds, st, p);
-            } else if (ranged) hipLaunchKernelGGL(hyd_bwd_dkdv_bf16_kernel<true>, grid, dim3(kKvThreads), kKvLds, st, p);
-            else hipLaunchKernelGGL(hyd_bwd_dkdv_bf16_kernel<false>, grid, dim3(kKvThreads), kKvLds, st, p);
+            const BwdKernel kernel = ranged ? (head_dim == 64 ? hyd_bwd_dkdv_bf16_kernel<true, 64> : hyd_bwd_dkdv_bf16_kernel<true, 128>)
+                                            : (head_dim == 64 ? hyd_bwd_dkdv_bf16_kernel<false, 64> : hyd_bwd_dkdv_bf16_kernel<false, 128>);
+            hipLaunchKernelGGL(kernel, dim3(grid_kv), dim3(kKvThreads), kKvLds, st, p, lkv);
         }
         if (sv_kv.part_max > 1) {
             SumParams sp;

@@ -41,13 +41,13 @@ __device__ __forceinline__ float pow2i(int k) { return __uint_as_float((uint32_t
 
 // Row statistics and scratch of the backward, all in the caller's workspace.
 struct BwdScratch {
-    float* Dq;          // [Hq][T]  -D,  D = rowsum(dO * O)                          (dQ kernel)
+    float* Dq;          // [Hq][T]  -D,  D = rowsum(dO * O)                          (dQ kernel; small batches: dK/dV too)
     float* kqmul;       // [Hq][T]  2^-kq, kq = shift_of(row max |dO|)               (dQ kernel: row scale and its inverse)
     float* lse2;        // [Hq][T]  -LSE * log2(e)                                   (both kernels)
     float* Dkv;         // [Hq][T]  -D * 2^kg, kg = shift_of(max |dO| of the tensor) (dK/dV kernel; written by dQ)
     uint32_t* absmax;   // [n_absmax, zeros up to a multiple of 4] maxima over parts of dO of the 15-bit magnitude pattern, one per workgroup of the statistics pass
     int n_absmax;
-    uint16_t* q16;      // [T][Hq][d]  fp16 copy of Q          (written by the dQ kernel, read by dK/dV)
+    uint16_t* q16;      // [T][Hq][d]  fp16 copy of Q          (written by the dQ kernel, in small batches by the statistics pass; read by dK/dV)
     uint16_t* do16;     // [T][Hq][d]  fp16 copy of dO * 2^kg  (written by the dQ kernel, read by dK/dV)
     uint16_t* k16;      // [T][Hkv][d] fp16 copy of K          (written by the statistics pass)
 };
@@ -111,6 +111,7 @@ inline size_t prep_lds(int hq, int tok, size_t schedule) {
 }
 struct PrepParams {
     const uint16_t* o; const uint16_t* d_o; const float* lse; const uint16_t* k;
+    const uint16_t* q;                                     // kCopyQ only
     BwdScratch sc;
     int T, hq, hkv, tok;
     const int32_t* cu; int nseq;
@@ -119,7 +120,8 @@ struct PrepParams {
     double* rope_tab; double log2_base;
 };
 
-template <bool R, int HD = kHeadDim>
+// kCopyQ: the fp16 copy of Q too, for a dK/dV that runs beside dQ (small batches)
+template <bool R, int HD = kHeadDim, bool kCopyQ = false>
 __global__ void __launch_bounds__(kPrepThreads) hyd_bwd_prep_bf16_kernel(PrepParams p) {
     extern __shared__ float st[];                  // [2][hq][tok]: -D, kq; then [tok] row flags (range variant)
     const int tid = threadIdx.x;
@@ -155,7 +157,7 @@ __global__ void __launch_bounds__(kPrepThreads) hyd_bwd_prep_bf16_kernel(PrepPar
         constexpr int kU = 4;                      // rows in flight
         const int n_rows = nt * hq;
         for (int r0 = grp; r0 < n_rows; r0 += kGrps * kU) {       // row r of the block = (token t0 + r / hq, head r % hq)
-            u32x4 a[kU], b[kU];
+            u32x4 a[kU], b[kU], q[kU];
             bool on[kU];
 #pragma unroll
             for (int u = 0; u < kU; ++u) {
@@ -163,6 +165,7 @@ __global__ void __launch_bounds__(kPrepThreads) hyd_bwd_prep_bf16_kernel(PrepPar
                 on[u] = r < n_rows && (!R || (flags[r / hq] & 1));
                 a[u] = u32x4{0u, 0u, 0u, 0u};
                 b[u] = u32x4{0u, 0u, 0u, 0u};
+                if (kCopyQ && on[u]) q[u] = *reinterpret_cast<const u32x4*>(p.q + ((int64_t)t0 * hq + r) * HD + c * 8);
                 if (on[u]) {
                     const int64_t at = ((int64_t)t0 * hq + r) * HD + c * 8;
                     a[u] = *reinterpret_cast<const u32x4*>(p.o + at);
@@ -190,6 +193,12 @@ __global__ void __launch_bounds__(kPrepThreads) hyd_bwd_prep_bf16_kernel(PrepPar
                     st[(hq + h) * tok + tl] = (float)shift_of(amax);
                 }
                 gmax = max(gmax, amax);
+                if (kCopyQ && on[u]) {
+                    u32x4 q16;
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) q16[e] = bf16x2_to_f16x2(q[u][e]);
+                    *reinterpret_cast<u32x4*>(p.sc.q16 + ((int64_t)t0 * hq + r) * HD + c * 8) = q16;
+                }
             }
         }
         for (int r0 = grp; r0 < nt * hkv; r0 += kGrps * kU) {     // the K rows of the same tokens
@@ -240,13 +249,14 @@ struct BwdParams {
     float* part;                      // dK/dV: [2][part_max][T][Hkv][d] sums of the items in parts (dK first)
     int part_max;
     float scale, scale_log2;
-    const int* hdr; int* cursors; const int* items;
-    HeadMap hm;
     WgTrace tr;
     const int32_t* ranges;            // range variants only: per sequence (q_begin, q_end, kv_begin, kv_end)
     const double* rope_tab;           // NULL, or the rotary frequency table: the dQ kernel rotates Q as it picks it up
                                       // (the fp16 copy it writes is the rotated Q) and turns dQ back before writing it
 };
+
+// The records of a tile kernel and how they are shared out.
+struct WorkList { const int* hdr; int* cursors; const int* items; HeadMap hm; };
 
 // ---------------------------------------------------------------------------------------------
 // dQ.  Work item = (sequence, query tile, query heads), 256 or 128 (row, head) pairs (see QuerySplit); each of 8
@@ -352,13 +362,14 @@ __device__ __forceinline__ void dq_block(int Kt, int Vt, const FragAddr& fa, int
 
 // R: range variant (see the forward kernel): query tiles outside the query range are skipped,
 // the tile loop covers the key range only, dQ holds that key range's contribution.
-template <bool R, int D = kHeadDim, int S = 0>
-__global__ void __launch_bounds__(kDqThreads, 1) hyd_bwd_dq_bf16_kernel(BwdParams p) {
+// kCopies: this kernel writes what dK/dV streams (else the preparation has).
+// wg: see WorkFetcher::first.
+template <bool R, int D, int S, bool kCopies>
+__device__ __forceinline__ void dq_items(const BwdParams& p, const WorkList& list, char* smem, int wg) {
     using QS = QuerySplit<S>;
     static_assert(D == 128 || D == 64, "head dimension");
     constexpr int kRowB = D * 2;                                      // bytes of a row in global memory
     static_assert(kDqBM == 256 && kDqStages == 3, "the Q / dO staging assumes a 256-row tile and a 3-stage ring");
-    extern __shared__ __attribute__((aligned(16))) char smem[];
     int* slot = reinterpret_cast<int*>(smem + kDqQxOff);
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -383,13 +394,13 @@ __global__ void __launch_bounds__(kDqThreads, 1) hyd_bwd_dq_bf16_kernel(BwdParam
     const float scale_log2 = fmaxf(fabsf(p.scale_log2), 1e-30f);
     const uint32_t sign_flip = p.scale_log2 < 0.f ? 0x80008000u : 0u;
     PartialMaxima pm;
-    pm.load(p.sc, lane);
+    if (kCopies) pm.load(p.sc, lane);
     const bool wave_first_half = half == 0;                           // both halves of a wave hold the same rows
 
     WorkFetcher wf;
     WorkItem wi;
-    bool have = wf.first(p.hm, p.hdr, p.cursors, p.items, slot, wi);
-    const float up = pow2i(pm.shift());                               // 2^kg
+    bool have = wf.first(list.hm, list.hdr, list.cursors, list.items, slot, wi, wg);
+    const float up = kCopies ? pow2i(pm.shift()) : 1.f;                               // 2^kg
     while (have) {
         ++n_done;
         __syncthreads();                                  // everybody has read the work slot: its bytes may be overwritten
@@ -400,7 +411,7 @@ __global__ void __launch_bounds__(kDqThreads, 1) hyd_bwd_dq_bf16_kernel(BwdParam
             const i32x4 rg = *reinterpret_cast<const i32x4*>(p.ranges + 4 * wi.seq);
             Lq = min(L, rg[1]); kb = max(rg[2], 0); kcap = min(L, rg[3]);
             if (q0 < rg[0] || q0 >= Lq) {
-                have = wf.next(p.hm, p.cursors, p.items, slot, wi);
+                have = wf.next(list.hm, list.cursors, list.items, slot, wi);
                 continue;
             }
         }
@@ -420,7 +431,7 @@ __global__ void __launch_bounds__(kDqThreads, 1) hyd_bwd_dq_bf16_kernel(BwdParam
 #pragma unroll
                 for (int i = 0; i < D / 8; ++i) *reinterpret_cast<u32x2*>(op + 8 * i) = z;
             }
-            have = wf.next(p.hm, p.cursors, p.items, slot, wi);
+            have = wf.next(list.hm, list.cursors, list.items, slot, wi);
             continue;
         }
         const int td = wrow0 / kDqBN;                     // this wave's diagonal (= last) tile
@@ -439,7 +450,7 @@ __global__ void __launch_bounds__(kDqThreads, 1) hyd_bwd_dq_bf16_kernel(BwdParam
             }
         };
         const bool short_item = n_kt - t_lo <= kShortItem;
-        if (short_item) wf.claim(p.hm, p.cursors);
+        if (short_item) wf.claim(list.hm, list.cursors);
         dma_tile(t_lo, 0);
         {   // the item's rows of Q and dO; rows past the query range read as zeros
             const uint32_t q_bytes = (uint32_t)(min(Lq - q0, QS::kRows) - 1) * q_stride_b + (kRowB << QS::kLh);
@@ -455,7 +466,7 @@ __global__ void __launch_bounds__(kDqThreads, 1) hyd_bwd_dq_bf16_kernel(BwdParam
             lse2 = p.sc.lse2[(int64_t)head * p.T + row0 + qrow];
             Dq = p.sc.Dq[(int64_t)head * p.T + row0 + qrow];
             unshift = p.sc.kqmul[(int64_t)head * p.T + row0 + qrow];
-            if (wave_first_half) p.sc.Dkv[(int64_t)head * p.T + row0 + qrow] = Dq * up;
+            if (kCopies && wave_first_half) p.sc.Dkv[(int64_t)head * p.T + row0 + qrow] = Dq * up;
         }
         // 2^kq, the exact reciprocal of the power of two 2^-kq; rows past the range keep 1
         const float shift = qvalid ? __uint_as_float((254u << 23) - __float_as_uint(unshift)) : 1.f;
@@ -486,37 +497,39 @@ __global__ void __launch_bounds__(kDqThreads, 1) hyd_bwd_dq_bf16_kernel(BwdParam
 #pragma unroll
                     for (int e = 0; e < 4; ++e) a[ks][e] = bf16x2_to_f16x2(a[ks][e]);
             }
-            // What the dK/dV kernel streams: the fp16 Q rows and dO * 2^kg.  Each wave puts its 32 rows
-            // back where it took them from (nobody else touches those bytes) and sends them out from
-            // there in 16-byte pieces of whole rows: four whole rows per store instruction.
-            typedef __attribute__((address_space(3))) u32x4 lds_u32x4_w;
-#pragma unroll
-            for (int ks = 0; ks < D / 16; ++ks) {
-                u32x4 s16;
-#pragma unroll
-                for (int e = 0; e < 4; ++e) s16[e] = bf16x2_to_f16x2(b[ks][e], up);
-                *(lds_u32x4_w*)(uintptr_t)(fa.row[ks] + (uint32_t)(kDqQxOff + row_stage)) = a[ks];
-                *(lds_u32x4_w*)(uintptr_t)(fa.row[ks] + (uint32_t)(kDqStageBytes + row_stage)) = s16;
-            }
-            // (the lane index is laundered so that these addresses are formed here: hoisted above the
-            // tile loop as lane constants they would occupy some 20 registers through it)
-            int ln = lane;
-            asm volatile("" : "+v"(ln));
-            const int cr = ln >> 4, ch = ln & 15;
-            const uint32_t wbase = (uint32_t)(uintptr_t)(lds_char*)smem + (uint32_t)(row_stage + cr * kRowBytes);
-            const int64_t goff = (int64_t)(row0 + wrow0 + cr) * q_stride + (int64_t)head * D + ch * 8;
-#pragma unroll
-            for (int which = 0; which < 2; ++which) {
-                uint16_t* dst = (which ? p.sc.do16 : p.sc.q16) + goff;
-                u32x4 x[8];
-#pragma unroll
-                for (int i = 0; i < 8; ++i)                 // row cr + 4 i of the wave: swz = (cr << 2) | (i & 3)
-                    x[i] = *(lds_u32x4*)(uintptr_t)(wbase + (uint32_t)((which ? kDqStageBytes : kDqQxOff) + 4 * i * kRowBytes +
-                                                                      ((ch ^ ((cr << 2) | (i & 3))) << 4)));
-#pragma unroll
-                for (int i = 0; i < 8; ++i)
-                    if (wrow0 + cr + 4 * i < Lq && (D == kHeadDim || ch < D / 8))
-                        *reinterpret_cast<u32x4*>(dst + (int64_t)(4 * i) * q_stride) = x[i];
+            if constexpr (kCopies) {
+                // What the dK/dV kernel streams: the fp16 Q rows and dO * 2^kg.  Each wave puts its 32 rows
+                // back where it took them from (nobody else touches those bytes) and sends them out from
+                // there in 16-byte pieces of whole rows: four whole rows per store instruction.
+                typedef __attribute__((address_space(3))) u32x4 lds_u32x4_w;
+    #pragma unroll
+                for (int ks = 0; ks < D / 16; ++ks) {
+                    u32x4 s16;
+    #pragma unroll
+                    for (int e = 0; e < 4; ++e) s16[e] = bf16x2_to_f16x2(b[ks][e], up);
+                    *(lds_u32x4_w*)(uintptr_t)(fa.row[ks] + (uint32_t)(kDqQxOff + row_stage)) = a[ks];
+                    *(lds_u32x4_w*)(uintptr_t)(fa.row[ks] + (uint32_t)(kDqStageBytes + row_stage)) = s16;
+                }
+                // (the lane index is laundered so that these addresses are formed here: hoisted above the
+                // tile loop as lane constants they would occupy some 20 registers through it)
+                int ln = lane;
+                asm volatile("" : "+v"(ln));
+                const int cr = ln >> 4, ch = ln & 15;
+                const uint32_t wbase = (uint32_t)(uintptr_t)(lds_char*)smem + (uint32_t)(row_stage + cr * kRowBytes);
+                const int64_t goff = (int64_t)(row0 + wrow0 + cr) * q_stride + (int64_t)head * D + ch * 8;
+    #pragma unroll
+                for (int which = 0; which < 2; ++which) {
+                    uint16_t* dst = (which ? p.sc.do16 : p.sc.q16) + goff;
+                    u32x4 x[8];
+    #pragma unroll
+                    for (int i = 0; i < 8; ++i)                 // row cr + 4 i of the wave: swz = (cr << 2) | (i & 3)
+                        x[i] = *(lds_u32x4*)(uintptr_t)(wbase + (uint32_t)((which ? kDqStageBytes : kDqQxOff) + 4 * i * kRowBytes +
+                                                                          ((ch ^ ((cr << 2) | (i & 3))) << 4)));
+    #pragma unroll
+                    for (int i = 0; i < 8; ++i)
+                        if (wrow0 + cr + 4 * i < Lq && (D == kHeadDim || ch < D / 8))
+                            *reinterpret_cast<u32x4*>(dst + (int64_t)(4 * i) * q_stride) = x[i];
+                }
             }
             __builtin_amdgcn_s_waitcnt(0xc07f);           // lgkmcnt(0): the staging areas have been read
 #pragma unroll
@@ -558,14 +571,20 @@ __global__ void __launch_bounds__(kDqThreads, 1) hyd_bwd_dq_bf16_kernel(BwdParam
             if (t + 1 < n_kt) step(std::integral_constant<int, 1>{}, t + 1);
             if (t + 2 < n_kt) step(std::integral_constant<int, 2>{}, t + 2);
         }
-        if (!short_item) wf.claim(p.hm, p.cursors);
+        if (!short_item) wf.claim(list.hm, list.cursors);
         if (active && p.rope_tab) rope_acc_inverse<D>(acc, p.rope_tab, qrow, half);     // gradient of the UNROTATED Q
         if (active)         // dQ leaves through this wave's 8 KB of the ring (free now): whole rows per store
             store_rows_via_lds<D>(p.dq + (int64_t)(row0 + wrow0) * q_stride + (int64_t)head * D, q_stride, Lq - wrow0,
                                acc, p.scale * unshift, o_stage, lane);
-        have = wf.next(p.hm, p.cursors, p.items, slot, wi);
+        have = wf.next(list.hm, list.cursors, list.items, slot, wi);
     }
     trace_write(p.tr, 2, t_start, n_done);
+}
+
+template <bool R, int D = kHeadDim, int S = 0>
+__global__ void __launch_bounds__(kDqThreads, 1) hyd_bwd_dq_bf16_kernel(BwdParams p, WorkList list) {
+    extern __shared__ __attribute__((aligned(16))) char smem[];
+    dq_items<R, D, S, true>(p, list, smem, blockIdx.x);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -595,19 +614,20 @@ __global__ void __launch_bounds__(kDqThreads, 1) hyd_bwd_dq_bf16_kernel(BwdParam
 constexpr int kKvPairs = 4, kKvWaves = 2 * kKvPairs;
 constexpr int kKvBN = 32 * kKvPairs, kKvBM = 64, kKvThreads = 64 * kKvWaves, kKvStages = 3;
 constexpr int kKvTileBytes = kKvBM * kRowBytes;                       // 16 KB
-constexpr int kKvStageBytes = 2 * kKvTileBytes + 2 * kKvBM * 4;       // Q, dO, LSE2, D
 constexpr int kKvPBytes = 64 * 16 * 4;                                // P buffer of a block (64 lanes x 16 values; fp16 fills half)
+constexpr int kKvStageBytes = 2 * kKvTileBytes + 2 * kKvBM * 4;       // Q, dO, LSE2, D
 constexpr int kKvPOff = kKvStages * kKvStageBytes;                    // P exchange: [pair][2][kKvPBytes]
 constexpr int kKvLds = kKvPOff + kKvPairs * 2 * kKvPBytes + 64;
 
+// kRaw: the caller's bf16 dO and -D are streamed instead of what the dQ kernel leaves; each wave converts the
+// pieces of a dO tile that it has loaded, in LDS, before the barrier that opens the tile, with the same bits as result.
 // R: range variant (see the forward kernel): key tiles outside the key range are skipped, the
 // query tiles run over the query range only, dK / dV hold that query range's contribution.
-template <bool R, int D = kHeadDim>
-__global__ void __launch_bounds__(kKvThreads, 1) hyd_bwd_dkdv_bf16_kernel(BwdParams p) {
+template <bool R, int D, bool kRaw>
+__device__ __forceinline__ void dkdv_items(const BwdParams& p, const WorkList& list, char* smem, int wg) {
     static_assert(D == 128 || D == 64, "head dimension");
     constexpr int kRowB = D * 2;                                      // bytes of a row in global memory
     constexpr int NK = D / 16, NDB = D / 32;
-    extern __shared__ __attribute__((aligned(16))) char smem[];
     int* slot = reinterpret_cast<int*>(smem + kKvPOff + kKvPairs * 2 * kKvPBytes);
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -647,8 +667,9 @@ __global__ void __launch_bounds__(kKvThreads, 1) hyd_bwd_dkdv_bf16_kernel(BwdPar
 
     WorkFetcher wf;
     WorkItem wi;
-    bool have = wf.first(p.hm, p.hdr, p.cursors, p.items, slot, wi);
-    const float unscale = pow2i(-pm.shift());                         // 2^-kg
+    bool have = wf.first(list.hm, list.hdr, list.cursors, list.items, slot, wi, wg);
+    const int kg = pm.shift();
+    const float unscale = pow2i(-kg), up = kRaw ? pow2i(kg) : 1.f;    // 2^-kg, 2^kg
     while (have) {
         ++n_done;
         const int lev = wi.lev & ((1 << kLevBits) - 1), g = wi.head, row0 = wi.row0, L = wi.len;
@@ -660,7 +681,7 @@ __global__ void __launch_bounds__(kKvThreads, 1) hyd_bwd_dkdv_bf16_kernel(BwdPar
             const i32x4 rg = *reinterpret_cast<const i32x4*>(p.ranges + 4 * wi.seq);
             qb = rg[0]; Lq = min(L, rg[1]); Lk = min(L, rg[3]);
             if (j0 < rg[2] || j0 >= Lk) {                     // the whole key tile is outside the range
-                have = wf.next(p.hm, p.cursors, p.items, slot, wi);
+                have = wf.next(list.hm, list.cursors, list.items, slot, wi);
                 continue;
             }
         }
@@ -691,7 +712,7 @@ __global__ void __launch_bounds__(kKvThreads, 1) hyd_bwd_dkdv_bf16_kernel(BwdPar
             if (++ld_h == G) { ld_h = 0; ++ld_qt; }
             const int64_t base = (int64_t)row0 * q_stride + (int64_t)h * D;
             const __amdgpu_buffer_rsrc_t rq = make_rsrc(p.sc.q16 + base, q_bytes);
-            const __amdgpu_buffer_rsrc_t rdo = make_rsrc(p.sc.do16 + base, q_bytes);
+            const __amdgpu_buffer_rsrc_t rdo = make_rsrc((kRaw ? p.d_o : p.sc.do16) + base, q_bytes);
             char* dst = smem + stage * kKvStageBytes + 4 * wave * kRowBytes;
 #pragma unroll
             for (int j = 0; j < 16 / kKvWaves; ++j) {
@@ -700,17 +721,28 @@ __global__ void __launch_bounds__(kKvThreads, 1) hyd_bwd_dkdv_bf16_kernel(BwdPar
                 __builtin_amdgcn_raw_ptr_buffer_load_lds(rq, (lds_void_b*)d, 16, dma_voff, soff, 0, 0);
                 __builtin_amdgcn_raw_ptr_buffer_load_lds(rdo, (lds_void_b*)(d + kKvTileBytes), 16, dma_voff, soff, 0, 0);
             }
-            // LSE2 and D of the tile's 64 rows: one 256-byte load each, by waves 0 and 1 (the other
+            // the statistics of the tile's 64 rows: one 256-byte load each, by waves 0 and 1 (the other
             // waves repeat wave 1's load so that all waves count alike); rows past the sequence
             // read as 0, which is harmless because their Q and dO rows are 0 too
             const int which = wave == 0 ? 0 : 1;
-            const float* src = (which == 0 ? p.sc.lse2 : p.sc.Dkv) + (int64_t)h * p.T + row0;
+            const float* src = (which == 0 ? p.sc.lse2 : (kRaw ? p.sc.Dq : p.sc.Dkv)) + (int64_t)h * p.T + row0;
             const __amdgpu_buffer_rsrc_t rs = make_rsrc(src, stat_bytes);
             __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (lds_void_b*)(smem + stage * kKvStageBytes + 2 * kKvTileBytes + which * kKvBM * 4),
                                                      4, (uint32_t)lane * 4, (uint32_t)qt * kKvBM * 4, 0, 0);
         };
+        // this wave's 16-byte pieces of the dO tile in `stage`, bf16 -> fp16 * 2^kg (they must have landed; see the
+        // fragment reads in hyd_device.h for the assembly)
+        auto convert_stage = [&](int stage) {
+            static_assert(kKvWaves * 4 * kRowBytes == 8192 && 16 / kKvWaves == 2, "two pieces per lane, 8 KB apart");
+            const uint32_t at = (uint32_t)(uintptr_t)(lds_char*)smem + (uint32_t)(stage * kKvStageBytes + kKvTileBytes + 4 * wave * kRowBytes + lane * 16);
+            u32x4 v0, v1;
+            asm volatile("ds_read_b128 %0, %2\n\tds_read_b128 %1, %2 offset:8192\n\ts_waitcnt lgkmcnt(0)" : "=&v"(v0), "=&v"(v1) : "v"(at) : "memory");
+#pragma unroll
+            for (int e = 0; e < 4; ++e) { v0[e] = bf16x2_to_f16x2(v0[e], up); v1[e] = bf16x2_to_f16x2(v1[e], up); }
+            asm volatile("ds_write_b128 %0, %1\n\tds_write_b128 %0, %2 offset:8192" : : "v"(at), "v"(v0), "v"(v1) : "memory");
+        };
         const bool short_item = n_iter <= kShortItem;
-        if (short_item) wf.claim(p.hm, p.cursors);
+        if (short_item) wf.claim(list.hm, list.cursors);
         if (n_iter > 0) dma_stage(0);
         if (n_iter > 1) dma_stage(1);
 
@@ -729,6 +761,12 @@ __global__ void __launch_bounds__(kKvThreads, 1) hyd_bwd_dkdv_bf16_kernel(BwdPar
         for (int db = 0; db < NDB; ++db)
 #pragma unroll
             for (int r = 0; r < 16; ++r) acc[db][r] = 0.f;
+        if constexpr (kRaw) {
+            __builtin_amdgcn_s_waitcnt(0x0F70);               // vmcnt(0)
+            if (n_iter > 0) convert_stage(0);
+            if (n_iter > 1) convert_stage(1);
+            __builtin_amdgcn_s_waitcnt(0xc07f);               // lgkmcnt(0)
+        }
         __syncthreads();                                      // stages 0 and 1 and the K / V rows have landed
         // this wave's register operand of the first product: K rows (role A, fp16 already) or V
         // rows (role B, converted from bf16 here)
@@ -776,7 +814,7 @@ __global__ void __launch_bounds__(kKvThreads, 1) hyd_bwd_dkdv_bf16_kernel(BwdPar
                     f32x4 i4 = {0.f, 0.f, 0.f, 0.f};
                     if (kB) i4 = *reinterpret_cast<const f32x4*>(stat + 32 * ib + 8 * rq + 4 * half);
 #pragma unroll
-                    for (int e = 0; e < 4; ++e) x[4 * rq + e] = i4[e];
+                    for (int e = 0; e < 4; ++e) x[4 * rq + e] = kRaw && kB ? i4[e] * up : i4[e];
                 }
                 // role A's -LSE2 values are requested before the product, so that they are there when
                 // the scores are (LDS reads return in order: the first fragment's wait covers them)
@@ -879,6 +917,7 @@ __global__ void __launch_bounds__(kKvThreads, 1) hyd_bwd_dkdv_bf16_kernel(BwdPar
             // step ago and precede this step's loads in the (in-order) vmcnt queue
             if (more2) __builtin_amdgcn_s_waitcnt(0x0F70 | (kDmaPerStage & 15) | ((kDmaPerStage >> 4) << 14));
             else __builtin_amdgcn_s_waitcnt(0x0F70);          // vmcnt(0)
+            if constexpr (kRaw) { if (it > 0 && it + 1 < n_iter) convert_stage((ST + 1) % kKvStages); }      // (0 and 1 are)
             block(role_tag, base, 1, 1, qt0);
         };
         auto tiles = [&](auto role_tag) {
@@ -890,7 +929,7 @@ __global__ void __launch_bounds__(kKvThreads, 1) hyd_bwd_dkdv_bf16_kernel(BwdPar
         };
         if (role_b) tiles(std::true_type{});
         else tiles(std::false_type{});
-        if (!short_item) wf.claim(p.hm, p.cursors);
+        if (!short_item) wf.claim(list.hm, list.cursors);
         __syncthreads();                                      // every wave is done with the ring
         const int64_t out = (int64_t)(row0 + wkey0) * kv_stride + (int64_t)g * D;
         const float mul = (role_b ? p.scale : 1.f) * unscale;
@@ -899,9 +938,35 @@ __global__ void __launch_bounds__(kKvThreads, 1) hyd_bwd_dkdv_bf16_kernel(BwdPar
         else if (active)
             store_rows_f32_via_lds<D>(p.part + ((role_b ? 0 : p.part_max) + part) * (int64_t)p.T * kv_stride + out, kv_stride,
                                       Lk - wkey0, acc, mul, o_stage, lane);
-        have = wf.next(p.hm, p.cursors, p.items, slot, wi);
+        have = wf.next(list.hm, list.cursors, list.items, slot, wi);
     }
     trace_write(p.tr, 1, t_start, n_done);
+}
+
+template <bool R, int D = kHeadDim>
+__global__ void __launch_bounds__(kKvThreads, 1) hyd_bwd_dkdv_bf16_kernel(BwdParams p, WorkList list) {
+    extern __shared__ __attribute__((aligned(16))) char smem[];
+    dkdv_items<R, D, false>(p, list, smem, blockIdx.x);
+}
+
+// ---------------------------------------------------------------------------------------------
+// dK/dV and dQ of a small batch in one launch: the first n_kv workgroups take dK/dV items, the others dQ
+// items, and who finds no more dK/dV work goes on with dQ's.  Bound by the longest dK/dV item (a step of 64 rows 1.7 us, 2.1 with
+// the conversion of dO); 2048 tokens, 8 heads: dQ 36 + dK/dV 38 us before, together 50.  (The same the other way
+// round, dQ's workgroups helping with dK/dV, takes registers enough to cost more than it gives: 46 -> 54 us.)
+// ---------------------------------------------------------------------------------------------
+constexpr int kBothLds = kDqLds > kKvLds ? kDqLds : kKvLds;
+template <int D, int S>
+__global__ void __launch_bounds__(kKvThreads, 1) hyd_bwd_both_bf16_kernel(BwdParams p, WorkList kv, WorkList q, int n_kv) {
+    static_assert(kKvThreads == kDqThreads, "one launch");
+    extern __shared__ __attribute__((aligned(16))) char smem[];
+    int wg = (int)blockIdx.x - n_kv;
+    if (wg < 0) {
+        wg = -1 - (int)blockIdx.x;
+        dkdv_items<false, D, true>(p, kv, smem, blockIdx.x);
+        __syncthreads();                                      // the last work slot has been read
+    }
+    dq_items<false, D, S, false>(p, q, smem, wg);
 }
 
 // ---------------------------------------------------------------------------------------------

@@ -394,7 +394,7 @@ __global__ void __launch_bounds__(64 * kF32Waves, 1) hyd_fwd_fp32_kernel(F32Para
     fl.init(lane, wave, split, smem, stride_b);
     WorkFetcher wf;
     WorkItem wi;
-    for (bool have = wf.first(p.hm, p.hdr, p.cursors, p.items, slot, wi); have; have = wf.next(p.hm, p.cursors, p.items, slot, wi)) {
+    for (bool have = wf.first(p.hm, p.hdr, p.cursors, p.items, slot, wi, blockIdx.x); have; have = wf.next(p.hm, p.cursors, p.items, slot, wi)) {
         const int head = wi.head, row0 = wi.row0, L = wi.len;
         bool rows = L <= kF32Short;
         if (rows) {
@@ -519,7 +519,7 @@ __global__ void __launch_bounds__(64 * kF32Waves, 1) hyd_bwd_dq_fp32_kernel(F32P
     fl.init(lane, wave, split, smem, stride_b);
     WorkFetcher wf;
     WorkItem wi;
-    for (bool have = wf.first(p.hm, p.hdr, p.cursors, p.items, slot, wi); have; have = wf.next(p.hm, p.cursors, p.items, slot, wi)) {
+    for (bool have = wf.first(p.hm, p.hdr, p.cursors, p.items, slot, wi, blockIdx.x); have; have = wf.next(p.hm, p.cursors, p.items, slot, wi)) {
         const int head = wi.head, row0 = wi.row0, L = wi.len;
         bool rows = kRows || (D == 64 && L <= kF32Short);
         if (rows) {
@@ -619,7 +619,7 @@ __global__ void __launch_bounds__(64 * kF32KvWaves, 1) hyd_bwd_dkdv_fp32_kernel(
     fl.init(lane, split, split, smem, stride_b);
     WorkFetcher wf;
     WorkItem wi;
-    for (bool have = wf.first(p.hm, p.hdr, p.cursors, p.items, slot, wi); have; have = wf.next(p.hm, p.cursors, p.items, slot, wi)) {
+    for (bool have = wf.first(p.hm, p.hdr, p.cursors, p.items, slot, wi, blockIdx.x); have; have = wf.next(p.hm, p.cursors, p.items, slot, wi)) {
         const int g = wi.head, row0 = wi.row0, L = wi.len;
         bool rows = kRows || (D == 64 && L <= kF32Short);
         if (rows) {

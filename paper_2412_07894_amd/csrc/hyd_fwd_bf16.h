@@ -269,7 +269,7 @@ __global__ void __launch_bounds__(kFwdThreads, 1) hyd_fwd_bf16_kernel(FwdParams 
 
     WorkFetcher wf;
     WorkItem wi;
-    bool have = wf.first(p.hm, p.hdr, p.cursors, p.items, slot, wi);
+    bool have = wf.first(p.hm, p.hdr, p.cursors, p.items, slot, wi, blockIdx.x);
     while (have) {
         ++n_done;
         const int lev = wi.lev, head0 = wi.head << QS::kLh, row0 = wi.row0, L = wi.len;
