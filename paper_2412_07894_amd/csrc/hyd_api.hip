@@ -10,6 +10,7 @@
 #include <vector>
 
 #include "hyd_bwd_bf16.h"
+#include "hyd_bwd_wide.h"
 #include "hyd_fp32.h"
 #include "hyd_fwd_bf16.h"
 #include "hyd_merge.h"
@@ -29,6 +30,7 @@ struct SchedLayout { size_t hdr, lev, order, items, exec; int n_lev, max_items; 
 struct WsLayout {
     SchedLayout sched[2];
     SchedLayout split;      // query side by QuerySplit tiles, where an item is not a whole tile (split > 0)
+    SchedLayout wide;       // bf16 backward: dK/dV by tiles of kKwBN keys
     int n_sched;
     int part_max;           // dK/dV items in parts: their number at most
     // used: what the call uses; need: what it demands; the parts' sums take what lies behind, up to total (see part_bytes)
@@ -105,6 +107,8 @@ WsLayout ws_layout(int T, int nseq, int tile0, int tile1, int split, int hq, int
     else w.sched[1] = w.sched[0];
     if (split > 0) at = sched_layout(w.split, at, T, nseq, (bwd ? tile1 : tile0) >> split, split, true);
     else w.split = w.sched[1];
+    if (bwd && dt == HYD_BF16) at = sched_layout(w.wide, at, T, nseq, kKwBN, 0, hq >= 4 * hkv);
+    else w.wide = w.sched[0];
     const int n_stat = !bwd ? 0 : (dt == HYD_BF16 ? kBwdStatVecs : 1);
     for (int i = 0; i < kBwdStatVecs; ++i) {
         w.stat[i] = at;
@@ -162,6 +166,24 @@ int finest_split(hyd_dtype dt, int hq, int hkv, bool compact) {
 // us, 3000 tokens 103 -> 80, 6000 184 -> 164 (8/1 heads 187 -> 191, one sequence 318 -> 383); 32 heads, 700 tokens 56 -> 48, 1500
 // 93 -> 86 (32/8 heads 94 -> 94), 3000 200 -> 208.
 constexpr long long kBothRows = 40960;
+// dK/dV by tiles of 256 keys (hyd_bwd_wide.h) instead of 128.  The host knows T, the number of sequences and a bound on
+// their length: with one sequence of that length and the others alike, `mean` is the length of a token's sequence on average
+// and `share` a workgroup's share of the work.
+//   Length: a step of the wide form is a fifth cheaper, an item's beginning and end are not hidden.  Equal sequences, 49152 tokens,
+// backward narrow -> wide in us, 32 heads, d = 128: 512 tokens 1585 -> 1590, 900 2099 -> 2127, 1300 2673 -> 2619, 2048 3530 -> 3362;
+// 32/8 heads, whose items are four times as long: 300 1115 -> 1171, 400 1277 -> 1286, 640 1472 -> 1425, 1024 1981 -> 1852; 32 heads,
+// d = 64: 300 1072 -> 1108, 400 1088 -> 1056, 1024 1380 -> 1287.
+//   Number: its longest item takes twice as long.  Backward, log-normal lengths unless noted, longest / share: 50000 tokens, 8 heads,
+// 1.04: 1014 -> 981; 24000 tokens of Pareto lengths, 8 heads, 1.29: 1014 -> 1024; one sequence of 12000, 32/8 heads, 1.34: 3705 ->
+// 3728; 12000 tokens of Pareto lengths, 32/8 heads, 1.63: 2520 -> 2729; 12000 tokens, 32/8 heads, 2.1: 897 -> 1047.
+// The range variants, whose visits are a part of these items, keep the narrow form, and so do items in parts.
+bool wide_kv(int T, int nseq, int max_seqlen, int hq, int hkv, int head_dim, int wgs) {
+    const double m = nseq > 1 ? nseq - 1 : 1, rest = (T - max_seqlen) / m;
+    const double mean = ((double)max_seqlen * max_seqlen + m * rest * rest) / T;
+    if (mean < (head_dim == 64 ? 400 : (hq / hkv >= 4 ? 600 : 1100))) return false;
+    const double steps = kKwBN / kKwBM * (hq / hkv);
+    return (double)max_seqlen / kKwBN * steps <= 1.25 * share_of_work(kKwBN, steps, T, nseq, max_seqlen, hkv, wgs);
+}
 int item_heads(int split) { return split == 2 ? 4 : 1; }
 
 // The forward's size does not depend on the heads: one workspace serves layers of different head counts.
@@ -334,6 +356,8 @@ hyd_status device_info(DeviceInfo** out) {
                 !prep_kernel(hyd_bwd_dkdv_bf16_kernel<true>, kKvThreads, kKvLds, nullptr) ||
                 !prep_kernel(hyd_bwd_dkdv_bf16_kernel<false, 64>, kKvThreads, kKvLds, nullptr) ||
                 !prep_kernel(hyd_bwd_dkdv_bf16_kernel<true, 64>, kKvThreads, kKvLds, nullptr) ||
+                !prep_kernel(hyd_bwd_dkdv_wide_bf16_kernel<128>, kKwThreads, kKwLds, nullptr) ||
+                !prep_kernel(hyd_bwd_dkdv_wide_bf16_kernel<64>, kKwThreads, kKwLds, nullptr) ||
                 !prep_f32<64>(d.occ_f32[0]) || !prep_f32<128>(d.occ_f32[1]))
                 return HYD_ERR_LAUNCH;
             void* sp = nullptr;
@@ -562,12 +586,17 @@ hyd_status bwd_impl(const void* q, const void* k, const void* v, const void* o, 
     const bool grouped = hq >= 4 * hkv;
     SchedView sv_kv = make_view(ws, w.sched[0], tile_kv(dt), 0, max_seqlen, dt, hkv, dev->cus * occ_kv, grouped);
     if (dt == HYD_BF16) set_parts(sv_kv, w.part_max, total_tokens, num_seqs, max_seqlen, hq, hkv, dev->cus * occ_kv);
+    const bool both = dt == HYD_BF16 && !ranged && rope_base == 0.f && (long long)total_tokens * hq <= kBothRows;
+    const bool wide = dt == HYD_BF16 && !ranged && !both && sv_kv.part_max == 1 &&
+                      wide_kv(total_tokens, num_seqs, max_seqlen, hq, hkv, head_dim, dev->cus);
+    const SchedView sv_wide = wide ? make_view(ws, w.wide, kKwBN, 0, max_seqlen, dt, hkv, dev->cus, grouped) : sv_kv;
+    if (wide) sv_kv.other = (int)(w.wide.hdr - w.sched[0].hdr);
     SchedView sv_whole = make_view(ws, w.sched[1], tile_q(dt), 0, max_seqlen, dt, units, dev->cus * occ_q, grouped);
     if (split) sv_whole.other = (int)(w.split.hdr - w.sched[1].hdr);
     const SchedView sv_q = split ? make_view(ws, w.split, 256 >> split, split, max_seqlen, dt, units, dev->cus * occ_q, grouped) : sv_whole;
     float* Dvec = reinterpret_cast<float*>(ws + w.stat[0]);
     double* rope_tab = rope_base != 0.f ? reinterpret_cast<double*>(ws + w.rope_tab) : nullptr;
-    const long long work_q = (long long)sv_q.max_items * units, work_kv = (long long)sv_kv.max_items * sv_kv.part_max * hkv;
+    const long long work_q = (long long)sv_q.max_items * units, work_kv = (long long)sv_wide.max_items * sv_kv.part_max * hkv;
     if (dt == HYD_BF16) {
         BwdScratch sc;
         sc.Dq = Dvec;
@@ -577,7 +606,6 @@ hyd_status bwd_impl(const void* q, const void* k, const void* v, const void* o, 
         sc.q16 = reinterpret_cast<uint16_t*>(ws + w.q16);
         sc.do16 = reinterpret_cast<uint16_t*>(ws + w.do16);
         sc.k16 = reinterpret_cast<uint16_t*>(ws + w.k16);
-        const bool both = !ranged && !rope_tab && (long long)total_tokens * hq <= kBothRows;
         // item lists of both tile kernels and the row statistics in one launch
         {
             PrepParams pp;
@@ -589,12 +617,15 @@ hyd_status bwd_impl(const void* q, const void* k, const void* v, const void* o, 
             pp.sc = sc;
             pp.cu = cu_seqlens; pp.nseq = num_seqs;
             pp.ranges = ranged ? ranges : nullptr;
-            pp.n_sched = split ? 3 : 2;
-            pp.tile[0] = tile_kv(dt); pp.tile[1] = tile_q(dt); pp.tile[2] = tile_q(dt) >> split;
-            pp.sv[0] = sv_kv; pp.sv[1] = sv_whole; pp.sv[2] = sv_q;
+            pp.n_sched = 0;
+            const auto add_list = [&](int tile, const SchedView& sv) { pp.tile[pp.n_sched] = tile; pp.sv[pp.n_sched++] = sv; };
+            add_list(tile_kv(dt), sv_kv);
+            add_list(tile_q(dt), sv_whole);
+            if (split) add_list(tile_q(dt) >> split, sv_q);
+            if (wide) add_list(kKwBN, sv_wide);
             pp.rope_tab = rope_tab; pp.log2_base = rope_tab ? log2((double)rope_base) : 0.0;
             const dim3 grid((unsigned)(pp.n_sched + sc.n_absmax)), block(kPrepThreads);
-            const size_t lds = prep_lds(hq, pp.tok, schedule_lds(sv_kv.n_lev, sv_whole.n_lev, sv_q.n_lev));
+            const size_t lds = prep_lds(hq, pp.tok, schedule_lds(sv_kv.n_lev, sv_whole.n_lev, sv_q.n_lev, sv_wide.n_lev));
             KernelTimer kt("bwd_prep_bf16", st);
             const auto kernel = both ? (head_dim == 64 ? hyd_bwd_prep_bf16_kernel<false, 64, true> : hyd_bwd_prep_bf16_kernel<false, 128, true>)
                 : ranged ? (head_dim == 64 ? hyd_bwd_prep_bf16_kernel<true, 64> : hyd_bwd_prep_bf16_kernel<true, 128>)
@@ -613,7 +644,7 @@ hyd_status bwd_impl(const void* q, const void* k, const void* v, const void* o, 
         p.part = reinterpret_cast<float*>(ws + w.need); p.part_max = sv_kv.part_max;
         const int grid_q = persistent_grid(*dev, occ_q, work_q), grid_kv = persistent_grid(*dev, occ_kv, work_kv);
         WorkList lq{sv_q.hdr, sv_q.hdr + kHdrCursor, sv_q.exec, head_map_q(units, hkv, grid_q)};
-        WorkList lkv{sv_kv.hdr + kHdrExec, sv_kv.hdr + kHdrCursor, sv_kv.exec, head_map_kv(hkv, grid_kv)};
+        WorkList lkv{sv_wide.hdr + kHdrExec, sv_wide.hdr + kHdrCursor, sv_wide.exec, head_map_kv(hkv, grid_kv)};
         if (both) {
             // the workgroups of dK/dV: one per item where there is room for all items, else four of seven (its share of the products)
             int n_kv = dev->cus * 4 / 7;
@@ -634,7 +665,8 @@ hyd_status bwd_impl(const void* q, const void* k, const void* v, const void* o, 
             KernelTimer kt(ranged ? "bwd_dkdv_range_bf16" : "bwd_dkdv_bf16", st);
             const BwdKernel kernel = ranged ? (head_dim == 64 ? hyd_bwd_dkdv_bf16_kernel<true, 64> : hyd_bwd_dkdv_bf16_kernel<true, 128>)
                                             : (head_dim == 64 ? hyd_bwd_dkdv_bf16_kernel<false, 64> : hyd_bwd_dkdv_bf16_kernel<false, 128>);
-            hipLaunchKernelGGL(kernel, dim3(grid_kv), dim3(kKvThreads), kKvLds, st, p, lkv);
+            if (wide) hipLaunchKernelGGL(head_dim == 64 ? hyd_bwd_dkdv_wide_bf16_kernel<64> : hyd_bwd_dkdv_wide_bf16_kernel<128>, dim3(grid_kv), dim3(kKwThreads), kKwLds, st, p, lkv);
+            else hipLaunchKernelGGL(kernel, dim3(grid_kv), dim3(kKvThreads), kKvLds, st, p, lkv);
         }
         if (sv_kv.part_max > 1) {
             SumParams sp;

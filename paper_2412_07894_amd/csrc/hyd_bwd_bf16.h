@@ -116,7 +116,7 @@ struct PrepParams {
     int T, hq, hkv, tok;
     const int32_t* cu; int nseq;
     const int32_t* ranges;                                 // range variant only
-    int n_sched; int tile[3]; SchedView sv[3];
+    int n_sched; int tile[4]; SchedView sv[4];
     double* rope_tab; double log2_base;
 };
 

@@ -87,9 +87,9 @@ __device__ __forceinline__ void wave_inclusive_scan(int* v, int n, int lane) {
 constexpr int kPreludeThreads = 1024;
 constexpr int kPreludeLdsLev = 4096;      // levels whose arrays fit the kernel's LDS
 // bytes of LDS that build_schedule needs for lists of these numbers of levels
-inline size_t schedule_lds(int nl0, int nl1, int nl2 = 0) {
+inline size_t schedule_lds(int nl0, int nl1, int nl2 = 0, int nl3 = 0) {
     size_t most = 0;
-    for (const int nl : {nl0, nl1, nl2})
+    for (const int nl : {nl0, nl1, nl2, nl3})
         if (nl <= kPreludeLdsLev && sizeof(int) * 3 * (size_t)(nl + 2) > most) most = sizeof(int) * 3 * (size_t)(nl + 2);
     return most;
 }

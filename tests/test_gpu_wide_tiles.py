@@ -1,0 +1,43 @@
+"""dK/dV by tiles of 256 keys, 64 to a wave, against the tiles of 128 that the range variant keeps: over the whole
+range both take the same products in the same order, so dK and dV agree bit for bit."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2412_07894_amd import binding, workloads as wl
+
+pytestmark = pytest.mark.gpu
+
+EDGES = [1, 31, 32, 33, 63, 64, 65, 95, 97, 127, 129, 191, 193, 255, 256, 257, 319, 321, 448, 511, 512, 513, 700, 1025]
+
+
+@pytest.mark.parametrize("hq,hkv,d,longest,n,scale", [(8, 8, 128, 4095, 12, 1.0), (8, 8, 64, 3000, 8, -1.0), (32, 8, 128, 2049, 16, 1.0), (20, 10, 64, 2111, 8, 1.0),
+                                                      (10, 10, 128, 2943, 14, 0.0)])
+@pytest.mark.parametrize("special", [False, True])
+def test_wide_tiles_equal_narrow_ones(hq, hkv, d, longest, n, scale, special):
+    lens = EDGES + [longest] * n
+    T, ml = sum(lens), max(lens)
+    g = torch.Generator(device="cuda")
+    g.manual_seed(53)
+    mk = lambda h: torch.randn((T, h, d), device="cuda", generator=g).to(torch.bfloat16)
+    q, k, v, do = mk(hq), mk(hkv), mk(hkv), mk(hq)
+    cu = torch.from_numpy(wl.cu_seqlens(lens)).cuda()
+    if special:             # rows of infinities and NaN: they spoil the keys up to their own block of 32 and no others
+        at = np.concatenate([[0], np.cumsum(lens)])
+        for s, row, x in ((len(lens) - 1, 640 + 5, float("inf")), (len(lens) - 3, 288, float("nan")), (15, 40, float("inf"))):
+            do[int(at[s]) + row, 0] = x
+    s = scale * d ** -0.5
+    o, lse = binding.varlen_attn_fwd(q, k, v, cu, ml, s)
+    ws = torch.empty(binding.workspace_bytes(T, len(lens), hq, hkv, d, binding.HYD_BF16, 1), dtype=torch.uint8, device="cuda")
+    _, dk, dv = binding.varlen_attn_bwd(q, k, v, o, lse, do, cu, ml, s, workspace=ws)
+    tile, _ = binding.executed_items(ws, T, len(lens), hq, hkv, d, binding.HYD_BF16, 1, 0)[:2]
+    print(f"\n{hq}/{hkv} d={d} longest={longest} special={special}: tile {tile}", flush=True)
+    assert tile == 256, "the sizes are meant to take the wide form"
+    full = [(0, 1 << 20, 0, 1 << 20)] * len(lens)
+    narrow = [torch.zeros_like(x) for x in (q, k, v)]
+    binding.varlen_attn_bwd_range(q, k, v, o, lse, do, cu, full, ml, s, *narrow)
+    for name, x, y in zip(("dk", "dv"), (dk, dv), narrow[1:]):
+        ok = torch.isfinite(y.float())
+        assert torch.equal(ok, torch.isfinite(x.float())) and torch.equal(x[ok], y[ok]), name
+        assert bool(ok.all()) != special
+        assert bool((x[ok] != 0).any()) or scale == 0.0
