@@ -314,6 +314,8 @@ template <int D>
 bool prep_f32(int* occ) {
     return prep_kernel(hyd_fwd_fp32_kernel<D>, 64 * kF32Waves, f32_lds<D>(), occ) &&
            prep_kernel(hyd_bwd_dq_fp32_kernel<D>, 64 * kF32Waves, f32_lds<D>(), occ + 1) &&
+           prep_kernel(hyd_fwd_self_fp32_kernel<D>, 64 * kF32Waves, f32_lds<D>(), nullptr) &&
+           prep_kernel(hyd_bwd_dq_self_fp32_kernel<D>, 64 * kF32Waves, f32_lds<D>(), nullptr) &&
            prep_kernel(hyd_bwd_dkdv_fp32_kernel<D>, 64 * kF32KvWaves, f32_lds<D>(), occ + 2);
 }
 
@@ -329,6 +331,9 @@ constexpr BwdKernel kDqKernels[4][2] = {{hyd_bwd_dq_bf16_kernel<false, 128, 0>, 
                                         {hyd_bwd_dq_bf16_kernel<false, 128, 2>, hyd_bwd_dq_bf16_kernel<false, 64, 2>},
                                         {hyd_bwd_dq_bf16_kernel<true, 128, 0>, hyd_bwd_dq_bf16_kernel<true, 64, 0>}};
 
+typedef void (*FwdSelfKernel)(FwdParams, SelfSchedule);
+constexpr FwdSelfKernel kFwdSelfKernels[2][2] = {{hyd_fwd_self_bf16_kernel<128, 0>, hyd_fwd_self_bf16_kernel<64, 0>},      // [half tiles][head_dim == 64]
+                                                 {hyd_fwd_self_bf16_kernel<128, 1>, hyd_fwd_self_bf16_kernel<64, 1>}};
 typedef void (*BothKernel)(BwdParams, WorkList, WorkList, int);
 constexpr BothKernel kBothKernels[3][2] = {{hyd_bwd_both_bf16_kernel<128, 0>, hyd_bwd_both_bf16_kernel<64, 0>},
                                            {hyd_bwd_both_bf16_kernel<128, 1>, hyd_bwd_both_bf16_kernel<64, 1>},
@@ -350,6 +355,8 @@ hyd_status device_info(DeviceInfo** out) {
                 if (!prep_kernel(kFwdKernels[i / 2][i % 2], kFwdThreads, kFwdLds, &d.occ_fwd) ||
                     !prep_kernel(kDqKernels[i / 2][i % 2], kDqThreads, kDqLds, &d.occ_dq))
                     return HYD_ERR_LAUNCH;
+            for (int i = 0; i < 4; ++i)
+                if (!prep_kernel(kFwdSelfKernels[i / 2][i % 2], kFwdThreads, kFwdSelfLds, nullptr)) return HYD_ERR_LAUNCH;
             for (int i = 0; i < 6; ++i)
                 if (!prep_kernel(kBothKernels[i / 2][i % 2], kKvThreads, kBothLds, nullptr)) return HYD_ERR_LAUNCH;
             if (!prep_kernel(hyd_bwd_dkdv_bf16_kernel<false>, kKvThreads, kKvLds, &d.occ_kv) ||
@@ -443,6 +450,25 @@ void set_parts(SchedView& sv, int limit, int T, int nseq, int max_seqlen, int hq
     sv.part_max = item_parts(sv.n_lev, sv.steps_per_level, sv.part_q, limit);
 }
 
+// tiles of num_seqs sequences that hold T tokens, at most
+long long most_items(int T, int nseq, int tile) { return ((long long)T + (long long)nseq * (tile - 1)) / tile; }
+// Every (item, head) pair gets a workgroup of its own, and the lists theirs (see SelfSchedule): where all run at once, and up
+// to 1.75 for each CU if none lasts long, since the hardware hands workgroups to the XCDs strictly in turn, which
+// balances the later ones badly.  Forward, list -> own items in us (one sequence unless noted): 3000 tokens, 8 heads 54.7 -> 52.9, 1500
+// tokens of log-normal lengths, 32 heads (430 items) 32.3 -> 25.8, 6000, 8 heads (400) 65.0 -> 62.8; 8000, 8 heads (504 items)
+// 186 -> 196, 16000 (504) 449 -> 485; 2000, 64/8 heads (512) 76.8 -> 79.0.
+bool self_schedule_ok(int nseq, long long work, int lists, int max_seqlen, int cus) {
+    if (nseq > kSelfSeqs) return false;
+    return work + lists <= cus || (4 * (work + lists) <= 7 * cus && max_seqlen <= 6144);
+}
+SelfSchedule self_schedule(const int32_t* cu, int nseq, int T, int work, int heads, int tile, const SchedView& sv) {
+    SelfSchedule ss;
+    ss.cu = cu; ss.nseq = nseq; ss.T = T; ss.n_work = work; ss.heads = heads; ss.tile = tile; ss.n_lev = sv.n_lev;
+    ss.n_lists = 0; ss.log2_base = 0.0;
+    return ss;
+}
+void add_list(SelfSchedule& ss, int tile, const SchedView& sv) { ss.tiles[ss.n_lists] = tile; ss.lists[ss.n_lists++] = sv; }
+
 int persistent_grid(const DeviceInfo& d, int occ, long long work_upper_bound) {
     long long g = (long long)d.cus * occ;
     if (g > work_upper_bound) g = work_upper_bound;
@@ -518,13 +544,20 @@ hyd_status fwd_impl(const void* q, const void* k, const void* v, const int32_t* 
     if (split) sv_whole.other = (int)(w.split.hdr - w.sched[0].hdr);
     const SchedView sv = split ? make_view(static_cast<char*>(workspace), w.split, 256 >> split, split, max_seqlen, dt, units, dev->cus * occ, grouped) : sv_whole;
     double* rope_tab = rope_base != 0.f ? reinterpret_cast<double*>(static_cast<char*>(workspace) + w.rope_tab) : nullptr;
-    {
+    const long long work = (long long)sv.max_items * units, self_work = most_items(total_tokens, num_seqs, tile >> split) * units;
+    const bool self = !ranged && split != 2 && self_schedule_ok(num_seqs, self_work, split ? 2 : 1, max_seqlen, dev->cus);
+    SelfSchedule ss;
+    if (self) {
+        ss = self_schedule(cu_seqlens, num_seqs, total_tokens, (int)self_work, units, tile >> split, sv);
+        add_list(ss, tile, sv_whole);
+        if (split) add_list(ss, tile >> split, sv);
+        ss.log2_base = rope_base != 0.f ? log2((double)rope_base) : 0.0;
+    } else {
         KernelTimer kt("schedule_prelude", st);
         hipLaunchKernelGGL(hyd_schedule_prelude, dim3(split ? 2 : 1), dim3(kPreludeThreads), schedule_lds(sv_whole.n_lev, sv.n_lev), st, cu_seqlens, num_seqs,
                            total_tokens, tile, sv_whole, tile >> split, sv,
                            rope_tab, head_dim / 2, rope_base != 0.f ? log2((double)rope_base) : 0.0);
     }
-    const long long work = (long long)sv.max_items * units;
     if (dt == HYD_BF16) {
         FwdParams p;
         p.q = static_cast<const uint16_t*>(q); p.k = static_cast<const uint16_t*>(k);
@@ -537,7 +570,8 @@ hyd_status fwd_impl(const void* q, const void* k, const void* v, const int32_t* 
         const dim3 grid(persistent_grid(*dev, occ, work));
         p.hm = head_map_q(units, hkv, grid.x);
         KernelTimer kt(ranged ? "fwd_range_bf16" : "fwd_bf16", st);
-        hipLaunchKernelGGL(kFwdKernels[ranged ? 3 : split][head_dim == 64], grid, dim3(kFwdThreads), kFwdLds, st, p);
+        if (self) hipLaunchKernelGGL(kFwdSelfKernels[split][head_dim == 64], dim3(ss.n_work + ss.n_lists), dim3(kFwdThreads), kFwdSelfLds, st, p, ss);
+        else hipLaunchKernelGGL(kFwdKernels[ranged ? 3 : split][head_dim == 64], grid, dim3(kFwdThreads), kFwdLds, st, p);
     } else {
         F32Params p;
         memset(&p, 0, sizeof(p));
@@ -548,7 +582,9 @@ hyd_status fwd_impl(const void* q, const void* k, const void* v, const int32_t* 
         const dim3 grid(persistent_grid(*dev, occ, work));
         p.hm = head_map_q(hq, hkv, grid.x);
         KernelTimer kt("fwd_fp32", st);
-        if (head_dim == 64) hipLaunchKernelGGL(hyd_fwd_fp32_kernel<64>, grid, dim3(64 * kF32Waves), f32_lds<64>(), st, p);
+        const auto self_kernel = head_dim == 64 ? hyd_fwd_self_fp32_kernel<64> : hyd_fwd_self_fp32_kernel<128>;
+        if (self) hipLaunchKernelGGL(self_kernel, dim3(ss.n_work + ss.n_lists), dim3(64 * kF32Waves), head_dim == 64 ? f32_lds<64>() : f32_lds<128>(), st, p, ss);
+        else if (head_dim == 64) hipLaunchKernelGGL(hyd_fwd_fp32_kernel<64>, grid, dim3(64 * kF32Waves), f32_lds<64>(), st, p);
         else hipLaunchKernelGGL(hyd_fwd_fp32_kernel<128>, grid, dim3(64 * kF32Waves), f32_lds<128>(), st, p);
     }
     return hipGetLastError() == hipSuccess ? HYD_OK : HYD_ERR_LAUNCH;
@@ -690,18 +726,26 @@ hyd_status bwd_impl(const void* q, const void* k, const void* v, const void* o, 
         p.dq = static_cast<float*>(dq); p.dk = static_cast<float*>(dk); p.dv = static_cast<float*>(dv);
         p.T = total_tokens; p.hq = hq; p.hkv = hkv; p.scale = softmax_scale;
         p.tr = t_trace;
-        {   // one launch builds both item lists, one workgroup each
+        const bool short_rows = max_seqlen <= kF32Short;
+        const long long self_work = most_items(total_tokens, num_seqs, tile_q(dt)) * hq;
+        const bool self = !short_rows && self_schedule_ok(num_seqs, self_work, 2, max_seqlen, dev->cus);
+        if (!self) {   // one launch builds both item lists, one workgroup each
             KernelTimer kt("schedule_prelude", st);
             hipLaunchKernelGGL(hyd_schedule_prelude, dim3(w.n_sched), dim3(kPreludeThreads), schedule_lds(sv_kv.n_lev, sv_q.n_lev), st, cu_seqlens,
                                num_seqs, total_tokens, tile_kv(dt), sv_kv, tile_q(dt), sv_q, nullptr, 0, 0.0);
         }
-        const bool short_rows = max_seqlen <= kF32Short;
         const dim3 grid_q(persistent_grid(*dev, occ_q, work_q)), grid_kv(persistent_grid(*dev, occ_kv, work_kv));
         // dQ first: it also writes the row sums D that dK/dV reads
         {
             p.hdr = sv_q.hdr; p.items = sv_q.exec; p.cursors = sv_q.hdr + kHdrCursor; p.hm = head_map_q(hq, hkv, grid_q.x);
             KernelTimer kt("bwd_dq_fp32", st);
-            if (head_dim == 64) hipLaunchKernelGGL(hyd_bwd_dq_fp32_kernel<64>, grid_q, dim3(64 * kF32Waves), f32_lds<64>(), st, p);
+            if (self) {
+                SelfSchedule ss = self_schedule(cu_seqlens, num_seqs, total_tokens, (int)self_work, hq, tile_q(dt), sv_q);
+                add_list(ss, tile_kv(dt), sv_kv);
+                add_list(ss, tile_q(dt), sv_q);
+                const auto self_kernel = head_dim == 64 ? hyd_bwd_dq_self_fp32_kernel<64> : hyd_bwd_dq_self_fp32_kernel<128>;
+                hipLaunchKernelGGL(self_kernel, dim3(ss.n_work + ss.n_lists), dim3(64 * kF32Waves), head_dim == 64 ? f32_lds<64>() : f32_lds<128>(), st, p, ss);
+            } else if (head_dim == 64) hipLaunchKernelGGL(hyd_bwd_dq_fp32_kernel<64>, grid_q, dim3(64 * kF32Waves), f32_lds<64>(), st, p);
             else if (short_rows) hipLaunchKernelGGL((hyd_bwd_dq_fp32_kernel<128, true>), grid_q, dim3(64 * kF32Waves), f32_rows_lds(), st, p);
             else hipLaunchKernelGGL(hyd_bwd_dq_fp32_kernel<128>, grid_q, dim3(64 * kF32Waves), f32_lds<128>(), st, p);
         }

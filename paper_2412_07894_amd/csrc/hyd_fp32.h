@@ -378,9 +378,9 @@ __device__ __forceinline__ bool f32_rows_finite(const float* base, int64_t strid
 }
 
 // Forward.  S^T[key][q] = K Q^T (one query row per lane), O^T[d][q] += V^T P^T.
-template <int D>
-__global__ void __launch_bounds__(64 * kF32Waves, 1) hyd_fwd_fp32_kernel(F32Params p) {
-    extern __shared__ __attribute__((aligned(16))) char smem[];
+// kSelf: one item per workgroup, found by itself (see SelfSchedule).
+template <int D, bool kSelf>
+__device__ __forceinline__ void fwd_fp32_items(const F32Params& p, const SelfSchedule* ss, char* smem) {
     constexpr int kT = f32_tile_bytes<D>(), NDB = D / 32, kL = F32Lds<D, kF32Waves>::kLoads;
     constexpr int kAcc = NDB * 64 * 64;                          // bytes of a wave's accumulators
     int* slot = reinterpret_cast<int*>(smem + 2 * kT);
@@ -394,11 +394,15 @@ __global__ void __launch_bounds__(64 * kF32Waves, 1) hyd_fwd_fp32_kernel(F32Para
     fl.init(lane, wave, split, smem, stride_b);
     WorkFetcher wf;
     WorkItem wi;
-    for (bool have = wf.first(p.hm, p.hdr, p.cursors, p.items, slot, wi, blockIdx.x); have; have = wf.next(p.hm, p.cursors, p.items, slot, wi)) {
+    auto claim = [&]() { if (!kSelf) wf.claim(p.hm, p.cursors); };
+    bool have;
+    if constexpr (kSelf) have = self_first(*ss, smem, 64 * kF32Waves, wi);
+    else have = wf.first(p.hm, p.hdr, p.cursors, p.items, slot, wi, blockIdx.x);
+    for (; have; have = kSelf ? false : wf.next(p.hm, p.cursors, p.items, slot, wi)) {
         const int head = wi.head, row0 = wi.row0, L = wi.len;
         bool rows = L <= kF32Short;
         if (rows) {
-            wf.claim(p.hm, p.cursors);
+            claim();
         } else {
             const int q0 = (wi.lev - 1) * kF32BM, kv_end = min(L, q0 + kF32BM), n_kt = (kv_end + kF32Tile - 1) / kF32Tile;
             const int g = head / G, wrow0 = q0 + 32 * rg, i = wrow0 + l32;
@@ -416,7 +420,7 @@ __global__ void __launch_bounds__(64 * kF32Waves, 1) hyd_fwd_fp32_kernel(F32Para
             for (int t = 0; t < n_kt; ++t) {
                 const uint32_t nxt = (uint32_t)(t + 1) * kF32Tile * stride_b;
                 const bool more = t + 1 < n_kt;
-                if (t == max(n_kt - 2, 0)) wf.claim(p.hm, p.cursors);
+                if (t == max(n_kt - 2, 0)) claim();
                 const int key0 = t * kF32Tile + 32 * split;
                 const bool work = key0 <= wrow0 && wrow0 < L;        // else the block is hidden from all rows of the wave
                 f32_arrive<kL>();                                    // K tile t is there
@@ -501,11 +505,21 @@ __global__ void __launch_bounds__(64 * kF32Waves, 1) hyd_fwd_fp32_kernel(F32Para
     }
 }
 
+template <int D>
+__global__ void __launch_bounds__(64 * kF32Waves, 1) hyd_fwd_fp32_kernel(F32Params p) {
+    extern __shared__ __attribute__((aligned(16))) char smem[];
+    fwd_fp32_items<D, false>(p, nullptr, smem);
+}
+template <int D>
+__global__ void __launch_bounds__(64 * kF32Waves, 1) hyd_fwd_self_fp32_kernel(F32Params p, SelfSchedule ss) {
+    extern __shared__ __attribute__((aligned(16))) char smem[];
+    fwd_fp32_items<D, true>(p, &ss, smem);
+}
+
 // dQ.  S^T = K Q^T, dP^T = V dO^T, dQ^T += K^T dS^T.  Also forms D = rowsum(dO * O) of its rows, which
 // the dK/dV kernel that follows reads.
-template <int D, bool kRows = false>
-__global__ void __launch_bounds__(64 * kF32Waves, 1) hyd_bwd_dq_fp32_kernel(F32Params p) {
-    extern __shared__ __attribute__((aligned(16))) char smem[];
+template <int D, bool kRows, bool kSelf>
+__device__ __forceinline__ void dq_fp32_items(const F32Params& p, const SelfSchedule* ss, char* smem) {
     constexpr int kT = f32_tile_bytes<D>(), NDB = D / 32, kL = F32Lds<D, kF32Waves>::kLoads;
     constexpr int kAcc = NDB * 64 * 64;
     int* slot = reinterpret_cast<int*>(smem + (kRows ? 0 : 2 * kT));
@@ -519,11 +533,15 @@ __global__ void __launch_bounds__(64 * kF32Waves, 1) hyd_bwd_dq_fp32_kernel(F32P
     fl.init(lane, wave, split, smem, stride_b);
     WorkFetcher wf;
     WorkItem wi;
-    for (bool have = wf.first(p.hm, p.hdr, p.cursors, p.items, slot, wi, blockIdx.x); have; have = wf.next(p.hm, p.cursors, p.items, slot, wi)) {
+    auto claim = [&]() { if (!kSelf) wf.claim(p.hm, p.cursors); };
+    bool have;
+    if constexpr (kSelf) have = self_first(*ss, smem, 64 * kF32Waves, wi);
+    else have = wf.first(p.hm, p.hdr, p.cursors, p.items, slot, wi, blockIdx.x);
+    for (; have; have = kSelf ? false : wf.next(p.hm, p.cursors, p.items, slot, wi)) {
         const int head = wi.head, row0 = wi.row0, L = wi.len;
         bool rows = kRows || (D == 64 && L <= kF32Short);
         if (rows) {
-            wf.claim(p.hm, p.cursors);
+            claim();
         } else {
             const int q0 = (wi.lev - 1) * kF32BM, kv_end = min(L, q0 + kF32BM), n_kt = (kv_end + kF32Tile - 1) / kF32Tile;
             const int g = head / G, wrow0 = q0 + 32 * rg, i = wrow0 + l32, ic = min(i, L - 1);
@@ -556,7 +574,7 @@ __global__ void __launch_bounds__(64 * kF32Waves, 1) hyd_bwd_dq_fp32_kernel(F32P
             for (int t = 0; t < n_kt; ++t) {
                 const uint32_t nxt = (uint32_t)(t + 1) * kF32Tile * stride_b;
                 const bool more = t + 1 < n_kt;
-                if (t == max(n_kt - 2, 0)) wf.claim(p.hm, p.cursors);
+                if (t == max(n_kt - 2, 0)) claim();
                 const int key0 = t * kF32Tile + 32 * split;
                 const bool work = key0 <= wrow0 && wrow0 < L;
                 f32x16 s[1], dp[1];
@@ -598,6 +616,18 @@ __global__ void __launch_bounds__(64 * kF32Waves, 1) hyd_bwd_dq_fp32_kernel(F32P
             for (int r = (wi.lev - 1) * kF32BM + wave; r < min(L, wi.lev * kF32BM); r += kF32Waves) f32_row_dq<D>(p, row0, r, head, lane);
         }
     }
+}
+
+template <int D, bool kRows = false>
+__global__ void __launch_bounds__(64 * kF32Waves, 1) hyd_bwd_dq_fp32_kernel(F32Params p) {
+    extern __shared__ __attribute__((aligned(16))) char smem[];
+    dq_fp32_items<D, kRows, false>(p, nullptr, smem);
+}
+// (builds the list of the dK/dV kernel that follows, besides its own)
+template <int D>
+__global__ void __launch_bounds__(64 * kF32Waves, 1) hyd_bwd_dq_self_fp32_kernel(F32Params p, SelfSchedule ss) {
+    extern __shared__ __attribute__((aligned(16))) char smem[];
+    dq_fp32_items<D, false, true>(p, &ss, smem);
 }
 
 // dK/dV.  S[i][j] = Q K^T and dP[i][j] = dO V^T (one key per lane), dV^T += dO^T P, dK^T += Q^T dS.  K and V

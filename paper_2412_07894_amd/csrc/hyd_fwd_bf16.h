@@ -60,6 +60,7 @@ constexpr int kFwdQxOff = kFwdStages * kFwdStageBytes;
 constexpr int kFwdQxBytes = 2 * kFwdTileBytes;
 constexpr int kFwdSlotOff = kFwdQxOff + kFwdQxBytes;                  // work slot (64 bytes), then the overflow flag
 constexpr int kFwdLds = kFwdSlotOff + 128;
+constexpr int kFwdTabOff = kFwdLds, kFwdSelfLds = kFwdTabOff + kHeadDim / 2 * 8;      // rotary frequencies
 __device__ __forceinline__ constexpr int fwd_q_stage_off(int j) {
     return j < 2 ? kFwdQxOff + j * kFwdTileBytes : (kFwdStages - 1) * kFwdStageBytes + (j - 2) * kFwdTileBytes;
 }
@@ -231,12 +232,12 @@ __device__ __forceinline__ void fwd_tile(int Kt, int Vt, const FragAddr& fa, con
 // outside the query range are skipped, the tile loop starts at the key range's first tile and
 // stops at its end, and a row that sees no key of the range gets O = 0 and LSE = -inf (the
 // neutral element of the log-sum-exp merge of partial results).
-template <bool R, int D = kHeadDim, int S = 0>
-__global__ void __launch_bounds__(kFwdThreads, 1) hyd_fwd_bf16_kernel(FwdParams p) {
+// kSelf: one item per workgroup, found by itself (see SelfSchedule).
+template <bool R, int D, int S, bool kSelf>
+__device__ __forceinline__ void fwd_items(const FwdParams& p, const SelfSchedule* ss, char* smem) {
     using QS = QuerySplit<S>;
     static_assert(D == 128 || D == 64, "head dimension");
     constexpr int kRowB = D * 2;                                      // bytes of a row in global memory
-    extern __shared__ __attribute__((aligned(16))) char smem[];
     static_assert(kFwdBM == 256 && kFwdStages == 3, "the Q staging assumes a 256-row tile and a free third stage");
     int* slot = reinterpret_cast<int*>(smem + kFwdSlotOff);
     volatile int* redo = slot + 16;                                            // a wave of the workgroup has overflowed
@@ -269,7 +270,10 @@ __global__ void __launch_bounds__(kFwdThreads, 1) hyd_fwd_bf16_kernel(FwdParams 
 
     WorkFetcher wf;
     WorkItem wi;
-    bool have = wf.first(p.hm, p.hdr, p.cursors, p.items, slot, wi, blockIdx.x);
+    bool have;
+    if constexpr (kSelf) have = self_first(*ss, smem, kFwdThreads, wi);
+    else have = wf.first(p.hm, p.hdr, p.cursors, p.items, slot, wi, blockIdx.x);
+    const double* rope_tab = p.rope_tab;
     while (have) {
         ++n_done;
         const int lev = wi.lev, head0 = wi.head << QS::kLh, row0 = wi.row0, L = wi.len;
@@ -329,6 +333,11 @@ __global__ void __launch_bounds__(kFwdThreads, 1) hyd_fwd_bf16_kernel(FwdParams 
                                 [&](int j) { return QS::tile_at(j, q_stride_b, kRowB); }, wave, dma_voff_q);
         }
         if (tid == 0) *redo = 0;
+        if (kSelf && rope_tab) {
+            double* tab = reinterpret_cast<double*>(smem + kFwdTabOff);
+            rope_table_fill(tab, D / 2, ss->log2_base, tid, kFwdThreads);
+            rope_tab = tab;
+        }
         __syncthreads();                                  // the first tiles and the Q rows have landed
         bf16x8 qf[D / 16];
         {
@@ -340,13 +349,13 @@ __global__ void __launch_bounds__(kFwdThreads, 1) hyd_fwd_bf16_kernel(FwdParams 
             for (int ks = 0; ks < D / 16; ++ks) {
                 asm volatile("" : "+v"(qv[ks]));          // the reads stay on this side of the barrier
             }
-            if (p.rope_tab) rope_row_frags<D, false>(qv, p.rope_tab, qrow, half);      // position = local row: reset per sequence
+            if (rope_tab) rope_row_frags<D, false>(qv, rope_tab, qrow, half);      // position = local row: reset per sequence
 #pragma unroll
             for (int ks = 0; ks < D / 16; ++ks) qf[ks] = as_bf16x8(qv[ks] ^ sign_flip);
         }
         __builtin_amdgcn_s_barrier();                     // the staged Q may be overwritten (tile t_lo+2 goes there)
         const bool short_item = n_kt - t_lo <= kShortItem;
-        if (short_item) wf.claim(p.hm, p.cursors);
+        if (!kSelf && short_item) wf.claim(p.hm, p.cursors);
 
         f32x16 acc_o[D / 32];
         float m_ref, l_run;
@@ -393,7 +402,7 @@ __global__ void __launch_bounds__(kFwdThreads, 1) hyd_fwd_bf16_kernel(FwdParams 
             if (t_lo + 1 < n_kt) dma_tile(t_lo + 1, 1);
             __syncthreads();
         }
-        if (!short_item) wf.claim(p.hm, p.cursors);
+        if (!kSelf && !short_item) wf.claim(p.hm, p.cursors);
         // epilogue: normalise, write O (bf16) and LSE (natural log)
         float l_lo, l_hi;
         both_halves(l_run, l_lo, l_hi);
@@ -408,9 +417,21 @@ __global__ void __launch_bounds__(kFwdThreads, 1) hyd_fwd_bf16_kernel(FwdParams 
                 p.lse[(int64_t)head * p.T + row0 + qrow] =
                     (m_ref + __builtin_amdgcn_logf(l_tot)) * 0.69314718055994530942f;
         }
-        have = wf.next(p.hm, p.cursors, p.items, slot, wi);
+        if constexpr (kSelf) have = false;
+        else have = wf.next(p.hm, p.cursors, p.items, slot, wi);
     }
     trace_write(p.tr, 0, t_start, n_done);
+}
+
+template <bool R, int D = kHeadDim, int S = 0>
+__global__ void __launch_bounds__(kFwdThreads, 1) hyd_fwd_bf16_kernel(FwdParams p) {
+    extern __shared__ __attribute__((aligned(16))) char smem[];
+    fwd_items<R, D, S, false>(p, nullptr, smem);
+}
+template <int D, int S>
+__global__ void __launch_bounds__(kFwdThreads, 1) hyd_fwd_self_bf16_kernel(FwdParams p, SelfSchedule ss) {
+    extern __shared__ __attribute__((aligned(16))) char smem[];
+    fwd_items<false, D, S, true>(p, &ss, smem);
 }
 
 }  // namespace hyd

@@ -1,0 +1,60 @@
+"""Launches in which each item has a workgroup that finds it by itself, against the same sequences in a batch that goes
+through the item list: O, LSE and dQ agree bit for bit; and the lists that are built beside such a launch."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import sched_oracle as so
+from paper_2412_07894_amd import binding, workloads as wl
+
+pytestmark = pytest.mark.gpu
+
+CASES = [[1], [0, 5, 0, 0, 300, 0], [64, 63, 65, 1, 255, 256, 257], [1] * 120, [0] * 200 + [129] + [0] * 54 + [17], [2] * 100 + [0] * 156, [1023]]
+
+
+@pytest.mark.parametrize("lens", CASES)
+@pytest.mark.parametrize("dtype,hq,hkv,d,rope_base", [("bf16", 2, 1, 128, None), ("bf16", 1, 1, 64, None), ("bf16", 1, 1, 128, 1e4), ("bf16", 2, 1, 64, 500.0),
+                                                      ("fp32", 2, 2, 64, None), ("fp32", 1, 1, 128, None)])
+def test_own_items_equal_listed_ones(lens, dtype, hq, hkv, d, rope_base):
+    dt, code = (torch.bfloat16, binding.HYD_BF16) if dtype == "bf16" else (torch.float32, binding.HYD_FP32)
+    T = sum(lens)
+    g = torch.Generator(device="cuda")
+    g.manual_seed(59)
+    mk = lambda h: torch.randn((T, h, d), device="cuda", generator=g).to(dt)
+    x = (mk(hq), mk(hkv), mk(hkv), mk(hq))
+    ws = torch.empty(binding.workspace_bytes(T, len(lens), hq, hkv, d, code, 0), dtype=torch.uint8, device="cuda")
+
+    def run(copies, workspace=None):
+        n = lens * copies
+        cu = torch.from_numpy(wl.cu_seqlens(n)).cuda()
+        q, k, v, do = (t.repeat(copies, 1, 1) for t in x)
+        o, lse = binding.varlen_attn_fwd(q, k, v, cu, max(n), d ** -0.5, workspace=workspace, rope_base=rope_base)
+        dq = binding.varlen_attn_bwd(q, k, v, o, lse, do, cu, max(n), d ** -0.5, rope_base=rope_base)[0]
+        return o[:T], lse[:, :T], dq[:T]
+
+    print(f"\n{len(lens)} sequences, {T} tokens, {dtype} {hq}/{hkv} d={d} rope={rope_base}", flush=True)
+    small = run(1, ws)
+    tile, rec = binding.schedule_items(ws, T, len(lens), hq, hkv, d, code, 0, 0)
+    assert sorted(map(tuple, rec.tolist())) == sorted(so.records(lens, tile))
+    assert binding.schedule_status(ws, T, len(lens), hq, hkv, d, code, 0) == 0
+    large = run(max(257 // len(lens) + 1, 257 // hq + 1))
+    for name, a, b in zip(("o", "lse", "dq"), small, large):
+        assert bool(torch.isfinite(a.float()).all()) and torch.equal(a, b), name
+
+
+def test_malformed_lengths_stay_inside():
+    """A cu_seqlens that decreases, ends early or holds a sequence longer than max_seqlen: every workgroup ends and the
+    status call says what was wrong; nothing behind the tensors is written."""
+    hq, d = 2, 64
+    for cu, status in (([0, 40, 20, 64], 6), ([0, 30, 60, 60], 6), ([0, 64, 64, 64], 2)):
+        T = 64
+        q, k, v = (torch.randn((T, hq, d), device="cuda").to(torch.bfloat16) for _ in range(3))
+        room = torch.full((T + 64, hq, d), 3.0, dtype=torch.bfloat16, device="cuda")
+        o, lse = room[:T], torch.zeros((hq, T), device="cuda")
+        ws = torch.empty(binding.workspace_bytes(T, 3, hq, hq, d, binding.HYD_BF16, 0), dtype=torch.uint8, device="cuda")
+        c = torch.tensor(cu, dtype=torch.int32, device="cuda")
+        binding.varlen_attn_fwd(q, k, v, c, 40 if status == 6 else 32, d ** -0.5, workspace=ws, out=o, lse=lse)
+        got = binding.schedule_status(ws, T, 3, hq, hq, d, binding.HYD_BF16, 0)
+        print(cu, binding.status_string(got), flush=True)
+        assert (got != 0) == (status == 6)
+        assert bool((room[T:] == 3.0).all())
