@@ -196,7 +196,7 @@ hyd_status hyd_varlen_attn_schedule_status(const void* workspace, size_t workspa
  * ceil(length / *tile)); at most *max_items records.
  *
  * That is the work of the batch in tiles of *tile rows.  What the kernel takes may be cut otherwise (64 rows of four query
- * heads, 128 rows; for dK/dV 256 keys, or parts of an item) and comes in an order of its own at the cheap end.  The header leads there:
+ * heads or of one, 128 rows; for dK/dV 256 keys, or parts of an item) and comes in an order of its own at the cheap end.  The header leads there:
  * [3] is the distance in bytes from this header to the header of the list that is handed out (0: this one), and in that
  * header [2] is the number of records handed out, [4] the distance in bytes from it to the first one, [5] the rows of a
  * tile and [6] the query heads of a record (dK/dV: 1 KV head).  Bits 24-26 of a record's level are the index of a part,

@@ -13,6 +13,7 @@
 #include "hyd_bwd_wide.h"
 #include "hyd_fp32.h"
 #include "hyd_fwd_bf16.h"
+#include "hyd_fwd_coop.h"
 #include "hyd_merge.h"
 #include "hyd_rope.h"
 
@@ -185,10 +186,24 @@ bool wide_kv(int T, int nseq, int max_seqlen, int hq, int hkv, int head_dim, int
     return (double)max_seqlen / kKwBN * steps <= 1.25 * share_of_work(kKwBN, steps, T, nseq, max_seqlen, hkv, wgs);
 }
 int item_heads(int split) { return split == 2 ? 4 : 1; }
+// Form 3, of the forward only: 64 rows of one head, the waves sharing them (hyd_fwd_coop.h).
+int form_shift(int split) { return split == 3 ? 2 : split; }      // rows of an item: 256 >> shift
+// tiles of num_seqs sequences that hold T tokens, at most
+long long most_items(int T, int nseq, int tile) { return ((long long)T + (long long)nseq * (tile - 1)) / tile; }
+// Instead of half tiles where the launch can start with all of its items, or nearly: those that come second cost what an item
+// costs at least, 8 us.  Forward, half tiles -> form 3 in us (in brackets its items), d = 128: one sequence of 256 tokens, 8 heads
+// (32) 9.9 -> 9.5, 700, 32 heads (352) 17.5 -> 15.5, 1500, 8 heads (192) 29.7 -> 23.2, 3000, 8 heads (376) 52.4 -> 41.6, 4000 (504)
+// 67.8 -> 64.4, 6000 (752) 103 -> 135; sequences of 64-1024: 2000 tokens, 8 heads (280) 16.8 -> 14.0, 3000 (416) 18.6 -> 20.2.  (With d = 64,
+// where the second product occupied two waves of four, 1500 tokens, 8 heads 19.1 -> 18.2, 700, 32 heads 13.7 -> 14.0.)
+int fwd_form(int split, int T, int nseq, int max_seqlen, int hq, int head_dim) {
+    if (split != 1 || head_dim != 128) return split;
+    const long long items = most_items(T, nseq, 64) * hq;
+    return items <= 384 || (items <= 512 && max_seqlen >= 2048) ? 3 : 1;
+}
 
 // The forward's size does not depend on the heads: one workspace serves layers of different head counts.
 WsLayout fwd_layout(int T, int nseq, int hq, int hkv, int head_dim, hyd_dtype dt, bool compact) {
-    WsLayout w = ws_layout(T, nseq, tile_q(dt), tile_q(dt), finest_split(dt, hq, hkv, compact), hq, hkv, head_dim, dt, false, compact);
+    WsLayout w = ws_layout(T, nseq, tile_q(dt), tile_q(dt), dt != HYD_BF16 || compact ? 0 : 2, hq, hkv, head_dim, dt, false, compact);
     if (!compact) {
         SchedLayout v;
         size_t most = sched_layout(v, 0, T, nseq, tile_q(dt), 0, false);
@@ -355,6 +370,8 @@ hyd_status device_info(DeviceInfo** out) {
                 if (!prep_kernel(kFwdKernels[i / 2][i % 2], kFwdThreads, kFwdLds, &d.occ_fwd) ||
                     !prep_kernel(kDqKernels[i / 2][i % 2], kDqThreads, kDqLds, &d.occ_dq))
                     return HYD_ERR_LAUNCH;
+            if (!prep_kernel(hyd_fwd_coop_bf16_kernel, kFwdThreads, kCoLds, nullptr) || !prep_kernel(hyd_fwd_coop_self_bf16_kernel, kFwdThreads, kCoLds, nullptr))
+                return HYD_ERR_LAUNCH;
             for (int i = 0; i < 4; ++i)
                 if (!prep_kernel(kFwdSelfKernels[i / 2][i % 2], kFwdThreads, kFwdSelfLds, nullptr)) return HYD_ERR_LAUNCH;
             for (int i = 0; i < 6; ++i)
@@ -409,7 +426,7 @@ struct KernelTimer {       // brackets one launch with events when timing is on
 // `heads` work items per record are shared by `wgs` workgroups.  Sequences are grouped up to
 // 1024 bf16 (512 fp32) rows, 512 KB of K and V for a head, unless four or more query heads share
 // a KV head: their workgroups share its stream already, and the list's own order is balanced best.
-SchedView make_view(char* ws, const SchedLayout& v, int tile, int split, int max_seqlen, hyd_dtype dt, int heads, int wgs, bool grouped_heads) {
+SchedView make_view(char* ws, const SchedLayout& v, int tile, int split, int max_seqlen, hyd_dtype dt, int heads, int wgs, bool grouped_heads, int rec_heads = 1) {
     SchedView sv;
     sv.hdr = reinterpret_cast<int*>(ws + v.hdr);
     sv.lev = reinterpret_cast<int*>(ws + v.lev);
@@ -422,7 +439,7 @@ SchedView make_view(char* ws, const SchedLayout& v, int tile, int split, int max
     sv.group_max = v.exec == v.items || grouped_heads ? 0 : (dt == HYD_BF16 ? 1024 : 512) / tile;
     sv.group_share = (float)heads / (16.f * (float)wgs);
     sv.part_max = 1; sv.part_q = 1; sv.steps_per_level = 0;
-    sv.other = 0; sv.rec_heads = item_heads(split);
+    sv.other = 0; sv.rec_heads = rec_heads;
     return sv;
 }
 
@@ -450,8 +467,6 @@ void set_parts(SchedView& sv, int limit, int T, int nseq, int max_seqlen, int hq
     sv.part_max = item_parts(sv.n_lev, sv.steps_per_level, sv.part_q, limit);
 }
 
-// tiles of num_seqs sequences that hold T tokens, at most
-long long most_items(int T, int nseq, int tile) { return ((long long)T + (long long)nseq * (tile - 1)) / tile; }
 // Every (item, head) pair gets a workgroup of its own, and the lists theirs (see SelfSchedule): where all run at once, and up
 // to 1.75 for each CU if none lasts long, since the hardware hands workgroups to the XCDs strictly in turn, which
 // balances the later ones badly.  Forward, list -> own items in us (one sequence unless noted): 3000 tokens, 8 heads 54.7 -> 52.9, 1500
@@ -533,7 +548,7 @@ hyd_status fwd_impl(const void* q, const void* k, const void* v, const int32_t* 
     if (ds != HYD_OK) return ds;
     hipStream_t st = static_cast<hipStream_t>(hip_stream);
 
-    const int split = ranged ? 0 : query_split(dt, total_tokens, num_seqs, max_seqlen, hq, hkv, compact);
+    const int split = ranged ? 0 : fwd_form(query_split(dt, total_tokens, num_seqs, max_seqlen, hq, hkv, compact), total_tokens, num_seqs, max_seqlen, hq, head_dim), shift = form_shift(split);
     const int tile = tile_q(dt), units = hq / item_heads(split);
     const WsLayout w = fwd_layout(total_tokens, num_seqs, hq, hkv, head_dim, dt, compact);
     const int occ = dt == HYD_BF16 ? dev->occ_fwd : dev->occ_f32[head_dim == 128][0];
@@ -542,20 +557,20 @@ hyd_status fwd_impl(const void* q, const void* k, const void* v, const int32_t* 
     const bool grouped = hq >= 4 * hkv;
     SchedView sv_whole = make_view(static_cast<char*>(workspace), w.sched[0], tile, 0, max_seqlen, dt, units, dev->cus * occ, grouped);
     if (split) sv_whole.other = (int)(w.split.hdr - w.sched[0].hdr);
-    const SchedView sv = split ? make_view(static_cast<char*>(workspace), w.split, 256 >> split, split, max_seqlen, dt, units, dev->cus * occ, grouped) : sv_whole;
+    const SchedView sv = split ? make_view(static_cast<char*>(workspace), w.split, 256 >> shift, shift, max_seqlen, dt, units, dev->cus * occ, grouped, item_heads(split)) : sv_whole;
     double* rope_tab = rope_base != 0.f ? reinterpret_cast<double*>(static_cast<char*>(workspace) + w.rope_tab) : nullptr;
-    const long long work = (long long)sv.max_items * units, self_work = most_items(total_tokens, num_seqs, tile >> split) * units;
+    const long long work = (long long)sv.max_items * units, self_work = most_items(total_tokens, num_seqs, tile >> shift) * units;
     const bool self = !ranged && split != 2 && self_schedule_ok(num_seqs, self_work, split ? 2 : 1, max_seqlen, dev->cus);
     SelfSchedule ss;
     if (self) {
-        ss = self_schedule(cu_seqlens, num_seqs, total_tokens, (int)self_work, units, tile >> split, sv);
+        ss = self_schedule(cu_seqlens, num_seqs, total_tokens, (int)self_work, units, tile >> shift, sv);
         add_list(ss, tile, sv_whole);
-        if (split) add_list(ss, tile >> split, sv);
+        if (split) add_list(ss, tile >> shift, sv);
         ss.log2_base = rope_base != 0.f ? log2((double)rope_base) : 0.0;
     } else {
         KernelTimer kt("schedule_prelude", st);
         hipLaunchKernelGGL(hyd_schedule_prelude, dim3(split ? 2 : 1), dim3(kPreludeThreads), schedule_lds(sv_whole.n_lev, sv.n_lev), st, cu_seqlens, num_seqs,
-                           total_tokens, tile, sv_whole, tile >> split, sv,
+                           total_tokens, tile, sv_whole, tile >> shift, sv,
                            rope_tab, head_dim / 2, rope_base != 0.f ? log2((double)rope_base) : 0.0);
     }
     if (dt == HYD_BF16) {
@@ -570,7 +585,9 @@ hyd_status fwd_impl(const void* q, const void* k, const void* v, const int32_t* 
         const dim3 grid(persistent_grid(*dev, occ, work));
         p.hm = head_map_q(units, hkv, grid.x);
         KernelTimer kt(ranged ? "fwd_range_bf16" : "fwd_bf16", st);
-        if (self) hipLaunchKernelGGL(kFwdSelfKernels[split][head_dim == 64], dim3(ss.n_work + ss.n_lists), dim3(kFwdThreads), kFwdSelfLds, st, p, ss);
+        if (split == 3 && self) hipLaunchKernelGGL(hyd_fwd_coop_self_bf16_kernel, dim3(ss.n_work + ss.n_lists), dim3(kFwdThreads), kCoLds, st, p, ss);
+        else if (split == 3) hipLaunchKernelGGL(hyd_fwd_coop_bf16_kernel, grid, dim3(kFwdThreads), kCoLds, st, p);
+        else if (self) hipLaunchKernelGGL(kFwdSelfKernels[split][head_dim == 64], dim3(ss.n_work + ss.n_lists), dim3(kFwdThreads), kFwdSelfLds, st, p, ss);
         else hipLaunchKernelGGL(kFwdKernels[ranged ? 3 : split][head_dim == 64], grid, dim3(kFwdThreads), kFwdLds, st, p);
     } else {
         F32Params p;
@@ -629,7 +646,7 @@ hyd_status bwd_impl(const void* q, const void* k, const void* v, const void* o, 
     if (wide) sv_kv.other = (int)(w.wide.hdr - w.sched[0].hdr);
     SchedView sv_whole = make_view(ws, w.sched[1], tile_q(dt), 0, max_seqlen, dt, units, dev->cus * occ_q, grouped);
     if (split) sv_whole.other = (int)(w.split.hdr - w.sched[1].hdr);
-    const SchedView sv_q = split ? make_view(ws, w.split, 256 >> split, split, max_seqlen, dt, units, dev->cus * occ_q, grouped) : sv_whole;
+    const SchedView sv_q = split ? make_view(ws, w.split, 256 >> split, split, max_seqlen, dt, units, dev->cus * occ_q, grouped, item_heads(split)) : sv_whole;
     float* Dvec = reinterpret_cast<float*>(ws + w.stat[0]);
     double* rope_tab = rope_base != 0.f ? reinterpret_cast<double*>(ws + w.rope_tab) : nullptr;
     const long long work_q = (long long)sv_q.max_items * units, work_kv = (long long)sv_wide.max_items * sv_kv.part_max * hkv;
