@@ -59,6 +59,13 @@ size_t sched_layout(SchedLayout& v, size_t at, int T, int nseq, int tile, int sp
     return at;
 }
 
+// Batches of up to so many (token, head) pairs run dK/dV beside dQ in one launch: each of the two leaves most of the chip
+// idle and lasts as long as its longest item.  dK/dV converts dO itself then, which costs it a fifth where the chip is
+// full.  Backward, one launch after the other -> beside each other (log-normal lengths, d = 128): 8 heads, 1500 tokens 70 -> 51
+// us, 3000 tokens 103 -> 80, 6000 184 -> 164 (8/1 heads 187 -> 191, one sequence 318 -> 383); 32 heads, 700 tokens 56 -> 48, 1500
+// 93 -> 86 (32/8 heads 94 -> 94), 3000 200 -> 208.
+constexpr long long kBothRows = 40960;
+
 // Parts of dK/dV items.  An item may be taken in as many parts as the sums of all rows fit behind the rest of the
 // workspace and into kPartBytes (splitting pays where few items keep few compute units busy, which needs a small
 // batch or few KV heads).  A call with a smaller workspace takes fewer parts or none: a workspace made for more tokens does for
@@ -66,6 +73,8 @@ size_t sched_layout(SchedLayout& v, size_t at, int T, int nseq, int tile, int sp
 // of key tiles of its longest sequence, so that the size asked for never falls as tokens are added.
 constexpr size_t kPartBytes = 256u << 20;
 constexpr int kPartSteps = 16;                             // see set_parts
+constexpr int kBothPartSteps = 4, kBothPartGain = 8;       // see both_parts
+constexpr size_t kBothPartBytes = 64u << 20;
 size_t part_bytes(int T, int hkv, int head_dim) { return 2 * sizeof(float) * (size_t)T * (size_t)hkv * (size_t)head_dim; }
 int part_limit(size_t bytes, int T, int hkv, int head_dim) {
     const size_t one = part_bytes(T, hkv, head_dim);
@@ -93,7 +102,13 @@ size_t useful_part_bytes(int T, int hq, int hkv, int head_dim) {
         if (q > 0 && most < (int)ceil(n * steps / q)) most = (int)ceil(n * steps / q);
         if ((double)n * steps < 1.6 * share) break;                 // and so on: a share grows with n squared
     }
-    const size_t bytes = most == 1 ? 0 : (size_t)most * part_bytes(T, hkv, head_dim);
+    size_t bytes = most == 1 ? 0 : (size_t)most * part_bytes(T, hkv, head_dim);
+    const int both = T < kBothRows / hq ? T : (int)(kBothRows / hq);        // tokens of the largest batch that both_parts takes
+    if (steps * ((both + kKvBN - 1) / kKvBN) >= kBothPartSteps + kBothPartGain) {
+        const int parts = hq / hkv < 4 ? 2 * (hq / hkv) + 1 : kPartsMax;     // (a part has a step per key tile of the item at least)
+        const size_t some = (size_t)parts * part_bytes(both, hkv, head_dim), room = some < kBothPartBytes ? some : kBothPartBytes;
+        if (bytes < room) bytes = room;
+    }
     return bytes < kPartBytes ? bytes : kPartBytes;
 }
 
@@ -161,12 +176,6 @@ int query_split(hyd_dtype dt, int T, int nseq, int max_seqlen, int hq, int hkv, 
 int finest_split(hyd_dtype dt, int hq, int hkv, bool compact) {
     return dt != HYD_BF16 || compact ? 0 : ((hq / hkv) % 4 == 0 ? 2 : 1);
 }
-// Batches of up to so many (token, head) pairs run dK/dV beside dQ in one launch: each of the two leaves most of the chip
-// idle and lasts as long as its longest item.  dK/dV converts dO itself then, which costs it a fifth where the chip is
-// full.  Backward, one launch after the other -> beside each other (log-normal lengths, d = 128): 8 heads, 1500 tokens 70 -> 51
-// us, 3000 tokens 103 -> 80, 6000 184 -> 164 (8/1 heads 187 -> 191, one sequence 318 -> 383); 32 heads, 700 tokens 56 -> 48, 1500
-// 93 -> 86 (32/8 heads 94 -> 94), 3000 200 -> 208.
-constexpr long long kBothRows = 40960;
 // dK/dV by tiles of 256 keys (hyd_bwd_wide.h) instead of 128.  The host knows T, the number of sequences and a bound on
 // their length: with one sequence of that length and the others alike, `mean` is the length of a token's sequence on average
 // and `share` a workgroup's share of the work.
@@ -467,6 +476,32 @@ void set_parts(SchedView& sv, int limit, int T, int nseq, int max_seqlen, int hq
     sv.part_max = item_parts(sv.n_lev, sv.steps_per_level, sv.part_q, limit);
 }
 
+// Where dK/dV shares a launch with dQ: the workgroups that it has, one per item where there is room for all items, else four of
+// seven (its share of the products);
+int both_kv_workgroups(int cus, long long work_q) {
+    const int n = cus * 4 / 7;
+    return n < cus - work_q ? (int)(cus - work_q) : n;
+}
+
+// Items in finer parts than those of set_parts, where dK/dV shares a launch with dQ and its longest item makes the launch: down
+// to 4 steps, as fine as the parts still all start at once (a level in n parts of q steps: half a part more than its steps / q on average), and
+// not finer than what the longest dQ item lasts (its tile of 64 keys counts 1.2 steps for 64 rows of four heads, half a step
+// where four waves share 128 rows).  A step takes 0.6-0.85 us and the adding pass 5-6, so that cutting has to take 8 steps off.
+// Backward in us, one sequence unless noted: 256 tokens, 8/1 heads 49.1 -> 28.8, 256, 32/8 heads 43.4 -> 32.0, 700, 32/8 54.0 -> 48.2, 900,
+// 2/1 47.4 -> 35.9, 1500, 8 heads 61.4 -> 53.4, 3000 tokens of 64-1024, 8/1 56.9 -> 51.2.  Without the bound by room 3000 tokens, 8 heads
+// 77.3 -> 80.6, 700, 32 heads 48.0 -> 58.1; without the one by dQ 2200, 2/1 heads 62.9 -> 65.1.
+void both_parts(SchedView& sv, int limit, int T, int nseq, int max_seqlen, int hq, int hkv, int cus, long long work_q, int split) {
+    const double longest = (double)sv.n_lev * sv.steps_per_level, room = both_kv_workgroups(cus, work_q) - 0.5 * most_items(T, nseq, kKvBN) * hkv;
+    if (limit <= 1 || room <= 0) return;
+    const int others = nseq > 1 ? ((T - max_seqlen) / (nseq - 1) + kKvBN - 1) / kKvBN : 0;      // tiles of each, if alike
+    const double steps = share_of_work(1, sv.steps_per_level, sv.n_lev + (nseq - 1) * others, nseq, sv.n_lev, hkv, 1);
+    double q = fmax(fmax(kBothPartSteps, steps / room), max_seqlen / (split == 2 ? 54.0 : 128.0));
+    q = fmax(q, longest / limit);
+    if (longest < q + kBothPartGain) return;
+    sv.part_q = (int)ceil(q);
+    sv.part_max = item_parts(sv.n_lev, sv.steps_per_level, sv.part_q, limit);
+}
+
 // Every (item, head) pair gets a workgroup of its own, and the lists theirs (see SelfSchedule): where all run at once, and up
 // to 1.75 for each CU if none lasts long, since the hardware hands workgroups to the XCDs strictly in turn, which
 // balances the later ones badly.  Forward, list -> own items in us (one sequence unless noted): 3000 tokens, 8 heads 54.7 -> 52.9, 1500
@@ -638,18 +673,20 @@ hyd_status bwd_impl(const void* q, const void* k, const void* v, const void* o, 
     const int units = hq / item_heads(split);
     const bool grouped = hq >= 4 * hkv;
     SchedView sv_kv = make_view(ws, w.sched[0], tile_kv(dt), 0, max_seqlen, dt, hkv, dev->cus * occ_kv, grouped);
-    if (dt == HYD_BF16) set_parts(sv_kv, w.part_max, total_tokens, num_seqs, max_seqlen, hq, hkv, dev->cus * occ_kv);
     const bool both = dt == HYD_BF16 && !ranged && rope_base == 0.f && (long long)total_tokens * hq <= kBothRows;
+    SchedView sv_whole = make_view(ws, w.sched[1], tile_q(dt), 0, max_seqlen, dt, units, dev->cus * occ_q, grouped);
+    if (split) sv_whole.other = (int)(w.split.hdr - w.sched[1].hdr);
+    const SchedView sv_q = split ? make_view(ws, w.split, 256 >> split, split, max_seqlen, dt, units, dev->cus * occ_q, grouped, item_heads(split)) : sv_whole;
+    const long long work_q = (long long)sv_q.max_items * units;
+    if (dt == HYD_BF16) set_parts(sv_kv, w.part_max, total_tokens, num_seqs, max_seqlen, hq, hkv, dev->cus * occ_kv);
+    if (both) both_parts(sv_kv, w.part_max, total_tokens, num_seqs, max_seqlen, hq, hkv, dev->cus, work_q, split);
     const bool wide = dt == HYD_BF16 && !ranged && !both && sv_kv.part_max == 1 &&
                       wide_kv(total_tokens, num_seqs, max_seqlen, hq, hkv, head_dim, dev->cus);
     const SchedView sv_wide = wide ? make_view(ws, w.wide, kKwBN, 0, max_seqlen, dt, hkv, dev->cus, grouped) : sv_kv;
     if (wide) sv_kv.other = (int)(w.wide.hdr - w.sched[0].hdr);
-    SchedView sv_whole = make_view(ws, w.sched[1], tile_q(dt), 0, max_seqlen, dt, units, dev->cus * occ_q, grouped);
-    if (split) sv_whole.other = (int)(w.split.hdr - w.sched[1].hdr);
-    const SchedView sv_q = split ? make_view(ws, w.split, 256 >> split, split, max_seqlen, dt, units, dev->cus * occ_q, grouped, item_heads(split)) : sv_whole;
     float* Dvec = reinterpret_cast<float*>(ws + w.stat[0]);
     double* rope_tab = rope_base != 0.f ? reinterpret_cast<double*>(ws + w.rope_tab) : nullptr;
-    const long long work_q = (long long)sv_q.max_items * units, work_kv = (long long)sv_wide.max_items * sv_kv.part_max * hkv;
+    const long long work_kv = (long long)sv_wide.max_items * sv_kv.part_max * hkv;
     if (dt == HYD_BF16) {
         BwdScratch sc;
         sc.Dq = Dvec;
@@ -699,9 +736,7 @@ hyd_status bwd_impl(const void* q, const void* k, const void* v, const void* o, 
         WorkList lq{sv_q.hdr, sv_q.hdr + kHdrCursor, sv_q.exec, head_map_q(units, hkv, grid_q)};
         WorkList lkv{sv_wide.hdr + kHdrExec, sv_wide.hdr + kHdrCursor, sv_wide.exec, head_map_kv(hkv, grid_kv)};
         if (both) {
-            // the workgroups of dK/dV: one per item where there is room for all items, else four of seven (its share of the products)
-            int n_kv = dev->cus * 4 / 7;
-            if (n_kv < dev->cus - work_q) n_kv = (int)(dev->cus - work_q);
+            int n_kv = both_kv_workgroups(dev->cus, work_q);
             if (n_kv > work_kv) n_kv = (int)work_kv;
             n_kv = (n_kv + kQueues - 1) / kQueues * kQueues;           // queue by XCD on both sides
             int n_q = dev->cus - n_kv;
