@@ -503,13 +503,19 @@ void both_parts(SchedView& sv, int limit, int T, int nseq, int max_seqlen, int h
 }
 
 // Every (item, head) pair gets a workgroup of its own, and the lists theirs (see SelfSchedule): where all run at once, and up
-// to 1.75 for each CU if none lasts long, since the hardware hands workgroups to the XCDs strictly in turn, which
-// balances the later ones badly.  Forward, list -> own items in us (one sequence unless noted): 3000 tokens, 8 heads 54.7 -> 52.9, 1500
-// tokens of log-normal lengths, 32 heads (430 items) 32.3 -> 25.8, 6000, 8 heads (400) 65.0 -> 62.8; 8000, 8 heads (504 items)
-// 186 -> 196, 16000 (504) 449 -> 485; 2000, 64/8 heads (512) 76.8 -> 79.0.
-bool self_schedule_ok(int nseq, long long work, int lists, int max_seqlen, int cus) {
+// to 1.75 for each CU (1.5 if no sequence is long) where the launch lasts as long as its longest item (see query_split): the hardware
+// hands workgroups to the XCDs strictly in turn, which balances the later ones badly.  Forward, list -> own items in us (one sequence unless
+// noted): 3000 tokens, 8 heads 54.7 -> 52.9, 1500 tokens of log-normal lengths, 32 heads (430 items) 32.3 -> 25.8, 6000, 8 heads (400)
+// 65.0 -> 62.8; 8000, 8 heads (504 items) 186 -> 196, 16000 (504) 449 -> 485; 2000, 64/8 heads (512) 76.8 -> 79.0; sequences of 64-1024:
+// 5500 tokens, 8 heads (376) 26.7 -> 28.0, 12000, 5 heads (280 even items) 34.9 -> 37.3.  fp32, d = 128: 2400 tokens of 64-1024, 8 heads 77.7 ->
+// 69.2; 2400 of equal lengths 53.7 -> 62.4, 5600, 4 heads 59 -> 89, so that none has more than one item per CU there.
+// (For an even batch the same holds of two or three sequences of up to 2048 tokens: 3 x 1000, 32 heads (384) 50.1 -> 46.7, 2 x 1500 56.9 -> 52.0;
+// 4 x 900, 20 heads (320) 41.9 -> 42.8, 4 x 2500, 10 heads (400) 85 -> 106.)
+bool self_schedule_ok(hyd_dtype dt, int nseq, long long work, int lists, bool uneven, int max_seqlen, int cus) {
     if (nseq > kSelfSeqs) return false;
-    return work + lists <= cus || (4 * (work + lists) <= 7 * cus && max_seqlen <= 6144);
+    if (work + lists <= cus) return true;
+    const bool few = nseq <= 3 && max_seqlen <= 2048;
+    return dt == HYD_BF16 && (uneven || few) && 4 * work <= (max_seqlen > 1024 || few ? 7 : 6) * cus && max_seqlen <= 6144;
 }
 SelfSchedule self_schedule(const int32_t* cu, int nseq, int T, int work, int heads, int tile, const SchedView& sv) {
     SelfSchedule ss;
@@ -595,7 +601,7 @@ hyd_status fwd_impl(const void* q, const void* k, const void* v, const int32_t* 
     const SchedView sv = split ? make_view(static_cast<char*>(workspace), w.split, 256 >> shift, shift, max_seqlen, dt, units, dev->cus * occ, grouped, item_heads(split)) : sv_whole;
     double* rope_tab = rope_base != 0.f ? reinterpret_cast<double*>(static_cast<char*>(workspace) + w.rope_tab) : nullptr;
     const long long work = (long long)sv.max_items * units, self_work = most_items(total_tokens, num_seqs, tile >> shift) * units;
-    const bool self = !ranged && split != 2 && self_schedule_ok(num_seqs, self_work, split ? 2 : 1, max_seqlen, dev->cus);
+    const bool self = !ranged && split != 2 && self_schedule_ok(dt, num_seqs, self_work, split ? 2 : 1, split != 0, max_seqlen, dev->cus);
     SelfSchedule ss;
     if (self) {
         ss = self_schedule(cu_seqlens, num_seqs, total_tokens, (int)self_work, units, tile >> shift, sv);
@@ -780,7 +786,7 @@ hyd_status bwd_impl(const void* q, const void* k, const void* v, const void* o, 
         p.tr = t_trace;
         const bool short_rows = max_seqlen <= kF32Short;
         const long long self_work = most_items(total_tokens, num_seqs, tile_q(dt)) * hq;
-        const bool self = !short_rows && self_schedule_ok(num_seqs, self_work, 2, max_seqlen, dev->cus);
+        const bool self = !short_rows && self_schedule_ok(dt, num_seqs, self_work, 2, false, max_seqlen, dev->cus);
         if (!self) {   // one launch builds both item lists, one workgroup each
             KernelTimer kt("schedule_prelude", st);
             hipLaunchKernelGGL(hyd_schedule_prelude, dim3(w.n_sched), dim3(kPreludeThreads), schedule_lds(sv_kv.n_lev, sv_q.n_lev), st, cu_seqlens,

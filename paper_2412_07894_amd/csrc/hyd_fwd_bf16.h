@@ -273,7 +273,6 @@ __device__ __forceinline__ void fwd_items(const FwdParams& p, const SelfSchedule
     bool have;
     if constexpr (kSelf) have = self_first(*ss, smem, kFwdThreads, wi);
     else have = wf.first(p.hm, p.hdr, p.cursors, p.items, slot, wi, blockIdx.x);
-    const double* rope_tab = p.rope_tab;
     while (have) {
         ++n_done;
         const int lev = wi.lev, head0 = wi.head << QS::kLh, row0 = wi.row0, L = wi.len;
@@ -333,11 +332,7 @@ __device__ __forceinline__ void fwd_items(const FwdParams& p, const SelfSchedule
                                 [&](int j) { return QS::tile_at(j, q_stride_b, kRowB); }, wave, dma_voff_q);
         }
         if (tid == 0) *redo = 0;
-        if (kSelf && rope_tab) {
-            double* tab = reinterpret_cast<double*>(smem + kFwdTabOff);
-            rope_table_fill(tab, D / 2, ss->log2_base, tid, kFwdThreads);
-            rope_tab = tab;
-        }
+        if (kSelf && p.rope_tab) rope_table_fill(reinterpret_cast<double*>(smem + kFwdTabOff), D / 2, ss->log2_base, tid, kFwdThreads);
         __syncthreads();                                  // the first tiles and the Q rows have landed
         bf16x8 qf[D / 16];
         {
@@ -349,7 +344,7 @@ __device__ __forceinline__ void fwd_items(const FwdParams& p, const SelfSchedule
             for (int ks = 0; ks < D / 16; ++ks) {
                 asm volatile("" : "+v"(qv[ks]));          // the reads stay on this side of the barrier
             }
-            if (rope_tab) rope_row_frags<D, false>(qv, rope_tab, qrow, half);      // position = local row: reset per sequence
+            if (p.rope_tab) rope_row_frags<D, false>(qv, kSelf ? reinterpret_cast<const double*>(smem + kFwdTabOff) : p.rope_tab, qrow, half);      // position = local row: reset per sequence
 #pragma unroll
             for (int ks = 0; ks < D / 16; ++ks) qf[ks] = as_bf16x8(qv[ks] ^ sign_flip);
         }

@@ -362,16 +362,14 @@ struct WorkFetcher {
         return true;
     }
     // `slot`: kSlotInts ints of LDS.  All threads must call first/next (each contains a barrier).  `wg`: number of the workgroup
-    // among those that share the queues, hm.grid of which start on a fixed index; the others, which come from
-    // another list (wg < 0: -1 - number there), claim their first item.
+    // among the hm.grid that share the queues.
     __device__ __forceinline__ bool first(const HeadMap& hm, const int* __restrict__ hdr, int* cursors,
-                                          const int* __restrict__ items, int* slot, WorkItem& w, int wg) {
+                                          const int* __restrict__ items, int* slot, WorkItem& w, unsigned wg) {
         cur = 0;
         if (threadIdx.x == 0) {
+            queue = wg & (kQueues - 1);
             n_items = hdr[0];
-            queue = (wg < 0 ? -1 - wg : wg) & (kQueues - 1);
-            if (wg < 0) issue_claim(hm, cursors);
-            resolve(hm, cursors, items, wg < 0 ? fixed(hm, queue) + claim_w : wg / kQueues);
+            resolve(hm, cursors, items, wg / kQueues);
             publish(slot);
         }
         __syncthreads();
