@@ -356,8 +356,8 @@ constexpr BwdKernel kDqKernels[4][2] = {{hyd_bwd_dq_bf16_kernel<false, 128, 0>, 
                                         {hyd_bwd_dq_bf16_kernel<true, 128, 0>, hyd_bwd_dq_bf16_kernel<true, 64, 0>}};
 
 typedef void (*FwdSelfKernel)(FwdParams, SelfSchedule);
-constexpr FwdSelfKernel kFwdSelfKernels[2][2] = {{hyd_fwd_self_bf16_kernel<128, 0>, hyd_fwd_self_bf16_kernel<64, 0>},      // [half tiles][head_dim == 64]
-                                                 {hyd_fwd_self_bf16_kernel<128, 1>, hyd_fwd_self_bf16_kernel<64, 1>}};
+constexpr FwdSelfKernel kFwdSelfKernels[2][2] = {{hyd_fwd_bf16_kernel<false, 128, 0, SelfSchedule>, hyd_fwd_bf16_kernel<false, 64, 0, SelfSchedule>},      // [half tiles][head_dim == 64]
+                                                 {hyd_fwd_bf16_kernel<false, 128, 1, SelfSchedule>, hyd_fwd_bf16_kernel<false, 64, 1, SelfSchedule>}};
 typedef void (*BothKernel)(BwdParams, WorkList, WorkList, int);
 constexpr BothKernel kBothKernels[3][2] = {{hyd_bwd_both_bf16_kernel<128, 0>, hyd_bwd_both_bf16_kernel<64, 0>},
                                            {hyd_bwd_both_bf16_kernel<128, 1>, hyd_bwd_both_bf16_kernel<64, 1>},
