@@ -227,12 +227,13 @@ __device__ __forceinline__ void fwd_tile(int Kt, int Vt, const FragAddr& fa, con
     }
 }
 
+__device__ __forceinline__ double self_log2_base(const SelfSchedule& ss) { return ss.log2_base; }
+
 // R: range variant.  Each sequence has a query range [q_begin, q_end) and a key range
 // [kv_begin, kv_end) in local positions, the begins multiples of the query tile: query tiles
 // outside the query range are skipped, the tile loop starts at the key range's first tile and
 // stops at its end, and a row that sees no key of the range gets O = 0 and LSE = -inf (the
 // neutral element of the log-sum-exp merge of partial results).
-__device__ __forceinline__ double self_log2_base(const SelfSchedule& ss) { return ss.log2_base; }
 // With a SelfSchedule as second argument: one item per workgroup, found by itself.  (Both are this kernel and not a function that two
 // kernels call: inlined, the compiler hoists the fetcher's divisions and orders the code in front of the tile loop otherwise, 0.3-0.6
 // us of every forward that takes a list; 65536 tokens, 32 heads 2870.7 -> 2864.9 us, 9000 tokens, 8 heads 36.0 -> 35.8.)
@@ -311,7 +312,11 @@ __global__ void __launch_bounds__(kFwdThreads, 1) hyd_fwd_bf16_kernel(FwdParams 
             have = wf.next(p.hm, p.cursors, p.items, slot, wi);
             continue;
         }
-        const int td = wrow0 / kFwdBN;                    // this wave's diagonal (= last) tile
+        int td = wrow0 / kFwdBN;                          // this wave's diagonal (= last) tile
+        // An item that the waves found by themselves is the workgroup's to the compiler too, and it would make the branches on the
+        // diagonal scalar and keep the accumulators twice, copied in every tile (see fwd_tile): one sequence of 65280 tokens, 1 head
+        // 1428 us from a list, 1559 so, 1438 now; 2040 tokens, 32/8 heads 58.2 and 57.1, now 53.5.
+        if constexpr (kSelf) asm volatile("" : "+v"(td));
         const int koff0 = 4 * half - qrow;                // first key slot of the lane minus its query row, tile 0
         // K/V rows [0, kv_end) of this sequence and KV head; reads past them return zero
         const uint32_t kv_bytes = (uint32_t)(kv_end - 1) * kv_stride_b + kRowB;
