@@ -503,23 +503,23 @@ void both_parts(SchedView& sv, int limit, int T, int nseq, int max_seqlen, int h
 }
 
 // Every (item, head) pair gets a workgroup of its own, and the lists theirs (see SelfSchedule): where all run at once, and up
-// to 1.75 for each CU (1.5 if no sequence is long) where the launch lasts as long as its longest item (see query_split): the hardware
-// hands workgroups to the XCDs strictly in turn, which balances the later ones badly.  Forward, list -> own items in us (one sequence unless
-// noted): 3000 tokens, 8 heads 54.7 -> 52.9, 1500 tokens of log-normal lengths, 32 heads (430 items) 32.3 -> 25.8, 6000, 8 heads (400)
-// 65.0 -> 62.8; 8000, 8 heads (504 items) 186 -> 196, 16000 (504) 449 -> 485; 2000, 64/8 heads (512) 76.8 -> 79.0; sequences of 64-1024:
-// 5500 tokens, 8 heads (376) 26.7 -> 28.0, 12000, 5 heads (280 even items) 34.9 -> 37.3.  fp32, d = 128: 2400 tokens of 64-1024, 8 heads 77.7 ->
-// 69.2; 2400 of equal lengths 53.7 -> 62.4, 5600, 4 heads 59 -> 89, so that none has more than one item per CU there.
-// (For an even batch the same holds of two or three sequences of up to 2048 tokens: 3 x 1000, 32 heads (384) 50.1 -> 46.7, 2 x 1500 56.9 -> 52.0;
-// 4 x 900, 20 heads (320) 41.9 -> 42.8, 4 x 2500, 10 heads (400) 85 -> 106.)
+// to 1.75 for each CU (1.5 if no sequence is long) where the launch lasts as long as its longest item (see query_split), or where two or
+// three sequences of up to 2048 tokens hold them; they then come longest first.  Forward, list -> own items in us: one sequence of
+// 1500 tokens, 32 heads (430 items) 32.3 -> 25.8; 10240 tokens of log-normal lengths, 5 heads (430) 67.8 -> 62.1; 6656 of 64-1024, 5 heads
+// (320) 29.3 -> 23.9; 2040 in sequences of 2000, 32/8 heads (288 whole tiles) 58.2 -> 53.5.  Beyond that the hardware, which
+// hands workgroups to the XCDs strictly in turn, balances the later ones badly (sequence by sequence, 8 heads: one sequence of 8000 tokens, 504
+// items, 186 -> 196; 16000, 504 whole tiles, 449 -> 485).  fp32, d = 128, sequence by sequence: 2400 tokens of 64-1024, 8 heads 77.7 -> 69.2; 2400
+// of equal lengths 53.7 -> 62.4, 5600, 4 heads 59 -> 89, so that none has more than one item per CU there.
 bool self_schedule_ok(hyd_dtype dt, int nseq, long long work, int lists, bool uneven, int max_seqlen, int cus) {
     if (nseq > kSelfSeqs) return false;
     if (work + lists <= cus) return true;
     const bool few = nseq <= 3 && max_seqlen <= 2048;
     return dt == HYD_BF16 && (uneven || few) && 4 * work <= (max_seqlen > 1024 || few ? 7 : 6) * cus && max_seqlen <= 6144;
 }
-SelfSchedule self_schedule(const int32_t* cu, int nseq, int T, int work, int heads, int tile, const SchedView& sv) {
+SelfSchedule self_schedule(const int32_t* cu, int nseq, int T, int work, int lists, int heads, int tile, const SchedView& sv, int cus) {
     SelfSchedule ss;
     ss.cu = cu; ss.nseq = nseq; ss.T = T; ss.n_work = work; ss.heads = heads; ss.tile = tile; ss.n_lev = sv.n_lev;
+    ss.by_level = work + lists > cus;
     ss.n_lists = 0; ss.log2_base = 0.0;
     return ss;
 }
@@ -604,7 +604,7 @@ hyd_status fwd_impl(const void* q, const void* k, const void* v, const int32_t* 
     const bool self = !ranged && split != 2 && self_schedule_ok(dt, num_seqs, self_work, split ? 2 : 1, split != 0, max_seqlen, dev->cus);
     SelfSchedule ss;
     if (self) {
-        ss = self_schedule(cu_seqlens, num_seqs, total_tokens, (int)self_work, units, tile >> shift, sv);
+        ss = self_schedule(cu_seqlens, num_seqs, total_tokens, (int)self_work, split ? 2 : 1, units, tile >> shift, sv, dev->cus);
         add_list(ss, tile, sv_whole);
         if (split) add_list(ss, tile >> shift, sv);
         ss.log2_base = rope_base != 0.f ? log2((double)rope_base) : 0.0;
@@ -798,7 +798,7 @@ hyd_status bwd_impl(const void* q, const void* k, const void* v, const void* o, 
             p.hdr = sv_q.hdr; p.items = sv_q.exec; p.cursors = sv_q.hdr + kHdrCursor; p.hm = head_map_q(hq, hkv, grid_q.x);
             KernelTimer kt("bwd_dq_fp32", st);
             if (self) {
-                SelfSchedule ss = self_schedule(cu_seqlens, num_seqs, total_tokens, (int)self_work, hq, tile_q(dt), sv_q);
+                SelfSchedule ss = self_schedule(cu_seqlens, num_seqs, total_tokens, (int)self_work, 2, hq, tile_q(dt), sv_q, dev->cus);
                 add_list(ss, tile_kv(dt), sv_kv);
                 add_list(ss, tile_q(dt), sv_q);
                 const auto self_kernel = head_dim == 64 ? hyd_bwd_dq_self_fp32_kernel<64> : hyd_bwd_dq_self_fp32_kernel<128>;

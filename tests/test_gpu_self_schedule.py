@@ -42,6 +42,41 @@ def test_own_items_equal_listed_ones(lens, dtype, hq, hkv, d, rope_base):
         assert bool(torch.isfinite(a.float()).all()) and torch.equal(a, b), name
 
 
+# more items than compute units: half tiles of equal sequences, the same of more sequences than a wave has lanes, 64-row tiles
+@pytest.mark.parametrize("lens,hq", [([2000] * 19, 1), ([200, 0, 130] * 34, 2), ([700] * 9 + [5], 3)])
+def test_own_items_of_a_second_round(lens, hq):
+    """They agree bit for bit with listed ones, and the workgroups take the longest first: those of the highest level last
+    about as long as each other (sequence by sequence they would be spread over all workgroups)."""
+    d, T = 128, sum(lens)
+    g = torch.Generator(device="cuda")
+    g.manual_seed(61)
+    q, k, v = (torch.randn((T, hq, d), device="cuda", generator=g).to(torch.bfloat16) for _ in range(3))
+    rec = torch.zeros((3 * 512, 4), dtype=torch.int64, device="cuda")
+
+    def run(copies):
+        n = lens * copies
+        return binding.varlen_attn_fwd(*(t.repeat(copies, 1, 1) for t in (q, k, v)), torch.from_numpy(wl.cu_seqlens(n)).cuda(), max(n), d ** -0.5)
+
+    print(f"\n{len(lens)} sequences, {T} tokens, {hq} heads", flush=True)
+    run(1)
+    binding.enable_kernel_timing(True)
+    binding.set_wg_trace(rec)
+    try:
+        o, lse = run(1)
+        names = [n for n, _ in binding.kernel_times()]
+    finally:
+        binding.set_wg_trace(None)
+        binding.enable_kernel_timing(False)
+    assert names == ["fwd_bf16"]
+    r = rec[:512].cpu().numpy()
+    took = (r[:, 2] - r[:, 1])[r[:, 3] > 0]
+    assert 256 < len(took) <= 448
+    first = lens.count(max(lens)) * hq
+    assert took[:first].min() > 0.5 * took.max() and took[-len(took) // 4:].mean() < took[:first].mean()
+    o2, lse2 = run(257 // len(lens) + 1)
+    assert torch.equal(o, o2[:T]) and torch.equal(lse, lse2[:, :T])
+
+
 def test_malformed_lengths_stay_inside():
     """A cu_seqlens that decreases, ends early or holds a sequence longer than max_seqlen: every workgroup ends and the
     status call says what was wrong; nothing behind the tensors is written."""
