@@ -199,17 +199,6 @@ int item_heads(int split) { return split == 2 ? 4 : 1; }
 int form_shift(int split) { return split == 3 ? 2 : split; }      // rows of an item: 256 >> shift
 // tiles of num_seqs sequences that hold T tokens, at most
 long long most_items(int T, int nseq, int tile) { return ((long long)T + (long long)nseq * (tile - 1)) / tile; }
-// Instead of half tiles where the launch can start with all of its items, or nearly: those that come second cost what an item
-// costs at least, 8 us.  Forward, half tiles -> form 3 in us (in brackets its items), d = 128: one sequence of 256 tokens, 8 heads
-// (32) 9.9 -> 9.5, 700, 32 heads (352) 17.5 -> 15.5, 1500, 8 heads (192) 29.7 -> 23.2, 3000, 8 heads (376) 52.4 -> 41.6, 4000 (504)
-// 67.8 -> 64.4, 6000 (752) 103 -> 135; sequences of 64-1024: 2000 tokens, 8 heads (280) 16.8 -> 14.0, 3000 (416) 18.6 -> 20.2.  (With d = 64,
-// where the second product occupied two waves of four, 1500 tokens, 8 heads 19.1 -> 18.2, 700, 32 heads 13.7 -> 14.0.)
-int fwd_form(int split, int T, int nseq, int max_seqlen, int hq, int head_dim) {
-    if (split != 1 || head_dim != 128) return split;
-    const long long items = most_items(T, nseq, 64) * hq;
-    return items <= 384 || (items <= 512 && max_seqlen >= 2048) ? 3 : 1;
-}
-
 // The forward's size does not depend on the heads: one workspace serves layers of different head counts.
 WsLayout fwd_layout(int T, int nseq, int hq, int hkv, int head_dim, hyd_dtype dt, bool compact) {
     WsLayout w = ws_layout(T, nseq, tile_q(dt), tile_q(dt), dt != HYD_BF16 || compact ? 0 : 2, hq, hkv, head_dim, dt, false, compact);
@@ -516,6 +505,22 @@ bool self_schedule_ok(hyd_dtype dt, int nseq, long long work, int lists, bool un
     const bool few = nseq <= 3 && max_seqlen <= 2048;
     return dt == HYD_BF16 && (uneven || few) && 4 * work <= (max_seqlen > 1024 || few ? 7 : 6) * cus && max_seqlen <= 6144;
 }
+// Form 3 instead of half tiles where the launch can start with all of its items, or nearly (1.5 for each CU): those that come second cost
+// what an item costs at least, 8 us, and 128 keys of the longest item take 0.48 us less, so that up to 2 for each CU pay from some 2048
+// tokens on.  Forward, half tiles -> form 3 in us (in brackets its items), d = 128: one sequence of 256 tokens, 8 heads
+// (32) 9.9 -> 9.5, 700, 32 heads (352) 17.5 -> 15.5, 1500, 8 heads (192) 29.7 -> 23.2, 3000, 8 heads (376) 52.4 -> 41.6, 4000 (504)
+// 67.8 -> 64.4, 6000 (752) 103 -> 135; sequences of 64-1024: 2000 tokens, 8 heads (280) 16.8 -> 14.0, 3000 (416) 18.6 -> 20.2.  (With d = 64,
+// where the second product occupied two waves of four, 1500 tokens, 8 heads 19.1 -> 18.2, 700, 32 heads 13.7 -> 14.0.)
+// From a list only where an XCD keeps to few heads (see head_map_q), since 64 rows read a head's keys four times as often as 256: one
+// sequence, from a list: 25600 tokens, 1 head (400) 382 -> 330, 6528, 5 heads (510) 107 -> 111, 2880, 10 heads (450) 49.3 -> 58.1, 3264 (510) 60.4 -> 67.8.
+int fwd_form(int split, int T, int nseq, int max_seqlen, int hq, int head_dim, int cus) {
+    if (split != 1 || head_dim != 128) return split;
+    const long long items = most_items(T, nseq, 64) * hq;
+    if (2 * items <= 3 * cus) return 3;
+    if (items > 2 * cus || max_seqlen < 2048) return 1;
+    return hq % kQueues == 0 || hq < 4 || self_schedule_ok(HYD_BF16, nseq, items, 2, true, max_seqlen, cus) ? 3 : 1;
+}
+
 SelfSchedule self_schedule(const int32_t* cu, int nseq, int T, int work, int lists, int heads, int tile, const SchedView& sv, int cus) {
     SelfSchedule ss;
     ss.cu = cu; ss.nseq = nseq; ss.T = T; ss.n_work = work; ss.heads = heads; ss.tile = tile; ss.n_lev = sv.n_lev;
@@ -589,7 +594,7 @@ hyd_status fwd_impl(const void* q, const void* k, const void* v, const int32_t* 
     if (ds != HYD_OK) return ds;
     hipStream_t st = static_cast<hipStream_t>(hip_stream);
 
-    const int split = ranged ? 0 : fwd_form(query_split(dt, total_tokens, num_seqs, max_seqlen, hq, hkv, compact), total_tokens, num_seqs, max_seqlen, hq, head_dim), shift = form_shift(split);
+    const int split = ranged ? 0 : fwd_form(query_split(dt, total_tokens, num_seqs, max_seqlen, hq, hkv, compact), total_tokens, num_seqs, max_seqlen, hq, head_dim, dev->cus), shift = form_shift(split);
     const int tile = tile_q(dt), units = hq / item_heads(split);
     const WsLayout w = fwd_layout(total_tokens, num_seqs, hq, hkv, head_dim, dt, compact);
     const int occ = dt == HYD_BF16 ? dev->occ_fwd : dev->occ_f32[head_dim == 128][0];

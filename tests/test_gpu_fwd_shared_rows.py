@@ -20,20 +20,42 @@ def inputs(T, hq, hkv, seed):
     return [torch.randn((T, h, D), device="cuda", generator=g).to(torch.bfloat16) for h in (hq, hkv, hkv)]
 
 
-# each sequence a workgroup's own; more sequences than such a launch takes; a list because the items are long
-CASES = [([1, 63, 64, 65, 127, 128, 129, 191, 193], 4, 2), ([1] * 257, 1, 1), ([2] * 250 + [300] * 8, 1, 1), ([6200], 4, 4)]
+def path(q, k, v, lens, scale, rope_base=None):
+    """O, LSE, the rows of a tile that the forward took, and whether it took them from a list."""
+    T, hq, hkv, d = sum(lens), q.shape[1], k.shape[1], q.shape[2]
+    ws = torch.empty(binding.workspace_bytes(T, len(lens), hq, hkv, d, binding.HYD_BF16, 0), dtype=torch.uint8, device="cuda")
+    binding.enable_kernel_timing(True)
+    try:
+        o, lse = binding.varlen_attn_fwd(q, k, v, torch.from_numpy(wl.cu_seqlens(lens)).cuda(), max(lens), scale, workspace=ws, rope_base=rope_base)
+        names = [n for n, _ in binding.kernel_times()]
+    finally:
+        binding.enable_kernel_timing(False)
+    return o, lse, binding.executed_items(ws, T, len(lens), hq, hkv, d, binding.HYD_BF16, 0, 0)[0], "schedule_prelude" in names
 
 
-@pytest.mark.parametrize("lens,hq,hkv", CASES)
+# each sequence a workgroup's own; the same of a second round; a list because there are more sequences than such a launch takes, or because the items are long
+CASES = [([1, 63, 64, 65, 127, 128, 129, 191, 193], 4, 2, False), ([130] * 60, 2, 1, False), ([2] * 250 + [300] * 8, 1, 1, True), ([6200], 3, 3, True)]
+
+
+@pytest.mark.parametrize("lens,hq,hkv,listed", CASES)
 @pytest.mark.parametrize("rope_base", [None, 1e4])
-def test_same_bits_as_whole_tiles(lens, hq, hkv, rope_base):
-    T, copies = sum(lens), 1 + 4000 // (len(lens) * hq) if max(lens) < 1000 else 24
+def test_same_bits_as_whole_tiles(lens, hq, hkv, listed, rope_base):
+    T, copies = sum(lens), 1 + 12000 // (len(lens) * hq) if max(lens) < 1000 else 24
     q, k, v = inputs(T, hq, hkv, 61)
     print(f"\n{len(lens)} sequences, {T} tokens, {hq}/{hkv}, rope {rope_base}", flush=True)
-    o, lse = forward(q, k, v, lens, D ** -0.5, rope_base)
-    o2, lse2 = forward(*(t.repeat(copies, 1, 1) for t in (q, k, v)), lens * copies, D ** -0.5, rope_base)
+    o, lse, tile, from_list = path(q, k, v, lens, D ** -0.5, rope_base)
+    assert (tile, from_list) == (64, listed), "the sizes are meant to take the form"
+    o2, lse2, tile, _ = path(*(t.repeat(copies, 1, 1) for t in (q, k, v)), lens * copies, D ** -0.5, rope_base)
+    assert tile == 256
     assert bool(torch.isfinite(o.float()).all())
     assert torch.equal(o, o2[-T:]) and torch.equal(lse, lse2[:, -T:])
+
+
+@pytest.mark.parametrize("lens,hq,tile", [([256], 8, 64), ([4000], 8, 64), ([25600], 1, 64), ([2880], 10, 128), ([6528], 5, 128), ([6000], 8, 128), ([2900], 10, 128)])
+def test_form_of_one_sequence(lens, hq, tile):
+    """64 rows per item where all or nearly all items begin at once; from a list only where an XCD keeps to few heads."""
+    q, k, v = inputs(sum(lens), hq, hq, 71)
+    assert path(q, k, v, lens, D ** -0.5)[2] == tile
 
 
 @pytest.mark.parametrize("scale", [D ** -0.5, -D ** -0.5])
