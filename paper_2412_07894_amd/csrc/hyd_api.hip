@@ -472,13 +472,15 @@ int both_kv_workgroups(int cus, long long work_q) {
     return n < cus - work_q ? (int)(cus - work_q) : n;
 }
 
-// Items in finer parts than those of set_parts, where dK/dV shares a launch with dQ and its longest item makes the launch: down
+// Items in other parts than those of set_parts, mostly finer, where dK/dV shares a launch with dQ and its longest item makes the launch: down
 // to 4 steps, as fine as the parts still all start at once (a level in n parts of q steps: half a part more than its steps / q on average), and
 // not finer than what the longest dQ item lasts (its tile of 64 keys counts 1.2 steps for 64 rows of four heads, half a step
 // where four waves share 128 rows).  A step takes 0.6-0.85 us and the adding pass 5-6, so that cutting has to take 8 steps off.
 // Backward in us, one sequence unless noted: 256 tokens, 8/1 heads 49.1 -> 28.8, 256, 32/8 heads 43.4 -> 32.0, 700, 32/8 54.0 -> 48.2, 900,
 // 2/1 47.4 -> 35.9, 1500, 8 heads 61.4 -> 53.4, 3000 tokens of 64-1024, 8/1 56.9 -> 51.2.  Without the bound by room 3000 tokens, 8 heads
 // 77.3 -> 80.6, 700, 32 heads 48.0 -> 58.1; without the one by dQ 2200, 2/1 heads 62.9 -> 65.1.
+// Where those of set_parts are taken (dK/dV after dQ, before, now): 17000 tokens, 2/1 heads 682 / 916 / 615, 14000 480 / 553 / 449, 7000, 4/2
+// 271 / 300 / 252, 20480 of log-normal lengths, 2/1 207 / 219 / 157, 10200, 4/2 133 / 143 / 104; always, 5120, 8/1 heads 250 -> 326, 5000, 4/1 135 -> 173.
 void both_parts(SchedView& sv, int limit, int T, int nseq, int max_seqlen, int hq, int hkv, int cus, long long work_q, int split) {
     const double longest = (double)sv.n_lev * sv.steps_per_level, room = both_kv_workgroups(cus, work_q) - 0.5 * most_items(T, nseq, kKvBN) * hkv;
     if (limit <= 1 || room <= 0) return;
@@ -486,6 +488,12 @@ void both_parts(SchedView& sv, int limit, int T, int nseq, int max_seqlen, int h
     const double steps = share_of_work(1, sv.steps_per_level, sv.n_lev + (nseq - 1) * others, nseq, sv.n_lev, hkv, 1);
     double q = fmax(fmax(kBothPartSteps, steps / room), max_seqlen / (split == 2 ? 54.0 : 128.0));
     q = fmax(q, longest / limit);
+    if (sv.part_max > 1) {
+        // Many items leave little room, and parts that all start at once are long then; those of set_parts, in turn, last about a
+        // workgroup's share and half a part.  (With 4/5 against what the estimate leaves out.)
+        const double again = fmax(steps / both_kv_workgroups(cus, work_q) + 0.5 * sv.part_q, max_seqlen / (split == 2 ? 54.0 : 128.0));
+        if (again < 0.8 * q) return;
+    }
     if (longest < q + kBothPartGain) return;
     sv.part_q = (int)ceil(q);
     sv.part_max = item_parts(sv.n_lev, sv.steps_per_level, sv.part_q, limit);
