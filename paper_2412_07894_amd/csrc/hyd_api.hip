@@ -65,6 +65,12 @@ size_t sched_layout(SchedLayout& v, size_t at, int T, int nseq, int tile, int sp
 // us, 3000 tokens 103 -> 80, 6000 184 -> 164 (8/1 heads 187 -> 191, one sequence 318 -> 383); 32 heads, 700 tokens 56 -> 48, 1500
 // 93 -> 86 (32/8 heads 94 -> 94), 3000 200 -> 208.
 constexpr long long kBothRows = 40960;
+// With three or more query heads per KV head the fifth weighs more, since such items go in parts of many steps: one sequence that nearly
+// fills the limit loses.  So `heads` times a workgroup's share of the steps stays within 300, which is 35000 pairs for one
+// sequence, and no limit where several hold them (one after the other -> beside each other: one sequence of 13600 tokens, 3/1 heads
+// 565 -> 608, 6800, 6/2 312 -> 329, 6/1 301 -> 330, 5800, 7/1 270 -> 277, 1280, 32/1 175 -> 183, 600, 64/1 164 -> 179; 10000, 3/1 398 -> 364,
+// 5000, 6/2 223 -> 202, 4000, 8/1 197 -> 159; with two, 20480, 2/1 896 -> 838; with one, 40960, 1 head 1881 -> 1654).
+constexpr double kBothHeadShares = 300;
 
 // Parts of dK/dV items.  An item may be taken in as many parts as the sums of all rows fit behind the rest of the
 // workspace and into kPartBytes (splitting pays where few items keep few compute units busy, which needs a small
@@ -85,6 +91,10 @@ int part_limit(size_t bytes, int T, int hkv, int head_dim) {
 double share_of_work(double tile, double steps_per_level, int T, int nseq, int max_seqlen, int heads, int wgs) {
     const double nm = max_seqlen / tile, m = nseq > 1 ? nseq - 1 : 1, nr = (T - max_seqlen) / m / tile;
     return heads * steps_per_level * (nm * (nm + 1) + m * nr * (nr + 1)) / 2 / wgs;
+}
+bool both_ok(int T, int nseq, int max_seqlen, int hq, int hkv, int cus) {
+    return (long long)T * hq <= kBothRows &&
+           (hq < 3 * hkv || hq * share_of_work(kKvBN, kKvBN / kKvBM * (hq / hkv), T, nseq, max_seqlen, hkv, cus) <= kBothHeadShares);
 }
 // steps of a part, 0: items stay whole (see set_parts)
 double steps_of_part(double longest, double share, int limit) {
@@ -692,7 +702,7 @@ hyd_status bwd_impl(const void* q, const void* k, const void* v, const void* o, 
     const int units = hq / item_heads(split);
     const bool grouped = hq >= 4 * hkv;
     SchedView sv_kv = make_view(ws, w.sched[0], tile_kv(dt), 0, max_seqlen, dt, hkv, dev->cus * occ_kv, grouped);
-    const bool both = dt == HYD_BF16 && !ranged && rope_base == 0.f && (long long)total_tokens * hq <= kBothRows;
+    const bool both = dt == HYD_BF16 && !ranged && rope_base == 0.f && both_ok(total_tokens, num_seqs, max_seqlen, hq, hkv, dev->cus);
     SchedView sv_whole = make_view(ws, w.sched[1], tile_q(dt), 0, max_seqlen, dt, units, dev->cus * occ_q, grouped);
     if (split) sv_whole.other = (int)(w.split.hdr - w.sched[1].hdr);
     const SchedView sv_q = split ? make_view(ws, w.split, 256 >> split, split, max_seqlen, dt, units, dev->cus * occ_q, grouped, item_heads(split)) : sv_whole;
