@@ -196,11 +196,18 @@ int finest_split(hyd_dtype dt, int hq, int hkv, bool compact) {
 //   Number: its longest item takes twice as long.  Backward, log-normal lengths unless noted, longest / share: 50000 tokens, 8 heads,
 // 1.04: 1014 -> 981; 24000 tokens of Pareto lengths, 8 heads, 1.29: 1014 -> 1024; one sequence of 12000, 32/8 heads, 1.34: 3705 ->
 // 3728; 12000 tokens of Pareto lengths, 32/8 heads, 1.63: 2520 -> 2729; 12000 tokens, 32/8 heads, 2.1: 897 -> 1047.
+//   Rounds: with few items of about one length for each workgroup the last round is half empty, or an item late, and lasts twice as long as in
+// the narrow form.  Backward, equal lengths: 12000 tokens (1.5 items for each workgroup): 700 long, 32/8 heads, d = 128 405 -> 432, 64/8 740 -> 771,
+// 1000, 32/8 477 -> 484; d = 64: 500, 32/8 219 -> 236, 64/8 398 -> 436, 16/8 120 -> 129, 1000, 32/8 306 -> 297; 12000 (1.8), 10 heads, d = 128: 2500
+// 322 -> 331; 16384 (2), 32/8: 640 509 -> 536, 1000 670 -> 692; 24000 (3), 32/8: 700 776 -> 796, 1000 961 -> 938; 8 heads, d = 64 700 170 -> 173;
+// 50000 (6), 8 heads, d = 64: 500 302 -> 305, 700 335 -> 329.
 // The range variants, whose visits are a part of these items, keep the narrow form, and so do items in parts.
 bool wide_kv(int T, int nseq, int max_seqlen, int hq, int hkv, int head_dim, int wgs) {
     const double m = nseq > 1 ? nseq - 1 : 1, rest = (T - max_seqlen) / m;
     const double mean = ((double)max_seqlen * max_seqlen + m * rest * rest) / T;
-    if (mean < (head_dim == 64 ? 400 : (hq / hkv >= 4 ? 600 : 1100))) return false;
+    const bool four = hq / hkv >= 4;
+    const double per_wg = (double)T / kKwBN * hkv / wgs, few = 1 + (four ? 1.4 : 2.5) / per_wg;       // items for each workgroup, about
+    if (mean < (head_dim == 64 ? 400 * few : (four ? 600 : 1100) * (per_wg < 4 ? few : 1))) return false;
     const double steps = kKwBN / kKwBM * (hq / hkv);
     return (double)max_seqlen / kKwBN * steps <= 1.25 * share_of_work(kKwBN, steps, T, nseq, max_seqlen, hkv, wgs);
 }

@@ -41,3 +41,23 @@ def test_wide_tiles_equal_narrow_ones(hq, hkv, d, longest, n, scale, special):
         assert torch.equal(ok, torch.isfinite(x.float())) and torch.equal(x[ok], y[ok]), name
         assert bool(ok.all()) != special
         assert bool((x[ok] != 0).any()) or scale == 0.0
+
+
+@pytest.mark.parametrize("lens,hq,hkv,d,tile", [([700] * 17 + [100], 32, 8, 128, 128), ([1000] * 24, 32, 8, 128, 256), ([640] * 25 + [384], 32, 8, 128, 128), ([500] * 24, 16, 8, 64, 128),
+                                                ([1500] * 8, 16, 8, 64, 256), ([500] * 100, 32, 32, 64, 256), ([1500] * 8, 40, 40, 128, 256), ([2500] * 5, 10, 10, 128, 128)])
+def test_wide_where_items_are_long_and_many(lens, hq, hkv, d, tile):
+    """dK and dV against the range variant, which keeps the narrow form: the same products in the same order."""
+    T, ml = sum(lens), max(lens)
+    g = torch.Generator(device="cuda")
+    g.manual_seed(59)
+    q, k, v, do = (torch.randn((T, h, d), device="cuda", generator=g).to(torch.bfloat16) for h in (hq, hkv, hkv, hq))
+    cu = torch.from_numpy(wl.cu_seqlens(lens)).cuda()
+    o, lse = binding.varlen_attn_fwd(q, k, v, cu, ml, d ** -0.5)
+    ws = torch.empty(binding.workspace_bytes(T, len(lens), hq, hkv, d, binding.HYD_BF16, 1), dtype=torch.uint8, device="cuda")
+    _, dk, dv = binding.varlen_attn_bwd(q, k, v, o, lse, do, cu, ml, d ** -0.5, workspace=ws)
+    got = binding.executed_items(ws, T, len(lens), hq, hkv, d, binding.HYD_BF16, 1, 0)[0]
+    print(f"\n{len(lens)} x {ml} {hq}/{hkv} d={d}: tile {got}", flush=True)
+    assert got == tile
+    other = [torch.zeros_like(x) for x in (q, k, v)]
+    binding.varlen_attn_bwd_range(q, k, v, o, lse, do, cu, [(0, 1 << 20, 0, 1 << 20)] * len(lens), ml, d ** -0.5, *other)
+    assert torch.equal(dk, other[1]) and torch.equal(dv, other[2])
