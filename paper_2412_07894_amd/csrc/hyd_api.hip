@@ -202,14 +202,30 @@ int finest_split(hyd_dtype dt, int hq, int hkv, bool compact) {
 // 322 -> 331; 16384 (2), 32/8: 640 509 -> 536, 1000 670 -> 692; 24000 (3), 32/8: 700 776 -> 796, 1000 961 -> 938; 8 heads, d = 64 700 170 -> 173;
 // 50000 (6), 8 heads, d = 64: 500 302 -> 305, 700 335 -> 329.
 // The range variants, whose visits are a part of these items, keep the narrow form, and so do items in parts.
-bool wide_kv(int T, int nseq, int max_seqlen, int hq, int hkv, int head_dim, int wgs) {
-    const double m = nseq > 1 ? nseq - 1 : 1, rest = (T - max_seqlen) / m;
-    const double mean = ((double)max_seqlen * max_seqlen + m * rest * rest) / T;
+//   A bound: max_seqlen may be far above the longest sequence.  Where it decides, that is, where sequences of equal length would not do (or one
+// of max_seqlen among them might be too long), and the caller has given no host copy of cu_seqlens, both kernels are launched and the
+// builders of their lists, who see the lengths, leave one of them empty (`pick` of a SchedView); that launch takes 4-9 us.  Backward, 32768 tokens
+// in sequences of 128 under a bound of 8192, 32 heads: narrow 933, wide 1123, now 939; 49152 of 300 under 49152, 8 heads 468, 518, 477; exact
+// bounds: 32768 tokens of Pareto lengths, 32 heads, d = 64 1062, 1026, 1026; 24000 of log-normal lengths, 10 heads 692, 669, 673.
+enum { kKvNarrow = 0, kKvWide = 1, kKvByLengths = 2 };
+int wide_kv(int T, int nseq, int max_seqlen, const int32_t* cu_host, int hq, int hkv, int head_dim, int wgs, long long* min_squares) {
     const bool four = hq / hkv >= 4;
     const double per_wg = (double)T / kKwBN * hkv / wgs, few = 1 + (four ? 1.4 : 2.5) / per_wg;       // items for each workgroup, about
-    if (mean < (head_dim == 64 ? 400 * few : (four ? 600 : 1100) * (per_wg < 4 ? few : 1))) return false;
-    const double steps = kKwBN / kKwBM * (hq / hkv);
-    return (double)max_seqlen / kKwBN * steps <= 1.25 * share_of_work(kKwBN, steps, T, nseq, max_seqlen, hkv, wgs);
+    const double need = head_dim == 64 ? 400 * few : (four ? 600 : 1100) * (per_wg < 4 ? few : 1);
+    *min_squares = (long long)(need * T);
+    const auto pays = [&](double squares, long long longest) { return wide_pays((unsigned long long)squares, longest, T, *min_squares, hkv, wgs); };
+    const double m = nseq > 1 ? nseq - 1 : 1, rest = T - max_seqlen;
+    if (!pays((double)max_seqlen * max_seqlen + rest * rest / m, max_seqlen)) return kKvNarrow;
+    if (pays((double)T * T / nseq, max_seqlen)) return kKvWide;
+    if (!cu_host) return kKvByLengths;
+    double squares = 0;
+    int longest = 0;
+    for (int i = 0; i < nseq; ++i) {
+        const int L = cu_host[i + 1] - cu_host[i];
+        squares += (double)L * L;
+        longest = L > longest ? L : longest;
+    }
+    return pays(squares, longest) ? kKvWide : kKvNarrow;
 }
 int item_heads(int split) { return split == 2 ? 4 : 1; }
 // Form 3, of the forward only: 64 rows of one head, the waves sharing them (hyd_fwd_coop.h).
@@ -455,6 +471,7 @@ SchedView make_view(char* ws, const SchedLayout& v, int tile, int split, int max
     sv.group_share = (float)heads / (16.f * (float)wgs);
     sv.part_max = 1; sv.part_q = 1; sv.steps_per_level = 0;
     sv.other = 0; sv.rec_heads = rec_heads;
+    sv.pick = 0; sv.pick_hkv = sv.pick_wgs = 1; sv.pick_squares = 0;
     return sv;
 }
 
@@ -716,13 +733,18 @@ hyd_status bwd_impl(const void* q, const void* k, const void* v, const void* o, 
     const long long work_q = (long long)sv_q.max_items * units;
     if (dt == HYD_BF16) set_parts(sv_kv, w.part_max, total_tokens, num_seqs, max_seqlen, hq, hkv, dev->cus * occ_kv);
     if (both) both_parts(sv_kv, w.part_max, total_tokens, num_seqs, max_seqlen, hq, hkv, dev->cus, work_q, split);
-    const bool wide = dt == HYD_BF16 && !ranged && !both && sv_kv.part_max == 1 &&
-                      wide_kv(total_tokens, num_seqs, max_seqlen, hq, hkv, head_dim, dev->cus);
-    const SchedView sv_wide = wide ? make_view(ws, w.wide, kKwBN, 0, max_seqlen, dt, hkv, dev->cus, grouped) : sv_kv;
+    long long min_squares = 0;
+    const int wide = dt == HYD_BF16 && !ranged && !both && sv_kv.part_max == 1 ?
+                     wide_kv(total_tokens, num_seqs, max_seqlen, cu_seqlens_host, hq, hkv, head_dim, dev->cus, &min_squares) : kKvNarrow;
+    SchedView sv_wide = wide ? make_view(ws, w.wide, kKwBN, 0, max_seqlen, dt, hkv, dev->cus, grouped) : sv_kv;
     if (wide) sv_kv.other = (int)(w.wide.hdr - w.sched[0].hdr);
+    if (wide == kKvByLengths) {
+        sv_kv.pick = -1; sv_wide.pick = 1;
+        sv_kv.pick_hkv = sv_wide.pick_hkv = hkv; sv_kv.pick_wgs = sv_wide.pick_wgs = dev->cus; sv_kv.pick_squares = sv_wide.pick_squares = min_squares;
+    }
     float* Dvec = reinterpret_cast<float*>(ws + w.stat[0]);
     double* rope_tab = rope_base != 0.f ? reinterpret_cast<double*>(ws + w.rope_tab) : nullptr;
-    const long long work_kv = (long long)sv_wide.max_items * sv_kv.part_max * hkv;
+    const long long work_kv = (long long)sv_kv.max_items * sv_kv.part_max * hkv;
     if (dt == HYD_BF16) {
         BwdScratch sc;
         sc.Dq = Dvec;
@@ -770,7 +792,7 @@ hyd_status bwd_impl(const void* q, const void* k, const void* v, const void* o, 
         p.part = reinterpret_cast<float*>(ws + w.need); p.part_max = sv_kv.part_max;
         const int grid_q = persistent_grid(*dev, occ_q, work_q), grid_kv = persistent_grid(*dev, occ_kv, work_kv);
         WorkList lq{sv_q.hdr, sv_q.hdr + kHdrCursor, sv_q.exec, head_map_q(units, hkv, grid_q)};
-        WorkList lkv{sv_wide.hdr + kHdrExec, sv_wide.hdr + kHdrCursor, sv_wide.exec, head_map_kv(hkv, grid_kv)};
+        WorkList lkv{sv_kv.hdr + kHdrExec, sv_kv.hdr + kHdrCursor, sv_kv.exec, head_map_kv(hkv, grid_kv)};
         if (both) {
             int n_kv = both_kv_workgroups(dev->cus, work_q);
             if (n_kv > work_kv) n_kv = (int)work_kv;
@@ -789,8 +811,12 @@ hyd_status bwd_impl(const void* q, const void* k, const void* v, const void* o, 
             KernelTimer kt(ranged ? "bwd_dkdv_range_bf16" : "bwd_dkdv_bf16", st);
             const BwdKernel kernel = ranged ? (head_dim == 64 ? hyd_bwd_dkdv_bf16_kernel<true, 64> : hyd_bwd_dkdv_bf16_kernel<true, 128>)
                                             : (head_dim == 64 ? hyd_bwd_dkdv_bf16_kernel<false, 64> : hyd_bwd_dkdv_bf16_kernel<false, 128>);
-            if (wide) hipLaunchKernelGGL(head_dim == 64 ? hyd_bwd_dkdv_wide_bf16_kernel<64> : hyd_bwd_dkdv_wide_bf16_kernel<128>, dim3(grid_kv), dim3(kKwThreads), kKwLds, st, p, lkv);
-            else hipLaunchKernelGGL(kernel, dim3(grid_kv), dim3(kKvThreads), kKvLds, st, p, lkv);
+            if (wide) {
+                const int grid = persistent_grid(*dev, 1, (long long)sv_wide.max_items * hkv);
+                const WorkList list{sv_wide.hdr + kHdrExec, sv_wide.hdr + kHdrCursor, sv_wide.exec, head_map_kv(hkv, grid)};
+                hipLaunchKernelGGL(head_dim == 64 ? hyd_bwd_dkdv_wide_bf16_kernel<64> : hyd_bwd_dkdv_wide_bf16_kernel<128>, dim3(grid), dim3(kKwThreads), kKwLds, st, p, list);
+            }
+            if (wide != kKvWide) hipLaunchKernelGGL(kernel, dim3(grid_kv), dim3(kKvThreads), kKvLds, st, p, lkv);
         }
         if (sv_kv.part_max > 1) {
             SumParams sp;

@@ -940,7 +940,7 @@ __device__ __forceinline__ void dkdv_items(const BwdParams& p, const WorkList& l
                                       Lk - wkey0, acc, mul, o_stage, lane);
         have = wf.next(list.hm, list.cursors, list.items, slot, wi);
     }
-    trace_write(p.tr, 1, t_start, n_done);
+    if (p.tr.rec && *list.hdr > 0) trace_write(p.tr, 1, t_start, n_done);       // (a list may be left to the wide form)
 }
 
 template <bool R, int D = kHeadDim>

@@ -407,7 +407,7 @@ __global__ void __launch_bounds__(kKwThreads, 1) hyd_bwd_dkdv_wide_bf16_kernel(B
         }
         have = wf.next(list.hm, list.cursors, list.items, slot, wi);
     }
-    trace_write(p.tr, 1, t_start, n_done);
+    if (p.tr.rec && *list.hdr > 0) trace_write(p.tr, 1, t_start, n_done);       // (a list may be left to the other form)
 }
 
 }  // namespace hyd

@@ -45,7 +45,17 @@ struct SchedView {            // device pointers into the workspace (all int32)
     int max_items;
     int part_max, part_q, steps_per_level;     // items in parts (see item_parts); part_max = 1: whole
     int other, rec_heads;     // header words kHdrOther, kHdrHeads
+    // Two lists of which one is handed out: the one with pick = 1 if wide_pays for the lengths there are, else the one with pick = -1, whose
+    // `other` leads to the first (pick = 0: handed out anyway)
+    int pick, pick_hkv, pick_wgs;
+    long long pick_squares;
 };
+
+// dK/dV by tiles of 256 keys: whether sequences with this sum of squared lengths and this longest one are long and even enough (the
+// host's rule says why): the sum is at least min_squares, and the longest item at most 1.25 of a workgroup's share.
+__host__ __device__ __forceinline__ bool wide_pays(unsigned long long squares, long long longest, long long T, long long min_squares, int hkv, int wgs) {
+    return squares >= (unsigned long long)min_squares && 8ull * 256 * (unsigned)wgs * (unsigned long long)longest <= 5ull * (unsigned)hkv * (squares + 256ull * (unsigned long long)T);
+}
 
 // An item can be handed out in parts (dK/dV kernel): level c, with c * steps_per_level steps, in
 // ceil(steps / part_q) of them, at most part_max.  exec then holds a record per part, which carries its
@@ -120,11 +130,17 @@ __device__ __forceinline__ void build_schedule(const int32_t* __restrict__ cu, i
     int* hist = lev;                       // [n]: sequences with exactly n tiles; later the arrival counters
     int* cnt = lev + (nl + 2);             // [r]: sequences with >= nl - r tiles (levels in reversed order)
     int* offs = lev + 2 * (nl + 2);        // [r]: list position after level nl - r
+    // behind the levels of cnt and offs: the sum of the squared lengths (8-byte aligned there), the longest one
+    unsigned long long* squares = reinterpret_cast<unsigned long long*>(cnt + nl);
+    int* longest = offs + nl;
+    if (tid == 0) { *squares = 0; *longest = 0; }
     for (int i = tid; i < nl + 2; i += nthreads) hist[i] = 0;
     for (int i = tid; i < kHdrTotal; i += nthreads) sv.hdr[i] = 0;
     __syncthreads();
     int flags = (tid == 0 && (cu[0] != 0 || cu[nseq] != T)) ? kSchedBadSeqlens : 0;
     float cost = 0.f;                      // sum of all levels
+    unsigned long long sq = 0;
+    int most = 0;
     for (int s = tid; s < nseq; s += nthreads) {
         const int L = cu[s + 1] - cu[s];
         if (L < 0) flags |= kSchedBadSeqlens;
@@ -132,7 +148,10 @@ __device__ __forceinline__ void build_schedule(const int32_t* __restrict__ cu, i
         const int n = min((L + tile - 1) / tile, nl);
         if (n > 0) atomicAdd(&hist[n], 1);
         cost += 0.5f * (float)n * (float)(n + 1);
+        most = max(most, L);
+        sq += (unsigned long long)max(L, 0) * (unsigned long long)max(L, 0);
     }
+    if (sv.pick != 0 && sq != 0) { atomicAdd(squares, sq); atomicMax(longest, most); }
     if (cost > 0.f) atomicAdd(reinterpret_cast<float*>(hist), cost);        // hist[0] is not a level
     if (flags) atomicOr(&sv.hdr[kHdrFlags], flags);
     __syncthreads();
@@ -148,9 +167,10 @@ __device__ __forceinline__ void build_schedule(const int32_t* __restrict__ cu, i
     const int n_items = nl > 0 ? min(offs[nl - 1], sv.max_items) : 0;
     // more items than any valid cu_seqlens has: positions of the grouped order would lie outside the records
     if (nl > 0 && offs[nl - 1] > sv.max_items) C = 0;
+    const bool handed = sv.pick == 0 || (sv.pick > 0) == wide_pays(*squares, *longest, T, sv.pick_squares, sv.pick_hkv, sv.pick_wgs);
     if (tid == 0) {
         sv.hdr[0] = n_items;
-        sv.hdr[kHdrOther] = sv.other;
+        sv.hdr[kHdrOther] = sv.pick != 0 && handed ? 0 : sv.other;
         sv.hdr[kHdrRecords] = (int)((const char*)sv.exec - (const char*)sv.hdr);
         sv.hdr[kHdrTile] = tile;
         sv.hdr[kHdrHeads] = sv.rec_heads;
@@ -176,7 +196,7 @@ __device__ __forceinline__ void build_schedule(const int32_t* __restrict__ cu, i
         }
         __syncthreads();
     }
-    if (tid == 0) sv.hdr[kHdrExec] = parts ? hist[nl - 1] : n_items;
+    if (tid == 0) sv.hdr[kHdrExec] = !handed ? 0 : (parts ? hist[nl - 1] : n_items);
     for (int pos = tid; pos < n_items; pos += nthreads) {
         int lo = 0, hi = nl - 1;               // first r with offs[r] > pos
         while (lo < hi) {

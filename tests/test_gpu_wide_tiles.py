@@ -61,3 +61,30 @@ def test_wide_where_items_are_long_and_many(lens, hq, hkv, d, tile):
     other = [torch.zeros_like(x) for x in (q, k, v)]
     binding.varlen_attn_bwd_range(q, k, v, o, lse, do, cu, [(0, 1 << 20, 0, 1 << 20)] * len(lens), ml, d ** -0.5, *other)
     assert torch.equal(dk, other[1]) and torch.equal(dv, other[2])
+
+
+# (bound, form): equal lengths that need no look at them; short ones under a bound; a few long ones among short ones; one long and all others alike, that the bound hides
+@pytest.mark.parametrize("lens,hq,hkv,d,bound,tile", [([1500] * 16, 32, 8, 128, 1500, 256), ([128] * 256, 32, 32, 128, 8192, 128), ([500] * 66, 8, 8, 64, 33000, 128), ([300] * 100, 32, 8, 128, 30000, 128),
+                                                      ([128] * 200 + [9000, 7000, 5000, 4000], 32, 32, 128, 9000, 256), ([128] * 200 + [9000, 7000, 5000, 4000], 32, 32, 128, 50600, 256),
+                                                      ([64] * 100 + [11000], 8, 8, 128, 17400, 128), ([0] * 30 + [40] * 5 + [3000] * 9 + [0], 16, 16, 64, 27200, 256)])
+@pytest.mark.parametrize("host", [False, True])
+def test_bound_above_the_lengths(lens, hq, hkv, d, bound, tile, host):
+    """max_seqlen may be any bound: where it would decide, the lengths on the device do (or a host copy of them), and of the
+    two lists one is left empty; dK and dV are those of the range variant, several times with one workspace."""
+    T, nseq = sum(lens), len(lens)
+    g = torch.Generator(device="cuda")
+    g.manual_seed(73)
+    q, k, v, do = (torch.randn((T, h, d), device="cuda", generator=g).to(torch.bfloat16) for h in (hq, hkv, hkv, hq))
+    cu = torch.from_numpy(wl.cu_seqlens(lens)).cuda()
+    at = [int(x) for x in wl.cu_seqlens(lens)] if host else None
+    o, lse = binding.varlen_attn_fwd(q, k, v, cu, bound, d ** -0.5)
+    ws = torch.full((binding.workspace_bytes(T, nseq, hq, hkv, d, binding.HYD_BF16, 1),), 0xff, dtype=torch.uint8, device="cuda")
+    other = [torch.zeros_like(x) for x in (q, k, v)]
+    binding.varlen_attn_bwd_range(q, k, v, o, lse, do, cu, [(0, 1 << 20, 0, 1 << 20)] * nseq, max(lens), d ** -0.5, *other)
+    for _ in range(2):
+        grads = [torch.full_like(x, float("nan")) for x in (q, k, v)]
+        binding.varlen_attn_bwd(q, k, v, o, lse, do, cu, bound, d ** -0.5, cu_seqlens_host=at, workspace=ws, dq=grads[0], dk=grads[1], dv=grads[2])
+        got, _, rec = binding.executed_items(ws, T, nseq, hq, hkv, d, binding.HYD_BF16, 1, 0)
+        print(f"\n{nseq} sequences, longest {max(lens)}, bound {bound}, {hq}/{hkv} d={d}: tile {got}, {len(rec)} items", flush=True)
+        assert got == tile and len(rec) == sum(-(-n // tile) for n in lens)
+        assert torch.equal(grads[1], other[1]) and torch.equal(grads[2], other[2])
