@@ -88,3 +88,25 @@ def test_bound_above_the_lengths(lens, hq, hkv, d, bound, tile, host):
         print(f"\n{nseq} sequences, longest {max(lens)}, bound {bound}, {hq}/{hkv} d={d}: tile {got}, {len(rec)} items", flush=True)
         assert got == tile and len(rec) == sum(-(-n // tile) for n in lens)
         assert torch.equal(grads[1], other[1]) and torch.equal(grads[2], other[2])
+
+
+@pytest.mark.parametrize("hq,hkv,d", [(40, 40, 128), (32, 8, 128), (32, 8, 64)])
+def test_rotary_positions(hq, hkv, d):
+    """Sequences that take the wide form, and the same beside many short ones, where the narrow form is taken: bit for bit."""
+    long = [1500, 1499, 1473, 1535] * 2
+    g = torch.Generator(device="cuda")
+    g.manual_seed(79)
+    x = [torch.randn((40000, h, d), device="cuda", generator=g).to(torch.bfloat16) for h in (hq, hkv, hkv, hq)]
+    got = []
+    for lens, tile in ((long, 256), (long + [64] * 380, 128)):
+        T, ml = sum(lens), max(lens)
+        q, k, v, do = (t[:T] for t in x)
+        cu = torch.from_numpy(wl.cu_seqlens(lens)).cuda()
+        o, lse = binding.varlen_attn_fwd(q, k, v, cu, ml, d ** -0.5, rope_base=1e4)
+        ws = torch.empty(binding.workspace_bytes(T, len(lens), hq, hkv, d, binding.HYD_BF16, 1), dtype=torch.uint8, device="cuda")
+        got.append([r[:sum(long)] for r in binding.varlen_attn_bwd(q, k, v, o, lse, do, cu, ml, d ** -0.5, workspace=ws, rope_base=1e4)])
+        taken = binding.executed_items(ws, T, len(lens), hq, hkv, d, binding.HYD_BF16, 1, 0)[0]
+        print(f"\n{hq}/{hkv} d={d} {len(lens)} sequences: tile {taken}", flush=True)
+        assert taken == tile
+    for name, a, b in zip(("dq", "dk", "dv"), *got):
+        assert bool(torch.isfinite(a.float()).all()) and torch.equal(a, b), name
