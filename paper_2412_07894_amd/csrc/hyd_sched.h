@@ -122,6 +122,7 @@ inline size_t schedule_lds(int nl0, int nl1, int nl2 = 0, int nl3 = 0) {
 // workgroups share a stream across the group, it is within 1.5 % either way and left alone; so are
 // striped queues, which deal neighbouring items to different XCDs (dealing blocks of eight instead
 // gained nothing).
+template <bool kPick = false>             // the list may be one of two (`pick` of the view)
 __device__ __forceinline__ void build_schedule(const int32_t* __restrict__ cu, int nseq, int T, int tile, const SchedView& sv,
                                                int* lds_lev, int nthreads) {
     const int tid = threadIdx.x;
@@ -133,7 +134,7 @@ __device__ __forceinline__ void build_schedule(const int32_t* __restrict__ cu, i
     // behind the levels of cnt and offs: the sum of the squared lengths (8-byte aligned there), the longest one
     unsigned long long* squares = reinterpret_cast<unsigned long long*>(cnt + nl);
     int* longest = offs + nl;
-    if (tid == 0) { *squares = 0; *longest = 0; }
+    if (kPick && tid == 0) { *squares = 0; *longest = 0; }
     for (int i = tid; i < nl + 2; i += nthreads) hist[i] = 0;
     for (int i = tid; i < kHdrTotal; i += nthreads) sv.hdr[i] = 0;
     __syncthreads();
@@ -148,10 +149,9 @@ __device__ __forceinline__ void build_schedule(const int32_t* __restrict__ cu, i
         const int n = min((L + tile - 1) / tile, nl);
         if (n > 0) atomicAdd(&hist[n], 1);
         cost += 0.5f * (float)n * (float)(n + 1);
-        most = max(most, L);
-        sq += (unsigned long long)max(L, 0) * (unsigned long long)max(L, 0);
+        if (kPick) { most = max(most, L); sq += (unsigned long long)max(L, 0) * (unsigned long long)max(L, 0); }
     }
-    if (sv.pick != 0 && sq != 0) { atomicAdd(squares, sq); atomicMax(longest, most); }
+    if (kPick && sq != 0) { atomicAdd(squares, sq); atomicMax(longest, most); }
     if (cost > 0.f) atomicAdd(reinterpret_cast<float*>(hist), cost);        // hist[0] is not a level
     if (flags) atomicOr(&sv.hdr[kHdrFlags], flags);
     __syncthreads();
@@ -167,10 +167,10 @@ __device__ __forceinline__ void build_schedule(const int32_t* __restrict__ cu, i
     const int n_items = nl > 0 ? min(offs[nl - 1], sv.max_items) : 0;
     // more items than any valid cu_seqlens has: positions of the grouped order would lie outside the records
     if (nl > 0 && offs[nl - 1] > sv.max_items) C = 0;
-    const bool handed = sv.pick == 0 || (sv.pick > 0) == wide_pays(*squares, *longest, T, sv.pick_squares, sv.pick_hkv, sv.pick_wgs);
+    const bool handed = !kPick || (sv.pick > 0) == wide_pays(*squares, *longest, T, sv.pick_squares, sv.pick_hkv, sv.pick_wgs);
     if (tid == 0) {
         sv.hdr[0] = n_items;
-        sv.hdr[kHdrOther] = sv.pick != 0 && handed ? 0 : sv.other;
+        sv.hdr[kHdrOther] = kPick && handed ? 0 : sv.other;
         sv.hdr[kHdrRecords] = (int)((const char*)sv.exec - (const char*)sv.hdr);
         sv.hdr[kHdrTile] = tile;
         sv.hdr[kHdrHeads] = sv.rec_heads;
