@@ -986,10 +986,16 @@ hyd_status hyd_attn_merge(const void* o_a, const float* lse_a, const void* o_b, 
     {
         KernelTimer kt("merge_bf16", st);
         const int chunks = merge_chunks(hq);
-        const dim3 mgrid((unsigned)((total_tokens + kMergeTok - 1) / kMergeTok) * (unsigned)chunks);
-        const auto kernel = head_dim == 64 ? hyd_merge_bf16_kernel<64> : hyd_merge_bf16_kernel<kHeadDim>;
-        hipLaunchKernelGGL(kernel, mgrid, dim3(kMergeThreads), 0, st, static_cast<const uint16_t*>(o_a), lse_a,
-                           static_cast<const uint16_t*>(o_b), lse_b, static_cast<uint16_t*>(o_out), lse_out, total_tokens, hq, chunks);
+        const bool apart = o_out != o_a && o_out != o_b;
+        const bool brief = apart && head_dim == kHeadDim && hq >= kMergeHeads && 6ll * total_tokens * hq * head_dim > kMergeCached;
+        const int most = brief ? kMergeShortTok : kMergeTok;
+        int log2_tok = 0;
+        while ((2 << log2_tok) <= most && ((long long)total_tokens >> (log2_tok + 1)) * chunks >= kMergeGroups) ++log2_tok;
+        const dim3 mgrid((unsigned)(((long long)total_tokens + (1 << log2_tok) - 1) >> log2_tok) * (unsigned)chunks);
+        const auto kernel = head_dim == 64 ? hyd_merge_bf16_kernel<64>
+                                           : brief ? hyd_merge_bf16_kernel<kHeadDim, kMergeShortThreads, kMergeShortTok, 1> : hyd_merge_bf16_kernel<kHeadDim>;
+        hipLaunchKernelGGL(kernel, mgrid, dim3(brief ? kMergeShortThreads : kMergeThreads), 0, st, static_cast<const uint16_t*>(o_a), lse_a,
+                           static_cast<const uint16_t*>(o_b), lse_b, static_cast<uint16_t*>(o_out), lse_out, total_tokens, hq, chunks, log2_tok);
     }
     return hipGetLastError() == hipSuccess ? HYD_OK : HYD_ERR_LAUNCH;
 }

@@ -10,26 +10,36 @@
 // formed first, a thread per row, so that the [Hq][T] vectors are read and written in runs of 32
 // floats; then kLanes lanes per row move 16 bytes each, four rows in flight.  Measured (16384 tokens, 32 heads): a merge
 // in place of 3030 tokens' rows 64 us before (event times), 27 now.
+//   Few rows: workgroups of fewer tokens, as long as there are 1024 of them, since one of 32 tokens loops over its rows
+// while CUs idle (one-row workgroups of 16 lanes before, 32 tokens always, now: 64 tokens, 8 heads 7.5, 9.4, 7.2 us; 2369 7.5, 10.4, 7.3;
+// 4000 tokens, 16 heads 8.3, 13.1, 7.4; 2369, 32 heads 10.4, 16.9, 9.1).
+//   Many rows that all move: the order of the accesses counts, which is that of the memory where workgroups are short and keep one
+// row per lane in flight.  A merge out of place, which moves every row, of more than the caches hold takes workgroups of 4 tokens
+// and 512 threads (d = 128: 16384 tokens, 32 heads 71, 82, 72 us; 33000 141, 164, 140; 131072, 8 heads 138, 157, 140; 10 heads 176, 196,
+// 186).  In place the long workgroups stay: they pass over rows without a partial in half the time (33000 tokens, 32 heads, a quarter of the
+// rows 141, 39, short ones 69), which costs a merge in place of all rows a sixth (141, 166, short ones 140).
 #pragma once
 #include "hyd_device.h"
 
 namespace hyd {
 
-constexpr int kMergeThreads = 256, kMergeTok = 32, kMergeHeads = 8;
+constexpr int kMergeThreads = 256, kMergeTok = 32, kMergeHeads = 8, kMergeGroups = 1024;
+constexpr int kMergeShortThreads = 512, kMergeShortTok = 4;
+constexpr long long kMergeCached = 300ll << 20;            // bytes of O, of three buffers
 inline int merge_chunks(int hq) { return (hq + kMergeHeads - 1) / kMergeHeads; }      // of the heads
 
 // o_out / lse_out may alias either input (what is overwritten has been read before).
-template <int D = kHeadDim>
-__global__ void __launch_bounds__(kMergeThreads) hyd_merge_bf16_kernel(const uint16_t* o_a, const float* lse_a,
-                                                                       const uint16_t* o_b, const float* lse_b,
-                                                                       uint16_t* o_out, float* lse_out, int T, int hq, int chunks) {
-    __shared__ float wt[2][kMergeTok * kMergeHeads];
+template <int D = kHeadDim, int kThreads = kMergeThreads, int kTok = kMergeTok, int kU = 4>          // kU: rows of a lane in flight
+__global__ void __launch_bounds__(kThreads) hyd_merge_bf16_kernel(const uint16_t* o_a, const float* lse_a,
+                                                                  const uint16_t* o_b, const float* lse_b,
+                                                                  uint16_t* o_out, float* lse_out, int T, int hq, int chunks, int log2_tok) {
+    __shared__ float wt[2][kTok * kMergeHeads];
     const int tid = threadIdx.x, per = (hq + chunks - 1) / chunks;             // heads of a chunk
-    const int t0 = (int)(blockIdx.x / (unsigned)chunks) * kMergeTok, h0 = (int)(blockIdx.x % (unsigned)chunks) * per;
-    const int nt = min(kMergeTok, T - t0), nh = min(per, hq - h0);
+    const int t0 = (int)(blockIdx.x / (unsigned)chunks) << log2_tok, h0 = (int)(blockIdx.x % (unsigned)chunks) * per;
+    const int nt = min(1 << log2_tok, T - t0), nh = min(per, hq - h0);
     if (nh <= 0) return;
     {
-        const int tl = tid % kMergeTok, hl = tid / kMergeTok;
+        const int tl = tid & ((1 << log2_tok) - 1), hl = tid >> log2_tok;
         if (tl < nt && hl < nh) {
             const int64_t si = (int64_t)(h0 + hl) * T + t0 + tl;
             const float la = lse_a[si], lb = lse_b[si];
@@ -49,7 +59,7 @@ __global__ void __launch_bounds__(kMergeThreads) hyd_merge_bf16_kernel(const uin
         }
     }
     __syncthreads();
-    constexpr int kLanes = D / 8, kGrps = kMergeThreads / kLanes, kU = 4;      // lanes per row, rows at a time, of them in flight
+    constexpr int kLanes = D / 8, kGrps = kThreads / kLanes;                   // lanes per row, rows at a time
     const int c = tid % kLanes, n_rows = nt * per;
     const bool in_a = o_out == o_a, in_b = o_out == o_b;
     for (int r0 = tid / kLanes; r0 < n_rows; r0 += kGrps * kU) {

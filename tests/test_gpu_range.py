@@ -308,3 +308,27 @@ def test_merge_rows_without_a_partial_stay(T, hq, d):
     assert np.array_equal(np.isneginf(gu.to_np(l)), np.isneginf(l_ref))
     assert torch.equal(a, o) and torch.equal(lda, l)
     assert torch.equal(a[keep].view(torch.int16), a0[keep].view(torch.int16))
+
+
+# groups of 1 to 32 tokens by the number of rows, and short ones where a large result lies apart from both inputs
+@pytest.mark.parametrize("hq,d,T", [(1, 128, 3), (8, 64, 1025), (5, 128, 4099), (17, 64, 1500), (32, 128, 700), (8, 128, 9001), (3, 64, 33003), (9, 128, 45001), (40, 128, 10301)])
+def test_merge_by_the_number_of_rows(hq, d, T):
+    """Each row is its own: the merge of a part of the tokens, out of place and in place into either input, agrees bit for bit."""
+    g = torch.Generator(device="cuda")
+    g.manual_seed(83)
+    oa, ob = (torch.randn((T, hq, d), device="cuda", generator=g).to(torch.bfloat16) for _ in range(2))
+    la, lb = (8 * torch.randn((hq, T), device="cuda", generator=g) for _ in range(2))
+    lb[:, T // 3:T // 2] = la[:, T // 2:T // 2 + 5] = -float("inf")
+    print(f"\n{T} tokens, {hq} heads, d = {d}", flush=True)
+    o, l = binding.attn_merge(oa, la, ob, lb)
+    rows = torch.randperm(T, generator=g, device="cuda")[:50]
+    wa, wb = (torch.exp(x[:, rows].double() - l[:, rows].double()).T.unsqueeze(-1) for x in (la, lb))
+    ref = wa * oa[rows].double() + wb * ob[rows].double()
+    assert float((o[rows].double() - ref).abs().max()) <= 2.0 ** -8 * float(ref.abs().max())
+    n = max(1, T // 2 + 3)
+    o2, l2 = binding.attn_merge(oa[:n].contiguous(), la[:, :n].contiguous(), ob[:n].contiguous(), lb[:, :n].contiguous())
+    assert torch.equal(o[:n], o2) and torch.equal(l[:, :n], l2)
+    for into in (0, 1):
+        x = [(oa.clone(), la.clone()), (ob.clone(), lb.clone())]
+        binding.attn_merge(x[0][0], x[0][1], x[1][0], x[1][1], out=x[into][0], lse_out=x[into][1])
+        assert torch.equal(x[into][0], o) and torch.equal(x[into][1], l)
