@@ -201,6 +201,11 @@ int finest_split(hyd_dtype dt, int hq, int hkv, bool compact) {
 // 1000, 32/8 477 -> 484; d = 64: 500, 32/8 219 -> 236, 64/8 398 -> 436, 16/8 120 -> 129, 1000, 32/8 306 -> 297; 12000 (1.8), 10 heads, d = 128: 2500
 // 322 -> 331; 16384 (2), 32/8: 640 509 -> 536, 1000 670 -> 692; 24000 (3), 32/8: 700 776 -> 796, 1000 961 -> 938; 8 heads, d = 64 700 170 -> 173;
 // 50000 (6), 8 heads, d = 64: 500 302 -> 305, 700 335 -> 329.
+//   Heads: with three or more of them for a queue, a workgroup's items come by heads in windows of eight records (decode_work), and the long ones of
+// the later heads begin late.  With less than 2.4 (d = 128: 3.1) items for each workgroup that outweighs the gain (dK/dV, narrow -> wide, items
+// for each): 32 heads, 3713 tokens, d = 128 (1.8) 230 -> 251, [1834, 1419], d = 64 (1.6) 74 -> 83; 48 heads, d = 64, 2373 (1.7) 105 -> 125, 2743 (2.0)
+// 128 -> 143, 3209 (2.4) 170 -> 174, 3051, 64 heads (3.0) 203 -> 194; d = 128, 40 heads [2804, 1029] (2.3) 190 -> 210, 48, 4122 (3.0) 398 -> 406, 40, 5417
+// (3.3) 556 -> 534; with fewer heads: 16, [3812, 3676] (1.9) 228 -> 228, 8279 (2.1) 518 -> 499.
 // The range variants, whose visits are a part of these items, keep the narrow form, and so do items in parts.
 //   A bound: max_seqlen may be far above the longest sequence.  Where it decides, that is, where sequences of equal length would not do (or one
 // of max_seqlen among them might be too long), and the caller has given no host copy of cu_seqlens, both kernels are launched and the
@@ -213,6 +218,7 @@ int wide_kv(int T, int nseq, int max_seqlen, const int32_t* cu_host, int hq, int
     const double per_wg = (double)T / kKwBN * hkv / wgs, few = 1 + (four ? 1.4 : 2.5) / per_wg;       // items for each workgroup, about
     const double need = head_dim == 64 ? 400 * few : (four ? 600 : 1100) * (per_wg < 4 ? few : 1);
     *min_squares = (long long)(need * T);
+    if (hkv >= 3 * kQueues && per_wg < (head_dim == 64 ? 2.4 : 3.1)) return kKvNarrow;
     const auto pays = [&](double squares, long long longest) { return wide_pays((unsigned long long)squares, longest, T, *min_squares, hkv, wgs); };
     const double m = nseq > 1 ? nseq - 1 : 1, rest = T - max_seqlen;
     if (!pays((double)max_seqlen * max_seqlen + rest * rest / m, max_seqlen)) return kKvNarrow;

@@ -44,7 +44,8 @@ def test_wide_tiles_equal_narrow_ones(hq, hkv, d, longest, n, scale, special):
 
 
 @pytest.mark.parametrize("lens,hq,hkv,d,tile", [([700] * 17 + [100], 32, 8, 128, 128), ([1000] * 24, 32, 8, 128, 256), ([640] * 25 + [384], 32, 8, 128, 128), ([500] * 24, 16, 8, 64, 128),
-                                                ([1500] * 8, 16, 8, 64, 256), ([500] * 100, 32, 32, 64, 256), ([1500] * 8, 40, 40, 128, 256), ([2500] * 5, 10, 10, 128, 128)])
+                                                ([1500] * 8, 16, 8, 64, 256), ([500] * 100, 32, 32, 64, 256), ([1500] * 8, 40, 40, 128, 256), ([2500] * 5, 10, 10, 128, 128),
+                                                ([3713], 32, 32, 128, 128), ([7000], 32, 32, 128, 256), ([2743], 48, 48, 64, 128), ([4700], 48, 48, 64, 256)])
 def test_wide_where_items_are_long_and_many(lens, hq, hkv, d, tile):
     """dK and dV against the range variant, which keeps the narrow form: the same products in the same order."""
     T, ml = sum(lens), max(lens)
