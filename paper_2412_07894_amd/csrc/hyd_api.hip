@@ -553,20 +553,28 @@ bool self_schedule_ok(hyd_dtype dt, int nseq, long long work, int lists, bool un
     const bool few = nseq <= 3 && max_seqlen <= 2048;
     return dt == HYD_BF16 && (uneven || few) && 4 * work <= (max_seqlen > 1024 || few ? 7 : 6) * cus && max_seqlen <= 6144;
 }
-// Form 3 instead of half tiles where the launch can start with all of its items, or nearly (1.5 for each CU): those that come second cost
-// what an item costs at least, 8 us, and 128 keys of the longest item take 0.48 us less, so that up to 2 for each CU pay from some 2048
-// tokens on.  Forward, half tiles -> form 3 in us (in brackets its items), d = 128: one sequence of 256 tokens, 8 heads
+// Form 3 instead of half tiles where the launch starts with all of its items.  Those that come second cost what an item costs at
+// least, 8 us (10 with rotary positions, whose angles the four waves of a row each form), and 128 keys of the longest item take 0.48 us
+// less: up to 1.5 items for each CU pay from some 800 tokens on (1000 with rotary positions), up to 2 from 2048.  Forward, half tiles ->
+// form 3 in us (in brackets its items), d = 128: one sequence of 256 tokens, 8 heads
 // (32) 9.9 -> 9.5, 700, 32 heads (352) 17.5 -> 15.5, 1500, 8 heads (192) 29.7 -> 23.2, 3000, 8 heads (376) 52.4 -> 41.6, 4000 (504)
-// 67.8 -> 64.4, 6000 (752) 103 -> 135; sequences of 64-1024: 2000 tokens, 8 heads (280) 16.8 -> 14.0, 3000 (416) 18.6 -> 20.2.  (With d = 64,
-// where the second product occupied two waves of four, 1500 tokens, 8 heads 19.1 -> 18.2, 700, 32 heads 13.7 -> 14.0.)
-// From a list only where an XCD keeps to few heads (see head_map_q), since 64 rows read a head's keys four times as often as 256: one
-// sequence, from a list: 25600 tokens, 1 head (400) 382 -> 330, 6528, 5 heads (510) 107 -> 111, 2880, 10 heads (450) 49.3 -> 58.1, 3264 (510) 60.4 -> 67.8.
-int fwd_form(int split, int T, int nseq, int max_seqlen, int hq, int head_dim, int cus) {
+// 67.8 -> 64.4, 6000 (752) 103 -> 135; sequences of 64-1024: 2000 tokens, 8 heads (280) 16.8 -> 14.0, 3000 (416) 18.6 -> 20.2; of 146, 8
+// heads (280) 8.5 -> 12.1, 410, 2 heads (336) 11.9 -> 12.7, 600, 3 heads (339) 16.9 -> 19.0, 773, 2 heads (340) 17.4 -> 15.8, 848, 10 heads
+// (280) 19.8 -> 17.0; with rotary positions 81, 8 heads (336) 9.6 -> 15.8 (whole tiles from a list 15.2), 822, 5 heads (345) 21.6 -> 23.1, 950, 1 head
+// (344) 21.5 -> 19.7.  (With d = 64, where the second product occupied two waves of four, 1500 tokens, 8 heads 19.1 -> 18.2, 700, 32
+// heads 13.7 -> 14.0.)
+// From a list only where an XCD keeps to few heads (see head_map_q), since 64 rows read a head's keys four times as often as 256, and from 3000
+// tokens on, since half tiles need none there: one sequence, from a list: 25600 tokens, 1 head (400) 382 -> 330, 6528, 5 heads (510) 107 -> 111,
+// 2880, 10 heads (450) 49.3 -> 58.1, 3264 (510) 60.4 -> 67.8; several up to 2712, 3 heads (501) 45.8 -> 51.2, 2499, 8 heads (496) 43.6 -> 46.7, 3094 (512)
+// 51.4 -> 49.4.
+int fwd_form(int split, int T, int nseq, int max_seqlen, int hq, int head_dim, bool rope, int cus) {
     if (split != 1 || head_dim != 128) return split;
     const long long items = most_items(T, nseq, 64) * hq;
+    if (items + 2 <= cus) return 3;
+    if (max_seqlen < (rope ? 1000 : 800)) return 1;
     if (2 * items <= 3 * cus) return 3;
     if (items > 2 * cus || max_seqlen < 2048) return 1;
-    return hq % kQueues == 0 || hq < 4 || self_schedule_ok(HYD_BF16, nseq, items, 2, true, max_seqlen, cus) ? 3 : 1;
+    return self_schedule_ok(HYD_BF16, nseq, items, 2, true, max_seqlen, cus) || ((hq % kQueues == 0 || hq < 4) && max_seqlen >= 3000) ? 3 : 1;
 }
 
 SelfSchedule self_schedule(const int32_t* cu, int nseq, int T, int work, int lists, int heads, int tile, const SchedView& sv, int cus) {
@@ -642,7 +650,7 @@ hyd_status fwd_impl(const void* q, const void* k, const void* v, const int32_t* 
     if (ds != HYD_OK) return ds;
     hipStream_t st = static_cast<hipStream_t>(hip_stream);
 
-    const int split = ranged ? 0 : fwd_form(query_split(dt, total_tokens, num_seqs, max_seqlen, hq, hkv, compact), total_tokens, num_seqs, max_seqlen, hq, head_dim, dev->cus), shift = form_shift(split);
+    const int split = ranged ? 0 : fwd_form(query_split(dt, total_tokens, num_seqs, max_seqlen, hq, hkv, compact), total_tokens, num_seqs, max_seqlen, hq, head_dim, rope_base != 0.f, dev->cus), shift = form_shift(split);
     const int tile = tile_q(dt), units = hq / item_heads(split);
     const WsLayout w = fwd_layout(total_tokens, num_seqs, hq, hkv, head_dim, dt, compact);
     const int occ = dt == HYD_BF16 ? dev->occ_fwd : dev->occ_f32[head_dim == 128][0];

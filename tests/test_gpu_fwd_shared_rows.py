@@ -34,13 +34,13 @@ def path(q, k, v, lens, scale, rope_base=None):
 
 
 # each sequence a workgroup's own; the same of a second round; a list because there are more sequences than such a launch takes, or because the items are long
-CASES = [([1, 63, 64, 65, 127, 128, 129, 191, 193], 4, 2, False), ([130] * 60, 2, 1, False), ([2] * 250 + [300] * 8, 1, 1, True), ([6200], 3, 3, True)]
+CASES = [([1, 63, 64, 65, 127, 128, 129, 191, 193], 4, 2, False), ([1100] * 9, 2, 1, False), ([28] * 256 + [1100], 1, 1, True), ([6200], 3, 3, True)]
 
 
 @pytest.mark.parametrize("lens,hq,hkv,listed", CASES)
 @pytest.mark.parametrize("rope_base", [None, 1e4])
 def test_same_bits_as_whole_tiles(lens, hq, hkv, listed, rope_base):
-    T, copies = sum(lens), 1 + 12000 // (len(lens) * hq) if max(lens) < 1000 else 24
+    T, copies = sum(lens), 1 + 12000 // (len(lens) * hq) if max(lens) < 1000 else 48
     q, k, v = inputs(T, hq, hkv, 61)
     print(f"\n{len(lens)} sequences, {T} tokens, {hq}/{hkv}, rope {rope_base}", flush=True)
     o, lse, tile, from_list = path(q, k, v, lens, D ** -0.5, rope_base)
@@ -56,6 +56,15 @@ def test_form_of_one_sequence(lens, hq, tile):
     """64 rows per item where all or nearly all items begin at once; from a list only where an XCD keeps to few heads."""
     q, k, v = inputs(sum(lens), hq, hq, 71)
     assert path(q, k, v, lens, D ** -0.5)[2] == tile
+
+
+# (tile without, with rotary positions)
+@pytest.mark.parametrize("lens,hq,tile,rotary", [([81] * 12, 8, 64, 64), ([81] * 19, 8, 128, 128), ([600] * 11, 3, 128, 128), ([900] * 8, 2, 64, 64), ([900] * 10, 2, 64, 128), ([1100] * 9, 2, 64, 64),
+                                                 ([2712] + [1926] * 4, 3, 128, 128), ([3200, 800], 8, 64, 64)])
+def test_form_where_items_come_second(lens, hq, tile, rotary):
+    """Items of 64 rows that do not all begin at once only where sequences are long; rotary positions make an item dearer."""
+    q, k, v = inputs(sum(lens), hq, hq, 73)
+    assert path(q, k, v, lens, D ** -0.5)[2] == tile and path(q, k, v, lens, D ** -0.5, 1e4)[2] == rotary
 
 
 @pytest.mark.parametrize("scale", [D ** -0.5, -D ** -0.5])

@@ -57,7 +57,7 @@ def test_own_items_equal_listed_ones(dtype, hq, hkv, d, rope_base, lens):
 
 
 # more items than compute units: half tiles of equal sequences, the same of more sequences than a wave has lanes, 64-row tiles
-@pytest.mark.parametrize("lens,hq", [([2000] * 19, 1), ([200, 0, 130] * 34, 2), ([700] * 9 + [5], 3)])
+@pytest.mark.parametrize("lens,hq", [([2000] * 19, 1), ([200, 0, 130] * 34, 2), ([1100] * 6 + [5], 3)])
 def test_own_items_of_a_second_round(lens, hq):
     """They agree bit for bit with listed ones, and the workgroups take the longest first: those of the highest level last
     about as long as each other (sequence by sequence they would be spread over all workgroups)."""
