@@ -12,9 +12,10 @@ namespace hyd {
 // Against the narrow form a fragment of Q or dO serves two products instead of one (half the LDS reads), the stream
 // of Q and dO is read once for 256 keys instead of twice, P does not travel between waves, and there is one barrier for 64
 // rows instead of two.  What two waves of a SIMD give there, vector work of one under the products of
-// the other, has to come from the order of instructions here: see `block`.  Bound by the power that the matrix pipe takes:
-// 131072 tokens, 64/8 heads, long sequences: pipe busy 70 % of the clocks at 1.73 GHz (narrow: 59 % at 1.87), 38.0 -> 33.1
-// ms; d = 64, 32768 tokens of heavy-tailed lengths, 32 heads 2.06 -> 1.72 ms.  On the way there: products left to the
+// the other, has to come from the order of instructions here: see `block`.  No unit is saturated: matrix pipe busy 61 % of a CU's
+// clocks, vector ALU 34 %, LDS 20 % (131072 tokens of heavy-tailed lengths, 40 heads).  Each direct-to-LDS load of a step stands in a
+// loop over the lanes' descriptors, which the compiler does not know to be alike; with one wave for a SIMD nothing covers it.  131072 tokens,
+// 64/8 heads, long sequences, narrow -> wide 38.0 -> 33.1 ms; d = 64, 32768 tokens of heavy-tailed lengths, 32 heads 2.06 -> 1.72 ms.  On the way there: products left to the
 // compiler 352 registers in scratch; one loop with a choice of bodies 371; exponentials right behind their scores 34.9
 // ms; pinned by empty assembly statements (a wait state each) 34.2; vector work in assembly 33.3.
 //
